@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -97,16 +98,20 @@ static void* resolve(const Ref& r, const Bindings& b) {
 }
 
 enum OpType { OP_FILL = 0, OP_WTRANS, OP_CONV, OP_BN_APPLY, OP_POOL_FWD, OP_HEAD_FWD, OP_HEAD_BWD, OP_POOL_BWD,
-              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST };
+              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV };
+// tensor references of an OP_FCONV operation
+enum FcRef { F_IN = 0, F_IN2, F_ADDIN, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMMA2, F_BETA2, F_WT, F_OUT, F_ADD0, F_OSTATS,
+             F_EY, F_ESTATS, F_EGAMMA, F_EBETA, F_ERED, F_EY2, F_ESTATS2, F_ERED2, F_COUNT };
 
 struct Op {
     int type = 0, cfg = 0;
     int phase = 0;                         // fused step: 0 forward, 1 loss, 2 backward, 3 multiplier update
     bool vec = true;
-    Ref r[14];
+    Ref r[F_COUNT];
     size_t fill_bytes = 0;
     size_t numel = 0;                      // OP_LOSS: elements of the interface tensor
     ConvProb conv;
+    FConvProb fc;
     WgradProb wg;
     WtransProb wt;
     BnApplyProb bna;
@@ -168,6 +173,8 @@ struct ModulePlan {
     std::vector<char> t_in_epilogue;       // per tensor: its update rides on a filter-gradient kernel
     size_t ws_G[2] = {0, 0}, ws_A = 0, ws_P = 0, ws_gpool = 0;
     Program fwd, bwd, bwd_dx0;             // bwd_dx0: variant that also produces dx for a stem-less module 0
+    Program ffwd, fbwd, fbwd_dx0;          // the same passes for narrow modules: batch norms folded into the convolutions (OP_FCONV)
+    Program fstep, fstep_dx0;
     Program step, step_dx0;                // forward, loss / terminal adjoint, backward, multiplier update in one list
 };
 struct AuxPlan {
@@ -204,6 +211,8 @@ struct lp_net {
     hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
     bool lanes_ready = false;              // every extra stream and event above exists
     bool keep_gradients = false;           // debug layout: no gradient buffer is reused inside a backward pass
+    bool narrow = false;                   // every module has the folded programs (ffwd ...)
+    bool lanes_set = false;                // the caller chose the stream lanes
     bool deterministic = false;            // lp_net_set_deterministic: every reduction in a fixed order
     // lp_net_set_fused_update: the parameter update runs inside lp_module_backward / lp_local_step
     bool fused_update = false;
@@ -342,6 +351,61 @@ struct Builder {
                 step.push_back(o);
             }
     }
+    // ---- narrow layers with the batch norms folded in (lp_fconv.hip)
+    struct Fx {                                    // what the convolution reads: FxMode and its tensors
+        int mode = FX_PLAIN;
+        bool relu = false;
+        Ref in, in2, addin, side, stats, gamma, beta, stats2, gamma2, beta2;
+    };
+    // the most output channels a tile takes: its filter fragments stay below 20 KB of LDS (four workgroups per compute unit)
+    int fconv_max_bn(const FConvProb& p) const {
+        return p.Ncol >= 32 && fconv_ksteps(p.ntr * p.nts, p.Cin, (int)net->esz) * 32 * 64 <= 20 * 1024 ? 32 : 16;
+    }
+    // pixels of a full-size tile: 16 KB of window at most for the wider layers
+    static int fconv_px(const FConvProb& p, int BN) { return p.Ncol <= 16 ? fconv_max_px(BN) : std::min(fconv_max_px(BN), 128); }
+    // the tile geometry of one problem: BN output channels and as many whole rows as fit max_px pixels
+    static void fconv_tile(FConvProb& p, int BN, int max_px) {
+        p.BN = (signed char)BN;
+        p.TH = (short)std::max(1, std::min<int>(p.OA, max_px / p.OB));
+        p.tpi = (short)((p.OA + p.TH - 1) / p.TH);
+        p.WH = (short)((p.TH - 1) * p.imul + std::max<int>(p.ntr, 1)); p.WW = (short)((p.OB - 1) * p.imul + std::max<int>(p.nts, 1));
+        p.wdiv = 65536 / p.WW + 1; p.odiv = 65536 / p.OB + 1;
+        p.tdiv = p.tpi == 1 ? 0 : (unsigned)((1ull << 32) / p.tpi + 1);
+    }
+    Op fconv(const ConvProb& c, const Fx& x, Ref wt, Ref out, Ref add0, Ref ostats) const {
+        Op o; o.type = OP_FCONV;
+        FConvProb& p = o.fc; memset(&p, 0, sizeof(p));
+        p.nimg = c.M / (c.OA * c.OB); p.ldw = c.ldw;
+        p.OA = c.OA; p.OB = c.OB; p.IH = c.IH; p.IW = c.IW; p.OH = c.OH; p.OW = c.OW; p.Cin = c.Cin; p.Ncol = c.Ncol;
+        p.imul = c.imul; p.omul = c.omul; p.ooh = c.ooh; p.oow = c.oow; p.ntr = c.ntr; p.nts = c.nts;
+        p.dh0 = c.dh0; p.dhs = c.dhs; p.dw0 = c.dw0; p.dws = c.dws; p.r0 = c.r0; p.rs = c.rs; p.s0 = c.s0; p.ss = c.ss; p.S = c.S;
+        p.dhmin = std::min(c.dh0, c.dh0 + c.dhs * (c.ntr - 1)); p.dwmin = std::min(c.dw0, c.dw0 + c.dws * (c.nts - 1));
+        p.mode = x.mode; p.relu = x.relu;
+        const int BN = fconv_max_bn(p);
+        fconv_tile(p, BN, fconv_px(p, BN));
+        o.r[F_IN] = x.in; o.r[F_IN2] = x.in2; o.r[F_ADDIN] = x.addin; o.r[F_SIDE] = x.side;
+        o.r[F_STATS] = x.stats; o.r[F_GAMMA] = x.gamma; o.r[F_BETA] = x.beta;
+        o.r[F_STATS2] = x.stats2; o.r[F_GAMMA2] = x.gamma2; o.r[F_BETA2] = x.beta2;
+        o.r[F_WT] = wt; o.r[F_OUT] = out; o.r[F_ADD0] = add0; o.r[F_OSTATS] = ostats;
+        return o;
+    }
+    // does the narrow kernel take this layer (forward and data-gradient)?
+    bool fconv_ok(const Unit& u) const {
+        auto width = [](int c) { return c == 16 || c == 32 || c == 64; };
+        if (!width(u.cin) || !width(u.cout) || u.R > 3 || u.R == 2 || u.stride > 2) return false;
+        if (u.H % u.stride || u.W % u.stride || u.H > 1024 || u.N > (1 << 20)) return false;
+        Step st;
+        st.push_back(fconv(conv_fwd(u, Ref(), Ref(), Ref(), Ref()).conv, Fx(), Ref(), Ref(), Ref(), Ref()));
+        Step dg;
+        conv_dgrad(u, Ref(), Ref(), Ref(), Ref(), Ref(), dg);
+        for (const Op& o : dg) st.push_back(fconv(o.conv, Fx(), Ref(), Ref(), Ref(), Ref()));
+        for (const Op& o : st) {
+            const FConvProb& p = o.fc;
+            // a row of pixels must fit a tile (of 64 pixels where 64 channels are one), the window the 16-bit quotients and a third of the LDS
+            if (p.OB > 64 || (long)p.nimg * p.tpi * 4 * p.tpi >= (1l << 32) || p.WH * p.WW * p.WW >= 65536 || fconv_lds_bytes(p, (int)net->esz) > 64 * 1024) return false;
+        }
+        return true;
+    }
     Op wgrad(const Unit& u, Ref x, Ref dy, Ref dw) const {
         Op o; o.type = OP_WGRAD;
         WgradProb& w = o.wg; memset(&w, 0, sizeof(w));
@@ -469,7 +533,7 @@ static void attach_update(lp_net* net, int k, WsAlloc& ws) {
     std::vector<size_t> cnt_off(m.tensors.size(), 0);
     m.ws_cnt0 = ws.off;
     bool first = true;
-    for (Program* P : {&m.bwd, &m.bwd_dx0}) {
+    for (Program* P : {&m.bwd, &m.bwd_dx0, &m.fbwd, &m.fbwd_dx0}) {
         for (Step& st : *P)
             for (Op& o : st) {
                 if (o.type != OP_WGRAD || o.r[2].space != SP_DPARAM) continue;
@@ -486,7 +550,7 @@ static void attach_update(lp_net* net, int k, WsAlloc& ws) {
     }
     m.ws_cnt_bytes = ws.off - m.ws_cnt0;
     Builder B{net};
-    for (Program* P : {&m.bwd, &m.bwd_dx0}) {
+    for (Program* P : {&m.bwd, &m.bwd_dx0, &m.fbwd, &m.fbwd_dx0}) {
         if (P->empty()) continue;
         for (Step& st : *P) {
             bool clears_grads = false;
@@ -496,6 +560,156 @@ static void attach_update(lp_net* net, int k, WsAlloc& ws) {
         Op o; o.type = OP_SGD_REST; o.r[0] = mk(SP_PARAM, k, 0);
         P->push_back(Step{o});
     }
+}
+
+// ---- the passes of a narrow module (conv-BN-ReLU order) with the batch norms folded into the convolutions -----------
+// Same tensors, same results as the programs of build_module; per unit one launch forward (the BN apply in front of a
+// convolution rides on its loads) and one backward (the BN backward of a unit rides on the loads of its data-gradient,
+// the sums of the next one on the epilogue) instead of two and three.
+static bool build_module_folded(lp_net* net, int k) {
+    ModulePlan& m = net->mods[k];
+    Builder B{net};
+    if (m.d.order != LP_ORDER_POST || (m.has_stem && m.d.stem != 1)) return false;
+    if (m.has_stem && m.stem.cout != 16 && m.stem.cout != 32 && m.stem.cout != 64) return false;
+    for (auto& bp : m.bp) {
+        if (bp.main.size() != 2) return false;
+        for (auto& u : bp.main) if (!B.fconv_ok(u)) return false;
+        if (bp.has_proj && !B.fconv_ok(bp.proj)) return false;
+    }
+    const bool last = (k == net->K - 1);
+    const bool first_block_dx_optional = (k == 0 && !m.has_stem);
+    auto W_ = [](size_t off) { return mk(SP_WS, 0, off); };
+    auto wref = [&](const Unit& u) { return param_ref(m, k, u.t_w); };
+    auto gref = [&](const Unit& u) { return param_ref(m, k, u.t_g); };
+    auto bref = [&](const Unit& u) { return param_ref(m, k, u.t_b); };
+    auto dg = [&](const Unit& u) { return grad_ref(m, k, u.t_g); };
+    auto db = [&](const Unit& u) { return grad_ref(m, k, u.t_b); };
+    auto Mof = [&](const Unit& u) { return u.N * u.Ho * u.Wo; };
+    auto geom = [&](const Unit& u) { return B.conv_fwd(u, Ref(), Ref(), Ref(), Ref()).conv; };
+    auto bn_of = [&](const Unit& u, bool relu, Ref side) {
+        Builder::Fx x; x.mode = FX_BN; x.relu = relu; x.in = W_(u.ws_y); x.side = side;
+        x.stats = W_(u.ws_stats); x.gamma = gref(u); x.beta = bref(u);
+        return x;
+    };
+    // ---- forward: the transform of a block's input is the previous block's end (BN, skip) or the stem's BN
+    Program& F = m.ffwd;
+    F.push_back(Step{B.fill(W_(m.ws_stats0), m.ws_stats_bytes)});
+    Builder::Fx xin;
+    if (m.has_stem) {
+        F.push_back(Step{B.conv_fwd(m.stem, mk(SP_X, k, 0), wref(m.stem), W_(m.stem.ws_y), W_(m.stem.ws_stats))});
+        xin = bn_of(m.stem, true, W_(m.ws_stem_act));
+    } else xin.in = mk(SP_X, k, 0);
+    for (size_t i = 0; i < m.bp.size(); ++i) {
+        BlockPlan& bp = m.bp[i];
+        const Unit &u0 = bp.main[0], &u1 = bp.main[1];
+        Step s{B.fconv(geom(u0), xin, wref(u0), W_(u0.ws_y), Ref(), W_(u0.ws_stats))};
+        if (bp.has_proj) {
+            Builder::Fx xp = xin; xp.side = Ref();
+            s.push_back(B.fconv(geom(bp.proj), xp, wref(bp.proj), W_(bp.proj.ws_y), Ref(), bp.proj_plain ? Ref() : W_(bp.proj.ws_stats)));
+        }
+        F.push_back(s);
+        F.push_back(Step{B.fconv(geom(u1), bn_of(u0, true, W_(bp.ws_act[0])), wref(u1), W_(u1.ws_y), Ref(), W_(u1.ws_stats))});
+        if (i + 1 < m.bp.size()) {
+            xin = bn_of(u1, bp.post_relu, bp.out);
+            if (bp.has_proj && !bp.proj_plain) {
+                xin.mode = FX_BN_BN; xin.in2 = W_(bp.proj.ws_y);
+                xin.stats2 = W_(bp.proj.ws_stats); xin.gamma2 = gref(bp.proj); xin.beta2 = bref(bp.proj);
+            } else { xin.mode = FX_BN_ADD; xin.in2 = bp.has_proj ? W_(bp.proj.ws_y) : bp.in; }
+        } else if (bp.has_proj && !bp.proj_plain) {
+            const Unit& p = bp.proj;
+            F.push_back(Step{B.bn_apply(Mof(u1), u1.cout, W_(u1.ws_y), bp.out, W_(u1.ws_stats), gref(u1), bref(u1), bp.post_relu, 2,
+                                        W_(p.ws_y), W_(p.ws_stats), gref(p), bref(p))});
+        } else
+            F.push_back(Step{B.bn_apply(Mof(u1), u1.cout, W_(u1.ws_y), bp.out, W_(u1.ws_stats), gref(u1), bref(u1), bp.post_relu, 1,
+                                        bp.has_proj ? W_(bp.proj.ws_y) : bp.in)});
+    }
+    if (last) F.push_back(m.fwd.back());           // pooling and linear layer
+
+    // ---- backward ----------------------------------------------------------------------------------------
+    for (int variant = 0; variant < (first_block_dx_optional ? 2 : 1); ++variant) {
+        const bool want_dx_first = first_block_dx_optional ? (variant == 1) : true;
+        Program& Bw = variant == 0 ? m.fbwd : m.fbwd_dx0;
+        const Program& plain = variant == 0 ? m.bwd : m.bwd_dx0;
+        // clears, filter re-layouts and the head's backward pass as in the plain program; its last step is the filter gradients
+        size_t at = 0;
+        while (at < plain.size() && (plain[at][0].type == OP_FILL || plain[at][0].type == OP_WTRANS || plain[at][0].type == OP_HEAD_BWD))
+            Bw.push_back(plain[at++]);
+        auto bwd_of = [&](const Unit& u, Ref g) {
+            Builder::Fx x; x.mode = FX_BWD; x.relu = u.relu; x.in = g; x.in2 = W_(u.ws_y); x.side = W_(u.ws_dy);
+            x.stats = W_(u.ws_stats); x.gamma = gref(u); x.beta = bref(u);
+            x.stats2 = W_(u.ws_red); x.gamma2 = dg(u); x.beta2 = db(u);
+            return x;
+        };
+        auto dgrad = [&](const Unit& u, const Builder::Fx& x, Ref dx, Ref add0, const Unit* e, const Unit* e2, Step& st) {
+            Step g;
+            B.conv_dgrad(u, Ref(), Ref(), Ref(), Ref(), Ref(), g);
+            // one problem per parity class; the first one reads its own pixels of the input and writes the transformed values
+            for (size_t c = 0; c < g.size(); ++c) {
+                Builder::Fx xc = x;
+                if (c > 0) xc.side = Ref();
+                Op o = B.fconv(g[c].conv, xc, W_(u.ws_wt), dx, add0, Ref());
+                if (e) {
+                    o.fc.erelu = e->relu;
+                    o.r[F_EY] = W_(e->ws_y); o.r[F_ESTATS] = W_(e->ws_stats); o.r[F_EGAMMA] = gref(*e); o.r[F_EBETA] = bref(*e);
+                    o.r[F_ERED] = W_(e->ws_red);
+                    if (e2) { o.r[F_EY2] = W_(e2->ws_y); o.r[F_ESTATS2] = W_(e2->ws_stats); o.r[F_ERED2] = W_(e2->ws_red); }
+                }
+                st.push_back(o);
+            }
+        };
+        auto reduce = [&](const Unit& u, Ref g) {
+            return B.bn_bwd(OP_BN_BWD_REDUCE, Mof(u), u.cout, g, W_(u.ws_y), W_(u.ws_dy), W_(u.ws_stats), gref(u), bref(u), W_(u.ws_red), dg(u), db(u), u.relu);
+        };
+        auto apply = [&](const Unit& u, Ref g) {
+            Op o = reduce(u, g); o.type = OP_BN_BWD_APPLY; return o;
+        };
+        Ref g = last ? W_(m.ws_dfeat) : mk(SP_DY, k, 0);
+        bool summed = false;                       // the backward sums of the block's last batch norms are there already
+        for (int i = (int)m.bp.size() - 1; i >= 0; --i) {
+            BlockPlan& bp = m.bp[i];
+            const Unit &u0 = bp.main[0], &u1 = bp.main[1];
+            const bool need_in_grad = (i > 0) || m.has_stem || want_dx_first;
+            const Ref gin = (i == 0 && !m.has_stem) ? mk(SP_DX, k, 0) : W_(bp.ws_gin);
+            const Ref Pp = W_(bp.ws_gproj), A = W_(bp.ws_gact[0]);
+            const bool proj_bn = bp.has_proj && !bp.proj_plain;
+            if (bp.post_relu) {
+                Op o; o.type = OP_RELU_MASK; o.numel = bp.out_elems;
+                o.r[0] = g; o.r[1] = bp.out; o.r[2] = W_(bp.ws_gmask);
+                Bw.push_back(Step{o});
+                g = o.r[2];
+            }
+            if (!summed) {
+                Step s{reduce(u1, g)};
+                if (proj_bn) s.push_back(reduce(bp.proj, g));
+                Bw.push_back(s);
+            }
+            Step s3;
+            dgrad(u1, bwd_of(u1, g), A, Ref(), &u0, nullptr, s3);
+            if (bp.has_proj) {
+                if (bp.proj_plain) {               // its filter gradient cannot wait for the tail: the next block reuses g's buffer
+                    s3.push_back(B.wgrad(bp.proj, bp.in, g, grad_ref(m, k, bp.proj.t_w)));
+                    Builder::Fx x; x.in = g;
+                    if (need_in_grad) dgrad(bp.proj, x, Pp, Ref(), nullptr, nullptr, s3);
+                } else if (need_in_grad) dgrad(bp.proj, bwd_of(bp.proj, g), Pp, Ref(), nullptr, nullptr, s3);
+                else s3.push_back(apply(bp.proj, g));
+            }
+            Bw.push_back(s3);
+            summed = false;
+            if (need_in_grad) {
+                const BlockPlan* pb = i > 0 ? &m.bp[i - 1] : nullptr;
+                const Unit *e = nullptr, *e2 = nullptr;
+                if (pb && !pb->post_relu) { e = &pb->main[1]; if (pb->has_proj && !pb->proj_plain) e2 = &pb->proj; summed = true; }
+                else if (!pb && m.has_stem) { e = &m.stem; summed = true; }
+                Step s4;
+                dgrad(u0, bwd_of(u0, A), gin, bp.has_proj ? Pp : g, e, e2, s4);
+                Bw.push_back(s4);
+            } else Bw.push_back(Step{apply(u0, A)});
+            g = gin;
+        }
+        if (m.has_stem) Bw.push_back(Step{apply(m.stem, g)});
+        Bw.push_back(plain.back());
+    }
+    return true;
 }
 
 // ---- build one module: units, tensors, workspace, programs ------------------------------------------------
@@ -836,6 +1050,7 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
         }
         Bw.push_back(wg_tail);
     }
+    if (!build_module_folded(net, k)) net->narrow = false;
     attach_update(net, k, ws);
     return LP_OK;
 }
@@ -1084,6 +1299,7 @@ static lp_status build_module_pre(lp_net* net, int k, WsAlloc& ws) {
         if (m.has_stem) wg_tail.push_back(B.wgrad(m.stem, mk(SP_X, k, 0), W_(m.ws_gstem), grad_ref(m, k, m.stem.t_w)));
         Bw.push_back(wg_tail);
     }
+    net->narrow = false;
     attach_update(net, k, ws);
     return LP_OK;
 }
@@ -1107,11 +1323,11 @@ static void build_step_programs(lp_net* net, int k) {
         o.r[4] = mk(SP_LOSS, 0, sizeof(float) * k);
         loss_step.push_back(o);     // with a multiplier step bound, the same kernel also writes lam + step*(y - x_next)
     }
-    for (int variant = 0; variant < 2; ++variant) {
-        const Program& bw = variant == 0 ? m.bwd : m.bwd_dx0;
-        Program& out = variant == 0 ? m.step : m.step_dx0;
+    for (int variant = 0; variant < 4; ++variant) {
+        const Program& bw = variant == 0 ? m.bwd : variant == 1 ? m.bwd_dx0 : variant == 2 ? m.fbwd : m.fbwd_dx0;
+        Program& out = variant == 0 ? m.step : variant == 1 ? m.step_dx0 : variant == 2 ? m.fstep : m.fstep_dx0;
         if (bw.empty()) continue;
-        out = m.fwd;
+        out = variant < 2 ? m.fwd : m.ffwd;
         // The pass that writes F_k(x_k) (the BN apply + skip of the last block, conv-BN-ReLU order) also evaluates the
         // local loss and the terminal adjoint on the value it stores: F_k(x_k) is not read again.  Where the module
         // output is written by something else (the convolution epilogue of the pre-activation order) the loss keeps
@@ -1286,6 +1502,15 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
             const double nimg = (double)w.M / ((double)w.Ho * w.Wo);
             bytes = (nimg * w.IH * w.IW * w.Cin + (double)w.M * w.Cout) * e + (double)w.Cout * w.Kg * 4.0;
         } break;
+        case OP_FCONV: {
+            const FConvProb& p = o.fc;
+            const double M = (double)p.nimg * p.OA * p.OB;
+            flops = 2.0 * M * p.Ncol * p.Cin * p.ntr * p.nts;
+            double in_e = (double)p.nimg * p.IH * p.IW * p.Cin / ((double)p.omul * p.omul), out_e = M * p.Ncol;
+            const double n_in = 1.0 + (p.mode >= FX_BN_ADD) + (o.r[F_SIDE].space != SP_NONE) * (double)p.omul * p.omul;
+            const double n_out = 1.0 + (o.r[F_ADD0].space != SP_NONE) + (o.r[F_EY].space != SP_NONE) + (o.r[F_EY2].space != SP_NONE);
+            bytes = (in_e * n_in + (double)p.Ncol * p.Cin * p.ntr * p.nts + out_e * n_out) * e;
+        } break;
         case OP_WTRANS: bytes = 2.0 * o.wt.Cout * o.wt.RS * o.wt.Cin * e; break;
         case OP_FILL: bytes = (double)o.fill_bytes; break;
         case OP_BN_APPLY:      // fused with the loss / terminal adjoint: + x_next, lam, dy (the multiplier written back: + 1)
@@ -1328,6 +1553,23 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
         const int ks = (kt + best_chunk - 1) / best_chunk;
         p.ksplit = ks;
         p.kchunk = (kt + ks - 1) / ks * 32;          // equal chunks
+    }
+}
+
+// Tile sizes of a grouped launch of the narrow kernel: the smallest tiles of which two per compute unit hold the whole
+// launch (the less a workgroup does, the shorter the launch), full-size tiles where even those are more.
+static void plan_fconv_tiles(const lp_net* net, FConvGroup& g) {
+    const Builder B{const_cast<lp_net*>(net)};
+    for (int level = 2; level >= 0; --level) {     // smallest tiles first
+        long tiles = 0;
+        for (int i = 0; i < g.nprob; ++i) {
+            FConvProb& p = g.p[i];
+            const int BN = level < 2 ? B.fconv_max_bn(p) : 16;
+            const int px = level == 0 ? B.fconv_px(p, BN) : level == 1 ? B.fconv_px(p, BN) / 2 : 64;
+            Builder::fconv_tile(p, BN, px);
+            tiles += (long)p.nimg * p.tpi * (p.Ncol / p.BN);
+        }
+        if (tiles <= 512) return;
     }
 }
 
@@ -1454,6 +1696,37 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 if (used_blocks) *used_blocks = tot;
                 err = win ? launch_conv_win(g, cfg, s) : fast ? launch_conv_fast(g, cfg, s) : launch_conv(g, dt, cfg, ops[base]->vec, s);
                 if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);
+            } break;
+            case OP_FCONV: {
+                FConvGroup g; g.nprob = n; g.eps = net->eps; g.pad_ = 0;
+                int tot = 0; size_t lds = 0;
+                for (int i = 0; i < n; ++i) {
+                    const Op& o = *ops[base + i];
+                    FConvProb& p = g.p[i]; p = o.fc;
+                    p.in = resolve(o.r[F_IN], b); p.in2 = resolve(o.r[F_IN2], b); p.addin = resolve(o.r[F_ADDIN], b);
+                    p.side = resolve(o.r[F_SIDE], b);
+                    p.stats = (const double*)resolve(o.r[F_STATS], b); p.gamma = (const float*)resolve(o.r[F_GAMMA], b);
+                    p.beta = (const float*)resolve(o.r[F_BETA], b);
+                    p.stats2 = (const double*)resolve(o.r[F_STATS2], b); p.gamma2 = (const float*)resolve(o.r[F_GAMMA2], b);
+                    p.beta2 = (const float*)resolve(o.r[F_BETA2], b);
+                    p.wt = resolve(o.r[F_WT], b); p.out = resolve(o.r[F_OUT], b); p.add0 = resolve(o.r[F_ADD0], b);
+                    p.ostats = (double*)resolve(o.r[F_OSTATS], b);
+                    p.ey = resolve(o.r[F_EY], b); p.estats = (const double*)resolve(o.r[F_ESTATS], b);
+                    p.egamma = (const float*)resolve(o.r[F_EGAMMA], b); p.ebeta = (const float*)resolve(o.r[F_EBETA], b);
+                    p.ered = (double*)resolve(o.r[F_ERED], b);
+                    p.ey2 = resolve(o.r[F_EY2], b); p.estats2 = (const double*)resolve(o.r[F_ESTATS2], b);
+                    p.ered2 = (double*)resolve(o.r[F_ERED2], b);
+                }
+                plan_fconv_tiles(net, g);
+                for (int i = 0; i < kMaxGroup; ++i) {
+                    if (i >= n) { g.start[i] = INT_MAX; continue; }
+                    FConvProb& p = g.p[i];
+                    g.start[i] = tot; tot += p.nimg * p.tpi * (p.Ncol / p.BN);
+                    lds = std::max(lds, fconv_lds_bytes(p, (int)net->esz));
+                }
+                g.total_tiles = tot;
+                if (used_blocks) *used_blocks = tot;
+                err = launch_fconv(g, dt, lds, s);
             } break;
             case OP_WGRAD: {
                 WgradGroup g; g.nprob = n; int tot = 0;
@@ -1772,9 +2045,17 @@ static lp_status run_programs(lp_net* net, const std::vector<const Program*>& pr
     return LP_OK;
 }
 
+// narrow networks run the folded programs; the fixed summation order of the deterministic mode keeps the plain ones
+static bool folded(const lp_net* net) { return net->narrow && !net->deterministic; }
+
 // stream lane of every selected module, in the order the programs are collected
 static std::vector<int> lanes_of(const lp_net* net, uint32_t module_mask) {
     std::vector<int> out;
+    // the folded programs: one launch holds the tiles of all modules, whatever their widths, so lanes would only split it
+    if (folded(net) && !net->lanes_set) {
+        for (int k = 0; k < net->K; ++k) if ((module_mask >> k) & 1u) out.push_back(0);
+        return out;
+    }
     for (int k = 0; k < net->K; ++k)
         if ((module_mask >> k) & 1u) out.push_back(k < (int)net->lane.size() ? net->lane[k] : 0);
     return out;
@@ -1831,6 +2112,7 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
     lp_net* net = new lp_net();
     net->K = K; net->dtype = dtype; net->eps = bn_eps; net->esz = dtype == LP_BF16 ? 2 : 4;
     net->keep_gradients = g_keep_gradients;
+    net->narrow = true;
     net->mods.resize(K);
     net->saved_x.assign(K, nullptr);
     net->saved_y.assign(K, nullptr);
@@ -1898,6 +2180,7 @@ lp_status lp_net_destroy(struct lp_net* net) {
 
 lp_status lp_net_set_stream_lanes(struct lp_net* net, const int* lanes) {
     if (!net) return fail(LP_ERR_INVALID_ARG, "net is NULL");
+    net->lanes_set = true;
     if (!lanes) { net->lane.assign(net->K, 0); return LP_OK; }
     for (int k = 0; k < net->K; ++k)
         if (lanes[k] < 0 || lanes[k] > 3) return fail(LP_ERR_INVALID_ARG, "lanes[%d] = %d outside [0, 3]", k, lanes[k]);
@@ -2169,7 +2452,7 @@ lp_status lp_module_forward(struct lp_net* net, void* stream, uint32_t module_ma
             if (!y || !y[k]) return fail(LP_ERR_INVALID_ARG, "y[%d] is NULL", k);
             if (misaligned(y[k])) return fail(LP_ERR_INVALID_ARG, "y[%d] is not 16-byte aligned", k);
         } else if (!logits) return fail(LP_ERR_INVALID_ARG, "logits is NULL");
-        progs.push_back(&net->mods[k].fwd);
+        progs.push_back(folded(net) ? &net->mods[k].ffwd : &net->mods[k].fwd);
     }
     Bindings b; b.ws = net->ws; b.x = x; b.params = params; b.y = y; b.logits = logits;
     const std::vector<int> lanes = lanes_of(net, module_mask);
@@ -2255,7 +2538,7 @@ lp_status lp_module_backward(struct lp_net* net, void* stream, uint32_t module_m
         const bool opt_dx = !m.has_stem && k == 0 && dx && dx[0];
         if (needs_dx && (!dx || !dx[k])) return fail(LP_ERR_INVALID_ARG, "dx[%d] is NULL", k);
         if ((needs_dx || opt_dx) && misaligned(dx[k])) return fail(LP_ERR_INVALID_ARG, "dx[%d] is not 16-byte aligned", k);
-        progs.push_back(opt_dx ? &m.bwd_dx0 : &m.bwd);
+        progs.push_back(folded(net) ? (opt_dx ? &m.fbwd_dx0 : &m.fbwd) : (opt_dx ? &m.bwd_dx0 : &m.bwd));
     }
     Bindings b; b.ws = net->ws; b.x = net->saved_x.data(); b.params = params; b.dparams = dparams; b.dy = dy; b.dx = dx;
     if (net->fused_update) { b.vel = net->fu_vel.data(); b.master = net->fu_master.data(); }
@@ -2290,7 +2573,7 @@ lp_status lp_local_step(struct lp_net* net, void* stream, uint32_t module_mask, 
         const bool opt_dx = !m.has_stem && k == 0 && dx && dx[0];
         if (needs_dx && (!dx || !dx[k])) return fail(LP_ERR_INVALID_ARG, "dx[%d] is NULL", k);
         if ((needs_dx || opt_dx) && misaligned(dx[k])) return fail(LP_ERR_INVALID_ARG, "dx[%d] is not 16-byte aligned", k);
-        progs.push_back(opt_dx ? &m.step_dx0 : &m.step);
+        progs.push_back(folded(net) ? (opt_dx ? &m.fstep_dx0 : &m.fstep) : (opt_dx ? &m.step_dx0 : &m.step));
     }
     hipStream_t s = (hipStream_t)stream;
     // loss[k] = 0 for the selected modules, ahead of the fork (the loss kernels accumulate with atomics)

@@ -4,68 +4,11 @@
 // channel index fastest, fp32 arithmetic, wavefront/LDS reductions, one atomic per channel per workgroup.
 #include "lp_kernels.h"
 #include "lp_mma.h"
+#include "lp_vec.h"
 
 namespace lp {
 
 namespace {
-
-template <typename T> struct Vec {
-    static constexpr int N = 16 / (int)sizeof(T);
-    __device__ static __forceinline__ void load(const T* p, float (&f)[N]) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(p);
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(v[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                f[2 * e] = __uint_as_float(v[e] << 16);
-                f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u);
-            }
-        }
-    }
-    // the 16 bytes as loaded, and their conversion: kernels that want many loads in flight issue all load_raw first
-    __device__ static __forceinline__ u32x4 load_raw(const T* p) { return *reinterpret_cast<const u32x4*>(p); }
-    __device__ static __forceinline__ void unpack(const u32x4& v, float (&f)[N]) {
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(v[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                f[2 * e] = __uint_as_float(v[e] << 16);
-                f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u);
-            }
-        }
-    }
-    __device__ static __forceinline__ void store(T* p, const float (&f)[N]) {
-        u32x4 v;
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(f[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                v[e] = pack_bf16x2(f[2 * e], f[2 * e + 1]);
-        }
-        *reinterpret_cast<u32x4*>(p) = v;
-    }
-};
-
-__device__ __forceinline__ void bn_coeffs(const double* stats, const float* gamma, const float* beta, int c, int C,
-                                          int M, float eps, float& sc, float& sh, float& mean, float& invstd) {
-    const double inv_m = 1.0 / (double)M;          // the same for every channel: the compiler hoists it out of loops
-    double s1 = 0.0, s2 = 0.0;
-    const int ns = stat_stripes(C);
-    for (int st = 0; st < ns; ++st) { s1 += stats[st * 2 * C + c]; s2 += stats[st * 2 * C + C + c]; }
-    const double mu = s1 * inv_m;
-    double var = s2 * inv_m - mu * mu;
-    if (var < 0.0) var = 0.0;
-    mean = (float)mu;
-    invstd = rsqrtf((float)var + eps);
-    sc = gamma[c] * invstd;
-    sh = beta[c] - mean * sc;
-}
 
 template <typename G> __device__ __forceinline__ int find_problem(const G& g, int bid) {
     int pi = 0;
@@ -73,8 +16,6 @@ template <typename G> __device__ __forceinline__ int find_problem(const G& g, in
         if (bid >= g.p[i].block_start) pi = i;
     return pi;
 }
-
-constexpr int kMaxC = 2048;
 
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_sum(float v, float* s_tmp);
@@ -377,8 +318,8 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
         float sc, sh, mu, is;
         bn_coeffs(P.stats, P.gamma, P.beta, c, C, M, g.eps, sc, sh, mu, is);
         const double inv_m = 1.0 / (double)M;
-        double rs0 = 0.0, rs1 = 0.0;
-        for (int st = 0; st < stat_stripes(C); ++st) { rs0 += P.red[st * 2 * C + c]; rs1 += P.red[st * 2 * C + C + c]; }
+        double rs0, rs1;
+        stripe_sums(P.red, c, C, rs0, rs1);
         const float r0 = (float)(rs0 * inv_m), r1 = (float)(rs1 * inv_m);
         const float k1 = P.gamma[c] * is;
         const float k2 = k1 * is * r1;

@@ -1,0 +1,468 @@
+// Narrow convolutions (16 / 32 / 64 channels, forward and data-gradient) with the batch-norm passes around them folded in.
+//
+// A layer of the CIFAR-sized networks moves 0.1 to 16 MB and computes 0.1 to 1.2 GFLOP: 1 to 4 us of the chip.  What such a
+// layer costs is the number of dependent launches and, inside a launch, the number of dependent trips to memory.  As
+// separate kernels a unit is conv, BN apply (forward) and BN reduce, BN apply, data-gradient (backward), 2 + 3 launches,
+// and an implicit GEMM whose k-tiles are loaded one after the other.  Here a unit is one launch each way:
+//   * the window of input pixels a tile reads (its rows and a halo) is requested once, all of it; while it is under way
+//     the batch-norm coefficients are computed from the summed statistics; then the window is transformed (BN [+ skip]
+//     [ReLU], or the BN backward of g and y) and written to LDS.  The tile that owns a pixel also stores the transformed
+//     value, which the skip path and the filter gradient need.
+//   * the taps read their fragments from the window; filter fragments go from memory straight into registers, D k-steps
+//     ahead (a wave needs each of them once, so LDS would only add a barrier).
+//   * the epilogue adds the skip gradient, stores 16-byte vectors, and sums either the statistics of the stored result
+//     (forward) or the backward sums of the batch norm(s) the result arrives at.
+// Tiles are whole rows of one image.  One kernel serves every width (a tile picks its shape by its problem), so that
+// modules of different width share a launch: 4096 / BN pixels x BN channels per workgroup of four waves.
+#include <algorithm>
+
+#include "lp_kernels.h"
+#include "lp_mma.h"
+#include "lp_vec.h"
+
+namespace lp {
+namespace {
+
+constexpr int FC_NT = 256;
+constexpr int FC_COEF = 0;                         // 5 x 64 floats: transform coefficients
+constexpr int FC_ECOEF = 5 * 64 * 4;               // 6 x 32 floats: sc, sh, mean, invstd of ey; mean, invstd of ey2
+constexpr int FC_FILT = FC_ECOEF + 6 * 32 * 4;     // filter fragments of the tile; behind the contraction: 16 x BN x 4 partial sums
+// then the input window, later the result tile
+// (fp32 with 64 channels: 36 k-steps in a ring of 18, so that three workgroups still fit a compute unit)
+constexpr int FC_RING = 18;
+__host__ __device__ inline int fconv_filt_bytes(int S, int BN) { const int f = (S < FC_RING ? S : FC_RING) * BN * 64, r = 16 * BN * 16; return f > r ? f : r; }
+
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// x + (x of the lane N places to the right in the same row of 16 lanes)
+template <int N> __device__ __forceinline__ float ror_add(float x) {
+    return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x120 | N, 0xf, 0xf, true));
+}
+
+// all k-steps of the first NM micro-tiles of a wave: fragments of the next step are requested ahead of this one's products
+template <typename T, bool PAIR, int MT, int NT, int NM>
+__device__ __forceinline__ void fconv_mma_steps(const char* fb, const char* const (&ab)[MT], int atab, int S, int lg, f32x4 (&acc)[MT][NT]) {
+    auto fetch = [&](int s, u32x4 (&af)[NM], u32x4 (&bf)[NT]) {
+        int off;
+        if (PAIR) {
+            const int t0 = __builtin_amdgcn_readlane(atab, 2 * s), t1 = __builtin_amdgcn_readlane(atab, 2 * s + 1);
+            off = lg >= 2 ? t1 : t0;
+        } else off = __builtin_amdgcn_readlane(atab, s);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) bf[j] = *reinterpret_cast<const u32x4*>(fb + (s * NT + j) * 1024);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) af[i] = *reinterpret_cast<const u32x4*>(ab[i] + off);
+    };
+    auto mma = [&](const u32x4 (&af)[NM], const u32x4 (&bf)[NT]) {
+        if constexpr (sizeof(T) == 4) {            // the four products of a k-step go round the accumulators: no chain of dependent ones
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < NM; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(af[i][e]), __uint_as_float(bf[j][e]), acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NM; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) Mma<T, 16>::run(af[i], bf[j], acc[i][j]);
+        }
+    };
+    u32x4 a0[NM], b0[NT], a1[NM], b1[NT];
+    fetch(0, a0, b0);
+    int s = 0;
+    for (; s + 2 <= S; s += 2) {
+        fetch(s + 1, a1, b1);
+        mma(a0, b0);
+        fetch(min(s + 2, S - 1), a0, b0);
+        mma(a1, b1);
+    }
+    if (s < S) mma(a0, b0);
+}
+template <typename T, int MT, int NT, int NM>
+__device__ __forceinline__ void fconv_mma(const char* fb, const char* const (&ab)[MT], int atab, int S, bool pair, int lg, f32x4 (&acc)[MT][NT]) {
+    if constexpr (sizeof(T) == 2) {
+        if (pair) { fconv_mma_steps<T, true, MT, NT, NM>(fb, ab, atab, S, lg, acc); return; }
+    }
+    fconv_mma_steps<T, false, MT, NT, NM>(fb, ab, atab, S, lg, acc);
+}
+
+template <typename T, int BN>
+__device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, const float eps, char* const lds) {
+    constexpr int EPV = 16 / (int)sizeof(T);
+    constexpr int NT = BN / 16, MT = 4 / NT;       // micro-tiles of a wave: MT of pixels (every fourth), NT of channels
+    constexpr int CH = 4 * EPV;                    // channels of a k-step
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lr = lane & 15, lg = lane >> 4;
+
+    // ---- tile ----------------------------------------------------------------------------------------
+    const int lgt = P.Ncol == BN ? 0 : P.Ncol == 2 * BN ? 1 : 2;     // log2 of the column tiles
+    const int tt = t >> lgt, tn = t & ((1 << lgt) - 1);
+    const int n = P.tdiv ? (int)(((unsigned long long)(unsigned)tt * P.tdiv) >> 32) : tt;
+    const int a0 = (tt - n * P.tpi) * P.TH;
+    const int OB = P.OB, Cin = P.Cin, WW = P.WW, IH = P.IH, IW = P.IW;
+    const int px = min((int)P.TH, P.OA - a0) * OB;
+    const int n0 = tn * BN;
+    const int PB = Cin * (int)sizeof(T) + 16;      // bytes between window pixels: the 16 lanes of a fragment on distinct banks
+
+    float* const s_cf = reinterpret_cast<float*>(lds + FC_COEF);
+    float* const s_ec = reinterpret_cast<float*>(lds + FC_ECOEF);
+    // ---- filter fragments: straight into LDS, one wave-load per (k-step, 16 output channels): lane -> filter row lr,
+    // channels of its k-group, which is also how a fragment is read back (consecutive lanes, 16 bytes each)
+    const bool pair = Cin < CH;                    // bf16, 16 channels: a k-step is two taps
+    const int ntaps = P.ntr * P.nts;
+    const int lgkc = Cin == 2 * CH ? 1 : Cin == 4 * CH ? 2 : 0;
+    const int S = fconv_ksteps(ntaps, Cin, (int)sizeof(T));
+    const int cl = pair ? (lg & 1) * EPV : lg * EPV;                 // the lane's channel offset inside a k-step
+    char* const s_filt = lds + FC_FILT;
+    float* const s_red = reinterpret_cast<float*>(s_filt);
+    char* const win = s_filt + fconv_filt_bytes(S, BN);
+    // Lane u holds where k-step u (pair: tap u) lies in a filter row and in the window, in bytes: 36 steps at most, computed
+    // once instead of in every iteration (readlane makes them scalar again).
+    int wtab, atab;
+    {
+        const int u = min(lane, max(pair ? ntaps : S, 1) - 1), tap = u >> lgkc, ch = (u & ((1 << lgkc) - 1)) * (CH * (int)sizeof(T));
+        const int nts = P.nts, tr = nts == 3 ? (tap * 11) >> 5 : nts == 2 ? tap >> 1 : tap, ts = tap - tr * nts;
+        wtab = ((P.r0 + P.rs * tr) * P.S + (P.s0 + P.ss * ts)) * Cin * (int)sizeof(T) + ch;
+        atab = ((P.dh0 + P.dhs * tr - P.dhmin) * WW + (P.dw0 + P.dws * ts - P.dwmin)) * PB + ch;
+    }
+    auto load_filters = [&](int i0, int i1) {      // wave-loads i0 .. i1 of (k-step, 16 output channels)
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.wt), 0, P.Ncol * P.ldw * (int)sizeof(T), 0x00020000);
+        const int row = ((n0 + lr) * P.ldw + cl) * (int)sizeof(T);
+        for (int i = i0 + wave; i < i1; i += 4) {
+            const int s = NT == 2 ? i >> 1 : i, j = NT == 2 ? i & 1 : 0;
+            int off = row;
+            if (pair) {                            // an odd number of taps: the last one's partner is zeros
+                const int o0 = __builtin_amdgcn_readlane(wtab, 2 * s), o1 = __builtin_amdgcn_readlane(wtab, 2 * s + 1);
+                off += lg >= 2 ? o1 : o0;
+                if (lg >= 2 && 2 * s + 1 >= ntaps) off = (int)0x80000000u;
+            } else off += __builtin_amdgcn_readlane(wtab, s);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(s_filt + (i < FC_RING * NT ? i : i - FC_RING * NT) * 1024), 16, off,
+                                                     j * 16 * P.ldw * (int)sizeof(T), 0, 0);
+        }
+    };
+    load_filters(0, min(S, FC_RING) * NT);
+
+    // ---- input window: request, coefficients, transform -------------------------------------------------
+    const int lgv = Cin == EPV * 2 ? 1 : Cin == EPV * 4 ? 2 : Cin == EPV * 8 ? 3 : 4;   // log2 vectors per pixel
+    const int kv = tid & ((1 << lgv) - 1), wp0 = tid >> lgv, wstep = FC_NT >> lgv;
+    const int WHW = P.WH * WW;
+    const int mode = P.mode;
+    const bool two = mode >= FX_BN_ADD;
+    const size_t img = (size_t)n * IH * IW * Cin;  // this image; offsets inside it fit 32 bits
+    const T* __restrict__ in = reinterpret_cast<const T*>(P.in) + img;
+    const T* __restrict__ in2 = reinterpret_cast<const T*>(P.in2) + img;
+    const T* __restrict__ addin = P.addin ? reinterpret_cast<const T*>(P.addin) + img : nullptr;
+    T* __restrict__ side = tn == 0 && P.side ? reinterpret_cast<T*>(P.side) + img : nullptr;
+    const int ihb = a0 * P.imul + P.dhmin, iwb = P.dwmin;
+    const int own0 = a0 * P.imul, own1 = min(IH, (a0 + P.TH) * P.imul);
+    constexpr int U = sizeof(T) == 4 ? 7 : 4;         // vectors of a trip per thread: a whole window of the usual sizes
+    u32x4 r1[U], r2[U];
+    unsigned off[U];                               // element offset inside the image
+    unsigned inside, owned;                        // per vector: an image pixel, one whose transformed value this tile stores
+    auto request = [&](int i0) {
+        inside = 0; owned = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int wp = wp0 + (i0 + u) * wstep;
+            const int wr = __mul24(wp, P.wdiv) >> 16, wc = wp - __mul24(wr, WW);
+            const int ih = ihb + wr, iw = iwb + wc;
+            const bool is = wp < WHW && (unsigned)ih < (unsigned)IH && (unsigned)iw < (unsigned)IW;
+            off[u] = is ? ((__umul24(ih, IW) + iw) << (lgv + (EPV == 8 ? 3 : 2))) + kv * EPV : 0u;
+            inside |= is ? 1u << u : 0u;
+            owned |= is && ih >= own0 && ih < own1 ? 1u << u : 0u;
+            r1[u] = Vec<T>::load_raw(in + off[u]);
+            if (two) r2[u] = Vec<T>::load_raw(in2 + off[u]);
+            else r2[u] = u32x4{0u, 0u, 0u, 0u};
+        }
+        if (!side) owned = 0;
+    };
+    if (S > 0) request(0);
+    // forward: value = (c0*a + c1) + (c2*b + c3), whatever the mode: c = (1, 0) for a tensor taken as it is, (0, 0) for none
+    if (wave == 0 && lane < Cin) {
+        const int Mi = P.nimg * IH * IW;
+        float sc = 1.f, sh = 0.f, mu, is;
+        if (mode != FX_PLAIN) bn_coeffs(P.stats, P.gamma, P.beta, lane, Cin, Mi, eps, sc, sh, mu, is);
+        s_cf[lane] = sc; s_cf[64 + lane] = sh;
+        if (mode == FX_BWD) {
+            const double inv_m = 1.0 / (double)Mi;
+            double rs0, rs1;
+            stripe_sums(P.stats2, lane, Cin, rs0, rs1);
+            const float k1 = sc;
+            const float k2 = k1 * is * (float)(rs1 * inv_m);
+            s_cf[128 + lane] = k1; s_cf[192 + lane] = k2; s_cf[256 + lane] = k2 * mu - k1 * (float)(rs0 * inv_m);
+            if (t == 0 && P.side) {
+                const_cast<float*>(P.gamma2)[lane] = (float)rs1;
+                const_cast<float*>(P.beta2)[lane] = (float)rs0;
+            }
+        }
+    }
+    if (wave == 1 && lane < Cin && mode != FX_BWD) {
+        float sc = mode == FX_BN_ADD ? 1.f : 0.f, sh = 0.f, mu, is;
+        if (mode == FX_BN_BN) bn_coeffs(P.stats2, P.gamma2, P.beta2, lane, Cin, P.nimg * IH * IW, eps, sc, sh, mu, is);
+        s_cf[128 + lane] = sc; s_cf[192 + lane] = sh;
+    }
+    if (wave == 2 && lane < BN && P.ey) {
+        float sc, sh, mu, is;
+        bn_coeffs(P.estats, P.egamma, P.ebeta, n0 + lane, P.Ncol, P.nimg * P.OH * P.OW, eps, sc, sh, mu, is);
+        s_ec[lane] = sc; s_ec[32 + lane] = sh; s_ec[64 + lane] = mu; s_ec[96 + lane] = is;
+    }
+    if (wave == 3 && lane < BN && P.ey2) {         // a projection's batch norm: no ReLU behind it, scale and shift are not needed
+        float sc, sh, mu, is;
+        bn_coeffs(P.estats2, P.egamma, P.ebeta, n0 + lane, P.Ncol, P.nimg * P.OH * P.OW, eps, sc, sh, mu, is);
+        s_ec[128 + lane] = mu; s_ec[160 + lane] = is;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0): this wave's filter fragments are in LDS (the window is needed next anyway)
+    __syncthreads();
+    if (S > 0) {
+        float c0[EPV], c1[EPV], c2[EPV], c3[EPV], c4[EPV];
+        auto coef = [&](int q, float (&c)[EPV]) {
+#pragma unroll
+            for (int e = 0; e < EPV; e += 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(s_cf + q * 64 + kv * EPV + e);
+                c[e] = v[0]; c[e + 1] = v[1]; c[e + 2] = v[2]; c[e + 3] = v[3];
+            }
+        };
+        coef(0, c0); coef(1, c1); coef(2, c2); coef(3, c3);
+        const bool relu = P.relu != 0;
+        auto put = [&](int i0, int u, u32x4 v) {
+            const int wp = wp0 + (i0 + u) * wstep;
+            if (!((inside >> u) & 1u)) v = u32x4{0u, 0u, 0u, 0u};
+            if (wp < WHW) *reinterpret_cast<u32x4*>(win + __mul24(wp, PB) + kv * 16) = v;
+            if ((owned >> u) & 1u) *reinterpret_cast<u32x4*>(side + off[u]) = v;
+        };
+        for (int i0 = 0;;) {
+            if (mode == FX_BWD) {
+                coef(4, c4);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float a[EPV], b[EPV], o[EPV];
+                    Vec<T>::unpack(r1[u], a);
+                    Vec<T>::unpack(r2[u], b);
+                    if (relu) {
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) a[e] = fmaf(c0[e], b[e], c1[e]) > 0.f ? a[e] : 0.f;
+                    }
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) o[e] = c2[e] * a[e] - c3[e] * b[e] + c4[e];
+                    if (addin) {
+                        Vec<T>::load(addin + off[u], a);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) o[e] += a[e];
+                    }
+                    put(i0, u, Vec<T>::pack(o));
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float a[EPV], b[EPV], o[EPV];
+                    Vec<T>::unpack(r1[u], a);
+                    Vec<T>::unpack(r2[u], b);
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c0[e], a[e], c1[e]) + fmaf(c2[e], b[e], c3[e]);
+                    if (relu) {
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) o[e] = fmaxf(o[e], 0.f);
+                    }
+                    put(i0, u, Vec<T>::pack(o));
+                }
+            }
+            i0 += U;
+            if (i0 * wstep >= WHW) break;
+            request(i0);
+        }
+    }
+    __syncthreads();
+
+    // ---- what the epilogue reads from memory, ahead of the contraction ----------------------------------------
+    constexpr int LGN = BN / EPV == 2 ? 1 : BN / EPV == 4 ? 2 : 3;  // log2 vectors per result pixel
+    constexpr int ER = FC_NT >> LGN, EI = 4096 / BN / ER;                                // pixel rows per pass, passes
+    const int ev = tid & ((1 << LGN) - 1), er = tid >> LGN;
+    const size_t oimg = (size_t)n * P.OH * P.OW * P.Ncol;
+    const T* __restrict__ add0 = reinterpret_cast<const T*>(P.add0) + oimg;
+    const T* __restrict__ ey = reinterpret_cast<const T*>(P.ey) + oimg;
+    const T* __restrict__ ey2 = reinterpret_cast<const T*>(P.ey2) + oimg;
+    u32x4 xa[EI], xe[EI], xf[EI];
+    int oo[EI];
+#pragma unroll
+    for (int i = 0; i < EI; ++i) {
+        const int p = er + i * ER;
+        const int a = __mul24(p, P.odiv) >> 16, b = p - __mul24(a, OB);
+        oo[i] = p < px ? (__mul24((a0 + a) * P.omul + P.ooh, P.OW) + b * P.omul + P.oow) * P.Ncol + n0 + ev * EPV : -1;
+        const unsigned o = p < px ? (unsigned)oo[i] : 0u;
+        if (P.add0) xa[i] = Vec<T>::load_raw(add0 + o);
+        if (P.ey) xe[i] = Vec<T>::load_raw(ey + o);
+        if (P.ey2) xf[i] = Vec<T>::load_raw(ey2 + o);
+    }
+
+    // ---- contraction ------------------------------------------------------------------------------------------
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nmt = (px + 15) >> 4;                // micro-tiles of 16 pixels in this tile
+    const char* ab[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int p = min((wave + 4 * i) * 16 + lr, px - 1);
+        const int a = __mul24(p, P.odiv) >> 16, b = p - __mul24(a, OB);
+        ab[i] = win + __mul24(__mul24(a * P.imul, WW) + b * P.imul, PB) + cl * (int)sizeof(T);
+    }
+    const char* const fb = s_filt + lane * 16;
+    const int nm = (nmt - wave + 3) >> 2;          // micro-tiles of this wave; the loops compute 1, 2 or 4 without a branch per tile
+    auto contract = [&](int tab, int slot, int steps) {
+        const char* const fs = fb + slot * (NT * 1024);
+        if (MT == 4 && nm > 2) fconv_mma<T, MT, NT, 4>(fs, ab, tab, steps, pair, lg, acc);
+        else if (nm > 1) fconv_mma<T, MT, NT, 2>(fs, ab, tab, steps, pair, lg, acc);
+        else fconv_mma<T, MT, NT, 1>(fs, ab, tab, steps, pair, lg, acc);
+    };
+    if (S > 0 && S <= FC_RING) contract(atab, 0, S);
+    else if (S > 0) {                              // twice the ring: its halves are refilled as they are done with
+        constexpr int H = FC_RING / 2;
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            if (c == 2) {                          // the refills of both halves have landed, in every wave
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+                __syncthreads();
+            }
+            contract(__builtin_amdgcn_ds_bpermute((lane + H * c) * 4, atab), (c & 1) * H, H);
+            if (c < 2) {
+                __syncthreads();
+                load_filters((FC_RING + c * H) * NT, (FC_RING + (c + 1) * H) * NT);
+            }
+        }
+    }
+
+    // ---- result tile through LDS, one 16-byte vector per access -------------------------------------------------
+    constexpr int SP = BN + 4;
+    float* const res = reinterpret_cast<float*>(win);
+    __syncthreads();                               // every wave is done with the window
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+        if (wave + 4 * i < nmt) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) res[((wave + 4 * i) * 16 + lg * 4 + r) * SP + j * 16 + lr] = acc[i][j][r];
+        }
+    __syncthreads();
+    T* __restrict__ out = reinterpret_cast<T*>(P.out) + oimg;
+    float q1[EPV], q2[EPV], q3[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) { q1[e] = 0.f; q2[e] = 0.f; q3[e] = 0.f; }
+    auto ecoef = [&](int q, float (&c)[EPV]) {
+#pragma unroll
+        for (int e = 0; e < EPV; e += 4) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(s_ec + q * 32 + ev * EPV + e);
+            c[e] = v[0]; c[e + 1] = v[1]; c[e + 2] = v[2]; c[e + 3] = v[3];
+        }
+    };
+    const bool erelu = P.erelu != 0;
+#pragma unroll
+    for (int i = 0; i < EI; ++i) {
+        if (oo[i] < 0) continue;
+        const int p = er + i * ER;
+        float v[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; e += 4) {
+            const f32x4 q = *reinterpret_cast<const f32x4*>(res + p * SP + ev * EPV + e);
+            v[e] = q[0]; v[e + 1] = q[1]; v[e + 2] = q[2]; v[e + 3] = q[3];
+        }
+        if (P.add0) {
+            float a[EPV];
+            Vec<T>::unpack(xa[i], a);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) v[e] += a[e];
+        }
+        const u32x4 st = Vec<T>::pack(v);
+        *reinterpret_cast<u32x4*>(out + (unsigned)oo[i]) = st;
+        Vec<T>::unpack(st, v);                     // the sums describe the values as stored
+        if (P.ey) {
+            float y[EPV], c[EPV], d[EPV];
+            Vec<T>::unpack(xe[i], y);
+            if (P.ey2) {                             // before the mask: there is no ReLU between the sum and a projection's batch norm
+                float y2[EPV];
+                Vec<T>::unpack(xf[i], y2);
+                ecoef(4, c); ecoef(5, d);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) q3[e] += v[e] * ((y2[e] - c[e]) * d[e]);
+            }
+            if (erelu) {
+                ecoef(0, c); ecoef(1, d);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) v[e] = fmaf(c[e], y[e], d[e]) > 0.f ? v[e] : 0.f;
+            }
+            ecoef(2, c); ecoef(3, d);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * ((y[e] - c[e]) * d[e]); }
+        } else {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * v[e]; }
+        }
+    }
+    double* const sums = P.ey ? P.ered : P.ostats;
+    if (!sums) return;
+    // over the pixel rows of 16 lanes by rotation, then 16 partial sums per channel through LDS
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+        q1[e] = ror_add<8>(q1[e]); q2[e] = ror_add<8>(q2[e]);
+        if (LGN <= 2) { q1[e] = ror_add<4>(q1[e]); q2[e] = ror_add<4>(q2[e]); }
+        if (LGN <= 1) { q1[e] = ror_add<2>(q1[e]); q2[e] = ror_add<2>(q2[e]); }
+        if (P.ey2) {
+            q3[e] = ror_add<8>(q3[e]);
+            if (LGN <= 2) q3[e] = ror_add<4>(q3[e]);
+            if (LGN <= 1) q3[e] = ror_add<2>(q3[e]);
+        }
+    }
+    if (lr < (1 << LGN)) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e)
+            *reinterpret_cast<f32x4*>(s_red + ((wave * 4 + lg) * BN + ev * EPV + e) * 4) = f32x4{q1[e], q2[e], q3[e], 0.f};
+    }
+    __syncthreads();
+    if (tid < BN) {
+        f32x4 a = *reinterpret_cast<const f32x4*>(s_red + tid * 4);
+#pragma unroll
+        for (int w = 1; w < 16; ++w) a += *reinterpret_cast<const f32x4*>(s_red + (w * BN + tid) * 4);
+        const size_t at = (size_t)(blockIdx.x % stat_stripes(P.Ncol)) * 2 * P.Ncol + n0 + tid;      // this workgroup's stripe
+        atomicAdd(&sums[at], (double)a[0]);
+        atomicAdd(&sums[at + P.Ncol], (double)a[1]);
+        if (P.ey2) {
+            atomicAdd(&P.ered2[at], (double)a[0]);
+            atomicAdd(&P.ered2[at + P.Ncol], (double)a[2]);
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(FC_NT, 4) void fconv_kernel(const FConvGroup g) {
+    extern __shared__ __attribute__((aligned(16))) char s_lds[];
+    int pi = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxGroup; ++i) pi += (int)blockIdx.x >= g.start[i] ? 1 : 0;
+    const FConvProb& P = g.p[pi];
+    const int t = (int)blockIdx.x - g.start[pi];
+    // one field of every cache line of the problem: the lines are fetched together, not one by one where they are first used
+    asm volatile("" ::"s"(P.in), "s"(P.stats2), "s"(P.ey), "s"(P.ldw), "s"((int)P.S));
+    if (P.BN == 16) fconv_tile<T, 16>(P, t, g.eps, s_lds);
+    else fconv_tile<T, 32>(P, t, g.eps, s_lds);
+}
+
+}  // namespace
+
+size_t fconv_lds_bytes(const FConvProb& p, int esz) {
+    const size_t win = (size_t)p.WH * p.WW * (p.Cin * esz + 16);
+    const size_t res = (size_t)((p.TH * p.OB + 15) & ~15) * (p.BN + 4) * 4;
+    return FC_FILT + fconv_filt_bytes(fconv_ksteps(p.ntr * p.nts, p.Cin, esz), p.BN) + std::max(win, res);
+}
+
+hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s) {
+    if (g.total_tiles <= 0) return hipSuccess;
+    if (dtype == 1) hipLaunchKernelGGL(fconv_kernel<bf16_t>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
+    else hipLaunchKernelGGL(fconv_kernel<float>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
+    return hipGetLastError();
+}
+
+}  // namespace lp

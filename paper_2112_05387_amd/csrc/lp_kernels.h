@@ -38,6 +38,50 @@ struct ConvGroup {
     ConvProb p[kMaxGroup];
 };
 
+// The same contraction for narrow layers (16 / 32 / 64 channels), with the batch-norm passes in front of it and behind it
+// folded in (lp_fconv.hip).  What the taps read is a function of one or two stored tensors,
+//   FX_PLAIN   in
+//   FX_BN      [ReLU] bn(in)
+//   FX_BN_ADD  [ReLU] (bn(in) + in2)
+//   FX_BN_BN   [ReLU] (bn(in) + bn2(in2))
+//   FX_BWD     the batch-norm backward of in = g at y = in2: k1*g' - k2*y + k3  [+ addin]
+// evaluated while the input window of a tile is copied to LDS, and stored to `side` (layout of in) by the tile that owns
+// the pixel.  Behind the sum: optional addend, statistics of the stored result (ostats), and for a data-gradient the
+// backward sums of up to two batch norms whose arriving gradient this result is (ey: the tensor they normalise).
+enum FxMode { FX_PLAIN = 0, FX_BN, FX_BN_ADD, FX_BN_BN, FX_BWD };
+struct FConvProb {
+    const void *in, *in2, *addin;
+    void* side;
+    const double* stats; const float *gamma, *beta;          // the batch norm of `in` (FX_BWD: of in2)
+    const double* stats2; const float *gamma2, *beta2;       // FX_BN_BN: the batch norm of in2; FX_BWD: its backward sums, and where dgamma / dbeta go
+    const void* wt;
+    void* out;
+    const void* add0;
+    double* ostats;
+    const void* ey; const double* estats; const float *egamma, *ebeta; double* ered;
+    const void* ey2; const double* estats2; double* ered2;
+    int nimg, ldw;
+    short OA, OB, IH, IW, OH, OW, Cin, Ncol;
+    short TH, tpi, WH, WW;                                   // rows of a tile, tiles per image, input window of a tile
+    int wdiv, odiv;                                          // 2^16 / WW + 1, 2^16 / OB + 1: quotients of window / tile pixels
+    unsigned tdiv;                                           // 2^32 / tpi + 1: quotient of a tile index (0: one tile per image)
+    signed char imul, omul, ooh, oow, ntr, nts, dh0, dhs, dw0, dws, r0, rs, s0, ss, S;
+    signed char dhmin, dwmin, mode, relu, erelu;
+    signed char BN;                                          // output channels of a tile: 16 or 32
+};
+struct FConvGroup {
+    int nprob, total_tiles;
+    float eps; int pad_;
+    int start[kMaxGroup];                                    // first tile of every problem: one cache line, unused entries INT_MAX
+    FConvProb p[kMaxGroup];
+};
+static_assert(sizeof(FConvGroup) <= 4096, "kernel-argument block");
+// pixels of a tile with BN output channels: four waves hold at most 4 micro-tiles of 16 x 16 each
+constexpr int fconv_max_px(int BN) { return 4096 / BN; }
+// k-steps of a tile: 64 bytes of channels of one tap each (bf16 with 16 channels: two taps)
+__host__ __device__ inline int fconv_ksteps(int ntaps, int Cin, int esz) { return Cin * esz < 64 ? (ntaps + 1) / 2 : ntaps * (Cin * esz / 64); }
+size_t fconv_lds_bytes(const FConvProb& p, int esz);
+
 // Weight gradient:  dW[co, (r,s,ci)] (+)= sum_m dY[m, co] * X[n, ho*stride - pad + r, wo*stride - pad + s, ci]
 // split over `ksplit` slices of the reduction; partial results are added to dW with fp32 atomics.
 struct WgradProb {
@@ -173,6 +217,7 @@ constexpr int conv_win_max_slabs(int BM, int NW) { return BM == 512 ? 10 : 7; }
 hipError_t launch_conv(const ConvGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_conv_win(const ConvGroup& g, int cfg, hipStream_t s);
+hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
 int wgrad_fast_blocks(const WgradProb& p);
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
