@@ -98,7 +98,7 @@ static void* resolve(const Ref& r, const Bindings& b) {
 }
 
 enum OpType { OP_FILL = 0, OP_WTRANS, OP_CONV, OP_BN_APPLY, OP_POOL_FWD, OP_HEAD_FWD, OP_HEAD_BWD, OP_POOL_BWD,
-              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV };
+              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV, OP_FWGRAD };
 // tensor references of an OP_FCONV operation
 enum FcRef { F_IN = 0, F_IN2, F_ADDIN, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMMA2, F_BETA2, F_WT, F_OUT, F_ADD0, F_OSTATS,
              F_EY, F_ESTATS, F_EGAMMA, F_EBETA, F_ERED, F_EY2, F_ESTATS2, F_ERED2, F_COUNT };
@@ -113,12 +113,13 @@ struct Op {
     ConvProb conv;
     FConvProb fc;
     WgradProb wg;
+    FWgradProb fw;
     WtransProb wt;
     BnApplyProb bna;
     BnBwdProb bnb;
     PoolProb pool;
     HeadProb head;
-    int key() const { return type * 64 + cfg * 2 + (vec ? 1 : 0); }
+    int key() const { return type == OP_FWGRAD ? type * 64 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
 };
 typedef std::vector<Op> Step;              // operations of one module that may run concurrently
 typedef std::vector<Step> Program;         // steps run in order
@@ -450,6 +451,34 @@ struct Builder {
         o.r[0] = x; o.r[1] = dy; o.r[2] = dw;
         return o;
     }
+    // The narrow kernel's form of a filter-gradient operation, where it takes the layer: a tile is as many rows as the
+    // registers of a workgroup hold (and 256 pixels of 16 channels, 128 of more).  The operation keeps its plain form
+    // (cfg, wg): the update in the epilogue and the fixed summation order are the plain kernels'.
+    Op fwgrad(const Unit& u, Ref x, Ref dy, Ref dw) const {
+        Op o = wgrad(u, x, dy, dw);
+        const int esz = (int)net->esz;
+        auto width = [](int c) { return c == 16 || c == 32 || c == 64; };
+        const bool stem = u.cin <= 3 && u.R == 3;
+        if (!width(u.cout) || !(stem || width(u.cin)) || (u.R != 1 && u.R != 3) || u.Wo > 128 || u.H > 1024) return o;
+        FWgradProb p; memset(&p, 0, sizeof(p));
+        p.Cin = u.cin; p.Cout = u.cout; p.IH = u.H; p.IW = u.W; p.Ho = u.Ho; p.Wo = u.Wo; p.stride = u.stride; p.pad = u.pad; p.R = u.R;
+        const int CB = std::min(u.cout, 32), CI = std::min(u.cin, 32), vy = CB * esz / 16, vx = CI * esz / 16;
+        int TH = std::min(u.Ho, std::max(1, (u.cin <= 16 && u.cout <= 16 ? 256 : 128) / u.Wo));
+        for (;; --TH) {
+            if (TH < 1) return o;
+            p.TH = TH; p.WH = (TH - 1) * u.stride + u.R; p.WW = (u.Wo - 1) * u.stride + u.R;
+            const int pxpad = (TH * u.Wo + 31) & ~31, whw = p.WH * p.WW;
+            if (pxpad * vy <= fwgrad_y_vecs(esz) * 256 && (stem ? whw * u.cin <= kFwStemElems * 256 : whw * vx <= fwgrad_x_vecs(esz) * 256) &&
+                whw * p.WW < 65536 && whw * u.cin * u.cin < 65536 * 16 && fwgrad_lds_bytes(p, esz) <= 64 * 1024) break;
+        }
+        p.tpi = (u.Ho + TH - 1) / TH; p.ntiles = u.N * p.tpi;
+        if ((long)p.ntiles * p.tpi >= (1l << 32)) return o;
+        p.wdiv = 65536 / p.WW + 1; p.odiv = 65536 / u.Wo + 1; p.cdiv = 65536 / u.cin + 1;
+        p.tdiv = p.tpi == 1 ? 0 : (unsigned)((1ull << 32) / p.tpi + 1);
+        o.fw = p;
+        o.type = OP_FWGRAD;
+        return o;
+    }
     Op wtrans(const Unit& u, Ref w, Ref wt) const {
         Op o; o.type = OP_WTRANS;
         memset(&o.wt, 0, sizeof(o.wt));
@@ -536,7 +565,7 @@ static void attach_update(lp_net* net, int k, WsAlloc& ws) {
     for (Program* P : {&m.bwd, &m.bwd_dx0, &m.fbwd, &m.fbwd_dx0}) {
         for (Step& st : *P)
             for (Op& o : st) {
-                if (o.type != OP_WGRAD || o.r[2].space != SP_DPARAM) continue;
+                if ((o.type != OP_WGRAD && o.type != OP_FWGRAD) || o.r[2].space != SP_DPARAM) continue;
                 int t = -1;
                 for (size_t i = 0; i < m.tensors.size(); ++i)
                     if (m.tensors[i].kind == LP_T_CONV && m.tensors[i].grad_offset == o.r[2].off) t = (int)i;
@@ -687,7 +716,7 @@ static bool build_module_folded(lp_net* net, int k) {
             dgrad(u1, bwd_of(u1, g), A, Ref(), &u0, nullptr, s3);
             if (bp.has_proj) {
                 if (bp.proj_plain) {               // its filter gradient cannot wait for the tail: the next block reuses g's buffer
-                    s3.push_back(B.wgrad(bp.proj, bp.in, g, grad_ref(m, k, bp.proj.t_w)));
+                    s3.push_back(B.fwgrad(bp.proj, bp.in, g, grad_ref(m, k, bp.proj.t_w)));
                     Builder::Fx x; x.in = g;
                     if (need_in_grad) dgrad(bp.proj, x, Pp, Ref(), nullptr, nullptr, s3);
                 } else if (need_in_grad) dgrad(bp.proj, bwd_of(bp.proj, g), Pp, Ref(), nullptr, nullptr, s3);
@@ -707,7 +736,18 @@ static bool build_module_folded(lp_net* net, int k) {
             g = gin;
         }
         if (m.has_stem) Bw.push_back(Step{apply(m.stem, g)});
-        Bw.push_back(plain.back());
+        Step tail;                                 // the filter gradients, in the order of the plain program
+        for (int i = (int)m.bp.size() - 1; i >= 0; --i) {
+            const BlockPlan& bp = m.bp[i];
+            for (int j = 1; j >= 0; --j) {
+                const Unit& u = bp.main[j];
+                tail.push_back(B.fwgrad(u, j == 0 ? bp.in : W_(bp.ws_act[0]), W_(u.ws_dy), grad_ref(m, k, u.t_w)));
+                if (j == 1 && bp.has_proj && !bp.proj_plain)
+                    tail.push_back(B.fwgrad(bp.proj, bp.in, W_(bp.proj.ws_dy), grad_ref(m, k, bp.proj.t_w)));
+            }
+        }
+        if (m.has_stem) tail.push_back(B.fwgrad(m.stem, mk(SP_X, k, 0), W_(m.stem.ws_dy), grad_ref(m, k, m.stem.t_w)));
+        Bw.push_back(tail);
     }
     return true;
 }
@@ -1463,7 +1503,7 @@ static lp_status build_aux(lp_net* net, int j, WsAlloc& ws) {
         const Ref y = W_(u.ws_y), dyc = W_(u.ws_dy), st = W_(u.ws_stats), red = W_(u.ws_red);
         a.bwd_b.push_back(Step{B.bn_bwd(OP_BN_BWD_REDUCE, Mof(u), u.cout, gcur, y, dyc, st, P_(u.t_g), P_(u.t_b), red, G_(u.t_g), G_(u.t_b), u.relu)});
         a.bwd_b.push_back(Step{B.bn_bwd(OP_BN_BWD_APPLY, Mof(u), u.cout, gcur, y, dyc, st, P_(u.t_g), P_(u.t_b), red, G_(u.t_g), G_(u.t_b), u.relu)});
-        wg_tail.push_back(B.wgrad(u, i == 0 ? din : W_(a.ws_act[i - 1]), dyc, G_(u.t_w)));
+        wg_tail.push_back(B.fwgrad(u, i == 0 ? din : W_(a.ws_act[i - 1]), dyc, G_(u.t_w)));
         if (i > 0) {
             Step s;
             B.conv_dgrad(u, dyc, W_(u.ws_wt), W_(a.ws_gact[i - 1]), Ref(), Ref(), s);
@@ -1496,7 +1536,8 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
             if (o.r[4].space != SP_NONE) out_e += (double)c.M * c.Ncol;
             bytes = (in_e + w_e + out_e) * e;
         } break;
-        case OP_WGRAD: {
+        case OP_WGRAD:
+        case OP_FWGRAD: {
             const WgradProb& w = o.wg;
             flops = 2.0 * w.M * w.Cout * w.Kg;
             const double nimg = (double)w.M / ((double)w.Ho * w.Wo);
@@ -1728,6 +1769,46 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 if (used_blocks) *used_blocks = tot;
                 err = launch_fconv(g, dt, lds, s);
             } break;
+            case OP_FWGRAD: {
+                if (net->deterministic || net->fused_update) {       // fixed order, or the update in the epilogue: the plain kernels
+                    std::vector<Op> plain(n);
+                    std::vector<char> done(n, 0);
+                    for (int i = 0; i < n; ++i) { plain[i] = *ops[base + i]; plain[i].type = OP_WGRAD; }
+                    for (int i = 0; i < n && err == hipSuccess; ++i) {
+                        if (done[i]) continue;
+                        std::vector<const Op*> sub;
+                        for (int j = i; j < n; ++j)
+                            if (!done[j] && plain[j].key() == plain[i].key()) { sub.push_back(&plain[j]); done[j] = 1; }
+                        err = launch_group_impl(net, sub, 0, (int)sub.size(), b, s, nullptr, nullptr);
+                    }
+                    break;
+                }
+                FWgradGroup g; g.nprob = n; g.pad_[0] = g.pad_[1] = 0;
+                size_t lds = 0;
+                for (int i = 0; i < n; ++i) {
+                    const Op& o = *ops[base + i];
+                    FWgradProb& p = g.p[i]; p = o.fw;
+                    p.x = resolve(o.r[0], b); p.dy = resolve(o.r[1], b); p.dw = (float*)resolve(o.r[2], b);
+                    lds = std::max(lds, fwgrad_lds_bytes(p, (int)net->esz));
+                }
+                // one number of tiles per workgroup for the whole launch: four workgroups per compute unit
+                auto blocks = [](const FWgradProb& p) { return (p.Cout == 64 ? 2 : 1) * (p.Cin == 64 ? 2 : 1); };
+                long work = 0;
+                for (int i = 0; i < n; ++i) work += (long)g.p[i].ntiles * blocks(g.p[i]);
+                const int per = (int)std::max(1l, (work + 1023) / 1024);
+                int tot = 0;
+                for (int i = 0; i < kMaxGroup; ++i) {
+                    if (i >= n) { g.start[i] = INT_MAX; continue; }
+                    FWgradProb& p = g.p[i];
+                    p.nranges = (p.ntiles + per - 1) / per;
+                    p.per = (p.ntiles + p.nranges - 1) / p.nranges;
+                    p.nranges = (p.ntiles + p.per - 1) / p.per;
+                    g.start[i] = tot; tot += p.nranges * blocks(p);
+                }
+                g.total_tiles = tot;
+                if (used_blocks) *used_blocks = tot;
+                err = launch_fwgrad(g, dt, lds, s);
+            } break;
             case OP_WGRAD: {
                 WgradGroup g; g.nprob = n; int tot = 0;
                 for (int i = 0; i < n; ++i) g.p[i] = ops[base + i]->wg;
@@ -1888,6 +1969,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
     return err;
 }
 
+static bool is_wgrad(int key) { return key / 64 == OP_WGRAD || key / 64 == OP_FWGRAD; }
+
 // Order of the grouped launches of a set of independent programs (no launch happens here).
 static void plan_programs(const std::vector<const Program*>& progs, std::vector<std::vector<const Op*>>& plan) {
     const size_t np = progs.size();
@@ -1925,14 +2008,14 @@ static void plan_programs(const std::vector<const Program*>& progs, std::vector<
         // most programs share), and every other program with the same operation pending joins the launch.  Filter
         // gradients only when nothing else is ready, so that the tails of all programs meet and merge.
         bool only_wgrad = true;
-        for (auto& kc : keys) only_wgrad = only_wgrad && (kc.first / 64 == OP_WGRAD);
+        for (auto& kc : keys) only_wgrad = only_wgrad && is_wgrad(kc.first);
         size_t lead = np, lead_left = 0;
         for (size_t i = 0; i < np; ++i) {
             if (off[i]) continue;
             const Step& st = (*progs[i])[step[i]];
             bool eligible = false;
             for (size_t j = 0; j < st.size(); ++j)
-                eligible = eligible || (!issued[i][j] && (only_wgrad || st[j].key() / 64 != OP_WGRAD));
+                eligible = eligible || (!issued[i][j] && (only_wgrad || !is_wgrad(st[j].key())));
             const size_t left = progs[i]->size() - step[i];
             if (eligible && left > lead_left) { lead = i; lead_left = left; }
         }
@@ -1941,7 +2024,7 @@ static void plan_programs(const std::vector<const Program*>& progs, std::vector<
             for (size_t j = 0; j < st.size(); ++j) {
                 if (issued[lead][j]) continue;
                 const int key = st[j].key();
-                if (!only_wgrad && key / 64 == OP_WGRAD) continue;
+                if (!only_wgrad && is_wgrad(key)) continue;
                 int cnt = 0;
                 for (auto& kc : keys) if (kc.first == key) cnt = kc.second;
                 if (cnt > best_cnt || (cnt == best_cnt && key < best_key)) { best_key = key; best_cnt = cnt; }

@@ -107,6 +107,27 @@ struct WgradGroup {
     WgradProb p[kMaxGroup];
 };
 
+// Filter gradient of a narrow layer (lp_fwgrad.hip): a workgroup walks over `per` tiles of whole image rows.
+struct FWgradProb {
+    const void *x, *dy;
+    float* dw;
+    int ntiles, per, nranges;                                // tiles, tiles of a workgroup, workgroups of a channel block
+    int wdiv, odiv, cdiv;                                    // 2^16 / WW + 1, 2^16 / Wo + 1, 2^16 / Cin + 1
+    unsigned tdiv;                                           // 2^32 / tpi + 1 (0: one tile per image)
+    short Cin, Cout, IH, IW, Ho, Wo, stride, pad, R, TH, tpi, WH, WW;
+};
+struct FWgradGroup {
+    int nprob, total_tiles;
+    int pad_[2];
+    int start[kMaxGroup];
+    FWgradProb p[kMaxGroup];
+};
+// 16-byte vectors of dY and of the input window a thread holds of a tile; elements of the window of an image-facing layer
+__host__ __device__ constexpr int fwgrad_y_vecs(int esz) { return esz == 2 ? 2 : 4; }
+__host__ __device__ constexpr int fwgrad_x_vecs(int esz) { return esz == 2 ? 3 : 6; }
+constexpr int kFwStemElems = 4;
+size_t fwgrad_lds_bytes(const FWgradProb& p, int esz);
+
 // filters [Cout][R][S][Cin] -> [Cin][R][S][Cout]
 struct WtransProb {
     const void* w;
@@ -218,6 +239,7 @@ hipError_t launch_conv(const ConvGroup& g, int dtype, int cfg, bool vec, hipStre
 hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_conv_win(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s);
+hipError_t launch_fwgrad(const FWgradGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
 int wgrad_fast_blocks(const WgradProb& p);
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
