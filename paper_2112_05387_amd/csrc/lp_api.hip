@@ -358,10 +358,7 @@ struct Builder {
         bool relu = false;
         Ref in, in2, addin, side, stats, gamma, beta, stats2, gamma2, beta2;
     };
-    // the most output channels a tile takes: its filter fragments stay below 20 KB of LDS (four workgroups per compute unit)
-    int fconv_max_bn(const FConvProb& p) const {
-        return p.Ncol >= 32 && fconv_ksteps(p.ntr * p.nts, p.Cin, (int)net->esz) * 32 * 64 <= 20 * 1024 ? 32 : 16;
-    }
+    static int fconv_max_bn(const FConvProb& p) { return p.Ncol >= 32 ? 32 : 16; }
     // pixels of a full-size tile: 16 KB of window at most for the wider layers
     static int fconv_px(const FConvProb& p, int BN) { return p.Ncol <= 16 ? fconv_max_px(BN) : std::min(fconv_max_px(BN), 128); }
     // the tile geometry of one problem: BN output channels and as many whole rows as fit max_px pixels
@@ -1599,14 +1596,13 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
 
 // Tile sizes of a grouped launch of the narrow kernel: the smallest tiles of which two per compute unit hold the whole
 // launch (the less a workgroup does, the shorter the launch), full-size tiles where even those are more.
-static void plan_fconv_tiles(const lp_net* net, FConvGroup& g) {
-    const Builder B{const_cast<lp_net*>(net)};
+static void plan_fconv_tiles(FConvGroup& g) {
     for (int level = 2; level >= 0; --level) {     // smallest tiles first
         long tiles = 0;
         for (int i = 0; i < g.nprob; ++i) {
             FConvProb& p = g.p[i];
-            const int BN = level < 2 ? B.fconv_max_bn(p) : 16;
-            const int px = level == 0 ? B.fconv_px(p, BN) : level == 1 ? B.fconv_px(p, BN) / 2 : 64;
+            const int BN = level < 2 ? Builder::fconv_max_bn(p) : 16;
+            const int px = level == 0 ? Builder::fconv_px(p, BN) : level == 1 ? Builder::fconv_px(p, BN) / 2 : 64;
             Builder::fconv_tile(p, BN, px);
             tiles += (long)p.nimg * p.tpi * (p.Ncol / p.BN);
         }
@@ -1739,6 +1735,9 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);
             } break;
             case OP_FCONV: {
+                // longest tiles first: the blocks of a launch are dispatched in order
+                std::stable_sort(ops.begin() + base, ops.begin() + base + n, [](const Op* x, const Op* y) {
+                    return x->fc.Cin * x->fc.ntr * x->fc.nts > y->fc.Cin * y->fc.ntr * y->fc.nts; });
                 FConvGroup g; g.nprob = n; g.eps = net->eps; g.pad_ = 0;
                 int tot = 0; size_t lds = 0;
                 for (int i = 0; i < n; ++i) {
@@ -1758,7 +1757,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.ey2 = resolve(o.r[F_EY2], b); p.estats2 = (const double*)resolve(o.r[F_ESTATS2], b);
                     p.ered2 = (double*)resolve(o.r[F_ERED2], b);
                 }
-                plan_fconv_tiles(net, g);
+                plan_fconv_tiles(g);
                 for (int i = 0; i < kMaxGroup; ++i) {
                     if (i >= n) { g.start[i] = INT_MAX; continue; }
                     FConvProb& p = g.p[i];

@@ -28,9 +28,11 @@ constexpr int FC_COEF = 0;                         // 5 x 64 floats: transform c
 constexpr int FC_ECOEF = 5 * 64 * 4;               // 6 x 32 floats: sc, sh, mean, invstd of ey; mean, invstd of ey2
 constexpr int FC_FILT = FC_ECOEF + 6 * 32 * 4;     // filter fragments of the tile; behind the contraction: 16 x BN x 4 partial sums
 // then the input window, later the result tile
-// (fp32 with 64 channels: 36 k-steps in a ring of 18, so that three workgroups still fit a compute unit)
-constexpr int FC_RING = 18;
-__host__ __device__ inline int fconv_filt_bytes(int S, int BN) { const int f = (S < FC_RING ? S : FC_RING) * BN * 64, r = 16 * BN * 16; return f > r ? f : r; }
+// More k-steps than the ring holds (64 channels; fp32 with 32): its halves of fconv_half(BN) steps are refilled as they are
+// done with, so that a tile can have 32 output channels (each column tile transforms the window again) and four workgroups
+// (three in fp32) still fit a compute unit.
+__host__ __device__ constexpr int fconv_half(int BN) { return BN == 32 ? 5 : 9; }
+__host__ __device__ inline int fconv_filt_bytes(int S, int BN) { const int R = 2 * fconv_half(BN), f = (S < R ? S : R) * BN * 64, r = 16 * BN * 16; return f > r ? f : r; }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
@@ -93,6 +95,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     constexpr int EPV = 16 / (int)sizeof(T);
     constexpr int NT = BN / 16, MT = 4 / NT;       // micro-tiles of a wave: MT of pixels (every fourth), NT of channels
     constexpr int CH = 4 * EPV;                    // channels of a k-step
+    constexpr int H = fconv_half(BN);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lr = lane & 15, lg = lane >> 4;
 
@@ -138,11 +141,13 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
                 off += lg >= 2 ? o1 : o0;
                 if (lg >= 2 && 2 * s + 1 >= ntaps) off = (int)0x80000000u;
             } else off += __builtin_amdgcn_readlane(wtab, s);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(s_filt + (i < FC_RING * NT ? i : i - FC_RING * NT) * 1024), 16, off,
+            int slot = i;
+            while (slot >= 2 * H * NT) slot -= 2 * H * NT;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(s_filt + slot * 1024), 16, off,
                                                      j * 16 * P.ldw * (int)sizeof(T), 0, 0);
         }
     };
-    load_filters(0, min(S, FC_RING) * NT);
+    load_filters(0, min(S, 2 * H) * NT);
 
     // ---- input window: request, coefficients, transform -------------------------------------------------
     const int lgv = Cin == EPV * 2 ? 1 : Cin == EPV * 4 ? 2 : Cin == EPV * 8 ? 3 : 4;   // log2 vectors per pixel
@@ -165,6 +170,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
         inside = 0; owned = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if ((i0 + u) * wstep >= WHW) continue;
             const int wp = wp0 + (i0 + u) * wstep;
             const int wr = __mul24(wp, P.wdiv) >> 16, wc = wp - __mul24(wr, WW);
             const int ih = ihb + wr, iw = iwb + wc;
@@ -237,6 +243,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
                 coef(4, c4);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
+                    if ((i0 + u) * wstep >= WHW) continue;
                     float a[EPV], b[EPV], o[EPV];
                     Vec<T>::unpack(r1[u], a);
                     Vec<T>::unpack(r2[u], b);
@@ -245,7 +252,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
                         for (int e = 0; e < EPV; ++e) a[e] = fmaf(c0[e], b[e], c1[e]) > 0.f ? a[e] : 0.f;
                     }
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) o[e] = c2[e] * a[e] - c3[e] * b[e] + c4[e];
+                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c2[e], a[e], fmaf(-c3[e], b[e], c4[e]));
                     if (addin) {
                         Vec<T>::load(addin + off[u], a);
 #pragma unroll
@@ -256,6 +263,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
+                    if ((i0 + u) * wstep >= WHW) continue;
                     float a[EPV], b[EPV], o[EPV];
                     Vec<T>::unpack(r1[u], a);
                     Vec<T>::unpack(r2[u], b);
@@ -318,19 +326,18 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
         else if (nm > 1) fconv_mma<T, MT, NT, 2>(fs, ab, tab, steps, pair, lg, acc);
         else fconv_mma<T, MT, NT, 1>(fs, ab, tab, steps, pair, lg, acc);
     };
-    if (S > 0 && S <= FC_RING) contract(atab, 0, S);
-    else if (S > 0) {                              // twice the ring: its halves are refilled as they are done with
-        constexpr int H = FC_RING / 2;
+    if (S > 0 && S <= 2 * H) contract(atab, 0, S);
+    else if (S > 0) {
 #pragma unroll 1
-        for (int c = 0; c < 4; ++c) {
-            if (c == 2) {                          // the refills of both halves have landed, in every wave
+        for (int c = 0; c * H < S; ++c) {
+            if (c >= 2) {                          // the refill of this half has landed, in every wave
                 __builtin_amdgcn_s_waitcnt(0x0f70);
                 __syncthreads();
             }
-            contract(__builtin_amdgcn_ds_bpermute((lane + H * c) * 4, atab), (c & 1) * H, H);
-            if (c < 2) {
+            contract(__builtin_amdgcn_ds_bpermute((lane + H * c) * 4, atab), (c & 1) * H, min(H, S - c * H));
+            if ((c + 2) * H < S) {
                 __syncthreads();
-                load_filters((FC_RING + c * H) * NT, (FC_RING + (c + 1) * H) * NT);
+                load_filters((c + 2) * H * NT, min((c + 3) * H, S) * NT);
             }
         }
     }
@@ -437,7 +444,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
 }
 
 template <typename T>
-__global__ __launch_bounds__(FC_NT, 4) void fconv_kernel(const FConvGroup g) {
+__global__ __launch_bounds__(FC_NT, sizeof(T) == 4 ? 3 : 4) void fconv_kernel(const FConvGroup g) {
     extern __shared__ __attribute__((aligned(16))) char s_lds[];
     int pi = 0;
 #pragma unroll
