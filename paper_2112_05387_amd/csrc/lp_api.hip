@@ -370,6 +370,23 @@ struct Builder {
         p.wdiv = 65536 / p.WW + 1; p.odiv = 65536 / p.OB + 1;
         p.tdiv = p.tpi == 1 ? 0 : (unsigned)((1ull << 32) / p.tpi + 1);
     }
+    // Mini-batches of 32 and more in bf16 take tiles in the order of the separate passes (FConvProb::ordered): such launches
+    // fill the chip with tiles of that size, and a bf16 network amplifies any other order of its sums to a rounding of every
+    // value within a few layers.  Smaller ones (and fp32) take the tiles that make a launch shortest.
+    bool fconv_exact(int nimg) const { return net->dtype == LP_BF16 && nimg >= 32; }
+    void fconv_order(FConvProb& p) const {
+        const int px = 8192 / p.Ncol, img = p.OA * p.OB;             // pixels of a trip of the separate reduction
+        if (!fconv_exact(p.nimg) || p.omul != 1 || p.ntr == 0 || (long)p.nimg * img > 256l * px) return;
+        FConvProb q = p;
+        fconv_tile(q, p.Ncol >= 32 ? 32 : 16, px);
+        q.ordered = 1; q.segs = 1;
+        if (img * 2 == px) q.segs = 2;
+        if (q.TH * q.OB * q.segs != px || q.OA % q.TH != 0) return;
+        q.WH = (short)((q.TH - 1) * q.imul + q.ntr);
+        if (q.WH * q.segs * q.WW * q.WW >= 65536 || fconv_lds_bytes(q, (int)net->esz) > (size_t)kFconvMaxLds) return;
+        p = q;
+    }
+    static int fconv_tiles(const FConvProb& p) { return (p.ordered ? (p.nimg + p.segs - 1) / p.segs : p.nimg) * p.tpi; }
     Op fconv(const ConvProb& c, const Fx& x, Ref wt, Ref out, Ref add0, Ref ostats) const {
         Op o; o.type = OP_FCONV;
         FConvProb& p = o.fc; memset(&p, 0, sizeof(p));
@@ -381,6 +398,7 @@ struct Builder {
         p.mode = x.mode; p.relu = x.relu;
         const int BN = fconv_max_bn(p);
         fconv_tile(p, BN, fconv_px(p, BN));
+        fconv_order(p);
         o.r[F_IN] = x.in; o.r[F_IN2] = x.in2; o.r[F_ADDIN] = x.addin; o.r[F_SIDE] = x.side;
         o.r[F_STATS] = x.stats; o.r[F_GAMMA] = x.gamma; o.r[F_BETA] = x.beta;
         o.r[F_STATS2] = x.stats2; o.r[F_GAMMA2] = x.gamma2; o.r[F_BETA2] = x.beta2;
@@ -724,7 +742,8 @@ static bool build_module_folded(lp_net* net, int k) {
             if (need_in_grad) {
                 const BlockPlan* pb = i > 0 ? &m.bp[i - 1] : nullptr;
                 const Unit *e = nullptr, *e2 = nullptr;
-                if (pb && !pb->post_relu) { e = &pb->main[1]; if (pb->has_proj && !pb->proj_plain) e2 = &pb->proj; summed = true; }
+                if (u0.stride == 2 && B.fconv_exact(u0.N)) {}      // (a parity class has every other pixel: the sums of those keep their own pass)
+                else if (pb && !pb->post_relu) { e = &pb->main[1]; if (pb->has_proj && !pb->proj_plain) e2 = &pb->proj; summed = true; }
                 else if (!pb && m.has_stem) { e = &m.stem; summed = true; }
                 Step s4;
                 dgrad(u0, bwd_of(u0, A), gin, bp.has_proj ? Pp : g, e, e2, s4);
@@ -732,7 +751,10 @@ static bool build_module_folded(lp_net* net, int k) {
             } else Bw.push_back(Step{apply(u0, A)});
             g = gin;
         }
-        if (m.has_stem) Bw.push_back(Step{apply(m.stem, g)});
+        if (m.has_stem) {
+            if (!summed) Bw.push_back(Step{reduce(m.stem, g)});
+            Bw.push_back(Step{apply(m.stem, g)});
+        }
         Step tail;                                 // the filter gradients, in the order of the plain program
         for (int i = (int)m.bp.size() - 1; i >= 0; --i) {
             const BlockPlan& bp = m.bp[i];
@@ -1601,6 +1623,7 @@ static void plan_fconv_tiles(FConvGroup& g) {
         long tiles = 0;
         for (int i = 0; i < g.nprob; ++i) {
             FConvProb& p = g.p[i];
+            if (p.ordered) { tiles += (long)Builder::fconv_tiles(p) * (p.Ncol / p.BN); continue; }
             const int BN = level < 2 ? Builder::fconv_max_bn(p) : 16;
             const int px = level == 0 ? Builder::fconv_px(p, BN) : level == 1 ? Builder::fconv_px(p, BN) / 2 : 64;
             Builder::fconv_tile(p, BN, px);
@@ -1761,7 +1784,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 for (int i = 0; i < kMaxGroup; ++i) {
                     if (i >= n) { g.start[i] = INT_MAX; continue; }
                     FConvProb& p = g.p[i];
-                    g.start[i] = tot; tot += p.nimg * p.tpi * (p.Ncol / p.BN);
+                    g.start[i] = tot; tot += Builder::fconv_tiles(p) * (p.Ncol / p.BN);
                     lds = std::max(lds, fconv_lds_bytes(p, (int)net->esz));
                 }
                 g.total_tiles = tot;

@@ -35,14 +35,18 @@ __host__ __device__ constexpr int fconv_half(int BN) { return BN == 32 ? 5 : 9; 
 __host__ __device__ inline int fconv_filt_bytes(int S, int BN) { const int R = 2 * fconv_half(BN), f = (S < R ? S : R) * BN * 64, r = 16 * BN * 16; return f > r ? f : r; }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
+// The kernel's argument where it lies in constant memory.  (Taken as an ordinary parameter the compiler keeps a private copy
+// of all 4 KB in scratch once a kernel has more than 300 uses of it.)
+typedef const __attribute__((address_space(4))) FConvProb FConvArg;
+typedef const __attribute__((address_space(4))) FConvGroup FConvGroupArg;
 
 // x + (x of the lane N places to the right in the same row of 16 lanes)
 template <int N> __device__ __forceinline__ float ror_add(float x) {
     return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x120 | N, 0xf, 0xf, true));
 }
 
-// all k-steps of the first NM micro-tiles of a wave: fragments of the next step are requested ahead of this one's products
-template <typename T, bool PAIR, int MT, int NT, int NM>
+// all k-steps of micro-tiles I0 .. I0 + NM of a wave: fragments of the next step are requested ahead of this one's products
+template <typename T, bool PAIR, int MT, int NT, int I0, int NM>
 __device__ __forceinline__ void fconv_mma_steps(const char* fb, const char* const (&ab)[MT], int atab, int S, int lg, f32x4 (&acc)[MT][NT]) {
     auto fetch = [&](int s, u32x4 (&af)[NM], u32x4 (&bf)[NT]) {
         int off;
@@ -53,7 +57,7 @@ __device__ __forceinline__ void fconv_mma_steps(const char* fb, const char* cons
 #pragma unroll
         for (int j = 0; j < NT; ++j) bf[j] = *reinterpret_cast<const u32x4*>(fb + (s * NT + j) * 1024);
 #pragma unroll
-        for (int i = 0; i < NM; ++i) af[i] = *reinterpret_cast<const u32x4*>(ab[i] + off);
+        for (int i = 0; i < NM; ++i) af[i] = *reinterpret_cast<const u32x4*>(ab[I0 + i] + off);
     };
     auto mma = [&](const u32x4 (&af)[NM], const u32x4 (&bf)[NT]) {
         if constexpr (sizeof(T) == 4) {            // the four products of a k-step go round the accumulators: no chain of dependent ones
@@ -63,12 +67,12 @@ __device__ __forceinline__ void fconv_mma_steps(const char* fb, const char* cons
                 for (int i = 0; i < NM; ++i)
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(af[i][e]), __uint_as_float(bf[j][e]), acc[i][j], 0, 0, 0);
+                        acc[I0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(af[i][e]), __uint_as_float(bf[j][e]), acc[I0 + i][j], 0, 0, 0);
         } else {
 #pragma unroll
             for (int i = 0; i < NM; ++i)
 #pragma unroll
-                for (int j = 0; j < NT; ++j) Mma<T, 16>::run(af[i], bf[j], acc[i][j]);
+                for (int j = 0; j < NT; ++j) Mma<T, 16>::run(af[i], bf[j], acc[I0 + i][j]);
         }
     };
     u32x4 a0[NM], b0[NT], a1[NM], b1[NT];
@@ -82,18 +86,20 @@ __device__ __forceinline__ void fconv_mma_steps(const char* fb, const char* cons
     }
     if (s < S) mma(a0, b0);
 }
-template <typename T, int MT, int NT, int NM>
+template <typename T, int MT, int NT, int I0, int NM>
 __device__ __forceinline__ void fconv_mma(const char* fb, const char* const (&ab)[MT], int atab, int S, bool pair, int lg, f32x4 (&acc)[MT][NT]) {
     if constexpr (sizeof(T) == 2) {
-        if (pair) { fconv_mma_steps<T, true, MT, NT, NM>(fb, ab, atab, S, lg, acc); return; }
+        if (pair) { fconv_mma_steps<T, true, MT, NT, I0, NM>(fb, ab, atab, S, lg, acc); return; }
     }
-    fconv_mma_steps<T, false, MT, NT, NM>(fb, ab, atab, S, lg, acc);
+    fconv_mma_steps<T, false, MT, NT, I0, NM>(fb, ab, atab, S, lg, acc);
 }
 
-template <typename T, int BN>
-__device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, const float eps, char* const lds) {
+// ORD (bf16, see FConvProb::ordered; 2: 64 channels): tiles of up to twice the pixels, two images where an image has 64,
+// and sums in the order of the passes they replace.
+template <typename T, int BN, int ORD>
+__device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float eps, char* const lds) {
     constexpr int EPV = 16 / (int)sizeof(T);
-    constexpr int NT = BN / 16, MT = 4 / NT;       // micro-tiles of a wave: MT of pixels (every fourth), NT of channels
+    constexpr int NT = BN / 16, MT = (ORD == 1 ? 8 : 4) / NT;       // micro-tiles of a wave: MT of pixels (every fourth), NT of channels
     constexpr int CH = 4 * EPV;                    // channels of a k-step
     constexpr int H = fconv_half(BN);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -102,10 +108,12 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     // ---- tile ----------------------------------------------------------------------------------------
     const int lgt = P.Ncol == BN ? 0 : P.Ncol == 2 * BN ? 1 : 2;     // log2 of the column tiles
     const int tt = t >> lgt, tn = t & ((1 << lgt) - 1);
-    const int n = P.tdiv ? (int)(((unsigned long long)(unsigned)tt * P.tdiv) >> 32) : tt;
-    const int a0 = (tt - n * P.tpi) * P.TH;
+    const int segs = ORD ? P.segs : 1;             // images of a tile (more than one: whole images)
+    const int ti = P.tdiv ? (int)(((unsigned long long)(unsigned)tt * P.tdiv) >> 32) : tt;
+    const int n = ti * segs, a0 = (tt - ti * P.tpi) * P.TH;
     const int OB = P.OB, Cin = P.Cin, WW = P.WW, IH = P.IH, IW = P.IW;
-    const int px = min((int)P.TH, P.OA - a0) * OB;
+    const int nseg = ORD ? min(segs, P.nimg - n) : 1;
+    const int spx = min((int)P.TH, P.OA - a0) * OB, px = spx * nseg;      // pixels of a segment, of the tile
     const int n0 = tn * BN;
     const int PB = Cin * (int)sizeof(T) + 16;      // bytes between window pixels: the 16 lanes of a fragment on distinct banks
 
@@ -130,7 +138,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
         wtab = ((P.r0 + P.rs * tr) * P.S + (P.s0 + P.ss * ts)) * Cin * (int)sizeof(T) + ch;
         atab = ((P.dh0 + P.dhs * tr - P.dhmin) * WW + (P.dw0 + P.dws * ts - P.dwmin)) * PB + ch;
     }
-    auto load_filters = [&](int i0, int i1) {      // wave-loads i0 .. i1 of (k-step, 16 output channels)
+    auto load_filters = [&](int i0, int i1) __attribute__((always_inline)) {      // wave-loads i0 .. i1 of (k-step, 16 output channels)
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.wt), 0, P.Ncol * P.ldw * (int)sizeof(T), 0x00020000);
         const int row = ((n0 + lr) * P.ldw + cl) * (int)sizeof(T);
         for (int i = i0 + wave; i < i1; i += 4) {
@@ -152,7 +160,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     // ---- input window: request, coefficients, transform -------------------------------------------------
     const int lgv = Cin == EPV * 2 ? 1 : Cin == EPV * 4 ? 2 : Cin == EPV * 8 ? 3 : 4;   // log2 vectors per pixel
     const int kv = tid & ((1 << lgv) - 1), wp0 = tid >> lgv, wstep = FC_NT >> lgv;
-    const int WHW = P.WH * WW;
+    const int SWH = P.WH, WHW = SWH * WW * nseg;       // window rows of a segment, window pixels
     const int mode = P.mode;
     const bool two = mode >= FX_BN_ADD;
     const size_t img = (size_t)n * IH * IW * Cin;  // this image; offsets inside it fit 32 bits
@@ -162,20 +170,23 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     T* __restrict__ side = tn == 0 && P.side ? reinterpret_cast<T*>(P.side) + img : nullptr;
     const int ihb = a0 * P.imul + P.dhmin, iwb = P.dwmin;
     const int own0 = a0 * P.imul, own1 = min(IH, (a0 + P.TH) * P.imul);
-    constexpr int U = sizeof(T) == 4 ? 7 : 4;         // vectors of a trip per thread: a whole window of the usual sizes
+    constexpr int U = sizeof(T) == 4 ? 7 : ORD ? 5 : 4;         // vectors of a trip per thread: a whole window of the usual sizes
     u32x4 r1[U], r2[U];
     unsigned off[U];                               // element offset inside the image
     unsigned inside, owned;                        // per vector: an image pixel, one whose transformed value this tile stores
-    auto request = [&](int i0) {
+    auto request = [&](int i0) __attribute__((always_inline)) {
         inside = 0; owned = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if ((i0 + u) * wstep >= WHW) continue;
             const int wp = wp0 + (i0 + u) * wstep;
-            const int wr = __mul24(wp, P.wdiv) >> 16, wc = wp - __mul24(wr, WW);
+            int wr = __mul24(wp, P.wdiv) >> 16;
+            const int wc = wp - __mul24(wr, WW);
+            int seg = 0;
+            if (ORD && wr >= SWH) { seg = IH; wr -= SWH; }
             const int ih = ihb + wr, iw = iwb + wc;
             const bool is = wp < WHW && (unsigned)ih < (unsigned)IH && (unsigned)iw < (unsigned)IW;
-            off[u] = is ? ((__umul24(ih, IW) + iw) << (lgv + (EPV == 8 ? 3 : 2))) + kv * EPV : 0u;
+            off[u] = is ? ((__umul24(seg + ih, IW) + iw) << (lgv + (EPV == 8 ? 3 : 2))) + kv * EPV : 0u;
             inside |= is ? 1u << u : 0u;
             owned |= is && ih >= own0 && ih < own1 ? 1u << u : 0u;
             r1[u] = Vec<T>::load_raw(in + off[u]);
@@ -197,7 +208,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
             stripe_sums(P.stats2, lane, Cin, rs0, rs1);
             const float k1 = sc;
             const float k2 = k1 * is * (float)(rs1 * inv_m);
-            s_cf[128 + lane] = k1; s_cf[192 + lane] = k2; s_cf[256 + lane] = k2 * mu - k1 * (float)(rs0 * inv_m);
+            s_cf[128 + lane] = k1; s_cf[192 + lane] = k2; s_cf[256 + lane] = fmaf(k2, mu, -(k1 * (float)(rs0 * inv_m)));
             if (t == 0 && P.side) {
                 const_cast<float*>(P.gamma2)[lane] = (float)rs1;
                 const_cast<float*>(P.beta2)[lane] = (float)rs0;
@@ -252,7 +263,7 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
                         for (int e = 0; e < EPV; ++e) a[e] = fmaf(c0[e], b[e], c1[e]) > 0.f ? a[e] : 0.f;
                     }
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c2[e], a[e], fmaf(-c3[e], b[e], c4[e]));
+                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c2[e], a[e], -(c3[e] * b[e])) + c4[e];
                     if (addin) {
                         Vec<T>::load(addin + off[u], a);
 #pragma unroll
@@ -284,25 +295,35 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     __syncthreads();
 
     // ---- what the epilogue reads from memory, ahead of the contraction ----------------------------------------
-    constexpr int LGN = BN / EPV == 2 ? 1 : BN / EPV == 4 ? 2 : 3;  // log2 vectors per result pixel
-    constexpr int ER = FC_NT >> LGN, EI = 4096 / BN / ER;                                // pixel rows per pass, passes
-    const int ev = tid & ((1 << LGN) - 1), er = tid >> LGN;
+    // The result passes through LDS in parts of PART pixels.  A thread has one vector of channels of
+    // every ER-th pixel; with ORD the backward sums are added up per thread and then over the ER threads in order, as the
+    // separate pass does with its 256 / (Ncol / 8) row lanes, so 64 channels use half of the threads.
+    constexpr int LGN = BN / EPV == 2 ? 1 : BN / EPV == 4 ? 2 : 3;                      // log2 vectors per result pixel
+    constexpr int ER = ORD == 2 ? 32 : FC_NT >> LGN;
+    constexpr int PART = ORD == 2 ? 64 : 4096 / BN, NP = ORD ? 2 : 1, EI = PART / ER;
+    const int ev = tid & ((1 << LGN) - 1);
+    const int er = tid >> LGN;
     const size_t oimg = (size_t)n * P.OH * P.OW * P.Ncol;
     const T* __restrict__ add0 = reinterpret_cast<const T*>(P.add0) + oimg;
     const T* __restrict__ ey = reinterpret_cast<const T*>(P.ey) + oimg;
     const T* __restrict__ ey2 = reinterpret_cast<const T*>(P.ey2) + oimg;
     u32x4 xa[EI], xe[EI], xf[EI];
-    int oo[EI];
+    int oo[EI];                                    // element offset of the vector in this image's output; -1: none
+    auto ahead = [&](int part) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < EI; ++i) {
-        const int p = er + i * ER;
-        const int a = __mul24(p, P.odiv) >> 16, b = p - __mul24(a, OB);
-        oo[i] = p < px ? (__mul24((a0 + a) * P.omul + P.ooh, P.OW) + b * P.omul + P.oow) * P.Ncol + n0 + ev * EPV : -1;
-        const unsigned o = p < px ? (unsigned)oo[i] : 0u;
-        if (P.add0) xa[i] = Vec<T>::load_raw(add0 + o);
-        if (P.ey) xe[i] = Vec<T>::load_raw(ey + o);
-        if (P.ey2) xf[i] = Vec<T>::load_raw(ey2 + o);
-    }
+        for (int i = 0; i < EI; ++i) {
+            const int p = part * PART + er + i * ER;
+            int a = __mul24(p, P.odiv) >> 16;
+            const int b = p - __mul24(a, OB);
+            if (ORD && a >= P.TH && segs > 1) a += P.OH - P.TH;      // the second image of the tile (TH = OH then)
+            oo[i] = p < px && er < ER ? (__mul24((a0 + a) * P.omul + P.ooh, P.OW) + b * P.omul + P.oow) * P.Ncol + n0 + ev * EPV : -1;
+            const unsigned o = oo[i] >= 0 ? (unsigned)oo[i] : 0u;
+            if (P.add0) xa[i] = Vec<T>::load_raw(add0 + o);
+            if (P.ey) xe[i] = Vec<T>::load_raw(ey + o);
+            if (P.ey2) xf[i] = Vec<T>::load_raw(ey2 + o);
+        }
+    };
+    ahead(0);
 
     // ---- contraction ------------------------------------------------------------------------------------------
     f32x4 acc[MT][NT];
@@ -316,15 +337,25 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     for (int i = 0; i < MT; ++i) {
         const int p = min((wave + 4 * i) * 16 + lr, px - 1);
         const int a = __mul24(p, P.odiv) >> 16, b = p - __mul24(a, OB);
-        ab[i] = win + __mul24(__mul24(a * P.imul, WW) + b * P.imul, PB) + cl * (int)sizeof(T);
+        const int seg = ORD && segs > 1 && a >= P.TH ? 1 : 0;
+        ab[i] = win + __mul24(__mul24((a - (seg ? P.TH : 0)) * P.imul + (seg ? SWH : 0), WW) + b * P.imul, PB) + cl * (int)sizeof(T);
     }
     const char* const fb = s_filt + lane * 16;
     const int nm = (nmt - wave + 3) >> 2;          // micro-tiles of this wave; the loops compute 1, 2 or 4 without a branch per tile
-    auto contract = [&](int tab, int slot, int steps) {
+    auto contract = [&](int tab, int slot, int steps) __attribute__((always_inline)) {
         const char* const fs = fb + slot * (NT * 1024);
-        if (MT == 4 && nm > 2) fconv_mma<T, MT, NT, 4>(fs, ab, tab, steps, pair, lg, acc);
-        else if (nm > 1) fconv_mma<T, MT, NT, 2>(fs, ab, tab, steps, pair, lg, acc);
-        else fconv_mma<T, MT, NT, 1>(fs, ab, tab, steps, pair, lg, acc);
+        if constexpr (MT == 8) {                   // (eight at a time would need 64 registers for fragments)
+            if (nm > 4) {
+                fconv_mma<T, MT, NT, 0, 4>(fs, ab, tab, steps, pair, lg, acc);
+                fconv_mma<T, MT, NT, 4, 4>(fs, ab, tab, steps, pair, lg, acc);
+                return;
+            }
+        }
+        if constexpr (MT >= 4) {
+            if (nm > 2) { fconv_mma<T, MT, NT, 0, 4>(fs, ab, tab, steps, pair, lg, acc); return; }
+        }
+        if (nm > 1) fconv_mma<T, MT, NT, 0, 2>(fs, ab, tab, steps, pair, lg, acc);
+        else fconv_mma<T, MT, NT, 0, 1>(fs, ab, tab, steps, pair, lg, acc);
     };
     if (S > 0 && S <= 2 * H) contract(atab, 0, S);
     else if (S > 0) {
@@ -345,16 +376,6 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
     // ---- result tile through LDS, one 16-byte vector per access -------------------------------------------------
     constexpr int SP = BN + 4;
     float* const res = reinterpret_cast<float*>(win);
-    __syncthreads();                               // every wave is done with the window
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-        if (wave + 4 * i < nmt) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) res[((wave + 4 * i) * 16 + lg * 4 + r) * SP + j * 16 + lr] = acc[i][j][r];
-        }
-    __syncthreads();
     T* __restrict__ out = reinterpret_cast<T*>(P.out) + oimg;
     float q1[EPV], q2[EPV], q3[EPV];
 #pragma unroll
@@ -367,50 +388,138 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
         }
     };
     const bool erelu = P.erelu != 0;
+    double* const sums = P.ey ? P.ered : P.ostats;
+    const bool stat_pass = ORD && !P.ey && sums;   // batch statistics in the order of the implicit-GEMM kernel's epilogue
 #pragma unroll
-    for (int i = 0; i < EI; ++i) {
-        if (oo[i] < 0) continue;
-        const int p = er + i * ER;
-        float v[EPV];
+    for (int part = 0; part < NP; ++part) {
+        if (part * PART >= px) continue;
+        if (part > 0) ahead(part);
+        __syncthreads();                           // every wave is done with the window, or with the part before
 #pragma unroll
-        for (int e = 0; e < EPV; e += 4) {
-            const f32x4 q = *reinterpret_cast<const f32x4*>(res + p * SP + ev * EPV + e);
-            v[e] = q[0]; v[e + 1] = q[1]; v[e + 2] = q[2]; v[e + 3] = q[3];
-        }
-        if (P.add0) {
-            float a[EPV];
-            Vec<T>::unpack(xa[i], a);
+        for (int i = 0; i < MT / NP; ++i) {
+            const int mt = wave + 4 * (part * (MT / NP) + i);
+            if (mt < nmt) {
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) v[e] += a[e];
-        }
-        const u32x4 st = Vec<T>::pack(v);
-        *reinterpret_cast<u32x4*>(out + (unsigned)oo[i]) = st;
-        Vec<T>::unpack(st, v);                     // the sums describe the values as stored
-        if (P.ey) {
-            float y[EPV], c[EPV], d[EPV];
-            Vec<T>::unpack(xe[i], y);
-            if (P.ey2) {                             // before the mask: there is no ReLU between the sum and a projection's batch norm
-                float y2[EPV];
-                Vec<T>::unpack(xf[i], y2);
-                ecoef(4, c); ecoef(5, d);
+                for (int j = 0; j < NT; ++j)
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) q3[e] += v[e] * ((y2[e] - c[e]) * d[e]);
+                    for (int r = 0; r < 4; ++r) res[((wave + 4 * i) * 16 + lg * 4 + r) * SP + j * 16 + lr] = acc[part * (MT / NP) + i][j][r];
             }
-            if (erelu) {
-                ecoef(0, c); ecoef(1, d);
+        }
+        __syncthreads();
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) v[e] = fmaf(c[e], y[e], d[e]) > 0.f ? v[e] : 0.f;
+        for (int i = 0; i < EI; ++i) {
+            if (oo[i] < 0) continue;
+            float* const rp = res + (er + i * ER) * SP + ev * EPV;
+            float v[EPV];
+#pragma unroll
+            for (int e = 0; e < EPV; e += 4) {
+                const f32x4 q = *reinterpret_cast<const f32x4*>(rp + e);
+                v[e] = q[0]; v[e + 1] = q[1]; v[e + 2] = q[2]; v[e + 3] = q[3];
             }
-            ecoef(2, c); ecoef(3, d);
+            if (P.add0) {
+                float a[EPV];
+                Vec<T>::unpack(xa[i], a);
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * ((y[e] - c[e]) * d[e]); }
-        } else {
+                for (int e = 0; e < EPV; ++e) v[e] += a[e];
+            }
+            const u32x4 st = Vec<T>::pack(v);
+            *reinterpret_cast<u32x4*>(out + (unsigned)oo[i]) = st;
+            Vec<T>::unpack(st, v);                 // the sums describe the values as stored
+            if (P.ey) {
+                float y[EPV], c[EPV], d[EPV];
+                Vec<T>::unpack(xe[i], y);
+                if (P.ey2) {                       // before the mask: there is no ReLU between the sum and a projection's batch norm
+                    float y2[EPV];
+                    Vec<T>::unpack(xf[i], y2);
+                    ecoef(4, c); ecoef(5, d);
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * v[e]; }
+                    for (int e = 0; e < EPV; ++e) q3[e] += v[e] * ((y2[e] - c[e]) * d[e]);
+                }
+                if (erelu) {
+                    ecoef(0, c); ecoef(1, d);
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) v[e] = fmaf(c[e], y[e], d[e]) > 0.f ? v[e] : 0.f;
+                }
+                ecoef(2, c); ecoef(3, d);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * ((y[e] - c[e]) * d[e]); }
+            } else if (stat_pass) {
+#pragma unroll
+                for (int e = 0; e < EPV; e += 4) *reinterpret_cast<f32x4*>(rp + e) = f32x4{v[e], v[e + 1], v[e + 2], v[e + 3]};
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * v[e]; }
+            }
+        }
+        if constexpr (ORD != 0) {
+            if (stat_pass) {
+                // runs of RW rows x 16 channels per wave: 64 rows, or 32 where the tile of that kernel is 64 x 64
+                __syncthreads();
+                constexpr int lgrw = ORD == 2 ? 5 : 6, runs = (PART >> lgrw) * NT;
+                for (int u = wave; u < runs; u += 4) {
+                    const int run = u / NT, j = u - run * NT, row0 = run << lgrw;
+                    float s1 = 0.f, s2 = 0.f;
+                    for (int i = 0; i < 1 << (lgrw - 4); ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int row = row0 + i * 16 + lg * 4 + r;
+                            if (part * PART + row < px) {
+                                const float x = res[row * SP + j * 16 + lr];
+                                s1 += x; s2 = fmaf(x, x, s2);
+                            }
+                        }
+                    s1 += __shfl_xor(s1, 16, 64); s2 += __shfl_xor(s2, 16, 64);
+                    s1 += __shfl_xor(s1, 32, 64); s2 += __shfl_xor(s2, 32, 64);
+                    if (lane < 16) {
+                        float* const q = s_red + (((part * PART >> lgrw) + run) * BN + j * 16 + lane) * 2;
+                        q[0] = s1; q[1] = s2;
+                    }
+                }
+            }
         }
     }
-    double* const sums = P.ey ? P.ered : P.ostats;
     if (!sums) return;
+    const size_t at = (size_t)(blockIdx.x % stat_stripes(P.Ncol)) * 2 * P.Ncol + n0 + tid;          // this workgroup's stripe
+    if constexpr (ORD != 0) {
+        double d1 = 0.0, d2 = 0.0, d3 = 0.0;
+        if (stat_pass) {                           // runs of one tile of the implicit-GEMM kernel in fp32, the tiles in fp64
+            __syncthreads();
+            if (tid >= BN) return;
+            constexpr int lgrw = ORD == 2 ? 5 : 6, per = ORD == 2 ? 2 : 4;
+            const int nrun = (px + (1 << lgrw) - 1) >> lgrw;
+            for (int r0 = 0; r0 < nrun; r0 += per) {
+                float s1 = 0.f, s2 = 0.f;
+                for (int w = r0; w < min(r0 + per, nrun); ++w) { s1 += s_red[(w * BN + tid) * 2]; s2 += s_red[(w * BN + tid) * 2 + 1]; }
+                d1 += (double)s1; d2 += (double)s2;
+            }
+        } else {                                   // row lane by row lane, per channel
+            __syncthreads();                       // the last part of the result has been read
+            float* const rs = res;                 // [row lane][channel][sum g', sum g' yhat, sum g yhat of the second batch norm]
+            if (er < ER) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    float* const q = rs + (er * BN + ev * EPV + e) * 3;
+                    q[0] = q1[e]; q[1] = q2[e]; q[2] = q3[e];
+                }
+            }
+            __syncthreads();
+            if (tid >= BN) return;
+            float s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll 8
+            for (int l = 0; l < ER; ++l) {
+                const float* const q = rs + (l * BN + tid) * 3;
+                s1 += q[0]; s2 += q[1]; s3 += q[2];
+            }
+            d1 = (double)s1; d2 = (double)s2; d3 = (double)s3;
+        }
+        atomicAdd(&sums[at], d1);
+        atomicAdd(&sums[at + P.Ncol], d2);
+        if (P.ey2) {
+            atomicAdd(&P.ered2[at], d1);
+            atomicAdd(&P.ered2[at + P.Ncol], d3);
+        }
+        return;
+    }
     // over the pixel rows of 16 lanes by rotation, then 16 partial sums per channel through LDS
 #pragma unroll
     for (int e = 0; e < EPV; ++e) {
@@ -433,7 +542,6 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
         f32x4 a = *reinterpret_cast<const f32x4*>(s_red + tid * 4);
 #pragma unroll
         for (int w = 1; w < 16; ++w) a += *reinterpret_cast<const f32x4*>(s_red + (w * BN + tid) * 4);
-        const size_t at = (size_t)(blockIdx.x % stat_stripes(P.Ncol)) * 2 * P.Ncol + n0 + tid;      // this workgroup's stripe
         atomicAdd(&sums[at], (double)a[0]);
         atomicAdd(&sums[at + P.Ncol], (double)a[1]);
         if (P.ey2) {
@@ -444,29 +552,47 @@ __device__ __forceinline__ void fconv_tile(const FConvProb& P, const int t, cons
 }
 
 template <typename T>
-__global__ __launch_bounds__(FC_NT, sizeof(T) == 4 ? 3 : 4) void fconv_kernel(const FConvGroup g) {
+__global__ __launch_bounds__(FC_NT, 3) void fconv_kernel(const FConvGroup) {
+    FConvGroupArg& g = *(FConvGroupArg*)__builtin_amdgcn_kernarg_segment_ptr();
     extern __shared__ __attribute__((aligned(16))) char s_lds[];
     int pi = 0;
 #pragma unroll
     for (int i = 1; i < kMaxGroup; ++i) pi += (int)blockIdx.x >= g.start[i] ? 1 : 0;
-    const FConvProb& P = g.p[pi];
+    FConvArg& P = g.p[pi];
     const int t = (int)blockIdx.x - g.start[pi];
     // one field of every cache line of the problem: the lines are fetched together, not one by one where they are first used
     asm volatile("" ::"s"(P.in), "s"(P.stats2), "s"(P.ey), "s"(P.ldw), "s"((int)P.S));
-    if (P.BN == 16) fconv_tile<T, 16>(P, t, g.eps, s_lds);
-    else fconv_tile<T, 32>(P, t, g.eps, s_lds);
+    if constexpr (sizeof(T) == 2) {
+        if (P.ordered) {
+            if (P.BN == 16) fconv_tile<T, 16, 1>(P, t, g.eps, s_lds);
+            else if (P.Ncol == 32) fconv_tile<T, 32, 1>(P, t, g.eps, s_lds);
+            else fconv_tile<T, 32, 2>(P, t, g.eps, s_lds);
+            return;
+        }
+    }
+    if (P.BN == 16) fconv_tile<T, 16, 0>(P, t, g.eps, s_lds);
+    else fconv_tile<T, 32, 0>(P, t, g.eps, s_lds);
 }
 
 }  // namespace
 
 size_t fconv_lds_bytes(const FConvProb& p, int esz) {
-    const size_t win = (size_t)p.WH * p.WW * (p.Cin * esz + 16);
-    const size_t res = (size_t)((p.TH * p.OB + 15) & ~15) * (p.BN + 4) * 4;
+    const int segs = p.ordered ? p.segs : 1, px = (p.TH * p.OB * segs + 15) & ~15;
+    const size_t win = (size_t)p.WH * p.WW * segs * (p.Cin * esz + 16);
+    size_t res = (size_t)std::min(px, p.ordered && p.Ncol == 64 ? 64 : fconv_max_px(p.BN)) * (p.BN + 4) * 4;
+    if (p.ordered && p.ey) res = std::max(res, (size_t)(p.Ncol == 64 ? 32 : 2048 / p.BN) * p.BN * 12);
     return FC_FILT + fconv_filt_bytes(fconv_ksteps(p.ntr * p.nts, p.Cin, esz), p.BN) + std::max(win, res);
 }
 
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
+    static bool configured = false;
+    if (!configured) {                             // (the windows of stride-2 layers in ordered tiles are the ones beyond 64 KB)
+        hipError_t e = hipFuncSetAttribute((const void*)fconv_kernel<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, kFconvMaxLds);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)fconv_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, kFconvMaxLds);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
     if (dtype == 1) hipLaunchKernelGGL(fconv_kernel<bf16_t>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
     else hipLaunchKernelGGL(fconv_kernel<float>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
     return hipGetLastError();

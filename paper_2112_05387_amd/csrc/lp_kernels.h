@@ -68,6 +68,10 @@ struct FConvProb {
     signed char imul, omul, ooh, oow, ntr, nts, dh0, dhs, dw0, dws, r0, rs, s0, ss, S;
     signed char dhmin, dwmin, mode, relu, erelu;
     signed char BN;                                          // output channels of a tile: 16 or 32
+    // ordered: the tile is as many pixels as the row lanes of the separate BN-backward reduction take in one trip (512, 256,
+    // 128 pixels of 16, 32, 64 channels), and statistics and backward sums are added up in the order of the separate passes,
+    // so that a step in bf16 gives the same bits as with separate passes; segs: images of a tile
+    signed char ordered, segs;
 };
 struct FConvGroup {
     int nprob, total_tiles;
@@ -80,6 +84,7 @@ static_assert(sizeof(FConvGroup) <= 4096, "kernel-argument block");
 constexpr int fconv_max_px(int BN) { return 4096 / BN; }
 // k-steps of a tile: 64 bytes of channels of one tap each (bf16 with 16 channels: two taps)
 __host__ __device__ inline int fconv_ksteps(int ntaps, int Cin, int esz) { return Cin * esz < 64 ? (ntaps + 1) / 2 : ntaps * (Cin * esz / 64); }
+constexpr int kFconvMaxLds = 80 * 1024;                      // two workgroups per compute unit at least
 size_t fconv_lds_bytes(const FConvProb& p, int esz);
 
 // Weight gradient:  dW[co, (r,s,ci)] (+)= sum_m dY[m, co] * X[n, ho*stride - pad + r, wo*stride - pad + s, ci]
