@@ -213,6 +213,7 @@ struct lp_net {
     bool lanes_ready = false;              // every extra stream and event above exists
     bool keep_gradients = false;           // debug layout: no gradient buffer is reused inside a backward pass
     bool narrow = false;                   // every module has the folded programs (ffwd ...)
+    bool deep = false;                     // a module of more than three blocks, or AuxNets (see Builder::fconv_exact)
     bool lanes_set = false;                // the caller chose the stream lanes
     bool deterministic = false;            // lp_net_set_deterministic: every reduction in a fixed order
     // lp_net_set_fused_update: the parameter update runs inside lp_module_backward / lp_local_step
@@ -370,10 +371,12 @@ struct Builder {
         p.wdiv = 65536 / p.WW + 1; p.odiv = 65536 / p.OB + 1;
         p.tdiv = p.tpi == 1 ? 0 : (unsigned)((1ull << 32) / p.tpi + 1);
     }
-    // Mini-batches of 32 and more in bf16 take tiles in the order of the separate passes (FConvProb::ordered): such launches
-    // fill the chip with tiles of that size, and a bf16 network amplifies any other order of its sums to a rounding of every
-    // value within a few layers.  Smaller ones (and fp32) take the tiles that make a launch shortest.
-    bool fconv_exact(int nimg) const { return net->dtype == LP_BF16 && nimg >= 32; }
+    // bf16 tiles in the order of the separate passes (FConvProb::ordered).  A bf16 network amplifies any other order of its
+    // sums to a rounding of every value within a few layers, and modules of more than three blocks to several percent of
+    // an adjoint; an AuxNet is distilled from single roundings of the auxiliary variables.  Shallow modules without AuxNets
+    // on mini-batches below 32 take the tiles that make a launch shortest instead (as fp32 always does); from 32 on the
+    // larger tiles fill the chip and are the faster ones as well.
+    bool fconv_exact(int nimg) const { return net->dtype == LP_BF16 && (nimg >= 32 || net->deep); }
     void fconv_order(FConvProb& p) const {
         const int px = 8192 / p.Ncol, img = p.OA * p.OB;             // pixels of a trip of the separate reduction
         if (!fconv_exact(p.nimg) || p.omul != 1 || p.ntr == 0 || (long)p.nimg * img > 256l * px) return;
@@ -418,7 +421,7 @@ struct Builder {
         for (const Op& o : st) {
             const FConvProb& p = o.fc;
             // a row of pixels must fit a tile (of 64 pixels where 64 channels are one), the window the 16-bit quotients and a third of the LDS
-            if (p.OB > 64 || (long)p.nimg * p.tpi * 4 * p.tpi >= (1l << 32) || p.WH * p.WW * p.WW >= 65536 || fconv_lds_bytes(p, (int)net->esz) > 64 * 1024) return false;
+            if (p.OB > 64 || (long)p.nimg * p.tpi * 4 * p.tpi >= (1l << 32) || p.WH * p.WW * p.WW >= 65536 || fconv_lds_bytes(p, (int)net->esz) > (size_t)kFconvMaxLds) return false;
         }
         return true;
     }
@@ -2218,6 +2221,8 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
     net->K = K; net->dtype = dtype; net->eps = bn_eps; net->esz = dtype == LP_BF16 ? 2 : 4;
     net->keep_gradients = g_keep_gradients;
     net->narrow = true;
+    net->deep = aux != nullptr;
+    for (int k = 0; k < K; ++k) net->deep = net->deep || mods[k].n_blocks > 3;
     net->mods.resize(K);
     net->saved_x.assign(K, nullptr);
     net->saved_y.assign(K, nullptr);
