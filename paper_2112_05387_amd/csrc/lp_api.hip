@@ -1619,6 +1619,67 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
     }
 }
 
+// A launch of the wide-layer kernels as a launch of lp_sconv.hip, if that is the faster one: `g` holds the launch as it would
+// go out (tiles of `ci`), `win` says whether in the window kernel.  Both are modelled as waves of workgroups over the compute
+// units this stream lane can expect: a workgroup of the large tiles runs at 7.5 TFLOP/s (two- and four-wave variants at 2.5
+// and 5) behind 25 us of prologue, window and epilogue (10 for the smaller variants); a small one takes a 128-byte line
+// into LDS per 4.5 clocks, and 5 us around that, statistics included.
+static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const CfgInfo& ci, SConvGroup& out, size_t& lds) {
+    out.nprob = g.nprob; out.pad_[0] = out.pad_[1] = 0;
+    lds = 0;
+    const int cap = std::max(1, 256 / std::max(1, net->lanes_in_flight));
+    const int waves = ci.BM / 64 * (ci.BN / 160);
+    double t_old = 0, t_new = 0;
+    long tot = 0, work_old = 0;
+    for (int i = 0; i < kMaxGroup; ++i) {
+        if (i >= g.nprob) { out.start[i] = INT_MAX; continue; }
+        const ConvProb& c = g.p[i];
+        SConvProb& p = out.p[i]; memset(&p, 0, sizeof(p));
+        const int ntaps = c.ntr * c.nts;
+        if (c.OB > 128 || c.Cin % 32 || c.Ncol % 8) return false;
+        p.in = c.in; p.wt = c.wt; p.add0 = c.add0; p.add1 = c.add1; p.out = c.out;
+        p.nimg = c.M / (c.OA * c.OB); p.ldw = c.ldw;
+        p.OA = c.OA; p.OB = c.OB; p.IH = c.IH; p.IW = c.IW; p.OH = c.OH; p.OW = c.OW; p.Cin = c.Cin; p.Ncol = c.Ncol;
+        p.imul = c.imul; p.omul = c.omul; p.ooh = c.ooh; p.oow = c.oow; p.ntr = c.ntr; p.nts = c.nts;
+        p.dh0 = c.dh0; p.dhs = c.dhs; p.dw0 = c.dw0; p.dws = c.dws; p.r0 = c.r0; p.rs = c.rs; p.s0 = c.s0; p.ss = c.ss; p.S = c.S;
+        p.dhmin = std::min(c.dh0, c.dh0 + c.dhs * (c.ntr - 1)); p.dwmin = std::min(c.dw0, c.dw0 + c.dws * (c.nts - 1));
+        const int tr = std::max(c.ntr, 1), ts = std::max(c.nts, 1);
+        const bool single = ntaps <= 1;
+        p.WW = single ? c.OB : (c.OB - 1) * c.imul + ts;
+        int TH = std::min(c.OA, std::max(1, 128 / c.OB));
+        auto npx = [&](int th) { return single ? th * c.OB : ((th - 1) * c.imul + tr) * p.WW; };
+        while (TH > 1 && npx(TH) > kSconvMaxPx) --TH;
+        if (npx(TH) > kSconvMaxPx) return false;
+        p.TH = TH; p.WH = single ? TH : (TH - 1) * c.imul + tr;
+        p.segs = TH == c.OA ? std::max(1, std::min(128 / (c.OA * c.OB), kSconvMaxPx / npx(TH))) : 1;
+        p.tpi = (c.OA + TH - 1) / TH;
+        p.wdiv = 65536 / p.WW + 1; p.odiv = 65536 / c.OB + 1;
+        p.win_bytes = (npx(TH) * p.segs + 7) / 8 * 1024;
+        p.slab = win ? 64 : ci.BK;
+        const int nslab = (c.Cin + 63) / 64, slab_bytes = p.win_bytes + ntaps * 4096;
+        p.gs = (short)std::max(1, std::min(nslab, 80 * 1024 / slab_bytes));
+        if ((size_t)2 * p.gs * slab_bytes > 160 * 1024) return false;
+        lds = std::max(lds, (size_t)std::min(2, (nslab + p.gs - 1) / p.gs) * p.gs * slab_bytes);
+        p.rot = win && c.Cin % 64 != 0;
+        p.row_tile_start = c.tile_start; p.row_tile = ci.BM; p.col_tiles = c.tiles_n; p.col_tile = ci.BN;
+        if (p.rot) {           // every tile inside one workgroup of the window kernel
+            const int rows = TH * c.OB * p.segs;
+            if (c.OA % TH != 0 || ci.BM % rows != 0 || ci.BN % 32 != 0) return false;
+        }
+        out.start[i] = (int)tot;
+        const long blocks = (long)((p.nimg + p.segs - 1) / p.segs) * p.tpi * ((c.Ncol + 31) / 32);
+        tot += blocks;
+        t_new += (double)blocks * (nslab * (npx(TH) * p.segs + ntaps * 32) * 4.5 / 2.1e3 + 5.0);
+        work_old += (long)c.tiles_m * c.tiles_n;
+        t_old += (double)c.tiles_m * c.tiles_n * (2.0 * ci.BM * ci.BN * c.Kg / (waves >= 8 ? 7.5e6 : waves >= 4 ? 5e6 : 2.5e6) + (waves >= 8 ? 25.0 : 10.0));
+    }
+    out.total_tiles = (int)tot;
+    if (!tot || !work_old) return false;
+    // average time of a workgroup times the number of rounds
+    const double r_old = (double)((work_old + cap - 1) / cap) / work_old, r_new = (double)((tot + cap - 1) / cap) / tot;
+    return t_new * r_new < t_old * r_old;
+}
+
 // Tile sizes of a grouped launch of the narrow kernel: the smallest tiles of which two per compute unit hold the whole
 // launch (the less a workgroup does, the shorter the launch), full-size tiles where even those are more.
 static void plan_fconv_tiles(FConvGroup& g) {
@@ -1756,6 +1817,23 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.tile_start = tot; tot += p.tiles_m * p.tiles_n;
                 }
                 g.total_tiles = tot;
+                SConvGroup small; size_t small_lds = 0;
+                if (fast && plan_sconv(net, g, win, ci, small, small_lds)) {
+                    if (used_cfg) *used_cfg = SMALL_128x32;
+                    if (used_blocks) *used_blocks = small.total_tiles;
+                    err = launch_sconv(small, small_lds, s);
+                    TileStatsGroup ts; ts.nprob = 0; ts.total_blocks = 0;
+                    for (int i = 0; i < n; ++i) {
+                        const ConvProb& c = g.p[i];
+                        if (!c.stats) continue;
+                        TileStatsProb& q = ts.p[ts.nprob++];
+                        q.y = c.out; q.stats = c.stats; q.M = c.M; q.C = c.Ncol; q.BM = ci.BM; q.block_start = ts.total_blocks;
+                        ts.total_blocks += c.tiles_m * ((c.Ncol + 63) / 64);
+                    }
+                    if (err == hipSuccess) err = launch_tile_stats(ts, s);
+                    if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);
+                    break;
+                }
                 if (used_blocks) *used_blocks = tot;
                 err = win ? launch_conv_win(g, cfg, s) : fast ? launch_conv_fast(g, cfg, s) : launch_conv(g, dt, cfg, ops[base]->vec, s);
                 if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);

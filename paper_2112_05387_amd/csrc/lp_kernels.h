@@ -87,6 +87,30 @@ __host__ __device__ inline int fconv_ksteps(int ntaps, int Cin, int esz) { retur
 constexpr int kFconvMaxLds = 80 * 1024;                      // two workgroups per compute unit at least
 size_t fconv_lds_bytes(const FConvProb& p, int esz);
 
+// A wide bf16 convolution on few pixels (lp_sconv.hip): tiles of TH rows of one image or `segs` whole images (at most 128
+// pixels) x 32 output channels, in the summation order of the wide-layer kernel the launch is taken from.
+constexpr int kSconvMaxPx = 320;                             // window pixels of a tile
+struct SConvProb {
+    const void *in, *wt, *add0, *add1;
+    void* out;
+    int nimg, ldw, wdiv, odiv;
+    int win_bytes;                                           // LDS bytes of a window slab of 64 channels
+    int row_tile_start, row_tile, col_tiles, col_tile;       // the other kernel's tiles (rot: which workgroup is odd)
+    short OA, OB, IH, IW, OH, OW, Cin, Ncol, TH, tpi, segs, WH, WW;
+    short slab, gs;                                          // channels of its slabs (64 or 32); slabs of 64 per group here
+    signed char imul, omul, ooh, oow, ntr, nts, dh0, dhs, dw0, dws, r0, rs, s0, ss, S, dhmin, dwmin, rot;
+};
+struct SConvGroup {
+    int nprob, total_tiles;
+    int pad_[2];
+    int start[kMaxGroup];
+    SConvProb p[kMaxGroup];
+};
+static_assert(sizeof(SConvGroup) <= 4096, "kernel-argument block");
+// per-channel sums of stored tensors in the order of the wide-layer kernels' epilogue (tiles of BM rows)
+struct TileStatsProb { const void* y; double* stats; int M, C, BM, block_start; };
+struct TileStatsGroup { int nprob, total_blocks; TileStatsProb p[kMaxGroup]; };
+
 // Weight gradient:  dW[co, (r,s,ci)] (+)= sum_m dY[m, co] * X[n, ho*stride - pad + r, wo*stride - pad + s, ci]
 // split over `ksplit` slices of the reduction; partial results are added to dW with fp32 atomics.
 struct WgradProb {
@@ -230,7 +254,7 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                FAST_128x320 = 10, FAST_128x160 = 11,   // ... its four- and two-wave variants, chosen per launch
                FAST64_256x320 = 12, FAST64_128x320 = 13, FAST64_128x160 = 14,   // ... with k-tiles of 64 channels
                FAST_256x160 = 15, FAST64_256x160 = 16,  // four-wave variants of the 160-wide family
-               WIN64_512x160 = 21, WIN64_256x320 = 23,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
+               WIN64_512x160 = 21, WIN64_256x320 = 23, SMALL_128x32 = 24,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
                WGRAD_FAST = 8 };                       // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
 struct CfgInfo { int BM, BN, BK; };
 CfgInfo conv_cfg_info(int cfg, int dtype);
@@ -243,6 +267,8 @@ constexpr int conv_win_max_slabs(int BM, int NW) { return BM == 512 ? 10 : 7; }
 hipError_t launch_conv(const ConvGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_conv_win(const ConvGroup& g, int cfg, hipStream_t s);
+hipError_t launch_sconv(const SConvGroup& g, size_t lds, hipStream_t s);
+hipError_t launch_tile_stats(const TileStatsGroup& g, hipStream_t s);
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_fwgrad(const FWgradGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
