@@ -25,11 +25,9 @@ namespace {
 constexpr int FW_NT = 256;
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 __device__ __forceinline__ u32x2 tr_read(const char* p) {
-    u32x2 r;
-    const unsigned a = (unsigned)(uintptr_t)(lds_ptr_t)const_cast<char*>(p);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r) : "v"(a));
-    return r;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lds_ptr_t)const_cast<char*>(p)));
 }
 
 // NTAP micro-tiles of columns: 9 taps, 1 tap, or (STEM) 2 groups of 16 of the 9 * Cin columns
@@ -157,27 +155,17 @@ __device__ __forceinline__ void fwgrad_body(const FWgradProb& P, const int t, ch
                 const char* const pa = s_y + __mul24(p0, YP) + cot * 32 + (lq & 3) * 8;
                 const char* const pb0 = s_x + win_pos(p0) + cit * 32 + (lq & 3) * 8;
                 const char* const pb1 = s_x + win_pos(p0 + 4) + cit * 32 + (lq & 3) * 8;
-                // nothing may touch the results before the wait that covers them; the empty asm behind it orders every use
-                u32x2 alo = tr_read(pa), ahi = tr_read(pa + 4 * YP);
+                // fragments one ahead of the products that use them
+                const u32x2 alo = tr_read(pa), ahi = tr_read(pa + 4 * YP);
+                const u32x4 af = {alo[0], alo[1], ahi[0], ahi[1]};
                 u32x2 blo[2], bhi[2];
                 blo[0] = tr_read(pb0 + toff[0]); bhi[0] = tr_read(pb1 + toff[0]);
-                u32x4 af = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < NTAP; ++j) {
                     const int q = j & 1;
-                    if (j + 1 < NTAP) {
-                        blo[q ^ 1] = tr_read(pb0 + toff[j + 1]); bhi[q ^ 1] = tr_read(pb1 + toff[j + 1]);
-                        __builtin_amdgcn_s_waitcnt(0xc07f | (2 << 8));       // lgkmcnt(2): all but the pair just issued
-                    } else __builtin_amdgcn_s_waitcnt(0xc07f);
-                    if (j == 0) {
-                        asm volatile("" : "+v"(alo), "+v"(ahi));
-                        af = u32x4{alo[0], alo[1], ahi[0], ahi[1]};
-                    }
-                    asm volatile("" : "+v"(blo[q]), "+v"(bhi[q]));
+                    if (j + 1 < NTAP) { blo[q ^ 1] = tr_read(pb0 + toff[j + 1]); bhi[q ^ 1] = tr_read(pb1 + toff[j + 1]); }
                     const u32x4 bf = {blo[q][0], blo[q][1], bhi[q][0], bhi[q][1]};
-                    __builtin_amdgcn_sched_barrier(0);
                     acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af), __builtin_bit_cast(bf16x8, bf), acc[j], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         } else {
