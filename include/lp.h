@@ -396,6 +396,14 @@ lp_status lp_debug_module_info(const struct lp_net* net, int k, lp_debug_module*
 lp_status lp_debug_filter_load_extent(int kernel, int bk, int bn, int nw, int Ncol, int Cin, int R, size_t* max_end,
                                       size_t* n_live);
 
+/* Which specialised kernels take a convolution layer [N,H,W,Cin] -> Cout, R x R, stride, pad R/2 (host only; the rules the
+ * library applies when it builds a network and when it launches): taken[4] =
+ *   {narrow convolution with the batch norms folded in, forward and data-gradient (every layer of a network has to have it),
+ *    filter gradient from one input window, small tiles of the wide layers for the forward launch, ... for the data-gradient
+ *    (strides of 1 and 2)}
+ * with `lanes` stream lanes in flight and the layer alone in its launch.  Errors: LP_ERR_INVALID_ARG. */
+lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Cout, int R, int stride, int lanes, int* taken);
+
 /* What the matrix cores of this device sustain (measurement aid of bench.py --measure-peak; no operand of the
  * library is touched).  Launches `blocks` workgroups of eight waves, each wave running `iters` times the 40
  * v_mfma_f32_32x32x16_bf16 of one filter tap of the convolution kernels' wave tile (2 x 5 micro-tiles, four k-steps):

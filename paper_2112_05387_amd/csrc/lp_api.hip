@@ -412,7 +412,8 @@ struct Builder {
     bool fconv_ok(const Unit& u) const {
         auto width = [](int c) { return c == 16 || c == 32 || c == 64; };
         if (!width(u.cin) || !width(u.cout) || u.R > 3 || u.R == 2 || u.stride > 2) return false;
-        if (u.H % u.stride || u.W % u.stride || u.H > 1024 || u.N > (1 << 20)) return false;
+        // a row of pixels must fit a tile (of 64 pixels where 64 channels are one); checked ahead of the 16-bit fields
+        if (u.H % u.stride || u.W % u.stride || u.H > 1024 || u.W > 64 * u.stride || u.N > (1 << 20)) return false;
         Step st;
         st.push_back(fconv(conv_fwd(u, Ref(), Ref(), Ref(), Ref()).conv, Fx(), Ref(), Ref(), Ref(), Ref()));
         Step dg;
@@ -420,8 +421,8 @@ struct Builder {
         for (const Op& o : dg) st.push_back(fconv(o.conv, Fx(), Ref(), Ref(), Ref(), Ref()));
         for (const Op& o : st) {
             const FConvProb& p = o.fc;
-            // a row of pixels must fit a tile (of 64 pixels where 64 channels are one), the window the 16-bit quotients and a third of the LDS
-            if (p.OB > 64 || (long)p.nimg * p.tpi * 4 * p.tpi >= (1l << 32) || p.WH * p.WW * p.WW >= 65536 || fconv_lds_bytes(p, (int)net->esz) > (size_t)kFconvMaxLds) return false;
+            // the window must fit the 16-bit quotients and half of the LDS
+            if ((long)p.nimg * p.tpi * 4 * p.tpi >= (1l << 32) || p.WH * p.WW * p.WW >= 65536 || fconv_lds_bytes(p, (int)net->esz) > (size_t)kFconvMaxLds) return false;
         }
         return true;
     }
@@ -478,6 +479,7 @@ struct Builder {
         auto width = [](int c) { return c == 16 || c == 32 || c == 64; };
         const bool stem = u.cin <= 3 && u.R == 3;
         if (!width(u.cout) || !(stem || width(u.cin)) || (u.R != 1 && u.R != 3) || u.Wo > 128 || u.H > 1024) return o;
+        if ((u.Wo - 1) * u.stride + u.R > 255) return o;       // wider than the quotients below hold, checked ahead of the 16-bit fields
         FWgradProb p; memset(&p, 0, sizeof(p));
         p.Cin = u.cin; p.Cout = u.cout; p.IH = u.H; p.IW = u.W; p.Ho = u.Ho; p.Wo = u.Wo; p.stride = u.stride; p.pad = u.pad; p.R = u.R;
         const int CB = std::min(u.cout, 32), CI = std::min(u.cin, 32), vy = CB * esz / 16, vx = CI * esz / 16;
@@ -487,7 +489,7 @@ struct Builder {
             p.TH = TH; p.WH = (TH - 1) * u.stride + u.R; p.WW = (u.Wo - 1) * u.stride + u.R;
             const int pxpad = (TH * u.Wo + 31) & ~31, whw = p.WH * p.WW;
             if (pxpad * vy <= fwgrad_y_vecs(esz) * 256 && (stem ? whw * u.cin <= kFwStemElems * 256 : whw * vx <= fwgrad_x_vecs(esz) * 256) &&
-                whw * p.WW < 65536 && whw * u.cin * u.cin < 65536 * 16 && fwgrad_lds_bytes(p, esz) <= 64 * 1024) break;
+                whw * p.WW < 65536 && fwgrad_lds_bytes(p, esz) <= 64 * 1024) break;
         }
         p.tpi = (u.Ho + TH - 1) / TH; p.ntiles = u.N * p.tpi;
         if ((long)p.ntiles * p.tpi >= (1l << 32)) return o;
@@ -1636,7 +1638,7 @@ static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const Cf
         const ConvProb& c = g.p[i];
         SConvProb& p = out.p[i]; memset(&p, 0, sizeof(p));
         const int ntaps = c.ntr * c.nts;
-        if (c.OB > 128 || c.Cin % 32 || c.Ncol % 8 || c.ntr > 3 || c.nts > 3) return false;
+        if (c.OB > 128 || std::max({c.IH, c.IW, c.OH, c.OW}) > SHRT_MAX || c.Cin % 32 || c.Ncol % 8 || c.ntr > 3 || c.nts > 3) return false;
         p.in = c.in; p.wt = c.wt; p.add0 = c.add0; p.add1 = c.add1; p.out = c.out;
         p.nimg = c.M / (c.OA * c.OB); p.ldw = c.ldw;
         p.OA = c.OA; p.OB = c.OB; p.IH = c.IH; p.IW = c.IW; p.OH = c.OH; p.OW = c.OW; p.Cin = c.Cin; p.Ncol = c.Ncol;
@@ -1701,6 +1703,53 @@ static void plan_fconv_tiles(FConvGroup& g) {
     }
 }
 
+// Tile variant of a grouped convolution launch: by the number of tiles the group has and the stream lanes in flight.
+static int conv_launch_cfg(const lp_net* net, const Op* const* ops, int n, bool& win, bool& fast) {
+    int cfg = ops[0]->cfg;
+    win = cfg >= WIN64_512x160;
+    fast = cfg >= FAST_256x320;
+    if (win) {
+        // The window kernel needs its eight-wave tiles (two waves per SIMD keep the matrix core fed) and
+        // about one tile per compute unit; a launch with fewer tiles goes to the implicit-GEMM kernel,
+        // whose smaller tile variants fill the chip.
+        // (next to the launches of other stream lanes the idle compute units are not lost: keep it)
+        const int TW = net->lanes_in_flight > 1 ? 0 : 200;
+        long big = 0;
+        for (int i = 0; i < n; ++i) {
+            const ConvProb& c = ops[i]->conv;
+            big += cfg == WIN64_256x320 ? (long)((c.M + 255) / 256) * ((c.Ncol + 319) / 320)
+                                        : (long)((c.M + 511) / 512) * ((c.Ncol + 159) / 160);
+        }
+        if (big < TW) { cfg = cfg == WIN64_256x320 ? FAST_256x320 : FAST_512x160; win = false; }
+    }
+    if (cfg == FAST_256x320 || cfg == FAST_512x160) {
+        // Too few full-size tiles for the chip: the four-wave variants (and the two-wave one of the
+        // 320-wide family).  k-tiles of 64 channels where every problem allows them and the tile fits.
+        long big = 0, mid = 0;
+        bool k64 = true;
+        for (int i = 0; i < n; ++i) {
+            const ConvProb& c = ops[i]->conv;
+            if (cfg == FAST_256x320) {
+                big += (long)((c.M + 255) / 256) * ((c.Ncol + 319) / 320);
+                mid += (long)((c.M + 127) / 128) * ((c.Ncol + 319) / 320);
+            } else {
+                big += (long)((c.M + 511) / 512) * ((c.Ncol + 159) / 160);
+            }
+            k64 = k64 && (c.Cin % 64 == 0);
+        }
+        // alone on the device a launch wants at least 200 tiles; next to the launches of other stream lanes
+        // the idle compute units are not lost, and the larger tile's better operand reuse wins
+        const int T1 = net->lanes_in_flight > 1 ? 64 : 200, T2 = 200, T3 = 200;
+        if (cfg == FAST_256x320) {
+            if (big < T1) cfg = mid < T2 ? FAST_128x160 : FAST_128x320;
+            if (k64) cfg = cfg == FAST_256x320 ? FAST64_256x320 : cfg == FAST_128x320 ? FAST64_128x320 : FAST64_128x160;
+        } else if (big < T3) {
+            cfg = k64 ? FAST64_256x160 : FAST_256x160;
+        }
+    }
+    return cfg;
+}
+
 static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, size_t base, int n, const Bindings& b, hipStream_t s,
                                     int* used_cfg, int* used_blocks);
 
@@ -1755,48 +1804,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
             } break;
             case OP_CONV: {
                 ConvGroup g; g.nprob = n; int tot = 0;
-                int cfg = ops[base]->cfg;
-                bool win = cfg >= WIN64_512x160;
-                const bool fast = cfg >= FAST_256x320;
-                if (win) {
-                    // The window kernel needs its eight-wave tiles (two waves per SIMD keep the matrix core fed) and
-                    // about one tile per compute unit; a launch with fewer tiles goes to the implicit-GEMM kernel,
-                    // whose smaller tile variants fill the chip.
-                    // (next to the launches of other stream lanes the idle compute units are not lost: keep it)
-                    const int TW = net->lanes_in_flight > 1 ? 0 : 200;
-                    long big = 0;
-                    for (int i = 0; i < n; ++i) {
-                        const ConvProb& c = ops[base + i]->conv;
-                        big += cfg == WIN64_256x320 ? (long)((c.M + 255) / 256) * ((c.Ncol + 319) / 320)
-                                                    : (long)((c.M + 511) / 512) * ((c.Ncol + 159) / 160);
-                    }
-                    if (big < TW) { cfg = cfg == WIN64_256x320 ? FAST_256x320 : FAST_512x160; win = false; }
-                }
-                if (cfg == FAST_256x320 || cfg == FAST_512x160) {
-                    // Too few full-size tiles for the chip: the four-wave variants (and the two-wave one of the
-                    // 320-wide family).  k-tiles of 64 channels where every problem allows them and the tile fits.
-                    long big = 0, mid = 0;
-                    bool k64 = true;
-                    for (int i = 0; i < n; ++i) {
-                        const ConvProb& c = ops[base + i]->conv;
-                        if (cfg == FAST_256x320) {
-                            big += (long)((c.M + 255) / 256) * ((c.Ncol + 319) / 320);
-                            mid += (long)((c.M + 127) / 128) * ((c.Ncol + 319) / 320);
-                        } else {
-                            big += (long)((c.M + 511) / 512) * ((c.Ncol + 159) / 160);
-                        }
-                        k64 = k64 && (c.Cin % 64 == 0);
-                    }
-                    // alone on the device a launch wants at least 200 tiles; next to the launches of other stream lanes
-                    // the idle compute units are not lost, and the larger tile's better operand reuse wins
-                    const int T1 = net->lanes_in_flight > 1 ? 64 : 200, T2 = 200, T3 = 200;
-                    if (cfg == FAST_256x320) {
-                        if (big < T1) cfg = mid < T2 ? FAST_128x160 : FAST_128x320;
-                        if (k64) cfg = cfg == FAST_256x320 ? FAST64_256x320 : cfg == FAST_128x320 ? FAST64_128x320 : FAST64_128x160;
-                    } else if (big < T3) {
-                        cfg = k64 ? FAST64_256x160 : FAST_256x160;
-                    }
-                }
+                bool win, fast;
+                const int cfg = conv_launch_cfg(net, &ops[base], n, win, fast);
                 if (used_cfg) *used_cfg = cfg;
                 const CfgInfo ci = win ? conv_win_cfg_info(cfg) : fast ? conv_fast_cfg_info(cfg) : conv_cfg_info(cfg, dt);
                 // longest tiles first: the blocks of a launch are dispatched in order
@@ -3119,6 +3128,41 @@ lp_status lp_debug_filter_load_extent(int kernel, int bk, int bn, int nw, int Nc
             }
         }
     *max_end = worst; *n_live = live;
+    return LP_OK;
+}
+
+lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Cout, int R, int stride, int lanes, int* taken) {
+    if (!taken) return fail(LP_ERR_INVALID_ARG, "NULL argument");
+    if ((dtype != LP_F32 && dtype != LP_BF16) || N < 1 || H < 1 || W < 1 || Cin < 1 || Cout < 1 || R < 1 || stride < 1 || lanes < 1)
+        return fail(LP_ERR_INVALID_ARG, "bad geometry");
+    lp_net net;
+    net.dtype = dtype; net.esz = dtype == LP_BF16 ? 2 : 4; net.lanes_in_flight = lanes;
+    Builder B{&net};
+    const Unit u = make_unit(R, Cin, Cout, stride, R / 2, N, H, W, true);
+    taken[0] = B.fconv_ok(u) ? 1 : 0;
+    taken[1] = B.fwgrad(u, Ref(), Ref(), Ref()).type == OP_FWGRAD ? 1 : 0;
+    Step fwd, dg;
+    fwd.push_back(B.conv_fwd(u, Ref(), Ref(), Ref(), Ref()));
+    if (stride <= 2 && H % stride == 0 && W % stride == 0) B.conv_dgrad(u, Ref(), Ref(), Ref(), Ref(), Ref(), dg);
+    for (int d = 0; d < 2; ++d) {
+        const Step& st = d == 0 ? fwd : dg;
+        taken[2 + d] = 0;
+        std::vector<const Op*> ops;
+        for (const Op& o : st) if (ops.empty() || o.key() == ops[0]->key()) ops.push_back(&o);
+        if (ops.empty() || ops.size() > (size_t)kMaxGroup) continue;
+        bool win, fast;
+        const int cfg = conv_launch_cfg(&net, ops.data(), (int)ops.size(), win, fast);
+        if (!fast) continue;
+        const CfgInfo ci = win ? conv_win_cfg_info(cfg) : conv_fast_cfg_info(cfg);
+        ConvGroup g; g.nprob = (int)ops.size(); g.total_tiles = 0;
+        for (int i = 0; i < g.nprob; ++i) {
+            ConvProb& p = g.p[i]; p = ops[i]->conv;
+            p.tiles_m = (p.M + ci.BM - 1) / ci.BM; p.tiles_n = (p.Ncol + ci.BN - 1) / ci.BN;
+            p.tile_start = g.total_tiles; g.total_tiles += p.tiles_m * p.tiles_n;
+        }
+        SConvGroup small; size_t lds = 0;
+        taken[2 + d] = plan_sconv(&net, g, win, ci, small, lds) ? 1 : 0;
+    }
     return LP_OK;
 }
 

@@ -303,3 +303,27 @@ def test_block_options_tensor_table_and_refusals():
             b.cin, b.cout, b.width = b.cin * 2, b.cout * 2, b.width * 2
     pre.modules[1].blocks[0].post_relu = True
     _expect(B.LP_ERR_SHAPE, B.lp_net_create, pre.modules, None, "f32", pre.bn_eps)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_specialised_kernels_refuse_sizes_beyond_their_fields(dtype):
+    """The narrow kernels and the small tiles keep their geometry in 16-bit fields: an image size that does not fit goes to
+    the general kernels, whatever it is modulo 2^16 (65536 + 32 wide must not pass for 32 wide)."""
+    q = B.lp_debug_layer_kernels
+    fits = q(dtype, 2, 8, 32, 16, 16, 3, 1)
+    assert fits["folded"] and fits["window_wgrad"]
+    for extra in (65536, 2 * 65536):
+        for w in (32, 64):
+            for r, st in ((3, 1), (3, 2), (1, 2)):
+                assert not q(dtype, 1, 4, extra + w, 16, 16, r, st)["folded"], (extra + w, r, st)
+    # the window of a strided filter gradient, (Wo - 1) * stride + 3 pixels wide: 65539 must not pass for 3
+    for cin in (3, 16):
+        assert q(dtype, 1, 8, 64, cin, 16, 3, 8)["window_wgrad"]                   # 59 pixels
+        assert not q(dtype, 1, 1024, 65 * 1024, cin, 16, 3, 1024)["window_wgrad"]
+        assert not q(dtype, 1, 512, 129 * 512, cin, 16, 3, 512)["window_wgrad"]
+    # tall images of one column in the small tiles of the wide layers
+    assert dtype == "f32" or q(dtype, 1, 8, 8, 160, 160, 3, 1)["small_fwd"]
+    for h in (32768, 65536, 65536 + 8):
+        for cin, cout, r in ((32, 128, 1), (32, 128, 3), (64, 128, 1)):
+            t = q(dtype, 1, h, 1, cin, cout, r, 1)
+            assert not t["small_fwd"] and not t["small_dgrad"], (h, cin, cout, r)
