@@ -404,6 +404,10 @@ lp_status lp_debug_filter_load_extent(int kernel, int bk, int bn, int nw, int Nc
  * with `lanes` stream lanes in flight and the layer alone in its launch.  Errors: LP_ERR_INVALID_ARG. */
 lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Cout, int R, int stride, int lanes, int* taken);
 
+/* How a call over all modules runs (host only): *folded = 1 if the passes are the narrow ones with the batch norms folded
+ * into the convolutions; lanes[k] (K entries) = the stream lane of module k, 0 = the caller's stream. */
+lp_status lp_debug_stream_lanes(const struct lp_net* net, int* folded, int* lanes);
+
 /* What the matrix cores of this device sustain (measurement aid of bench.py --measure-peak; no operand of the
  * library is touched).  Launches `blocks` workgroups of eight waves, each wave running `iters` times the 40
  * v_mfma_f32_32x32x16_bf16 of one filter tap of the convolution kernels' wave tile (2 x 5 micro-tiles, four k-steps):

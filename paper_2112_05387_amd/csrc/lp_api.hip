@@ -215,6 +215,7 @@ struct lp_net {
     bool narrow = false;                   // every module has the folded programs (ffwd ...)
     bool deep = false;                     // a module of more than three blocks, or AuxNets (see Builder::fconv_exact)
     bool lanes_set = false;                // the caller chose the stream lanes
+    bool fold_lanes = false;               // the folded programs use the stream lanes too (fold_uses_lanes)
     bool deterministic = false;            // lp_net_set_deterministic: every reduction in a fixed order
     // lp_net_set_fused_update: the parameter update runs inside lp_module_backward / lp_local_step
     bool fused_update = false;
@@ -2247,11 +2248,30 @@ static lp_status run_programs(lp_net* net, const std::vector<const Program*>& pr
 // narrow networks run the folded programs; the fixed summation order of the deterministic mode keeps the plain ones
 static bool folded(const lp_net* net) { return net->narrow && !net->deterministic; }
 
+// Do the folded programs use the stream lanes by default?  One launch holds the tiles of all modules, whatever their widths, so
+// on small mini-batches lanes only split it, and the host cannot issue several times the launches fast enough (ResNet-20 of
+// 8 samples, four lanes: 359 us, one stream: 273).  Where a lane's own launches fill the chip, the lanes fill each other's tails
+// and dependent trips to memory (same network, fp32: 32 samples 393 / 395 us, 48 samples 391 / 451, 128 samples 664 / 773, 512
+// samples 2162 / 2559; bf16: 80 samples 390 / 373, 96 samples 393 / 405; ResNet-56 of 256 samples 3068 / 3565).  Both types and
+// one to four lanes cross over where the convolutions of a lane write 8 to 10 MB a pass.
+static bool fold_uses_lanes(const lp_net* net) {
+    size_t elems = 0;
+    for (const ModulePlan& m : net->mods) {
+        if (m.has_stem) elems += m.stem.out_elems();
+        for (const BlockPlan& bp : m.bp) {
+            for (const Unit& u : bp.main) elems += u.out_elems();
+            if (bp.has_proj) elems += bp.proj.out_elems();
+        }
+    }
+    int used = 0;
+    for (int l = 0; l < 4; ++l) used += std::count(net->lane.begin(), net->lane.end(), l) > 0;
+    return elems * net->esz >= (size_t)used * (9u << 20);
+}
+
 // stream lane of every selected module, in the order the programs are collected
 static std::vector<int> lanes_of(const lp_net* net, uint32_t module_mask) {
     std::vector<int> out;
-    // the folded programs: one launch holds the tiles of all modules, whatever their widths, so lanes would only split it
-    if (folded(net) && !net->lanes_set) {
+    if (folded(net) && !net->lanes_set && !net->fold_lanes) {
         for (int k = 0; k < net->K; ++k) if ((module_mask >> k) & 1u) out.push_back(0);
         return out;
     }
@@ -2361,6 +2381,7 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
             net->lane[k] = (int)std::min<size_t>(i, 3);
         }
     }
+    net->fold_lanes = fold_uses_lanes(net);
     *out = net;
     return LP_OK;
 }
@@ -3163,6 +3184,14 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
         SConvGroup small; size_t lds = 0;
         taken[2 + d] = plan_sconv(&net, g, win, ci, small, lds) ? 1 : 0;
     }
+    return LP_OK;
+}
+
+lp_status lp_debug_stream_lanes(const struct lp_net* net, int* is_folded, int* lanes) {
+    if (!net || !is_folded || !lanes) return fail(LP_ERR_INVALID_ARG, "NULL argument");
+    *is_folded = folded(net) ? 1 : 0;
+    const std::vector<int> l = lanes_of(net, ~0u);
+    std::copy(l.begin(), l.end(), lanes);
     return LP_OK;
 }
 

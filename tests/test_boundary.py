@@ -327,3 +327,34 @@ def test_specialised_kernels_refuse_sizes_beyond_their_fields(dtype):
         for cin, cout, r in ((32, 128, 1), (32, 128, 3), (64, 128, 1)):
             t = q(dtype, 1, h, 1, cin, cout, r, 1)
             assert not t["small_fwd"] and not t["small_dgrad"], (h, cin, cout, r)
+
+
+def _lanes(net, after=None):
+    h = B.lp_net_create(net.modules, net.aux, net.dtype, net.bn_eps)
+    try:
+        if after:
+            after(h)
+        return B.lp_debug_stream_lanes(h, net.K)
+    finally:
+        B.lp_net_destroy(h)
+
+
+def test_folded_passes_use_the_stream_lanes_of_large_mini_batches():
+    """Narrow networks run on the caller's stream alone only where a lane's launches are too small to fill the chip."""
+    def net(name, batch, dtype, split=None):
+        n = wl.make_config(name, batch=batch, split=split)
+        n.dtype = dtype
+        return n
+    for name, dtype, small, large in (("resnet20", "f32", 32, 128), ("resnet20", "bf16", 80, 128), ("resnet56", "f32", 8, 32),
+                                      ("resnet56", "f32", 8, 256), ("resnet56", "bf16", 16, 128)):
+        assert _lanes(net(name, small, dtype)) == (True, [0] * net(name, 1, dtype).K), (name, dtype, small)
+        folded, lanes = _lanes(net(name, large, dtype))
+        assert folded and len(set(lanes)) >= 3, (name, dtype, large, lanes)
+    assert _lanes(net("resnet56", 256, "f32", [7, 7, 7, 6])) == (True, [0, 1, 2, 3])
+    assert _lanes(net("resnet20", 128, "f32", [9])) == (True, [0])
+    assert _lanes(wl.make_config("tiny")) == (True, [0, 0])
+    # the caller's own choice stands, and so does the order of networks that are not folded
+    assert _lanes(net("resnet20", 128, "f32"), lambda h: B.lp_net_set_stream_lanes(h, None)) == (True, [0] * 4)
+    assert _lanes(net("resnet20", 4, "f32"), lambda h: B.lp_net_set_stream_lanes(h, [0, 1, 0, 2])) == (True, [0, 1, 0, 2])
+    assert _lanes(net("resnet20", 4, "f32"), lambda h: B.lp_net_set_deterministic(h, 1)) == (False, [0, 1, 2, 3])
+    assert _lanes(wl.make_config("wrn28_10", batch=4)) == (False, [0, 1, 2, 3])
