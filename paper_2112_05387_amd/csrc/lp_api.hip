@@ -2268,6 +2268,26 @@ static bool fold_uses_lanes(const lp_net* net) {
     return elems * net->esz >= (size_t)used * (9u << 20);
 }
 
+// Do the separate passes beat the folded ones?  Folding saves passes over memory and launches; its convolutions multiply at a
+// lower rate, the more so the more channels (each of the two column tiles of a 64-channel layer transforms the window again).
+// Where 64 -> 64 channel layers are most of the arithmetic and have many pixels, that is the larger part (six blocks in two
+// modules, us per step folded / separate: fp32 32 x 32, 32 samples 1243 / 1408, 64 samples 2322 / 2163, 16 x 16, 128 samples
+// 1185 / 1346, 256 samples 2245 / 2099; bf16 32 x 32, 64 samples 760 / 902, 128 samples 1345 / 1256, 256 samples 2636 / 2234; images
+// smaller than a tile of 128 pixels, bf16 8 x 8, 512 samples 490 / 606, 1024 samples 970 / 791).  One module has no other
+// lane beside its separate passes: three blocks of 32 x 32, 64 samples 1329 / 1550 and 582 / 740, 256 samples 4831 / 4775 and 1634 / 1472.
+static bool folding_loses(const lp_net* net) {
+    double all = 0, wide = 0;
+    for (const ModulePlan& m : net->mods)
+        for (const BlockPlan& bp : m.bp)
+            for (const Unit& u : bp.main) {
+                const double f = (double)u.out_elems() * u.cin * u.R * u.R;
+                const int few = net->K == 1 ? 131072 : net->dtype == LP_F32 || u.Ho * u.Wo < 128 ? 32768 : 65536;
+                all += f;
+                if (u.cin == 64 && u.cout == 64 && (long)u.N * u.Ho * u.Wo > few) wide += f;
+            }
+    return wide > 0.5 * all;
+}
+
 // stream lane of every selected module, in the order the programs are collected
 static std::vector<int> lanes_of(const lp_net* net, uint32_t module_mask) {
     std::vector<int> out;
@@ -2381,6 +2401,7 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
             net->lane[k] = (int)std::min<size_t>(i, 3);
         }
     }
+    net->narrow = net->narrow && !folding_loses(net);
     net->fold_lanes = fold_uses_lanes(net);
     *out = net;
     return LP_OK;

@@ -358,3 +358,27 @@ def test_folded_passes_use_the_stream_lanes_of_large_mini_batches():
     assert _lanes(net("resnet20", 4, "f32"), lambda h: B.lp_net_set_stream_lanes(h, [0, 1, 0, 2])) == (True, [0, 1, 0, 2])
     assert _lanes(net("resnet20", 4, "f32"), lambda h: B.lp_net_set_deterministic(h, 1)) == (False, [0, 1, 2, 3])
     assert _lanes(wl.make_config("wrn28_10", batch=4)) == (False, [0, 1, 2, 3])
+
+
+def test_folding_is_refused_where_the_separate_passes_are_faster():
+    """Networks that are mostly 64-channel layers of many pixels keep the separate passes; the same layers as the last
+    stage of a network, or on fewer pixels, are folded."""
+    from workloads import configs as cfg
+
+    def net(widths, batch, side, dtype, split):
+        blocks, cin = [], widths[0]
+        for i, c in enumerate(widths):
+            for j in range(3):
+                s = 2 if (i and not j) else 1
+                blocks.append(Block("basic", cin, c, c, s, proj=(s != 1 or cin != c)))
+                cin = c
+        n = cfg._assemble("n", cfg._split(blocks, split), batch, side, side, 3, 1, widths[0], 10, seed=1)
+        n.dtype = dtype
+        return n
+    for dtype, few, many in (("f32", 32, 64), ("bf16", 64, 128)):
+        assert _lanes(net([64], few, 32, dtype, [2, 1]))[0]
+        assert not _lanes(net([64], many, 32, dtype, [2, 1]))[0]
+        assert _lanes(net([64], 512, 8, dtype, [2, 1]))[0] and not _lanes(net([64], 1024, 8, dtype, [2, 1]))[0]
+        assert _lanes(net([64], 128, 32, dtype, [3]))[0] and not _lanes(net([64], 256, 32, dtype, [3]))[0]
+        assert _lanes(net([16, 32, 64], 4096, 32, dtype, [3, 3, 3]))[0]
+        assert _lanes(wl.make_config("resnet20", batch=1024))[0] and _lanes(wl.make_config("resnet56", batch=256))[0]
