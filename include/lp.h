@@ -404,6 +404,10 @@ lp_status lp_debug_filter_load_extent(int kernel, int bk, int bn, int nw, int Nc
  * with `lanes` stream lanes in flight and the layer alone in its launch.  Errors: LP_ERR_INVALID_ARG. */
 lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Cout, int R, int stride, int lanes, int* taken);
 
+/* Does the linear layer of a head (N samples, C channels) run in its tiled kernels (host only)?  tiled[2] = {forward, filter
+ * gradient}.  Errors: LP_ERR_INVALID_ARG. */
+lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled);
+
 /* How a call over all modules runs (host only): *folded = 1 if the passes are the narrow ones with the batch norms folded
  * into the convolutions; lanes[k] (K entries) = the stream lane of module k, 0 = the caller's stream. */
 lp_status lp_debug_stream_lanes(const struct lp_net* net, int* folded, int* lanes);

@@ -3208,6 +3208,15 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
     return LP_OK;
 }
 
+lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled) {
+    if (!tiled || N < 1 || classes < 1 || C < 1) return fail(LP_ERR_INVALID_ARG, "bad argument");
+    HeadProb p; memset(&p, 0, sizeof(p));
+    p.N = N; p.classes = classes; p.C = C;
+    tiled[0] = fc_fwd_tiled(p) ? 1 : 0;
+    tiled[1] = fc_bwd_w_tiled(p) ? 1 : 0;
+    return LP_OK;
+}
+
 lp_status lp_debug_stream_lanes(const struct lp_net* net, int* is_folded, int* lanes) {
     if (!net || !is_folded || !lanes) return fail(LP_ERR_INVALID_ARG, "NULL argument");
     *is_folded = folded(net) ? 1 : 0;

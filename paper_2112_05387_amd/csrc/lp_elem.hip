@@ -702,7 +702,7 @@ __global__ void fc_fwd_kernel(const HeadProb P) {          // one wave per (n, c
     for (int sh = 32; sh > 0; sh >>= 1) s += __shfl_xor(s, sh, 64);
     if (lane == 0) P.logits[o] = s + P.b[j];
 }
-// The same sums in the same order where one output per wave would read its two rows from L2 2^22 times and more (1 GB for 64
+// The same sums in the same order where one output per wave would read too much from L2, two rows for every output (1 GB for 64
 // samples x 1000 classes x 2048 channels): a wave owns 8 samples x 4 classes and reads 12 rows for its 32 outputs.
 constexpr int kFcSamples = 8, kFcClasses = 4;
 __global__ __launch_bounds__(256) void fc_fwd_tiled_kernel(const HeadProb P) {
@@ -817,7 +817,9 @@ __global__ __launch_bounds__(256) void fc_bwd_x_kernel(const HeadProb P) {
         const int c = cbase + threadIdx.x;
         float acc = 0.f;
         // The chain over the classes is one of trips to L2: 64 rows of w in flight (with 8, 66 us for 1000 classes
-        // whatever the mini-batch).  The last rows go 16 at a time, those beyond the end read but not added.
+        // whatever the mini-batch).  The last rows go 16, 8 and 4 at a time, so that at most three are read in vain (all
+        // samples of a large mini-batch together are bound by what they read: with 16 for two classes of 2048 samples and
+        // 1024 channels the backward pass of the head took 137 us instead of 125).
         int j = 0;
         for (; j + 63 < classes; j += 64) {
             float w[64];
@@ -826,12 +828,27 @@ __global__ __launch_bounds__(256) void fc_bwd_x_kernel(const HeadProb P) {
 #pragma unroll
             for (int u = 0; u < 64; ++u) acc += s_dl[j + u] * w[u];
         }
-        for (; j < classes; j += 16) {
+        for (; j + 15 < classes; j += 16) {
             float w[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) w[u] = P.w[(size_t)min(j + u, classes - 1) * C + c];
+            for (int u = 0; u < 16; ++u) w[u] = P.w[(size_t)(j + u) * C + c];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) if (j + u < classes) acc += s_dl[j + u] * w[u];
+            for (int u = 0; u < 16; ++u) acc += s_dl[j + u] * w[u];
+        }
+        if (j + 7 < classes) {
+            float w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = P.w[(size_t)(j + u) * C + c];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += s_dl[j + u] * w[u];
+            j += 8;
+        }
+        for (; j < classes; j += 4) {
+            float w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = P.w[(size_t)min(j + u, classes - 1) * C + c];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) if (j + u < classes) acc += s_dl[j + u] * w[u];
         }
         s_dp[threadIdx.x] = acc * inv;
     }
@@ -968,12 +985,21 @@ hipError_t launch_maxpool_bwd(const PoolProb& p, int dtype, hipStream_t s) {
     LP_DISPATCH_T(dtype, maxpool_bwd_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), s, p);
     return hipGetLastError();
 }
-// the linear layer's tiled kernels: from 2^22 multiply-adds on
-static bool fc_tiled(const HeadProb& p) { return (size_t)p.N * p.classes * p.C >= (1u << 22); }
+// The linear layer's tiled kernels do less but take longer chains, a few workgroups of them do not fill the chip.  Forward: the
+// tiled kernel takes 17 us until its waves fill it, one output per wave 9 us and 0.1 ns + 0.6 ps * C per output (tiled / plain:
+// 128 samples x 100 classes x 640 channels 18.1 / 15.4 us, 256 samples 18.3 / 22.3; 8 x 1000 x 2048 25.6 / 24.3, 12 samples 24.8 /
+// 33.7; 4096 x 10 x 128 17.4 / 16.0, 8192 x 10 x 64 17.4 / 20.5).
+bool fc_fwd_tiled(const HeadProb& p) { return (size_t)p.N * p.classes * (p.C + 170) >= 18000000u; }
+// Filter gradient: a thread of the tiled kernel has four classes, so it wants that many more of them (whole backward pass of the
+// head, tiled / plain: 128 samples x 100 classes x 640 channels 20.6 / 15.3 us, 512 x 200 x 1024 68.0 / 60.6, 2048 x 1000 x 64 199 /
+// 149, 8192 x 10 x 64 681 / 424; 1024 x 512 x 640 137 / 148, 64 x 1000 x 512 29 / 50, 64 x 1000 x 2048 38 / 76).
+bool fc_bwd_w_tiled(const HeadProb& p) {
+    return (size_t)p.classes * p.C >= (1u << 18) && (size_t)p.N * p.classes * p.C >= (1u << 22);
+}
 hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s) {
     const int epv = dtype == 1 ? 8 : 4;
     LP_DISPATCH_T(dtype, avgpool_kernel, dim3((p.N * (p.C / epv) + 63) / 64), dim3(64), s, p);
-    if (fc_tiled(p)) {
+    if (fc_fwd_tiled(p)) {
         const size_t waves = (size_t)((p.N + kFcSamples - 1) / kFcSamples) * ((p.classes + kFcClasses - 1) / kFcClasses);
         hipLaunchKernelGGL(fc_fwd_tiled_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, p);
     } else
@@ -981,7 +1007,7 @@ hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s) {
     return hipGetLastError();
 }
 hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s) {
-    if (fc_tiled(p))
+    if (fc_bwd_w_tiled(p))
         hipLaunchKernelGGL(fc_bwd_w_tiled_kernel, dim3((p.classes + kFcClasses - 1) / kFcClasses, (p.C + 255) / 256), dim3(256), 0, s, p);
     else
         hipLaunchKernelGGL(fc_bwd_w_kernel, dim3((p.classes * p.C + 255) / 256), dim3(256), 0, s, p);

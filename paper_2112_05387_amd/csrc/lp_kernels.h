@@ -290,6 +290,9 @@ hipError_t launch_bn_stats(const BnBwdGroup& g, int dtype, hipStream_t s);
 constexpr int kSgdElemsPerBlock = 4096;
 hipError_t launch_maxpool_fwd(const PoolProb& p, int dtype, hipStream_t s);
 hipError_t launch_maxpool_bwd(const PoolProb& p, int dtype, hipStream_t s);
+// does the linear layer of the head run in its tiled kernels (forward, filter gradient)?
+bool fc_fwd_tiled(const HeadProb& p);
+bool fc_bwd_w_tiled(const HeadProb& p);
 hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s);
 hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s);
 hipError_t launch_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits,

@@ -382,3 +382,11 @@ def test_folding_is_refused_where_the_separate_passes_are_faster():
         assert _lanes(net([64], 128, 32, dtype, [3]))[0] and not _lanes(net([64], 256, 32, dtype, [3]))[0]
         assert _lanes(net([16, 32, 64], 4096, 32, dtype, [3, 3, 3]))[0]
         assert _lanes(wl.make_config("resnet20", batch=1024))[0] and _lanes(wl.make_config("resnet56", batch=256))[0]
+
+
+@pytest.mark.parametrize("n,classes,c,fwd,bwd", [
+    (128, 100, 640, False, False), (96, 100, 640, False, False), (256, 100, 640, True, False), (4096, 10, 128, False, False),
+    (8192, 10, 64, True, False), (2048, 2, 1024, False, False), (64, 1000, 512, True, True), (64, 1000, 2048, True, True),
+    (8, 1000, 2048, False, True), (3, 1000, 2048, False, True), (2, 1000, 2048, False, False), (2048, 1000, 64, True, False)])
+def test_tiled_linear_layer_only_where_it_is_the_faster_one(n, classes, c, fwd, bwd):
+    assert B.lp_debug_linear_kernels(n, classes, c) == (fwd, bwd)

@@ -155,3 +155,17 @@ def test_small_tiles_of_wide_layers(case):
     net = wide_net(**case)
     check_units(net, note=f" {case}")
     assert (CONV, SMALL_TILES) in launches(net)
+
+
+@pytest.mark.parametrize("batch,classes,width,tiled", [
+    # the last group of samples, classes and channels not full; more samples than a chunk of the filter gradient holds
+    (13, 1003, 2040, (True, True)), (150, 509, 648, (True, True)), (9, 2047, 1288, (True, True)),
+    # one of the two kernels tiled
+    (3, 1001, 2048, (False, True)), (300, 101, 632, (True, False)),
+    (150, 100, 640, (False, False))])
+def test_linear_layer_kernels(batch, classes, width, tiled):
+    from paper_2112_05387_amd import binding as B
+    say("case linear layer", batch, classes, width)
+    assert B.lp_debug_linear_kernels(batch, classes, width) == tiled
+    net = cfg._assemble("linear", [[Block("bottleneck", width, width, 8, 1, False)]], batch, 2, 2, width, 0, 0, classes, seed=47)
+    check_units(net)
