@@ -382,13 +382,9 @@ hipError_t fast_launch(const ConvGroup& g, hipStream_t s) {
     const size_t operands = std::max((size_t)STAGES * (BM + BN) * BK * 2, (size_t)WGM * WGN * 32 * 336);   // ring / epilogue staging
     const size_t lds = operands + BM * sizeof(int);
     static_assert((size_t)STAGES * (BM + BN) * BK * 2 + BM * sizeof(int) <= 160 * 1024, "LDS budget");
-    static bool configured = false;
     auto kern = conv_igemm_fast_kernel<WGM, WGN, STAGES, BK>;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static OncePerDevice configured;
+    if (const hipError_t e = raise_lds_limit(configured, {(const void*)kern}, 160 * 1024); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(g.total_tiles), dim3(WGM * WGN * 64), lds, s, g);
     return hipGetLastError();
 }

@@ -427,13 +427,9 @@ hipError_t win_launch(const ConvGroup& g, hipStream_t s) {
                                 (size_t)conv_win_max_slabs(BM, WGM * WGN) * WGM * WGN * 64 * sizeof(unsigned));
     }
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static bool configured = false;
     auto kern = conv_win_kernel<WGM, WGN, STAGES, BK>;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static OncePerDevice configured;
+    if (const hipError_t e = raise_lds_limit(configured, {(const void*)kern}, 160 * 1024); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(g.total_tiles), dim3(WGM * WGN * 64), lds, s, g);
     return hipGetLastError();
 }

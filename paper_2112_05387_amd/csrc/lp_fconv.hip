@@ -586,13 +586,9 @@ size_t fconv_lds_bytes(const FConvProb& p, int esz) {
 
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
-    static bool configured = false;
-    if (!configured) {                             // (the windows of stride-2 layers in ordered tiles are the ones beyond 64 KB)
-        hipError_t e = hipFuncSetAttribute((const void*)fconv_kernel<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, kFconvMaxLds);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)fconv_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, kFconvMaxLds);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static OncePerDevice configured;               // (the windows of stride-2 layers in ordered tiles are the ones beyond 64 KB)
+    if (const hipError_t e = raise_lds_limit(configured, {(const void*)fconv_kernel<bf16_t>, (const void*)fconv_kernel<float>}, kFconvMaxLds);
+        e != hipSuccess) return e;
     if (dtype == 1) hipLaunchKernelGGL(fconv_kernel<bf16_t>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
     else hipLaunchKernelGGL(fconv_kernel<float>, dim3(g.total_tiles), dim3(FC_NT), lds, s, g);
     return hipGetLastError();

@@ -6,6 +6,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
+#include "lp_once.h"
+
 namespace lp {
 
 constexpr int kMaxGroup = 16;   // problems per grouped launch (bounded by the 4 KiB kernel-argument block)
@@ -264,6 +268,14 @@ CfgInfo conv_win_cfg_info(int cfg);
 // window slabs (1 KiB wave-loads) a wave of the window kernel can hold addresses for
 constexpr int conv_win_max_slabs(int BM, int NW) { return BM == 512 ? 10 : 7; }
 
+// dynamic LDS of up to `bytes` for these kernels, on the current device
+inline hipError_t raise_lds_limit(OncePerDevice& once, std::initializer_list<const void*> kernels, int bytes) {
+    return once.run([](int* dev) { return hipGetDevice(dev); }, [&] {
+        for (const void* k : kernels)
+            if (const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); e != hipSuccess) return e;
+        return hipSuccess;
+    });
+}
 hipError_t launch_conv(const ConvGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_conv_win(const ConvGroup& g, int cfg, hipStream_t s);

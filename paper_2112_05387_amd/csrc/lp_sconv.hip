@@ -259,12 +259,8 @@ __global__ __launch_bounds__(SC_NT) void stats_of_tiles_kernel(const TileStatsGr
 hipError_t launch_sconv(const SConvGroup& g, size_t lds, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)sconv_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static OncePerDevice configured;
+    if (const hipError_t e = raise_lds_limit(configured, {(const void*)sconv_kernel}, 160 * 1024); e != hipSuccess) return e;
     hipLaunchKernelGGL(sconv_kernel, dim3(g.total_tiles), dim3(SC_NT), lds, s, g);
     return hipGetLastError();
 }

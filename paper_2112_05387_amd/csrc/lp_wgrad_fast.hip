@@ -326,12 +326,8 @@ int wgrad_fast_blocks(const WgradProb& p) {
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
     const size_t lds = (size_t)WF_STAGES * WF_STAGE_BYTES;
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)conv_wgrad_fast_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    static OncePerDevice configured;
+    if (const hipError_t e = raise_lds_limit(configured, {(const void*)conv_wgrad_fast_kernel}, (int)lds); e != hipSuccess) return e;
     hipLaunchKernelGGL(conv_wgrad_fast_kernel, dim3(g.total_tiles), dim3(WF_NT), lds, s, g);
     return hipGetLastError();
 }
