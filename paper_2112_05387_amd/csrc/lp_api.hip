@@ -100,7 +100,7 @@ static void* resolve(const Ref& r, const Bindings& b) {
 enum OpType { OP_FILL = 0, OP_WTRANS, OP_CONV, OP_BN_APPLY, OP_POOL_FWD, OP_HEAD_FWD, OP_HEAD_BWD, OP_POOL_BWD,
               OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV, OP_FWGRAD };
 // tensor references of an OP_FCONV operation
-enum FcRef { F_IN = 0, F_IN2, F_ADDIN, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMMA2, F_BETA2, F_WT, F_OUT, F_ADD0, F_OSTATS,
+enum FcRef { F_IN = 0, F_IN2, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMMA2, F_BETA2, F_WT, F_OUT, F_ADD0, F_OSTATS,
              F_EY, F_ESTATS, F_EGAMMA, F_EBETA, F_ERED, F_EY2, F_ESTATS2, F_ERED2, F_COUNT };
 
 struct Op {
@@ -358,7 +358,7 @@ struct Builder {
     struct Fx {                                    // what the convolution reads: FxMode and its tensors
         int mode = FX_PLAIN;
         bool relu = false;
-        Ref in, in2, addin, side, stats, gamma, beta, stats2, gamma2, beta2;
+        Ref in, in2, side, stats, gamma, beta, stats2, gamma2, beta2;
     };
     static int fconv_max_bn(const FConvProb& p) { return p.Ncol >= 32 ? 32 : 16; }
     // pixels of a full-size tile: 16 KB of window at most for the wider layers
@@ -403,7 +403,7 @@ struct Builder {
         const int BN = fconv_max_bn(p);
         fconv_tile(p, BN, fconv_px(p, BN));
         fconv_order(p);
-        o.r[F_IN] = x.in; o.r[F_IN2] = x.in2; o.r[F_ADDIN] = x.addin; o.r[F_SIDE] = x.side;
+        o.r[F_IN] = x.in; o.r[F_IN2] = x.in2; o.r[F_SIDE] = x.side;
         o.r[F_STATS] = x.stats; o.r[F_GAMMA] = x.gamma; o.r[F_BETA] = x.beta;
         o.r[F_STATS2] = x.stats2; o.r[F_GAMMA2] = x.gamma2; o.r[F_BETA2] = x.beta2;
         o.r[F_WT] = wt; o.r[F_OUT] = out; o.r[F_ADD0] = add0; o.r[F_OSTATS] = ostats;
@@ -1861,7 +1861,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
                     FConvProb& p = g.p[i]; p = o.fc;
-                    p.in = resolve(o.r[F_IN], b); p.in2 = resolve(o.r[F_IN2], b); p.addin = resolve(o.r[F_ADDIN], b);
+                    p.in = resolve(o.r[F_IN], b); p.in2 = resolve(o.r[F_IN2], b);
                     p.side = resolve(o.r[F_SIDE], b);
                     p.stats = (const double*)resolve(o.r[F_STATS], b); p.gamma = (const float*)resolve(o.r[F_GAMMA], b);
                     p.beta = (const float*)resolve(o.r[F_BETA], b);

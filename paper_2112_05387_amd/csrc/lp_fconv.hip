@@ -13,7 +13,8 @@
 //   * the epilogue adds the skip gradient, stores 16-byte vectors, and sums either the statistics of the stored result
 //     (forward) or the backward sums of the batch norm(s) the result arrives at.
 // Tiles are whole rows of one image.  One kernel serves every width (a tile picks its shape by its problem), so that
-// modules of different width share a launch: 4096 / BN pixels x BN channels per workgroup of four waves.
+// modules of different width share a launch: at most 4096 / BN pixels x BN channels per workgroup of four waves, in the
+// ordered tiles of 16 and 32 channels (FConvProb::ordered) 8192 / BN pixels or two images.
 #include <algorithm>
 
 #include "lp_kernels.h"
@@ -166,7 +167,6 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
     const size_t img = (size_t)n * IH * IW * Cin;  // this image; offsets inside it fit 32 bits
     const T* __restrict__ in = reinterpret_cast<const T*>(P.in) + img;
     const T* __restrict__ in2 = reinterpret_cast<const T*>(P.in2) + img;
-    const T* __restrict__ addin = P.addin ? reinterpret_cast<const T*>(P.addin) + img : nullptr;
     T* __restrict__ side = tn == 0 && P.side ? reinterpret_cast<T*>(P.side) + img : nullptr;
     const int ihb = a0 * P.imul + P.dhmin, iwb = P.dwmin;
     const int own0 = a0 * P.imul, own1 = min(IH, (a0 + P.TH) * P.imul);
@@ -264,11 +264,6 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
                     }
 #pragma unroll
                     for (int e = 0; e < EPV; ++e) o[e] = fmaf(c2[e], a[e], -(c3[e] * b[e])) + c4[e];
-                    if (addin) {
-                        Vec<T>::load(addin + off[u], a);
-#pragma unroll
-                        for (int e = 0; e < EPV; ++e) o[e] += a[e];
-                    }
                     put(i0, u, Vec<T>::pack(o));
                 }
             } else {

@@ -48,13 +48,13 @@ struct ConvGroup {
 //   FX_BN      [ReLU] bn(in)
 //   FX_BN_ADD  [ReLU] (bn(in) + in2)
 //   FX_BN_BN   [ReLU] (bn(in) + bn2(in2))
-//   FX_BWD     the batch-norm backward of in = g at y = in2: k1*g' - k2*y + k3  [+ addin]
+//   FX_BWD     the batch-norm backward of in = g at y = in2: k1*g' - k2*y + k3
 // evaluated while the input window of a tile is copied to LDS, and stored to `side` (layout of in) by the tile that owns
 // the pixel.  Behind the sum: optional addend, statistics of the stored result (ostats), and for a data-gradient the
 // backward sums of up to two batch norms whose arriving gradient this result is (ey: the tensor they normalise).
 enum FxMode { FX_PLAIN = 0, FX_BN, FX_BN_ADD, FX_BN_BN, FX_BWD };
 struct FConvProb {
-    const void *in, *in2, *addin;
+    const void *in, *in2;
     void* side;
     const double* stats; const float *gamma, *beta;          // the batch norm of `in` (FX_BWD: of in2)
     const double* stats2; const float *gamma2, *beta2;       // FX_BN_BN: the batch norm of in2; FX_BWD: its backward sums, and where dgamma / dbeta go
@@ -84,7 +84,8 @@ struct FConvGroup {
     FConvProb p[kMaxGroup];
 };
 static_assert(sizeof(FConvGroup) <= 4096, "kernel-argument block");
-// pixels of a tile with BN output channels: four waves hold at most 4 micro-tiles of 16 x 16 each
+// pixels of a tile with BN output channels: four waves hold at most 4 micro-tiles of 16 x 16 each (ordered tiles of 16 and 32
+// channels: 8, in two parts)
 constexpr int fconv_max_px(int BN) { return 4096 / BN; }
 // k-steps of a tile: 64 bytes of channels of one tap each (bf16 with 16 channels: two taps)
 __host__ __device__ inline int fconv_ksteps(int ntaps, int Cin, int esz) { return Cin * esz < 64 ? (ntaps + 1) / 2 : ntaps * (Cin * esz / 64); }
@@ -258,7 +259,8 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                FAST_128x320 = 10, FAST_128x160 = 11,   // ... its four- and two-wave variants, chosen per launch
                FAST64_256x320 = 12, FAST64_128x320 = 13, FAST64_128x160 = 14,   // ... with k-tiles of 64 channels
                FAST_256x160 = 15, FAST64_256x160 = 16,  // four-wave variants of the 160-wide family
-               WIN64_512x160 = 21, WIN64_256x320 = 23, SMALL_128x32 = 24,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
+               WIN64_512x160 = 21, WIN64_256x320 = 23,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
+               SMALL_128x32 = 24,                      // bf16 wide layers on few pixels, recorded only (lp_sconv.hip)
                WGRAD_FAST = 8 };                       // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
 struct CfgInfo { int BM, BN, BK; };
 CfgInfo conv_cfg_info(int cfg, int dtype);
