@@ -408,6 +408,11 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
  * gradient}.  Errors: LP_ERR_INVALID_ARG. */
 lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled);
 
+/* A per-thread switch read by lp_net_create: nets created while it is on run the kernels that the specialised ones stand in
+ * for (batch norms as passes of their own, the large tiles of wide layers, the general filter gradients), for comparisons of
+ * the two. */
+lp_status lp_debug_separate_passes(int on);
+
 /* How a call over all modules runs (host only): *folded = 1 if the passes are the narrow ones with the batch norms folded
  * into the convolutions; lanes[k] (K entries) = the stream lane of module k, 0 = the caller's stream. */
 lp_status lp_debug_stream_lanes(const struct lp_net* net, int* folded, int* lanes);

@@ -25,6 +25,7 @@ using namespace lp;
 // ----------------------------------------------------------------------------------------------------
 static thread_local std::string g_err;
 static thread_local bool g_keep_gradients = false;   // lp_debug_keep_gradients: nets created on this thread keep every gradient
+static thread_local bool g_separate_passes = false;  // lp_debug_separate_passes: nets created on this thread use the general kernels
 
 static lp_status fail(lp_status st, const char* fmt, ...) {
     char buf[512];
@@ -212,6 +213,7 @@ struct lp_net {
     hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
     bool lanes_ready = false;              // every extra stream and event above exists
     bool keep_gradients = false;           // debug layout: no gradient buffer is reused inside a backward pass
+    bool separate = false;                 // debug: no folded passes, no small tiles, no window filter gradients
     bool narrow = false;                   // every module has the folded programs (ffwd ...)
     bool deep = false;                     // a module of more than three blocks, or AuxNets (see Builder::fconv_exact)
     bool lanes_set = false;                // the caller chose the stream lanes
@@ -1628,6 +1630,7 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
 // and 5) behind 25 us of prologue, window and epilogue (10 for the smaller variants); a small one takes a 128-byte line
 // into LDS per 4.5 clocks, and 5 us around that, statistics included.
 static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const CfgInfo& ci, SConvGroup& out, size_t& lds) {
+    if (net->separate) return false;
     out.nprob = g.nprob; out.pad_[0] = out.pad_[1] = 0;
     lds = 0;
     const int cap = std::max(1, 256 / std::max(1, net->lanes_in_flight));
@@ -1887,7 +1890,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 err = launch_fconv(g, dt, lds, s);
             } break;
             case OP_FWGRAD: {
-                if (net->deterministic || net->fused_update) {       // fixed order, or the update in the epilogue: the plain kernels
+                if (net->deterministic || net->fused_update || net->separate) {       // fixed order, or the update in the epilogue: the plain kernels
                     std::vector<Op> plain(n);
                     std::vector<char> done(n, 0);
                     for (int i = 0; i < n; ++i) { plain[i] = *ops[base + i]; plain[i].type = OP_WGRAD; }
@@ -2246,7 +2249,7 @@ static lp_status run_programs(lp_net* net, const std::vector<const Program*>& pr
 }
 
 // narrow networks run the folded programs; the fixed summation order of the deterministic mode keeps the plain ones
-static bool folded(const lp_net* net) { return net->narrow && !net->deterministic; }
+static bool folded(const lp_net* net) { return net->narrow && !net->deterministic && !net->separate; }
 
 // Do the folded programs use the stream lanes by default?  One launch holds the tiles of all modules, whatever their widths, so
 // on small mini-batches lanes only split it, and the host cannot issue several times the launches fast enough (ResNet-20 of
@@ -2351,6 +2354,7 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
     lp_net* net = new lp_net();
     net->K = K; net->dtype = dtype; net->eps = bn_eps; net->esz = dtype == LP_BF16 ? 2 : 4;
     net->keep_gradients = g_keep_gradients;
+    net->separate = g_separate_passes;
     net->narrow = true;
     net->deep = aux != nullptr;
     for (int k = 0; k < K; ++k) net->deep = net->deep || mods[k].n_blocks > 3;
@@ -3089,6 +3093,8 @@ static void collect_units(const ModulePlan& m, std::vector<lp_debug_unit>& out, 
         }
     }
 }
+
+lp_status lp_debug_separate_passes(int on) { g_separate_passes = on != 0; return LP_OK; }
 
 lp_status lp_debug_unit_count(const struct lp_net* net, int k, int* n) {
     if (!net || !n) return fail(LP_ERR_INVALID_ARG, "NULL argument");

@@ -169,3 +169,113 @@ def test_linear_layer_kernels(batch, classes, width, tiled):
     assert B.lp_debug_linear_kernels(batch, classes, width) == tiled
     net = cfg._assemble("linear", [[Block("bottleneck", width, width, 8, 1, False)]], batch, 2, 2, width, 0, 0, classes, seed=47)
     check_units(net)
+def step_outputs(net, separate):
+    """Tensors of one local step through the specialised kernels, or through those they stand in for; and what was launched."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    B.lp_debug_separate_passes(separate)
+    try:
+        ls = LocalStep(net)
+    finally:
+        B.lp_debug_separate_passes(False)
+    try:
+        for k in range(net.K):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        B.lp_profile_enable(ls.net, 2)
+        ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        kinds = {(r["kind"], r["cfg"]) for r in B.lp_profile_fetch(ls.net)}
+        B.lp_profile_enable(ls.net, 0)
+        exact = {f"{n}{k}": t.clone() for n, ts in (("y", ls.y), ("dy", ls.dy), ("dx", ls.dx[1:])) for k, t in enumerate(ts)}
+        exact.update(logits=ls.logits.clone(), dlogits=ls.dlogits.clone())
+        sums = {}
+        for k in range(net.K):
+            for i, (info, spec) in enumerate(zip(ls.tables[k], cfg.module_tensor_specs(net.modules[k]))):
+                o = info.grad_offset // 4
+                g = ls.dparams[k][o:o + int(info.numel)].clone()
+                (exact if spec.kind.startswith("bn") else sums)[f"m{k}.{spec.name}"] = g
+    finally:
+        ls.close()
+    return exact, sums, kinds
+
+
+def assert_same_bits(net, used):
+    """Everything but the filter gradients (their partial sums meet in atomics) has the bits of the kernels stood in for."""
+    import torch
+    got, got_sums, kinds = step_outputs(net, False)
+    want, want_sums, general = step_outputs(net, True)
+    assert used in kinds and used not in general, (kinds, general)
+    differ = {n: int((got[n] != want[n]).sum()) for n in got if not torch.equal(got[n], want[n])}
+    say(f"    {len(got)} tensors, differing: {differ}")
+    assert all(torch.isfinite(t.float()).all() for t in got.values())
+    assert not differ, differ
+    for n, g in got_sums.items():                  # fp32 sums of up to 2^17 products in two orders
+        assert float((g - want_sums[n]).abs().max()) <= 1e-4 * float(want_sums[n].abs().max()), n
+
+
+@pytest.mark.parametrize("case", [
+    # every width, images of more and of half a tile; 32 samples and more, or modules of more than three blocks
+    dict(batch=32, side=(32, 32)), dict(batch=33, side=(32, 32)), dict(batch=3, side=(32, 32), split=[4]),
+    dict(batch=128, side=(32, 32), widths=(16, 32)), dict(batch=40, side=(16, 16), widths=(32, 64)), dict(batch=34, side=(8, 8), widths=(64,), stride=1),
+    dict(batch=32, side=(32, 32), flags=True),
+], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()).replace(" ", ""))
+def test_ordered_tiles_have_the_bits_of_the_separate_passes(case):
+    say("case ordered tiles", case)
+    assert_same_bits(narrow_net(dtype="bf16", **case), (FOLDED, 0))
+
+
+@pytest.mark.parametrize("case", [
+    # slabs of 64 channels and a half one (160: odd workgroups start there), of 32 (strided layers of 160), 1x1, all tile variants
+    dict(batch=1, side=(8, 8), widths=(160, 320)), dict(batch=3, side=(8, 8), widths=(320, 640)), dict(batch=6, side=(16, 16), widths=(160, 320)),
+    dict(batch=2, side=(12, 20), widths=(160, 320)), dict(batch=3, side=(14, 14), widths=(640, 1280), kind="bottleneck"),
+], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()).replace(" ", ""))
+def test_small_tiles_have_the_bits_of_the_large_ones(case):
+    say("case small tiles, bits", case)
+    assert_same_bits(wide_net(**case), (CONV, SMALL_TILES))
+
+
+@pytest.mark.parametrize("lanes", [None, [0, 1], [2, 1], [3, 3]])
+def test_narrow_stream_lanes(lanes):
+    """The folded passes with the modules on streams of their own."""
+    from tests.gpu_common import compare_step
+    say("case narrow, stream lanes", lanes)
+    compare_step(narrow_net(batch=3, side=(16, 16)), lanes=lanes)
+
+
+@pytest.mark.parametrize("fixed_forward", [False, True])
+def test_fixed_order_switched_between_the_passes(fixed_forward):
+    """A forward pass leaves what either backward pass needs: the folded one, or that of the fixed order."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    from tests.helpers import rel_err
+    say("case fixed order switched, forward", fixed_forward)
+    net = narrow_net(batch=3, side=(12, 20))
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    ls = LocalStep(net)
+    try:
+        for k in range(net.K):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        grads = []
+        for switch in (False, True):
+            ls.ws.zero_()
+            B.lp_net_set_deterministic(ls.net, fixed_forward)
+            ls.module_forward()
+            ls.local_loss_grad(net.rho, 1.0)
+            if switch:
+                B.lp_net_set_deterministic(ls.net, not fixed_forward)
+            ls.module_backward()
+            torch.cuda.synchronize()
+            grads.append([g.cpu().numpy() for g in ls.dparams + ls.dx[1:]])
+    finally:
+        ls.close()
+    for a, b in zip(*grads):                       # two orders of the same fp32 sums
+        assert rel_err(a, b) <= 1e-4

@@ -183,18 +183,23 @@ def test_module_mask_subsets(mask, fused):
         ls.close()
 
 
-@pytest.mark.parametrize("which", ["mini_basic", "wrn28_10"])
+@pytest.mark.parametrize("which", ["mini_basic", "wrn28_10", "narrow_f32", "narrow_bf16", "narrow_lanes"])
 def test_step_as_hip_graph_replays(which):
     """The local step captured into a HIP graph (the stream lanes forked and joined by events inside the capture, the
     multiplier update included): three replays, with eager work of the library and synchronisations between them, each
     against the eager step from the same state.  mini_basic: three lanes, register-staged kernels; wrn28_10 at batch 2:
-    four lanes, the wide-layer kernels with their split-K atomics."""
+    four lanes, the wide-layer kernels with their split-K atomics; narrow: the folded passes, on one stream and on two lanes."""
     import torch
     from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
     from tests.gpu_common import load_step
     from tests.helpers import step_inputs
+    from tests.test_gpu_narrow import narrow_net
     if which == "mini_basic":
         net = gpu_mini_basic(dtype="bf16")
+        net.al, net.lam_sigma, net.rho = True, 0.05, 1.5
+    elif which.startswith("narrow"):
+        net = narrow_net(3, (16, 16), dtype="bf16" if which == "narrow_bf16" else "f32")
         net.al, net.lam_sigma, net.rho = True, 0.05, 1.5
     else:
         net = wl.make_config("wrn28_10", batch=2)
@@ -205,6 +210,9 @@ def test_step_as_hip_graph_replays(which):
     ls = LocalStep(net)
     try:
         load_step(ls, net, inp)
+        if which == "narrow_lanes":
+            ls.set_stream_lanes([1, 2])
+        assert B.lp_debug_stream_lanes(ls.net, K)[0] == which.startswith("narrow")
 
         def snapshot():
             torch.cuda.synchronize()
@@ -850,7 +858,10 @@ def _read_like_grads(ls, buf, k):
 @pytest.mark.parametrize("case,momentum,wd,use_master,fused_call", [
     ("basic_f32", 0.9, 5e-4, False, True), ("basic_bf16", 0.9, 5e-4, True, True), ("basic_bf16", 0.0, 0.0, False, False),
     ("bottleneck_bf16", 0.9, 0.0, False, True), ("wide", 0.9, 5e-4, True, True), ("wide", 0.5, 0.0, False, False),
-    ("wide_strided", 0.9, 5e-4, False, True), ("wrn_batch_8", 0.9, 5e-4, True, True)])
+    ("wide_strided", 0.9, 5e-4, False, True), ("wrn_batch_8", 0.9, 5e-4, True, True),
+    # the folded passes of narrow networks; "flags": a bare projection, whose filter gradient runs in the middle of the pass
+    ("narrow_f32", 0.9, 5e-4, False, True), ("narrow_bf16", 0.9, 5e-4, True, True), ("narrow_f32", 0.0, 0.0, False, False),
+    ("narrow_flags_f32", 0.9, 0.0, False, False), ("narrow_flags_bf16", 0.9, 5e-4, True, True)])
 def test_update_inside_backward(case, momentum, wd, use_master, fused_call):
     """The parameter update in the epilogues of the filter-gradient kernels (Sec. 4.1: W is updated right after the
     adjoint at its layer): two local steps in a row with the update switched on.  After each step the oracle's update
@@ -862,9 +873,13 @@ def test_update_inside_backward(case, momentum, wd, use_master, fused_call):
     from paper_2112_05387_amd import binding as B
     from tests.gpu_common import gpu_mini_wide_strided
     from tests.gpu_unitwise import seeded_step_inputs
+    from tests.test_gpu_narrow import FOLDED, narrow_net
     net = {"basic_f32": lambda: gpu_mini_basic(batch=3, dtype="f32"), "basic_bf16": lambda: gpu_mini_basic(batch=3, dtype="bf16"),
            "bottleneck_bf16": lambda: gpu_mini_bottleneck(batch=2, dtype="bf16"), "wide": lambda: gpu_mini_wide(batch=3),
-           "wide_strided": lambda: gpu_mini_wide_strided(batch=5), "wrn_batch_8": lambda: wl.make_config("wrn28_10", batch=8)}[case]()
+           "wide_strided": lambda: gpu_mini_wide_strided(batch=5), "wrn_batch_8": lambda: wl.make_config("wrn28_10", batch=8),
+           "narrow_f32": lambda: narrow_net(3, (12, 20)), "narrow_bf16": lambda: narrow_net(33, (32, 32), dtype="bf16"),
+           "narrow_flags_f32": lambda: narrow_net(3, (16, 16), flags=True),
+           "narrow_flags_bf16": lambda: narrow_net(5, (16, 16), dtype="bf16", flags=True)}[case]()
     lr = 1.0        # large on purpose: every tensor's update must stand far above the comparison tolerance
     say("case update inside backward", case, momentum, wd, "master" if use_master else "", "one call" if fused_call else "separate calls")
     params, image, labels, xs, lams = seeded_step_inputs(net)
@@ -886,6 +901,7 @@ def test_update_inside_backward(case, momentum, wd, use_master, fused_call):
         ls.set_fused_update(True, lr, momentum, wd, velocity=vel, master=master)
         worst = {"param": 0.0, "velocity": 0.0, "master": 0.0}
         smallest = 1e30
+        B.lp_profile_enable(ls.net, 1)
         for it in range(2):
             before_w = [(_read_like_grads(ls, master, k) if use_master else _read_params(ls, k)) for k in range(net.K)]
             before_v = [(_read_like_grads(ls, vel, k) if momentum else None) for k in range(net.K)]
@@ -922,6 +938,7 @@ def test_update_inside_backward(case, momentum, wd, use_master, fused_call):
                         worst["master"] = max(worst["master"], e)
         say(f"    update inside backward, {case}: worst parameter {worst['param']:.2e}, velocity {worst['velocity']:.2e}, master {worst['master']:.2e}; "
             f"smallest update of a tensor {smallest:.1e} of its magnitude")
+        assert case.startswith("narrow") == (FOLDED in {r["kind"] for r in B.lp_profile_fetch(ls.net)})
     finally:
         ls.close()
 
