@@ -413,9 +413,9 @@ lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled);
  * the two. */
 lp_status lp_debug_separate_passes(int on);
 
-/* How a call over all modules runs (host only): *folded = 1 if the passes are the narrow ones with the batch norms folded
+/* How a call over all modules runs (host only; whole_step: lp_local_step, otherwise a pass of its own): *folded = 1 if the passes are the narrow ones with the batch norms folded
  * into the convolutions; lanes[k] (K entries) = the stream lane of module k, 0 = the caller's stream. */
-lp_status lp_debug_stream_lanes(const struct lp_net* net, int* folded, int* lanes);
+lp_status lp_debug_stream_lanes(const struct lp_net* net, int whole_step, int* folded, int* lanes);
 
 /* What the matrix cores of this device sustain (measurement aid of bench.py --measure-peak; no operand of the
  * library is touched).  Launches `blocks` workgroups of eight waves, each wave running `iters` times the 40

@@ -121,7 +121,7 @@ def lib():
         L.lp_debug_conv_geometry.argtypes = [c_int] * 12 + [POINTER(c_int)]
         L.lp_debug_conv_offsets.argtypes = [c_void_p] + [c_int] * 12 + [c_void_p] * 6 + [c_int]
         L.lp_debug_mfma_peak.argtypes = [c_void_p, c_int, c_int, c_int, c_void_p, c_void_p]
-        L.lp_debug_stream_lanes.argtypes = [c_void_p, POINTER(c_int), POINTER(c_int)]
+        L.lp_debug_stream_lanes.argtypes = [c_void_p, c_int, POINTER(c_int), POINTER(c_int)]
         L.lp_debug_linear_kernels.argtypes = [c_int] * 3 + [POINTER(c_int)]
         L.lp_debug_separate_passes.argtypes = [c_int]
         L.lp_debug_layer_kernels.argtypes = [c_int] * 9 + [POINTER(c_int)]
@@ -374,10 +374,10 @@ def lp_debug_linear_kernels(N, classes, C):
     return bool(t[0]), bool(t[1])
 
 
-def lp_debug_stream_lanes(net, K):
+def lp_debug_stream_lanes(net, K, whole_step=True):
     """(runs the folded passes, stream lane of every module)"""
     f, lanes = c_int(), (c_int * K)()
-    _check(lib().lp_debug_stream_lanes(net, ctypes.byref(f), lanes))
+    _check(lib().lp_debug_stream_lanes(net, int(whole_step), ctypes.byref(f), lanes))
     return bool(f.value), list(lanes)
 
 

@@ -217,7 +217,7 @@ struct lp_net {
     bool narrow = false;                   // every module has the folded programs (ffwd ...)
     bool deep = false;                     // a module of more than three blocks, or AuxNets (see Builder::fconv_exact)
     bool lanes_set = false;                // the caller chose the stream lanes
-    bool fold_lanes = false;               // the folded programs use the stream lanes too (fold_uses_lanes)
+    size_t lane_bytes = 0;                 // what the convolutions of a stream lane write in a pass
     bool deterministic = false;            // lp_net_set_deterministic: every reduction in a fixed order
     // lp_net_set_fused_update: the parameter update runs inside lp_module_backward / lp_local_step
     bool fused_update = false;
@@ -2251,13 +2251,17 @@ static lp_status run_programs(lp_net* net, const std::vector<const Program*>& pr
 // narrow networks run the folded programs; the fixed summation order of the deterministic mode keeps the plain ones
 static bool folded(const lp_net* net) { return net->narrow && !net->deterministic && !net->separate; }
 
-// Do the folded programs use the stream lanes by default?  One launch holds the tiles of all modules, whatever their widths, so
-// on small mini-batches lanes only split it, and the host cannot issue several times the launches fast enough (ResNet-20 of
-// 8 samples, four lanes: 359 us, one stream: 273).  Where a lane's own launches fill the chip, the lanes fill each other's tails
-// and dependent trips to memory (same network, fp32: 32 samples 393 / 395 us, 48 samples 391 / 451, 128 samples 664 / 773, 512
-// samples 2162 / 2559; bf16: 80 samples 390 / 373, 96 samples 393 / 405; ResNet-56 of 256 samples 3068 / 3565).  Both types and
-// one to four lanes cross over where the convolutions of a lane write 8 to 10 MB a pass.
-static bool fold_uses_lanes(const lp_net* net) {
+// Bytes the convolutions of a stream lane write in a pass (the mean over the lanes in use), from which on the folded programs use
+// the lanes by default: in a call of their own, and in the step that does both passes in one call.  One launch holds the tiles of
+// all modules, whatever their widths, so on small mini-batches lanes only split it: the host cannot issue several times the
+// launches fast enough, and fork and join cost 10 us a call.  Where a lane's own launches fill the chip, the lanes fill each other's
+// tails and dependent trips to memory.  One stream / lanes, us, over networks of two to four lanes (the host's share varies):
+//   step     ResNet-20 bf16 64 samples (6 MB a lane) 356 / 420, 128 (12) 429 / 414, 192 (18) 534 / 493; fp32 96 (18) 647 / 534,
+//            512 (98) 2540 / 2156; ResNet-56 in four modules bf16 64 (17) 731 / 746, 96 (25) 833 / 750
+//   forward  ResNet-20 bf16 192 (18) 188 / 223, 256 (25) 237 / 226; ResNet-56 in four modules fp32 64 (33) 386 / 406, 96 (50)
+//            550 / 501, bf16 128 (33) 325 / 378, 160 (42) 405 / 376; the backward pass crosses over between 20 and 37 MB
+constexpr size_t kFoldLaneBytesCall = 40u << 20, kFoldLaneBytesStep = 18u << 20;
+static size_t lane_bytes(const lp_net* net) {
     size_t elems = 0;
     for (const ModulePlan& m : net->mods) {
         if (m.has_stem) elems += m.stem.out_elems();
@@ -2268,7 +2272,7 @@ static bool fold_uses_lanes(const lp_net* net) {
     }
     int used = 0;
     for (int l = 0; l < 4; ++l) used += std::count(net->lane.begin(), net->lane.end(), l) > 0;
-    return elems * net->esz >= (size_t)used * (9u << 20);
+    return elems * net->esz / (size_t)used;
 }
 
 // Do the separate passes beat the folded ones?  Folding saves passes over memory and launches; its convolutions multiply at a
@@ -2292,9 +2296,9 @@ static bool folding_loses(const lp_net* net) {
 }
 
 // stream lane of every selected module, in the order the programs are collected
-static std::vector<int> lanes_of(const lp_net* net, uint32_t module_mask) {
+static std::vector<int> lanes_of(const lp_net* net, uint32_t module_mask, bool whole_step = false) {
     std::vector<int> out;
-    if (folded(net) && !net->lanes_set && !net->fold_lanes) {
+    if (folded(net) && !net->lanes_set && net->lane_bytes < (whole_step ? kFoldLaneBytesStep : kFoldLaneBytesCall)) {
         for (int k = 0; k < net->K; ++k) if ((module_mask >> k) & 1u) out.push_back(0);
         return out;
     }
@@ -2406,7 +2410,7 @@ lp_status lp_net_create(int K, const lp_module_desc* mods, const lp_aux_desc* au
         }
     }
     net->narrow = net->narrow && !folding_loses(net);
-    net->fold_lanes = fold_uses_lanes(net);
+    net->lane_bytes = lane_bytes(net);
     *out = net;
     return LP_OK;
 }
@@ -2831,7 +2835,7 @@ lp_status lp_local_step(struct lp_net* net, void* stream, uint32_t module_mask, 
     b.dparams = dparams; b.dy = dy; b.dx = dx; b.dlogits = dlogits;
     if (net->fused_update) { b.vel = net->fu_vel.data(); b.master = net->fu_master.data(); }
     b.xnext = x_next; b.lam = lam; b.loss = loss; b.labels = labels; b.rho = rho; b.scale = loss_scale; b.mstep = mult_step;
-    const std::vector<int> lanes = lanes_of(net, module_mask);
+    const std::vector<int> lanes = lanes_of(net, module_mask, true);
     st = run_programs(net, progs, b, s, &lanes);
     if (st == LP_OK)
         for (int k = 0; k < net->K; ++k)
@@ -3223,10 +3227,10 @@ lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled) {
     return LP_OK;
 }
 
-lp_status lp_debug_stream_lanes(const struct lp_net* net, int* is_folded, int* lanes) {
+lp_status lp_debug_stream_lanes(const struct lp_net* net, int whole_step, int* is_folded, int* lanes) {
     if (!net || !is_folded || !lanes) return fail(LP_ERR_INVALID_ARG, "NULL argument");
     *is_folded = folded(net) ? 1 : 0;
-    const std::vector<int> l = lanes_of(net, ~0u);
+    const std::vector<int> l = lanes_of(net, ~0u, whole_step != 0);
     std::copy(l.begin(), l.end(), lanes);
     return LP_OK;
 }

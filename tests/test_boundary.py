@@ -329,12 +329,12 @@ def test_specialised_kernels_refuse_sizes_beyond_their_fields(dtype):
             assert not t["small_fwd"] and not t["small_dgrad"], (h, cin, cout, r)
 
 
-def _lanes(net, after=None):
+def _lanes(net, after=None, whole_step=True):
     h = B.lp_net_create(net.modules, net.aux, net.dtype, net.bn_eps)
     try:
         if after:
             after(h)
-        return B.lp_debug_stream_lanes(h, net.K)
+        return B.lp_debug_stream_lanes(h, net.K, whole_step)
     finally:
         B.lp_net_destroy(h)
 
@@ -345,12 +345,16 @@ def test_folded_passes_use_the_stream_lanes_of_large_mini_batches():
         n = wl.make_config(name, batch=batch, split=split)
         n.dtype = dtype
         return n
-    for name, dtype, small, large in (("resnet20", "f32", 32, 128), ("resnet20", "bf16", 80, 128), ("resnet56", "f32", 8, 32),
-                                      ("resnet56", "f32", 8, 256), ("resnet56", "bf16", 16, 128)):
+    for name, dtype, small, large in (("resnet20", "f32", 64, 128), ("resnet20", "bf16", 128, 256), ("resnet56", "f32", 16, 48),
+                                      ("resnet56", "f32", 8, 256), ("resnet56", "bf16", 32, 128)):
         assert _lanes(net(name, small, dtype)) == (True, [0] * net(name, 1, dtype).K), (name, dtype, small)
         folded, lanes = _lanes(net(name, large, dtype))
         assert folded and len(set(lanes)) >= 3, (name, dtype, large, lanes)
     assert _lanes(net("resnet56", 256, "f32", [7, 7, 7, 6])) == (True, [0, 1, 2, 3])
+    # a pass in a call of its own has a third to two thirds of a step's work behind the same fork and join
+    assert _lanes(net("resnet20", 128, "f32"), whole_step=False) == (True, [0] * 4)
+    assert _lanes(net("resnet20", 256, "f32"), whole_step=False) == (True, [0, 1, 2, 3])
+    assert len(set(_lanes(net("resnet56", 128, "bf16"), whole_step=False)[1])) == 3
     assert _lanes(net("resnet20", 128, "f32", [9])) == (True, [0])
     assert _lanes(wl.make_config("tiny")) == (True, [0, 0])
     # the caller's own choice stands, and so does the order of networks that are not folded
