@@ -346,17 +346,18 @@ def main():
         a = agg.setdefault((r["kind"], r["cfg"]), {"ms": 0.0, "flops": 0.0, "bytes": 0.0, "launches": 0, "blocks": 0, "cu_ms": 0.0})
         a["ms"] += r["ms"]; a["flops"] += r["flops"]; a["bytes"] += r["bytes"]; a["launches"] += 1; a["blocks"] += r["blocks"]
         a["cu_ms"] += r["ms"] * min(1.0, r["blocks"] / N_CUS)
-    conv_ms = sum(a["ms"] for (k, _), a in agg.items() if k in (2, 10))
-    conv_flops = sum(a["flops"] for (k, _), a in agg.items() if k in (2, 10))
+    convs = (2, 10, 17, 18)                                # convolutions and filter gradients, general and narrow
+    conv_ms = sum(a["ms"] for (k, _), a in agg.items() if k in convs)
+    conv_flops = sum(a["flops"] for (k, _), a in agg.items() if k in convs)
     (dk, dcfg), dom = max(agg.items(), key=lambda kv: kv[1]["ms"])
     peak = PEAK_TFLOPS[net.dtype]
     # a convolution whose algorithmic intensity lies under the ridge of its dtype (peak flop/s over peak bytes/s: 312 flop/B
     # in bf16, 20 in fp32) is bounded by HBM, like the elementwise passes: the 16- and 32-channel layers of ResNet-20 / -56
     ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)
-    if dk in (2, 10) and dom["flops"] >= ridge * dom["bytes"]:
+    if dk in convs and dom["flops"] >= ridge * dom["bytes"]:
         achieved = dom["flops"] / (dom["ms"] * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak}
-        if dom["cu_ms"] > 0 and dcfg >= 8:       # the direct-to-LDS kernels: one workgroup per compute unit
+        if dom["cu_ms"] > 0 and dk in (2, 10) and dcfg >= 8:       # the direct-to-LDS kernels: one workgroup per compute unit
             # a lane's launch is sized to share the chip with the other lanes: workgroups per launch, and the rate per
             # compute unit it occupies (one workgroup per CU) against a CU's share of the peak
             roof["workgroups_per_launch"] = dom["blocks"] / dom["launches"]

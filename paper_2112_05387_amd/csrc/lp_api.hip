@@ -1890,6 +1890,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 err = launch_fconv(g, dt, lds, s);
             } break;
             case OP_FWGRAD: {
+                if (used_cfg) *used_cfg = 0;               // (the operation's own cfg is that of its plain form)
                 if (net->deterministic || net->fused_update || net->separate) {       // fixed order, or the update in the epilogue: the plain kernels
                     std::vector<Op> plain(n);
                     std::vector<char> done(n, 0);
