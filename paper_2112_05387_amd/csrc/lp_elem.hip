@@ -992,7 +992,7 @@ hipError_t launch_maxpool_bwd(const PoolProb& p, int dtype, hipStream_t s) {
 bool fc_fwd_tiled(const HeadProb& p) { return (size_t)p.N * p.classes * (p.C + 170) >= 18000000u; }
 // Filter gradient: a thread of the tiled kernel has four classes, so it wants that many more of them (whole backward pass of the
 // head, tiled / plain: 128 samples x 100 classes x 640 channels 20.6 / 15.3 us, 512 x 200 x 1024 68.0 / 60.6, 2048 x 1000 x 64 199 /
-// 149, 8192 x 10 x 64 681 / 424; 1024 x 512 x 640 137 / 148, 64 x 1000 x 512 29 / 50, 64 x 1000 x 2048 38 / 76).
+// 149, 8192 x 10 x 64 681 / 424; 1024 x 512 x 640 137 / 148, 64 x 1000 x 512 29 / 50, 16 x 1000 x 2048 39 / 79).
 bool fc_bwd_w_tiled(const HeadProb& p) {
     return (size_t)p.classes * p.C >= (1u << 18) && (size_t)p.N * p.classes * p.C >= (1u << 22);
 }
