@@ -2432,11 +2432,11 @@ lp_status lp_net_destroy(struct lp_net* net) {
 
 lp_status lp_net_set_stream_lanes(struct lp_net* net, const int* lanes) {
     if (!net) return fail(LP_ERR_INVALID_ARG, "net is NULL");
-    net->lanes_set = true;
-    if (!lanes) { net->lane.assign(net->K, 0); return LP_OK; }
+    if (!lanes) { net->lane.assign(net->K, 0); net->lanes_set = true; return LP_OK; }
     for (int k = 0; k < net->K; ++k)
         if (lanes[k] < 0 || lanes[k] > 3) return fail(LP_ERR_INVALID_ARG, "lanes[%d] = %d outside [0, 3]", k, lanes[k]);
     net->lane.assign(lanes, lanes + net->K);
+    net->lanes_set = true;
     return LP_OK;
 }
 

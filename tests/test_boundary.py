@@ -357,6 +357,8 @@ def test_folded_passes_use_the_stream_lanes_of_large_mini_batches():
     assert len(set(_lanes(net("resnet56", 128, "bf16"), whole_step=False)[1])) == 3
     assert _lanes(net("resnet20", 128, "f32", [9])) == (True, [0])
     assert _lanes(wl.make_config("tiny")) == (True, [0, 0])
+    # a refused choice changes nothing
+    assert _lanes(net("resnet20", 4, "f32"), lambda h: _expect(B.LP_ERR_INVALID_ARG, B.lp_net_set_stream_lanes, h, [0, 1, 9, 2])) == (True, [0] * 4)
     # the caller's own choice stands, and so does the order of networks that are not folded
     assert _lanes(net("resnet20", 128, "f32"), lambda h: B.lp_net_set_stream_lanes(h, None)) == (True, [0] * 4)
     assert _lanes(net("resnet20", 4, "f32"), lambda h: B.lp_net_set_stream_lanes(h, [0, 1, 0, 2])) == (True, [0, 1, 0, 2])
