@@ -17,6 +17,7 @@
 #include "../../include/lp.h"
 #include "lp_addr.h"
 #include "lp_kernels.h"
+#include "lp_wgsplit.h"
 
 using namespace lp;
 
@@ -1596,31 +1597,26 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
     }
 }
 
-// Split-K of a grouped launch of the wide-layer filter-gradient kernel.  Every block has the same tile, so its time
-// is its number of 32-pixel k-tiles plus a fixed epilogue (the atomic adds of its 160 x 480 partial sums, which
-// cost about as much as 24 k-tiles); one block runs per CU.  Pick the common chunk length that minimises
-// rounds x (chunk + epilogue).  The gradients were zeroed at the start of the backward pass and are accumulated
-// atomically, so the split may differ from launch to launch.
+// Pieces of a grouped launch of the wide-layer filter-gradient kernel (lp_wgsplit.h).  The gradients were zeroed at the start
+// of the backward pass and are accumulated atomically, so the split may differ from launch to launch.
 static void plan_wgrad_fast_splits(WgradGroup& g) {
-    const int kEpilogue = 24, kCUs = 256;
-    int best_chunk = 16; double best_cost = 1e300;
-    int max_kt = 1;
-    for (int i = 0; i < g.nprob; ++i) max_kt = std::max(max_kt, (g.p[i].M + 31) / 32);
-    for (int chunk = 16; chunk <= std::max(16, max_kt); ++chunk) {
-        long blocks = 0;
-        for (int i = 0; i < g.nprob; ++i) {
-            const int kt = (g.p[i].M + 31) / 32;
-            blocks += (long)g.p[i].tiles_m * g.p[i].tiles_n * ((kt + chunk - 1) / chunk);
-        }
-        const double cost = (double)((blocks + kCUs - 1) / kCUs) * (chunk + kEpilogue);
-        if (cost < best_cost) { best_cost = cost; best_chunk = chunk; }
-    }
-    for (int i = 0; i < g.nprob; ++i) {
-        WgradProb& p = g.p[i];
+    SplitPart part[kMaxGroup];
+    for (int i = 0; i < g.nprob; ++i) part[i] = {g.p[i].tiles_m * g.p[i].tiles_n, (g.p[i].M + 31) / 32, 1};
+    int rest_split = 1, rest = plan_wgrad_pieces(part, g.nprob, rest_split);
+    if (g.nprob == kMaxGroup) rest = 0;
+    auto set = [](WgradProb& p, int tile0, int ntile, int ks) {
         const int kt = (p.M + 31) / 32;
-        const int ks = (kt + best_chunk - 1) / best_chunk;
-        p.ksplit = ks;
+        p.tile0 = tile0; p.ntile = ntile;
         p.kchunk = (kt + ks - 1) / ks * 32;          // equal chunks
+        p.ksplit = (p.M + p.kchunk - 1) / p.kchunk;
+    };
+    for (int i = 0; i < g.nprob; ++i) set(g.p[i], 0, part[i].tiles, part[i].ksplit);
+    if (rest) {
+        const int n = g.nprob - 1, keep = part[n].tiles - rest;
+        g.p[n + 1] = g.p[n];
+        set(g.p[n], 0, keep, 1);
+        set(g.p[n + 1], keep, rest, rest_split);
+        ++g.nprob;
     }
 }
 
@@ -1932,11 +1928,11 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
             } break;
             case OP_WGRAD: {
                 WgradGroup g; g.nprob = n; int tot = 0;
-                for (int i = 0; i < n; ++i) g.p[i] = ops[base + i]->wg;
+                for (int i = 0; i < n; ++i) { g.p[i] = ops[base + i]->wg; g.p[i].tile0 = 0; g.p[i].ntile = g.p[i].tiles_m * g.p[i].tiles_n; }
                 if (net->deterministic) {       // one block per output tile runs through all pixels: no partial sums to add
                     const int bk = ops[base]->cfg == WGRAD_FAST ? 32 : wgrad_cfg_info(ops[base]->cfg, dt).BK;
                     for (int i = 0; i < n; ++i) { g.p[i].ksplit = 1; g.p[i].kchunk = (g.p[i].M + bk - 1) / bk * bk; }
-                } else if (ops[base]->cfg == WGRAD_FAST) plan_wgrad_fast_splits(g);
+                }
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
                     WgradProb& p = g.p[i];
@@ -1948,9 +1944,9 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         if (b.vel && b.vel[k]) p.vel = (float*)((char*)b.vel[k] + o.r[2].off);
                         if (b.master && b.master[k]) p.master = (float*)((char*)b.master[k] + o.r[2].off);
                     }
-                    p.tile_start = tot;
-                    tot += ops[base]->cfg == WGRAD_FAST ? wgrad_fast_blocks(p) : p.tiles_m * p.tiles_n * p.ksplit;
                 }
+                if (ops[base]->cfg == WGRAD_FAST && !net->deterministic) plan_wgrad_fast_splits(g);
+                for (int i = 0; i < g.nprob; ++i) { g.p[i].tile_start = tot; tot += g.p[i].ntile * g.p[i].ksplit; }
                 g.total_tiles = tot;
                 g.lr = net->fu_lr; g.momentum = net->fu_momentum; g.wd = net->fu_wd; g.lowp = dt == LP_BF16;
                 if (used_blocks) *used_blocks = tot;

@@ -126,6 +126,7 @@ struct WgradProb {
     int Ho, Wo, IH, IW, stride, pad, R, S;
     int ksplit, kchunk;
     int tiles_m, tiles_n, tile_start;
+    int tile0, ntile;                // wide-layer kernel: the output tiles this entry is about (tiles_m * tiles_n of them in one or two entries)
     unsigned mulW, shW, mulH, shH;   // fast division by IW and IH (wide-layer kernel)
     // parameter update in the epilogue (w != NULL): the workgroup that adds the LAST partial sum of an output tile
     // (ticket from cnt[tile], zero before the launch) reads the finished gradient tile back and updates the filter
@@ -140,6 +141,7 @@ struct WgradGroup {
     int lowp;                        // the filters are bf16
     WgradProb p[kMaxGroup];
 };
+static_assert(sizeof(WgradGroup) <= 4096, "kernel-argument block");
 
 // Filter gradient of a narrow layer (lp_fwgrad.hip): a workgroup walks over `per` tiles of whole image rows.
 struct FWgradProb {
@@ -286,7 +288,6 @@ hipError_t launch_tile_stats(const TileStatsGroup& g, hipStream_t s);
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_fwgrad(const FWgradGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
-int wgrad_fast_blocks(const WgradProb& p);
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
 hipError_t launch_wgrad(const WgradGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_wtrans(const WtransGroup& g, int dtype, hipStream_t s);

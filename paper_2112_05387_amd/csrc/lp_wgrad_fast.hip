@@ -24,13 +24,13 @@
 // LDS rows are 320 B; the 32-byte channel pairs of a row swap places in rows with bit 3 set, which keeps the
 // transposing reads of a half-wave (pixel rows p..p+3 and p+8..p+11) on distinct banks.
 //
-// Blocks are numbered XCD-major: the hardware deals consecutive block ids round-robin to the 8 XCDs, so logical
-// neighbours (the filter-row and channel tiles that read the same pixel chunk) are given ids that are 8 apart and
-// share one L2.
+// Logical neighbours (the filter-row and channel tiles that read the same pixel chunk) go to one XCD and share its L2, and
+// every XCD gets the same number of blocks (lp_wgsplit.h).
 #include <algorithm>
 
 #include "lp_kernels.h"
 #include "lp_mma.h"
+#include "lp_wgsplit.h"
 
 namespace lp {
 namespace {
@@ -92,18 +92,11 @@ __global__ __launch_bounds__(WF_NT) void conv_wgrad_fast_kernel(const WgradGroup
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int pi = 0;
-    for (int i = 1; i < g.nprob; ++i)
-        if ((int)blockIdx.x >= g.p[i].tile_start) pi = i;
+    int pi = 0, L = 0;
+    if (!xcd_piece((int)blockIdx.x, g.nprob, [&](int i) { return g.p[i].ntile * g.p[i].ksplit; }, pi, L)) return;
     const WgradProb& P = g.p[pi];
-    // XCD-major numbering (tile_start is a multiple of 8)
-    const int T = P.tiles_m * P.tiles_n;
-    const int nb = T * P.ksplit;
-    const int local = blockIdx.x - P.tile_start;
-    const int L = (local & 7) * ((nb + 7) >> 3) + (local >> 3);
-    if (L >= nb) return;
     // (block-uniform quotients: the division runs on the vector ALU; readfirstlane puts the results into scalar registers)
-    const int split = __builtin_amdgcn_readfirstlane(L / T), tile = L - split * T;
+    const int split = __builtin_amdgcn_readfirstlane(L / P.ntile), tile = P.tile0 + L - split * P.ntile;
     const int tile_m = __builtin_amdgcn_readfirstlane(tile / P.tiles_n), tile_n = tile - tile_m * P.tiles_n;
     const int r = tile_n % 3, ci0 = (tile_n / 3) * WF_TILE, co0 = tile_m * WF_TILE;
     const int Cin = P.Cin, Cout = P.Cout, H = P.IH, W = P.IW;
@@ -317,18 +310,12 @@ __global__ __launch_bounds__(WF_NT) void conv_wgrad_fast_kernel(const WgradGroup
     }
 }
 
-// number of blocks the kernel is launched with for one problem (a multiple of 8: XCD-major numbering)
-int wgrad_fast_blocks(const WgradProb& p) {
-    const int nb = p.tiles_m * p.tiles_n * p.ksplit;
-    return (nb + 7) / 8 * 8;
-}
-
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
     const size_t lds = (size_t)WF_STAGES * WF_STAGE_BYTES;
     static OncePerDevice configured;
     if (const hipError_t e = raise_lds_limit(configured, {(const void*)conv_wgrad_fast_kernel}, (int)lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(conv_wgrad_fast_kernel, dim3(g.total_tiles), dim3(WF_NT), lds, s, g);
+    hipLaunchKernelGGL(conv_wgrad_fast_kernel, dim3(xcd_grid(g.total_tiles)), dim3(WF_NT), lds, s, g);
     return hipGetLastError();
 }
 

@@ -1,0 +1,75 @@
+// How a grouped launch of the wide-layer filter-gradient kernel is cut into workgroups and dealt to the chip: which output
+// tiles are cut along the pixels, and which workgroup of the grid does which piece.  Plain functions of integers, for the
+// launcher, the kernel and the host's own test alike.
+#pragma once
+#ifdef __HIPCC__
+#define LP_WG_HD __host__ __device__ inline
+#else
+#define LP_WG_HD inline
+#endif
+
+namespace lp {
+
+constexpr int kXcds = 8;
+
+// The hardware deals consecutive workgroups round-robin to the 8 XCDs, each with an L2 of its own, and the workgroups of one
+// pixel chunk (its filter rows and channel tiles) read the same pixels.  So an XCD gets consecutive pieces of every problem,
+// as many as any other: where a problem does not divide by 8 the next one continues with the XCD behind the last that got one
+// more.  (Dealt problem by problem, each from XCD 0 and rounded up, five problems of 51 pieces gave seven XCDs 35 pieces for
+// 32 compute units: a second round of the whole launch, 589 us instead of 345.)
+// piece(i, local) of workgroup `block` of a grid of `blocks(total)` workgroups; false: the workgroup has none.
+// count(i): pieces of problem i.
+LP_WG_HD int xcd_grid(int total) { return (total + kXcds - 1) / kXcds * kXcds; }
+template <class Count>
+LP_WG_HD bool xcd_piece(int block, int nprob, Count count, int& prob, int& local) {
+    const int x = block & (kXcds - 1);
+    int j = block / kXcds, first = 0;              // first: the XCD that gets the first piece of a problem
+    for (int i = 0; i < nprob; ++i) {
+        const int n = count(i), base = n / kXcds, rem = n - base * kXcds, xr = (x - first) & (kXcds - 1);
+        const int mine = base + (xr < rem ? 1 : 0);
+        if (j < mine) { prob = i; local = xr * base + (xr < rem ? xr : rem) + j; return true; }
+        j -= mine;
+        first = (first + rem) & (kXcds - 1);
+    }
+    return false;
+}
+
+// One problem of the plan: `tiles` output tiles of `kt` k-tiles (32 pixels) each, every one cut into `ksplit` pieces.
+struct SplitPart { int tiles, kt, ksplit; };
+
+// Time of a launch in k-tiles (1.25 us each): a workgroup has a compute unit to itself, and what it does besides its k-tiles is
+// worth kEpilogueAdd where partial sums are added with atomics and kEpilogueStore where its piece is the whole reduction (one
+// and two rounds of 256, 128, 64 k-tiles: 305 us with stores, 385 with atomics and half the pieces, 456 with a quarter).
+constexpr int kWgradCUs = 256, kEpilogueAdd = 28, kEpilogueStore = 4;
+inline double wgrad_round(int chunk, bool whole) { return chunk + (whole ? kEpilogueStore : kEpilogueAdd); }
+
+// Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
+// are the pieces and the last round would be nearly empty (288 tiles), the tiles of that round -- the last `rest` of the last
+// problem -- are cut finer, so that one more, short round holds them.  Returns rest (0: nothing more to cut), cuts in
+// `rest_split`.
+inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split) {
+    int max_kt = 1, best_chunk = 16, rest = 0;
+    double best = 1e300;
+    for (int i = 0; i < n; ++i) max_kt = p[i].kt > max_kt ? p[i].kt : max_kt;
+    rest_split = 1;
+    for (int chunk = 16; chunk <= (max_kt > 16 ? max_kt : 16); ++chunk) {
+        long blocks = 0;
+        bool whole = true;
+        for (int i = 0; i < n; ++i) {
+            const int ks = (p[i].kt + chunk - 1) / chunk;
+            blocks += (long)p[i].tiles * ks;
+            whole = whole && ks == 1;
+        }
+        const double cost = (double)((blocks + kWgradCUs - 1) / kWgradCUs) * wgrad_round(chunk, whole);
+        if (cost < best) { best = cost; best_chunk = chunk; rest = 0; }
+        const int over = (int)(blocks % kWgradCUs), s = over ? kWgradCUs / over : 1;
+        const SplitPart& q = p[n - 1];
+        if (!whole || blocks < kWgradCUs || s < 2 || over >= q.tiles || q.kt / s < 8) continue;
+        const double two = (double)(blocks / kWgradCUs) * wgrad_round(chunk, true) + wgrad_round((q.kt + s - 1) / s, false);
+        if (two < best) { best = two; best_chunk = chunk; rest = over; rest_split = s; }
+    }
+    for (int i = 0; i < n; ++i) p[i].ksplit = (p[i].kt + best_chunk - 1) / best_chunk;
+    return rest;
+}
+
+}  // namespace lp

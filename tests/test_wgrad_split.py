@@ -1,0 +1,73 @@
+"""How a launch of the wide filter-gradient kernel is dealt to the XCDs and cut into pieces (csrc/lp_wgsplit.h), compiled for
+the host: every piece goes to exactly one workgroup, no XCD has two more than another, consecutive pieces share an XCD."""
+import os
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2112_05387_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "lp_wgsplit.h"
+#define CHECK(c) do { if (!(c)) { std::printf("failed: %s\n", #c); return 1; } } while (0)
+using namespace lp;
+static int deal(const std::vector<int>& n) {
+    int total = 0;
+    for (int v : n) total += v;
+    const int grid = xcd_grid(total), np = (int)n.size();
+    std::vector<std::vector<int>> at(np);
+    for (int i = 0; i < np; ++i) at[i].assign(n[i], -1);
+    std::vector<int> per(8, 0);
+    for (int b = 0; b < grid; ++b) {
+        int prob = -1, local = -1;
+        if (!xcd_piece(b, np, [&](int i) { return n[i]; }, prob, local)) continue;
+        CHECK(prob >= 0 && prob < np && local >= 0 && local < n[prob] && at[prob][local] < 0);
+        at[prob][local] = b & 7;
+        ++per[b & 7];
+    }
+    int lo = 1 << 30, hi = 0;
+    for (int v : per) { lo = v < lo ? v : lo; hi = v > hi ? v : hi; }
+    CHECK(hi - lo <= 1);
+    for (int i = 0; i < np; ++i) {
+        int changes = 0;
+        for (int j = 0; j < n[i]; ++j) { CHECK(at[i][j] >= 0); changes += j && at[i][j] != at[i][j - 1]; }
+        CHECK(changes <= 7);
+    }
+    return 0;
+}
+int main() {
+    std::srand(1);
+    CHECK(!deal({51, 51, 51, 51, 51}) && !deal({1}) && !deal({7, 9, 0, 8}) && !deal({255}) && !deal({256, 32}));
+    for (int t = 0; t < 300; ++t) {
+        std::vector<int> n(1 + std::rand() % 16);
+        for (int& v : n) v = std::rand() % 80;
+        CHECK(!deal(n));
+    }
+    for (int t = 0; t < 300; ++t) {                // the plan: pieces that cover every reduction, a rest inside the last problem
+        SplitPart p[16];
+        const int n = 1 + std::rand() % 16;
+        for (int i = 0; i < n; ++i) p[i] = {1 + std::rand() % 60, 1 + std::rand() % (t % 2 ? 4200 : 300), 0};
+        int s = 0;
+        const int rest = plan_wgrad_pieces(p, n, s);
+        for (int i = 0; i < n; ++i) CHECK(p[i].ksplit >= 1 && p[i].ksplit <= p[i].kt);
+        CHECK(rest >= 0 && rest < p[n - 1].tiles && (!rest || (s >= 2 && p[n - 1].ksplit == 1 && rest * s <= 256)));
+    }
+    SplitPart a[6];                                // 288 whole tiles: 256 in one round, the other 32 cut into eight
+    for (auto& q : a) q = {48, 256, 0};
+    int s = 0;
+    CHECK(plan_wgrad_pieces(a, 6, s) == 32 && s == 8 && a[0].ksplit == 1);
+    SplitPart b[5];                                // five problems of three long tiles: one round
+    for (auto& q : b) q = {3, 4096, 0};
+    CHECK(plan_wgrad_pieces(b, 5, s) == 0 && b[0].ksplit == 17);
+    return 0;
+}
+"""
+
+
+def test_split_and_deal(tmp_path):
+    src, exe = tmp_path / "split.cpp", tmp_path / "split"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=undefined,address", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
