@@ -9,24 +9,30 @@
 // transpose; ds_read_tr16_b64 delivers exactly that: within 16 lanes it reads a 4-pixel x 16-channel block and
 // hands lane c the 4 pixels of channel c.
 //
-// One block (768 threads, 12 waves, three per SIMD) owns a 160 (co) x 160 (ci) filter tile for the three taps of
-// one filter row r and a chunk of the pixel range; partial sums are added to dW with fp32 atomics (split-K).
-// Wave (wc, wj): co half wc, tap s = wj/2, ci half wj%2 -> an 80 x 80 tile of 5 x 5 v_mfma_f32_16x16x32_bf16
-// micro-tiles (100 accumulators).
+// One block (512 threads, 8 waves, two per SIMD) owns a 160 (co) x 160 (ci) filter tile for the three taps of one filter row r
+// and a chunk of the pixel range; partial sums are added to dW with fp32 atomics (split-K).  The 30 columns (ten groups of 16
+// channels x 3 taps) fall into halves of five channel groups, and a half into a set of 8 columns (two groups, two taps of the
+// third) and one of 7 (its third tap, the other two groups): wave (wc, half, set) has 80 co x 8 or 7 columns of 5
+// v_mfma_f32_16x16x32_bf16 micro-tiles (160 or 140 accumulators), and the two waves of a SIMD are the two sets of one half.
+// The taps of a filter row read the same pixels shifted by one, so a lane reads ten pixels of a channel once (three transposing
+// reads) and makes the three fragments of eight from them: tap 0 as they are, tap 2 from the second register on, tap 1 by four
+// v_alignbit.  LDS reads per k-step of 32 pixels: 152 instead of the 240 that twelve waves of 80 x 80 with a fragment per tap
+// took (LDS bandwidth and the wait for the first fragments were what the matrix cores stood still for).  Five layers of
+// 131072 pixels x 160 channels in one launch: 351 -> 282 us (1.07 PFLOP/s); 32768 x 320: 342 -> 275; 8192 x 640: 301 -> 232..257.
 //
 // A ring stage holds 64 pixels: the dY rows of pixels m0..m0+63 and ONE window of X shared by the three taps,
 // the 66 pixels m0-1+(r-1)W .. m0+64+(r-1)W (flattened pixel index; tap s of pixel m reads window row m-m0+s).
 // What the flattened window cannot express is patched in two places: window pixels whose image row is outside the
 // image for this filter row are loaded as zeros (out-of-range offsets), and the column wrap of taps 0 and 2 (the
 // left neighbour of column 0 is the last pixel of the previous row) is masked in the fragments.  One barrier per
-// stage; inside a stage the two 32-pixel k-steps of a wave follow each other, so that after the first k-step the
-// waves of a SIMD are out of phase and LDS reads overlap MFMAs.
+// stage, ahead of the products of its last channel group, so that the first reads of the next stage run under them.
 // LDS rows are 320 B; the 32-byte channel pairs of a row swap places in rows with bit 3 set, which keeps the
 // transposing reads of a half-wave (pixel rows p..p+3 and p+8..p+11) on distinct banks.
 //
 // Logical neighbours (the filter-row and channel tiles that read the same pixel chunk) go to one XCD and share its L2, and
 // every XCD gets the same number of blocks (lp_wgsplit.h).
 #include <algorithm>
+#include <type_traits>
 
 #include "lp_kernels.h"
 #include "lp_mma.h"
@@ -41,8 +47,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsig
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr_t;
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
@@ -53,7 +57,7 @@ __device__ __forceinline__ unsigned fastdiv(unsigned n, unsigned mul, unsigned s
     return (__umulhi(n, mul) + n) >> shift;
 }
 
-constexpr int WF_NW = 12, WF_NT = 768, WF_BK = 64;   // pixels per ring stage (two MFMA k-steps of 32)
+constexpr int WF_NW = 8, WF_NT = 512, WF_BK = 64;    // pixels per ring stage (two MFMA k-steps of 32)
 constexpr int WF_TILE = 160;                         // channels per operand tile
 constexpr int WF_ROW = WF_TILE * 2;                  // bytes per LDS row
 constexpr int WF_Y_BYTES = WF_BK * WF_ROW;           // dY rows of a stage: 20 KiB = 20 wave-loads
@@ -63,7 +67,8 @@ constexpr int WF_X_SLABS = (WF_X_ROWS * WF_ROW + 1023) / 1024;     // 21 wave-lo
 constexpr int WF_STAGE_BYTES = WF_Y_BYTES + WF_X_SLABS * 1024;
 constexpr int WF_STAGES = 3;
 constexpr int WF_SLABS = WF_Y_SLABS + WF_X_SLABS;    // 41 wave-loads per stage
-constexpr int WF_LPW = (WF_SLABS + WF_NW - 1) / WF_NW;   // at most 4 per wave
+constexpr int WF_LPW = (WF_SLABS + WF_NW - 1) / WF_NW;   // at most 6 per wave
+constexpr int WF_LDS = WF_STAGES * WF_STAGE_BYTES + 1024;      // (a read's last two window rows, which nobody uses, lie behind the stage)
 
 }  // namespace
 
@@ -88,7 +93,180 @@ __device__ __attribute__((noinline)) void wgrad_fast_update_tile(void* w, float*
                               c, tid);
 }
 
-__global__ __launch_bounds__(WF_NT) void conv_wgrad_fast_kernel(const WgradGroup g) {
+// What a wave reads, multiplies and adds up; see the head of the file.  TY: which of the two column sets (8 or 7 columns of 16
+// channels x one tap).
+template <int TY> struct WfCols {
+    static constexpr int NC = TY == 0 ? 8 : 7;
+    static constexpr int group(int gi) { return TY == 0 ? gi : gi + 2; }           // channel group of sixteen inside the half
+    static constexpr int tap0(int gi) { return TY == 1 && gi == 0 ? 2 : 0; }       // first tap of the group
+    static constexpr int ntap(int gi) { return TY == 0 ? (gi == 2 ? 2 : 3) : (gi == 0 ? 1 : 3); }
+    static constexpr int col(int gi) { return TY == 0 ? 3 * gi : (gi == 0 ? 0 : 3 * gi - 2); }     // accumulator column of the first tap
+};
+
+// The transposing LDS read as inline assembly with explicit lgkmcnt waits.  Through the compiler's builtin the read carries no
+// memory operand, so the waitcnt pass cannot tell it from the in-flight direct-to-LDS loads and puts s_waitcnt vmcnt(0) in
+// front of it.  The compiler does not know that the result is pending: nothing may touch it before the wait that covers it,
+// and the empty asm behind that wait is where its value becomes usable.  No read is in flight over a back edge.
+template <int OFF> __device__ __forceinline__ u32x2 tr_read(unsigned a) {
+    u32x2 r;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(a), "i"(OFF));
+    return r;
+}
+template <int N> __device__ __forceinline__ void wait_lgkm() { __builtin_amdgcn_s_waitcnt(0xc07f | (N << 8)); }
+
+template <int TY, class Load>
+__device__ __forceinline__ void wgrad_fast_loop(unsigned lds0, int nk, int k_begin, int W, unsigned mulW, unsigned shW, int lane, int wc, int half,
+                                                bool six, const Load& issue_load, f32x4 (&acc)[5][WfCols<TY>::NC]) {
+    typedef WfCols<TY> C;
+    const int lq = lane & 15, lg = lane >> 4;
+    const int lrow = 8 * lg + (lq >> 2);                 // this lane's row inside a 32-pixel k-step
+    const int sw = (lg & 1) * 32;
+    // dY: pairs 5 * wc + i, row bit 3 = lg & 1 in both halves of a fragment; the parity of i = 0 is that of wc
+    const unsigned a0 = lds0 + lrow * WF_ROW + 8 * (lq & 3) + 160 * wc;
+    const unsigned ae = wc ? a0 - sw : a0 + sw, ao = wc ? a0 + sw : a0 - sw;
+    // X: pairs 5 * half + group; rows 0..7 of the lane with row bit 3 = lg & 1, rows 8..11 with the other value
+    const unsigned x0 = lds0 + WF_Y_BYTES + lrow * WF_ROW + 8 * (lq & 3) + 160 * half;
+    const unsigned xe = half ? x0 - sw : x0 + sw, xo = half ? x0 + sw : x0 - sw;
+    const unsigned ye = half ? x0 - (32 - sw) : x0 + (32 - sw), yo = half ? x0 + (32 - sw) : x0 - (32 - sw);
+
+    u32x2 a_lo[5], a_hi[5], x[3], xn[3];
+    u32x4 af[5];
+    unsigned m0[4], m2[4];                               // column wrap: element k of the lane's 8 is invalid for tap 0 at column 0, for tap 2 at column W - 1
+    auto masks = [&](int k0) __attribute__((always_inline)) {
+        const int ow = k0 - (int)fastdiv((unsigned)k0, mulW, shW) * W;
+        if (W >= 8) {                                    // at most one of the 8 is bad: one half of one register
+            int e0 = ow == 0 ? 0 : W - ow;
+            const int e2 = W - 1 - ow;
+            const unsigned h0 = (e0 & 1) ? 0x0000ffffu : 0xffff0000u, h2 = (e2 & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) { m0[d] = (e0 >> 1) == d ? h0 : 0xffffffffu; m2[d] = (e2 >> 1) == d ? h2 : 0xffffffffu; }
+        } else {
+            unsigned b0 = 0, b2 = 0;
+            for (int e = ow == 0 ? 0 : W - ow; e < 8; e += W) b0 |= 1u << e;
+            for (int e = W - 1 - ow; e < 8; e += W) b2 |= 1u << e;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                m0[d] = ((b0 >> (2 * d)) & 1u ? 0u : 0xffffu) | ((b0 >> (2 * d)) & 2u ? 0u : 0xffff0000u);
+                m2[d] = ((b2 >> (2 * d)) & 1u ? 0u : 0xffffu) | ((b2 >> (2 * d)) & 2u ? 0u : 0xffff0000u);
+            }
+        }
+    };
+    const bool fixed_masks = 32 % W == 0;                // the same in every k-step
+    masks(k_begin + 8 * lg);
+
+#define WF_READ_A(i, sub) do { \
+        constexpr int o_ = 32 * (i) + (sub) * 32 * WF_ROW; \
+        a_lo[i] = tr_read<o_>(((i) & 1 ? ao : ae) + sb); a_hi[i] = tr_read<o_ + 4 * WF_ROW>(((i) & 1 ? ao : ae) + sb); } while (0)
+#define WF_READ_X(dst, gi, sub) do { \
+        constexpr int g_ = C::group(gi), o_ = 32 * g_ + (sub) * 32 * WF_ROW; \
+        dst[0] = tr_read<o_>((g_ & 1 ? xo : xe) + sb); dst[1] = tr_read<o_ + 4 * WF_ROW>((g_ & 1 ? xo : xe) + sb); \
+        dst[2] = tr_read<o_ + 8 * WF_ROW>((g_ & 1 ? yo : ye) + sb); } while (0)
+    auto have_x = [](u32x2 (&v)[3]) __attribute__((always_inline)) { asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2])); };
+    auto have_a = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            asm volatile("" : "+v"(a_lo[i]), "+v"(a_hi[i]));
+            af[i] = u32x4{a_lo[i][0], a_lo[i][1], a_hi[i][0], a_hi[i][1]};
+        }
+    };
+    // the taps of a channel group share the lane's ten pixels: tap 0 takes 0..7, tap 1 1..8, tap 2 2..9
+    auto mma_group = [&](const u32x2 (&v)[3], auto gi_) __attribute__((always_inline)) {
+        constexpr int gi = decltype(gi_)::value;
+#pragma unroll
+        for (int q = 0; q < C::ntap(gi); ++q) {
+            const int tap = C::tap0(gi) + q;
+            u32x4 b;
+            if (tap == 0) b = u32x4{v[0][0] & m0[0], v[0][1] & m0[1], v[1][0] & m0[2], v[1][1] & m0[3]};
+            else if (tap == 2) b = u32x4{v[0][1] & m2[0], v[1][0] & m2[1], v[1][1] & m2[2], v[2][0] & m2[3]};
+            else b = u32x4{__builtin_amdgcn_alignbit(v[0][1], v[0][0], 16), __builtin_amdgcn_alignbit(v[1][0], v[0][1], 16),
+                           __builtin_amdgcn_alignbit(v[1][1], v[1][0], 16), __builtin_amdgcn_alignbit(v[2][0], v[1][1], 16)};
+#pragma unroll
+            for (int i = 0; i < 5; ++i) Mma<bf16_t, 16>::run(af[i], b, acc[i][C::col(gi) + q]);
+        }
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
+#define WF_FENCE __builtin_amdgcn_sched_barrier(0)
+#define WF_TIE_A(i) asm volatile("" : "+v"(a_lo[i]), "+v"(a_hi[i]))
+
+    unsigned sb = 0;                                     // the stage being read
+    WF_READ_A(0, 0); WF_READ_A(1, 0); WF_READ_A(2, 0); WF_READ_A(3, 0); WF_READ_A(4, 0);
+    WF_READ_X(x, 0, 0);
+    wait_lgkm<0>();
+    have_a(); have_x(x);
+    int st = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        int st_free = st + WF_STAGES - 1;                // the stage that stage kt - 1 used
+        if (st_free >= WF_STAGES) st_free -= WF_STAGES;
+        const int kn = kt + WF_STAGES - 1;
+        // Six channel groups (three a k-step): one direct-to-LDS load of the stage two ahead, the next group's pixels and a part
+        // of the next k-step's dY fragments are requested ahead of a group's products and waited for behind them.
+        if (!fixed_masks && kt) masks(k_begin + kt * WF_BK + 8 * lg);
+        issue_load(0, st_free, kn);
+        WF_READ_X(xn, 1, 0); WF_READ_A(0, 1); WF_READ_A(1, 1); WF_FENCE;
+        mma_group(x, I0()); WF_FENCE;
+        wait_lgkm<0>(); have_x(xn); WF_TIE_A(0); WF_TIE_A(1);
+        issue_load(1, st_free, kn);
+        WF_READ_X(x, 2, 0); WF_READ_A(2, 1); WF_READ_A(3, 1); WF_FENCE;
+        mma_group(xn, I1()); WF_FENCE;
+        wait_lgkm<0>(); have_x(x); WF_TIE_A(2); WF_TIE_A(3);
+        issue_load(2, st_free, kn);
+        WF_READ_X(xn, 0, 1); WF_READ_A(4, 1); WF_FENCE;
+        mma_group(x, I2()); WF_FENCE;
+        wait_lgkm<0>(); have_x(xn); have_a();
+        if (!fixed_masks) masks(k_begin + kt * WF_BK + 32 + 8 * lg);
+        issue_load(3, st_free, kn);
+        WF_READ_X(x, 1, 1); WF_FENCE;
+        mma_group(xn, I0()); WF_FENCE;
+        wait_lgkm<0>(); have_x(x);
+        issue_load(4, st_free, kn);
+        WF_READ_X(xn, 2, 1); WF_FENCE;
+        mma_group(x, I1()); WF_FENCE;
+        wait_lgkm<0>(); have_x(xn);                      // this wave has read all it needs of the stage
+        issue_load(5, st_free, kn);
+        if (six) wait_vmcnt<6>(); else wait_vmcnt<5>();  // stage kt + 1 landed (this wave's share)
+        __builtin_amdgcn_s_barrier();                    // ... everyone's; and stage kt is free
+        if (++st == WF_STAGES) st = 0;
+        sb = (unsigned)(st * WF_STAGE_BYTES);
+        WF_READ_A(0, 0); WF_READ_A(1, 0); WF_READ_A(2, 0); WF_READ_A(3, 0); WF_READ_A(4, 0);
+        WF_READ_X(x, 0, 0); WF_FENCE;
+        mma_group(xn, I2()); WF_FENCE;
+        wait_lgkm<0>(); have_a(); have_x(x);
+    }
+#undef WF_READ_A
+#undef WF_READ_X
+#undef WF_TIE_A
+#undef WF_FENCE
+}
+
+// partial sums of a wave -> dW[co][r][s][ci]
+template <int TY>
+__device__ __forceinline__ void wgrad_fast_store(float* __restrict__ dw, const f32x4 (&acc)[5][WfCols<TY>::NC], int r, int co0, int ci0, int Cin, int Cout,
+                                                 bool add, int lane, int wc, int half) {
+    typedef WfCols<TY> C;
+    const int lq = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+#pragma unroll
+        for (int gi = 0; gi < 3; ++gi)
+#pragma unroll
+            for (int q = 0; q < C::ntap(gi); ++q) {
+                const int ci = ci0 + 80 * half + 16 * C::group(gi) + lq, tap = r * 3 + C::tap0(gi) + q;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int co = co0 + 80 * wc + 16 * i + 4 * lg + e;
+                    if (co < Cout && ci < Cin) {
+                        float* const dst = dw + ((size_t)co * 9 + tap) * Cin + ci;
+                        const float v = acc[i][C::col(gi) + q][e];
+                        if (add) atomicAdd(dst, v);
+                        else *dst = v;
+                    }
+                }
+            }
+}
+
+__global__ __launch_bounds__(WF_NT, 2) void conv_wgrad_fast_kernel(const WgradGroup g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -110,186 +288,58 @@ __global__ __launch_bounds__(WF_NT) void conv_wgrad_fast_kernel(const WgradGroup
     // ---- loads: wave-load q = wave + 12*i; q < 20: bytes [1024*q, +1024) of the dY rows, else of the X window.
     // Lane l supplies the 16 bytes that land at +16*l, i.e. row b/320 and the (swizzled) channel chunk of that row.
     // (Everything is recomputed per stage rather than kept in registers: the accumulators need them.)
-    const int nld = wave + WF_NW * (WF_LPW - 1) < WF_SLABS ? WF_LPW : WF_LPW - 1;
+    const bool six = wave + WF_NW * (WF_LPW - 1) < WF_SLABS;
     const int Mtot = P.M;
     // the division constants in scalar registers for good (left alone, the compiler re-reads them from the kernel
     // arguments inside the loops and every re-read is a wait on the scalar cache)
     unsigned mulW = P.mulW, shW = P.shW, mulH = P.mulH, shH = P.shH;
     asm volatile("" : "+s"(mulW), "+s"(shW), "+s"(mulH), "+s"(shH));
-    auto issue_loads = [&](int st, int kt) {
+    auto issue_load = [&](int i, int st, int kt) __attribute__((always_inline)) {
         const int mt = k_begin + kt * WF_BK;                 // first pixel of the stage (beyond k_end: all zeros)
         const bool live = mt < k_end;
-#pragma unroll
-        for (int i = 0; i < WF_LPW; ++i) {
-            const int q = wave + WF_NW * i;
-            if (q < WF_SLABS) {
-                const bool isx = q >= WF_Y_SLABS;
-                const int b = (isx ? q - WF_Y_SLABS : q) * 1024 + lane * 16;
-                const int row = b / WF_ROW, cb = b - row * WF_ROW;
-                const int ce = ((((cb >> 5) ^ ((row >> 3) & 1)) << 5) | (cb & 31)) >> 1;   // first channel fetched
-                bool ok = live;
-                unsigned off;
-                if (!isx) {
-                    ok = ok && (co0 + ce < Cout) && (mt + row < k_end);
-                    off = (unsigned)(((mt + row) * Cout + co0 + ce) * 2);
-                } else {
-                    // window pixel p; zero unless it exists and its image row hp has hp-(r-1) inside the image
-                    const int p = mt + row - 1 + (r - 1) * W;
-                    const unsigned t = fastdiv((unsigned)p, mulW, shW);
-                    const int hp = (int)t - (int)fastdiv(t, mulH, shH) * H;
-                    ok = ok && row < WF_X_ROWS && (ci0 + ce < Cin) && p >= 0 && p < Mtot && (unsigned)(hp - (r - 1)) < (unsigned)H;
-                    off = (unsigned)((p * Cin + ci0 + ce) * 2);
-                }
-                if (!ok) off = kOOB;
-                unsigned char* dst = smem + st * WF_STAGE_BYTES + q * 1024;
-                if (!isx) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_y, (lds_ptr_t)dst, 16, (int)off, 0, 0, 0);
-                else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_x, (lds_ptr_t)dst, 16, (int)off, 0, 0, 0);
-            }
+        const int q = wave + WF_NW * i;
+        if (q >= WF_SLABS) return;
+        const bool isx = q >= WF_Y_SLABS;
+        const int b = (isx ? q - WF_Y_SLABS : q) * 1024 + lane * 16;
+        const int row = b / WF_ROW, cb = b - row * WF_ROW;
+        const int ce = ((((cb >> 5) ^ ((row >> 3) & 1)) << 5) | (cb & 31)) >> 1;   // first channel fetched
+        unsigned char* dst = smem + st * WF_STAGE_BYTES + q * 1024;
+        if (!isx) {
+            const bool ok = live && (co0 + ce < Cout) && (mt + row < k_end);
+            const unsigned off = ok ? (unsigned)(((mt + row) * Cout + co0 + ce) * 2) : kOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_y, (lds_ptr_t)dst, 16, (int)off, 0, 0, 0);
+        } else {
+            // window pixel p; zero unless it exists and its image row hp has hp-(r-1) inside the image
+            const int p = mt + row - 1 + (r - 1) * W;
+            const unsigned t = fastdiv((unsigned)p, mulW, shW);
+            const int hp = (int)t - (int)fastdiv(t, mulH, shH) * H;
+            const bool ok = live && row < WF_X_ROWS && (ci0 + ce < Cin) && p >= 0 && p < Mtot && (unsigned)(hp - (r - 1)) < (unsigned)H;
+            const unsigned off = ok ? (unsigned)((p * Cin + ci0 + ce) * 2) : kOOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_x, (lds_ptr_t)dst, 16, (int)off, 0, 0, 0);
         }
     };
-
-    // ---- fragment addressing (transposing reads): lane l, l' = l%16, g = l/16 supplies pixel row 8g + 4h + l'/4
-    // (h = which half of the 8 reduction elements) and channels cbase + 4*(l'%4)..+3, and receives channel cbase + l'.
-    // The 32-byte channel pair P of a row sits at pair slot P ^ s, s = bit 3 of the LDS row: P + s for even P, P - s
-    // for odd P.  So a fragment address is one of two lane registers (even / odd pair) plus a compile-time offset.
-    const int wc = wave & 1, wj = wave >> 1;
-    const int tap_s = wj >> 1, half = wj & 1;
-    const int lq = lane & 15, lg = lane >> 4;
-    const int lrow = 8 * lg + (lq >> 2);                 // this lane's row inside a 32-pixel k-step (h = 0)
-    // dY: pairs 5*wc + i, row bit 3 = g & 1 in both halves
-    const int a_row_off = lrow * WF_ROW + 8 * (lq & 3) + 160 * wc;
-    const int a_sw = (lg & 1) * 32;
-    const int a_even = a_row_off + ((wc & 1) ? -a_sw : a_sw);      // pair parity of i = 0 is wc & 1
-    const int a_odd = a_row_off + ((wc & 1) ? a_sw : -a_sw);
-    const int b_row_off = WF_Y_BYTES + (lrow + tap_s) * WF_ROW + 8 * (lq & 3) + 160 * half;
-    // The transposing LDS read as inline assembly with explicit lgkmcnt waits below.  Through the compiler's builtin
-    // the read carries no memory operand, so the waitcnt pass cannot tell it from the in-flight direct-to-LDS loads
-    // and puts s_waitcnt vmcnt(0) in front of it: every k-step then waited for the loads of the stage two ahead.
-    auto tr_read = [&](const unsigned char* p) -> u32x2 {
-        u32x2 r;
-        const unsigned a = (unsigned)(uintptr_t)(lds_ptr_t)const_cast<unsigned char*>(p);
-        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r) : "v"(a));
-        return r;
+    const int wc = wave & 1, half = (wave >> 1) & 1;     // waves w and w + 4 (one SIMD) have the two column sets
+    auto work = [&](auto ty_) __attribute__((always_inline)) {
+        constexpr int TY = decltype(ty_)::value;
+        f32x4 acc[5][WfCols<TY>::NC];
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+#pragma unroll
+            for (int j = 0; j < WfCols<TY>::NC; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        wgrad_fast_loop<TY>((unsigned)(uintptr_t)(lds_ptr_t)smem, nk, k_begin, W, mulW, shW, lane, wc, half, six, issue_load, acc);
+        wait_vmcnt<0>();                 // trailing out-of-range loads still write zeros into LDS
+        wgrad_fast_store<TY>(P.dw, acc, r, co0, ci0, Cin, Cout, P.ksplit > 1, lane, wc, half);
     };
-
-    f32x4 acc[5][5];
+    // (every workgroup has at least one stage: k_begin < k_end)
 #pragma unroll
-    for (int i = 0; i < 5; ++i)
+    for (int kt = 0; kt < WF_STAGES - 1; ++kt)
 #pragma unroll
-        for (int j = 0; j < 5; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    if (nk > 0) {
-        issue_loads(0, 0);
-        issue_loads(1, 1);
-        // this wave's share of stage 0 landed once at most one stage of its loads (nld of them) is outstanding
-        if (nld == 4) wait_vmcnt<4>(); else wait_vmcnt<3>();
-        __builtin_amdgcn_s_barrier();
-        int st = 0;
-        for (int kt = 0; kt < nk; ++kt) {
-            int st_free = st + WF_STAGES - 1;
-            if (st_free >= WF_STAGES) st_free -= WF_STAGES;
-            issue_loads(st_free, kt + WF_STAGES - 1);          // into the stage that stage kt-1 used
-            const unsigned char* S = smem + st * WF_STAGE_BYTES;
-#pragma unroll 1
-            for (int sub = 0; sub < 2; ++sub) {     // not unrolled: the second k-step's addresses would be kept in registers
-                const unsigned char* Ss = S + sub * (32 * WF_ROW);
-                // column wrap: pixel k of this lane's 8 reduction elements is invalid for tap 0 at column 0 and for
-                // tap 2 at column W-1 (tap 1 never)
-                unsigned km0 = 0xffffffffu, km1 = 0xffffffffu, km2 = 0xffffffffu, km3 = 0xffffffffu;
-                if (tap_s != 1) {
-                    const int k0 = k_begin + kt * WF_BK + sub * 32 + 8 * lg;
-                    const int ow0 = k0 - (int)fastdiv((unsigned)k0, mulW, shW) * W;
-                    const int bad = tap_s == 0 ? 0 : W - 1;
-                    int e = bad - ow0;                        // first of this lane's 8 elements in the bad column
-                    if (e < 0) e += W;
-                    if (W >= 8) {
-                        // at most one of the 8 is bad: one half of one mask register
-                        const unsigned half = (e & 1) ? 0x0000ffffu : 0xffff0000u;
-                        const int d = e >> 1;
-                        km0 = d == 0 ? half : 0xffffffffu; km1 = d == 1 ? half : 0xffffffffu;
-                        km2 = d == 2 ? half : 0xffffffffu; km3 = d == 3 ? half : 0xffffffffu;
-                    } else {
-                        unsigned bits = 0xffu;
-                        for (; e < 8; e += W) bits &= ~(1u << e);
-                        km0 = ((bits & 1u) ? 0xffffu : 0u) | ((bits & 2u) ? 0xffff0000u : 0u);
-                        km1 = ((bits & 4u) ? 0xffffu : 0u) | ((bits & 8u) ? 0xffff0000u : 0u);
-                        km2 = ((bits & 16u) ? 0xffffu : 0u) | ((bits & 32u) ? 0xffff0000u : 0u);
-                        km3 = ((bits & 64u) ? 0xffffu : 0u) | ((bits & 128u) ? 0xffff0000u : 0u);
-                    }
-                }
-                // The compiler does not know that the results of these reads are pending: nothing may touch them before
-                // the s_waitcnt that covers them, and the empty asm behind that wait is where their values become
-                // usable (it orders every use after the wait).  LDS reads return in order.
-                u32x2 alo[5], ahi[5];
-#pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    const unsigned char* pa = Ss + ((i & 1) ? a_odd : a_even) + 32 * i;
-                    alo[i] = tr_read(pa);
-                    ahi[i] = tr_read(pa + 4 * WF_ROW);
-                }
-                // window rows of this lane for h = 0 and h = 1; the pair swizzle follows the actual LDS row
-                const int wr0 = 32 * sub + lrow + tap_s, wr1 = wr0 + 4;
-                const int s0 = ((wr0 >> 3) & 1) * 32, s1 = ((wr1 >> 3) & 1) * 32;
-                const unsigned char* B0 = Ss + b_row_off;
-                const unsigned char* B1 = B0 + 4 * WF_ROW;
-                // pair 5*half + j: its parity for j = 0 is half & 1
-                const unsigned char* B0e = B0 + ((half & 1) ? -s0 : s0);
-                const unsigned char* B0o = B0 + ((half & 1) ? s0 : -s0);
-                const unsigned char* B1e = B1 + ((half & 1) ? -s1 : s1);
-                const unsigned char* B1o = B1 + ((half & 1) ? s1 : -s1);
-                // the X fragments one ahead of the MFMAs that use them (and no further: registers)
-                u32x2 blo[5], bhi[5];
-                blo[0] = tr_read(B0e); bhi[0] = tr_read(B1e);
-                u32x4 af[5];
-#pragma unroll
-                for (int j = 0; j < 5; ++j) {
-                    if (j + 1 < 5) {
-                        blo[j + 1] = tr_read((((j + 1) & 1) ? B0o : B0e) + 32 * (j + 1));
-                        bhi[j + 1] = tr_read((((j + 1) & 1) ? B1o : B1e) + 32 * (j + 1));
-                        __builtin_amdgcn_s_waitcnt(0xc07f | (2 << 8));                 // lgkmcnt(2): all but the pair just issued
-                    } else {
-                        __builtin_amdgcn_s_waitcnt(0xc07f);                            // lgkmcnt(0)
-                    }
-                    if (j == 0) {
-#pragma unroll
-                        for (int i = 0; i < 5; ++i) {
-                            asm volatile("" : "+v"(alo[i]), "+v"(ahi[i]));
-                            af[i] = u32x4{alo[i][0], alo[i][1], ahi[i][0], ahi[i][1]};
-                        }
-                    }
-                    asm volatile("" : "+v"(blo[j]), "+v"(bhi[j]));
-                    const u32x4 bfj = {blo[j][0] & km0, blo[j][1] & km1, bhi[j][0] & km2, bhi[j][1] & km3};
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int i = 0; i < 5; ++i) Mma<bf16_t, 16>::run(af[i], bfj, acc[i][j]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (nld == 4) wait_vmcnt<4>(); else wait_vmcnt<3>();    // stage kt+1 landed (this wave's share)
-            __builtin_amdgcn_s_barrier();                         // ... everyone's; and stage st is free again
-            if (++st == WF_STAGES) st = 0;
-        }
-    }
-    wait_vmcnt<0>();                     // trailing out-of-range loads still write zeros into LDS
-
-    // ---- epilogue: partial sums -> dW[co][r][s][ci]
-    float* __restrict__ dw = P.dw;
-    const int tap = r * 3 + tap_s;
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int ci = ci0 + 80 * half + 16 * j + lq;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int co = co0 + 80 * wc + 16 * i + 4 * lg + e;
-                if (co < Cout && ci < Cin) {
-                    float* dst = dw + ((size_t)co * 9 + tap) * Cin + ci;
-                    if (P.ksplit == 1) *dst = acc[i][j][e];
-                    else atomicAdd(dst, acc[i][j][e]);
-                }
-            }
-        }
+        for (int i = 0; i < WF_LPW; ++i) issue_load(i, kt, kt);
+    // this wave's share of stage 0 landed once at most one stage of its loads is outstanding
+    if (six) wait_vmcnt<6>(); else wait_vmcnt<5>();
+    __builtin_amdgcn_s_barrier();
+    if (wave < 4) work(std::integral_constant<int, 0>());
+    else work(std::integral_constant<int, 1>());
     // ---- parameter update by the workgroup that completed this tile (Cin and Cout are multiples of 8: whole vectors)
     if (P.w) {
         __shared__ unsigned s_last;
@@ -306,13 +356,13 @@ __global__ __launch_bounds__(WF_NT) void conv_wgrad_fast_kernel(const WgradGroup
             __syncthreads();
             if (!s_last) return;
         }
-        wgrad_fast_update_tile(P.w, P.vel, P.master, dw, co0, ci0, r, Cin, Cout, g.lowp != 0, g.lr, g.momentum, g.wd, t2);
+        wgrad_fast_update_tile(P.w, P.vel, P.master, P.dw, co0, ci0, r, Cin, Cout, g.lowp != 0, g.lr, g.momentum, g.wd, t2);
     }
 }
 
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s) {
     if (g.total_tiles <= 0) return hipSuccess;
-    const size_t lds = (size_t)WF_STAGES * WF_STAGE_BYTES;
+    const size_t lds = WF_LDS;
     static OncePerDevice configured;
     if (const hipError_t e = raise_lds_limit(configured, {(const void*)conv_wgrad_fast_kernel}, (int)lds); e != hipSuccess) return e;
     hipLaunchKernelGGL(conv_wgrad_fast_kernel, dim3(xcd_grid(g.total_tiles)), dim3(WF_NT), lds, s, g);

@@ -37,10 +37,10 @@ LP_WG_HD bool xcd_piece(int block, int nprob, Count count, int& prob, int& local
 // One problem of the plan: `tiles` output tiles of `kt` k-tiles (32 pixels) each, every one cut into `ksplit` pieces.
 struct SplitPart { int tiles, kt, ksplit; };
 
-// Time of a launch in k-tiles (1.25 us each): a workgroup has a compute unit to itself, and what it does besides its k-tiles is
+// Time of a launch in k-tiles (0.9 us each): a workgroup has a compute unit to itself, and what it does besides its k-tiles is
 // worth kEpilogueAdd where partial sums are added with atomics and kEpilogueStore where its piece is the whole reduction (one
-// and two rounds of 256, 128, 64 k-tiles: 305 us with stores, 385 with atomics and half the pieces, 456 with a quarter).
-constexpr int kWgradCUs = 256, kEpilogueAdd = 28, kEpilogueStore = 4;
+// and two rounds of 256 and 128 k-tiles: 251 us with stores, 282 with atomics, 337 with atomics and half the length).
+constexpr int kWgradCUs = 256, kEpilogueAdd = 52, kEpilogueStore = 16;
 inline double wgrad_round(int chunk, bool whole) { return chunk + (whole ? kEpilogueStore : kEpilogueAdd); }
 
 // Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
