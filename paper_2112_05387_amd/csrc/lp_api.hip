@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -107,6 +108,7 @@ enum FcRef { F_IN = 0, F_IN2, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMM
 
 struct Op {
     int type = 0, cfg = 0;
+    bool cfg_mid = false;                  // a convolution the tiles of lp_conv_fast.hip may take although its cfg is a general one
     int phase = 0;                         // fused step: 0 forward, 1 loss, 2 backward, 3 multiplier update
     bool vec = true;
     Ref r[F_COUNT];
@@ -253,6 +255,13 @@ static bool conv_fast_ok(const lp_net* net, const ConvProb& c) {
     return in_bytes < 2.0e9 && w_bytes < 2.0e9;
 }
 
+// the tiles with waves of 32 pixels take a layer of whole 64-channel k-tiles whatever its output width
+static bool conv_mid_ok(const lp_net* net, const ConvProb& c) {
+    if (net->dtype != LP_BF16 || c.Cin % 64 != 0 || c.Ncol % 8 != 0 || c.Ncol < 48 || c.ntr * c.nts > 32) return false;
+    const double in_bytes = (double)c.M / ((double)c.OA * c.OB) * c.IH * c.IW * c.Cin * 2.0;
+    return in_bytes < 2.0e9 && (double)c.Ncol * c.ldw * 2.0 < 2.0e9;
+}
+
 // pick the wide-layer configuration of a problem; returns false if the wide-layer kernel does not apply
 static bool pick_fast_cfg(const lp_net* net, const ConvProb& c, int& cfg) {
     if (!conv_fast_ok(net, c)) return false;
@@ -323,6 +332,7 @@ struct Builder {
         c.OH = u.Ho; c.OW = u.Wo; c.omul = 1; c.ooh = 0; c.oow = 0;
         o.vec = (u.cin % epv()) == 0;
         o.cfg = conv_cfg_for(c.Ncol, o.vec, c.M);
+        o.cfg_mid = conv_mid_ok(net, c);
         pick_fast_cfg(net, c, o.cfg);
         pick_win_cfg(net, c, o.cfg);
         o.r[0] = in; o.r[1] = w; o.r[2] = out; o.r[5] = stats;
@@ -351,6 +361,7 @@ struct Builder {
                 c.Kg = c.ntr * c.nts * c.Cin;
                 o.vec = (u.cout % epv()) == 0;
                 o.cfg = conv_cfg_for(c.Ncol, o.vec, c.M);
+                o.cfg_mid = conv_mid_ok(net, c);
                 pick_fast_cfg(net, c, o.cfg);
                 pick_win_cfg(net, c, o.cfg);
                 o.r[0] = dy; o.r[1] = wt; o.r[2] = dx; o.r[3] = add0; o.r[4] = add1;
@@ -1625,13 +1636,12 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
 // units this stream lane can expect: a workgroup of the large tiles runs at 7.5 TFLOP/s (two- and four-wave variants at 2.5
 // and 5) behind 25 us of prologue, window and epilogue (10 for the smaller variants); a small one takes a 128-byte line
 // into LDS per 4.5 clocks, and 5 us around that, statistics included.
-static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const CfgInfo& ci, SConvGroup& out, size_t& lds) {
-    if (net->separate) return false;
+static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const CfgInfo& ci, SConvGroup& out, size_t& lds, double& time) {
     out.nprob = g.nprob; out.pad_[0] = out.pad_[1] = 0;
     lds = 0;
     const int cap = std::max(1, 256 / std::max(1, net->lanes_in_flight));
     const int waves = ci.BM / 64 * (ci.BN / 160);
-    double t_old = 0, t_new = 0;
+    double t_old = 0, t_new = 0, t_real = 0;
     long tot = 0, work_old = 0;
     for (int i = 0; i < kMaxGroup; ++i) {
         if (i >= g.nprob) { out.start[i] = INT_MAX; continue; }
@@ -1671,7 +1681,9 @@ static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const Cf
         out.start[i] = (int)tot;
         const long blocks = (long)((p.nimg + p.segs - 1) / p.segs) * p.tpi * ((c.Ncol + 31) / 32);
         tot += blocks;
-        t_new += (double)blocks * (nslab * (npx(TH) * p.segs + ntaps * 32) * 4.5 / 2.1e3 + 5.0);
+        const double lines = nslab * (npx(TH) * p.segs + ntaps * 32) * 4.5 / 2.1e3;
+        t_new += (double)blocks * (lines + 5.0);
+        t_real += (double)blocks * (2.3 * lines + 5.0);    // measured; the comparison with the large tiles is calibrated on t_new
         work_old += (long)c.tiles_m * c.tiles_n;
         t_old += (double)c.tiles_m * c.tiles_n * (2.0 * ci.BM * ci.BN * c.Kg / (waves >= 8 ? 7.5e6 : waves >= 4 ? 5e6 : 2.5e6) + (waves >= 8 ? 25.0 : 10.0));
     }
@@ -1683,9 +1695,30 @@ static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const Cf
     // average time of a workgroup times the number of rounds; what the model calls equal is left where it was (batch 24 of the
     // same network: launches within 15 % of each other made the step 1 % slower)
     const double r_old = (double)((work_old + cap - 1) / cap) / work_old, r_new = (double)((tot + cap - 1) / cap) / tot;
+    time = t_real * r_new + (g.p[0].stats ? 6.0 : 0.0);    // and the launch that sums its statistics
     return t_new * r_new < 0.85 * t_old * r_old;
 }
 
+// What a launch takes, in us: a workgroup of nk k-tiles of 64 channels is done in lat * nk + lat0 where it does not wait for
+// others, and a compute unit that always has the next one at hand does one per thr * nk + thr0.  The two meet as the root of
+// the sum of squares: the chip is neither empty nor always full.  The numbers are fitted to launches with cold filters and the
+// input in the memory-side cache, as a step leaves them.  One workgroup a compute unit (lat): two ring stages, 64 KB, 0.89 us a
+// k-tile of 128 x 128, since a k-tile has to come from memory in the time of one; three stages 0.50, four stages of 64 x 64
+// 0.32.  Full chip (thr): a 128-byte line per 4.5 clocks, so the larger tile wins and the second or third workgroup per compute
+// unit hides what the ring does not.  Layers of 64 samples, two / three stages of 128 x 128 / tiles of 256 x 320 or 128 x 160 as
+// before: 14 x 14 x 256, 3 x 3: 43 / 31 / 56 us; 56 x 56, 64 -> 256: 48 / 76 / 56; 8 x 8 x 640, 3 x 3: 89 / 59 / 110; of 6 samples
+// 64 x 64: 14 x 14 x 256, 3 x 3: 20 us (51), 7 x 7 x 512: 31 (90).
+struct ConvTileTime { int cfg; double lat, lat0, thr, thr0; };
+static double conv_time(const ConvTileTime& t, const CfgInfo& ci, const Op* const* ops, int n, double cus) {
+    double longest = 0, work = 0;
+    for (int i = 0; i < n; ++i) {
+        const ConvProb& c = ops[i]->conv;
+        const double nk = c.ntr * c.nts * (c.Cin / 64.0), tiles = (double)((c.M + ci.BM - 1) / ci.BM) * ((c.Ncol + ci.BN - 1) / ci.BN);
+        longest = std::max(longest, t.lat * nk + t.lat0);
+        work += tiles * (t.thr * nk + t.thr0);
+    }
+    return std::sqrt(longest * longest + work / cus * (work / cus));
+}
 // Tile sizes of a grouped launch of the narrow kernel: the smallest tiles of which two per compute unit hold the whole
 // launch (the less a workgroup does, the shorter the launch), full-size tiles where even those are more.
 static void plan_fconv_tiles(FConvGroup& g) {
@@ -1750,6 +1783,77 @@ static int conv_launch_cfg(const lp_net* net, const Op* const* ops, int n, bool&
     return cfg;
 }
 
+static void set_conv_tiles(ConvGroup& g, const CfgInfo& ci) {
+    g.total_tiles = 0;
+    for (int i = 0; i < g.nprob; ++i) {
+        ConvProb& p = g.p[i];
+        p.tiles_m = (p.M + ci.BM - 1) / ci.BM; p.tiles_n = (p.Ncol + ci.BN - 1) / ci.BN;
+        p.tile_start = g.total_tiles; g.total_tiles += p.tiles_m * p.tiles_n;
+    }
+}
+
+// Which kernel a grouped convolution launch goes to, and its tiles: the large tiles (of the rule above), the small ones of
+// lp_sconv.hip where their model sees a gain over those, or the tiles of 32-pixel waves (layers of whole 64-channel k-tiles),
+// whichever is the shortest.  A bf16 network of more than a few blocks answers to any other order of its sums with another rounding
+// of everything (0.1 of an adjoint's norm in the six-block stage of ResNet-50), so a choice between them must not show: the sums
+// over k run in the same order (slabs of 64 channels, tap by tap; with slabs of 32 only where there is one tap), and the batch
+// statistics are those of the large tiles: summed by tiles of as many rows in their order, by others in a launch of their own.
+// ResNet-50 of 64 / 6 samples, WRN-28-10 forward of 75 samples (38 workgroups of 256 x 320 in its 640-channel layers): see the
+// figures of conv_time; steps 6644 -> 6305 us, 1826 -> 1602, 1178 -> 1039; at 128 samples the large tiles of WRN-28-10 stay the faster ones (4878 us a step, 5211 with its 640-channel
+// layers in 128 x 128).  Half or twice the share of the chip in `cus` changes the steps by less than 1 %.
+struct ConvPlan {
+    int cfg;
+    bool win, fast;
+    bool small;            // launch_sconv
+    int stats_rows;        // != 0: the statistics by launch_tile_stats, tiles of so many rows
+};
+static ConvPlan plan_conv(const lp_net* net, const Op* const* ops, int n, ConvGroup& g, SConvGroup& small, size_t& small_lds) {
+    ConvPlan r{};
+    r.cfg = conv_launch_cfg(net, ops, n, r.win, r.fast);
+    auto info = [&] { return r.win ? conv_win_cfg_info(r.cfg) : r.fast ? conv_fast_cfg_info(r.cfg) : conv_cfg_info(r.cfg, net->dtype); };
+    const int rows = info().BM;
+    const bool slab64 = r.win || r.cfg == FAST64_256x320 || r.cfg == FAST64_128x320 || r.cfg == FAST64_128x160 || r.cfg == FAST64_256x160;
+    bool stats = false, mid_ok = !net->separate && (r.fast || (!net->narrow && r.cfg == CFG_N64));
+    double stat_bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        const ConvProb& c = g.p[i];
+        const int taps = c.ntr * c.nts;
+        mid_ok = mid_ok && ops[i]->cfg_mid && (slab64 || taps <= 1 || (!r.fast && c.Cin == 64)) && (r.fast || !c.stats);
+        stats = stats || c.stats;
+        if (c.stats) stat_bytes += 2.0 * c.M * c.Ncol;
+    }
+    const double cus = 256.0 / std::max(1, net->lanes_in_flight);       // this lane's share of the chip
+    double t_mid = 1e300, t_large = 1e300, t_small = 1e300;
+    int mid = -1;
+    bool own_stats = false;
+    if (mid_ok) {
+        static const ConvTileTime tiles[] = {
+            {MID_128x128, 0.885, 3.5, 0.54, 3.1}, {MID_128x128_R3, 0.495, 4.0, 0.54, 4.5}, {MID_128x64, 0.85, 3.5, 0.40, 2.05}, {MID_128x64_R3, 0.44, 3.5, 0.40, 2.9},
+            {MID_128x32_R4, 0.36, 4.6, 0.34, 4.9}, {MID_64x128_R3, 0.44, 3.0, 0.40, 2.6}, {MID_64x64_R4, 0.32, 3.5, 0.27, 2.3},
+            {MID_256x128_R3, 0.73, 4.6, 0.80, 8.5}, {MID_256x64_R3, 0.51, 4.0, 0.67, 6.2}, {MID_256x32_R4, 0.43, 4.3, 0.60, 5.6}};
+        for (const ConvTileTime& t : tiles) {
+            const CfgInfo ci = conv_fast_cfg_info(t.cfg);
+            const bool sep = stats && ci.BM != rows;
+            const double v = conv_time(t, ci, ops, n, cus) + (sep ? 5.0 + stat_bytes / 3.0e6 : 0.0);
+            if (v < t_mid) { t_mid = v; mid = t.cfg; own_stats = sep; }
+        }
+        if (r.cfg == WIN64_256x320) t_large = conv_time({r.cfg, 1.4, 16, 1.4, 16}, info(), ops, n, cus);
+        else if (r.cfg == WIN64_512x160 || r.cfg == FAST_512x160) t_large = conv_time({r.cfg, 1.94, 16, 1.94, 16}, info(), ops, n, cus);
+        else if (r.cfg == FAST64_256x320) t_large = conv_time({r.cfg, 1.58, 7, 1.3, 15}, info(), ops, n, cus);
+    }
+    set_conv_tiles(g, info());
+    if (r.fast && plan_sconv(net, g, r.win, info(), small, small_lds, t_small) && t_small < t_mid) {
+        if (!net->separate) { r.small = true; r.stats_rows = stats ? rows : 0; }
+        return r;
+    }
+    if (mid >= 0 && t_mid < t_large) {
+        r.cfg = mid; r.win = false; r.fast = true;
+        r.stats_rows = own_stats ? rows : 0;
+        set_conv_tiles(g, info());
+    }
+    return r;
+}
+
 static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, size_t base, int n, const Bindings& b, hipStream_t s,
                                     int* used_cfg, int* used_blocks);
 
@@ -1803,11 +1907,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 err = launch_wtrans(g, dt, s);
             } break;
             case OP_CONV: {
-                ConvGroup g; g.nprob = n; int tot = 0;
-                bool win, fast;
-                const int cfg = conv_launch_cfg(net, &ops[base], n, win, fast);
-                if (used_cfg) *used_cfg = cfg;
-                const CfgInfo ci = win ? conv_win_cfg_info(cfg) : fast ? conv_fast_cfg_info(cfg) : conv_cfg_info(cfg, dt);
+                ConvGroup g; g.nprob = n;
                 // longest tiles first: the blocks of a launch are dispatched in order
                 std::stable_sort(ops.begin() + base, ops.begin() + base + n,
                                  [](const Op* a, const Op* b2) { return a->conv.Kg > b2->conv.Kg; });
@@ -1826,29 +1926,24 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         sg.cmax = std::max(sg.cmax, q.C); ++sg.nprob;
                         p.stats = nullptr;
                     }
-                    p.tiles_m = (p.M + ci.BM - 1) / ci.BM; p.tiles_n = (p.Ncol + ci.BN - 1) / ci.BN;
-                    p.tile_start = tot; tot += p.tiles_m * p.tiles_n;
                 }
-                g.total_tiles = tot;
                 SConvGroup small; size_t small_lds = 0;
-                if (fast && plan_sconv(net, g, win, ci, small, small_lds)) {
-                    if (used_cfg) *used_cfg = SMALL_128x32;
-                    if (used_blocks) *used_blocks = small.total_tiles;
-                    err = launch_sconv(small, small_lds, s);
-                    TileStatsGroup ts; ts.nprob = 0; ts.total_blocks = 0;
-                    for (int i = 0; i < n; ++i) {
-                        const ConvProb& c = g.p[i];
-                        if (!c.stats) continue;
-                        TileStatsProb& q = ts.p[ts.nprob++];
-                        q.y = c.out; q.stats = c.stats; q.M = c.M; q.C = c.Ncol; q.BM = ci.BM; q.block_start = ts.total_blocks;
-                        ts.total_blocks += c.tiles_m * ((c.Ncol + 63) / 64);
-                    }
-                    if (err == hipSuccess) err = launch_tile_stats(ts, s);
-                    if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);
-                    break;
+                const ConvPlan plan = plan_conv(net, &ops[base], n, g, small, small_lds);
+                if (used_cfg) *used_cfg = plan.cfg;
+                TileStatsGroup ts; ts.nprob = 0; ts.total_blocks = 0;
+                for (int i = 0; i < n && plan.stats_rows; ++i) {
+                    ConvProb& c = g.p[i];
+                    if (!c.stats) continue;
+                    TileStatsProb& q = ts.p[ts.nprob++];
+                    q.y = c.out; q.stats = c.stats; q.M = c.M; q.C = c.Ncol; q.BM = plan.stats_rows; q.block_start = ts.total_blocks;
+                    ts.total_blocks += (c.M + q.BM - 1) / q.BM * ((c.Ncol + 63) / 64);
+                    c.stats = nullptr;
                 }
-                if (used_blocks) *used_blocks = tot;
-                err = win ? launch_conv_win(g, cfg, s) : fast ? launch_conv_fast(g, cfg, s) : launch_conv(g, dt, cfg, ops[base]->vec, s);
+                if (used_cfg && plan.small) *used_cfg = SMALL_128x32;
+                if (used_blocks) *used_blocks = plan.small ? small.total_tiles : g.total_tiles;
+                err = plan.small ? launch_sconv(small, small_lds, s) : plan.win ? launch_conv_win(g, plan.cfg, s)
+                      : plan.fast ? launch_conv_fast(g, plan.cfg, s) : launch_conv(g, dt, plan.cfg, ops[base]->vec, s);
+                if (err == hipSuccess && ts.nprob) err = launch_tile_stats(ts, s);
                 if (err == hipSuccess && sg.nprob) err = launch_bn_stats(sg, dt, s);
             } break;
             case OP_FCONV: {
@@ -3199,18 +3294,10 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
         std::vector<const Op*> ops;
         for (const Op& o : st) if (ops.empty() || o.key() == ops[0]->key()) ops.push_back(&o);
         if (ops.empty() || ops.size() > (size_t)kMaxGroup) continue;
-        bool win, fast;
-        const int cfg = conv_launch_cfg(&net, ops.data(), (int)ops.size(), win, fast);
-        if (!fast) continue;
-        const CfgInfo ci = win ? conv_win_cfg_info(cfg) : conv_fast_cfg_info(cfg);
-        ConvGroup g; g.nprob = (int)ops.size(); g.total_tiles = 0;
-        for (int i = 0; i < g.nprob; ++i) {
-            ConvProb& p = g.p[i]; p = ops[i]->conv;
-            p.tiles_m = (p.M + ci.BM - 1) / ci.BM; p.tiles_n = (p.Ncol + ci.BN - 1) / ci.BN;
-            p.tile_start = g.total_tiles; g.total_tiles += p.tiles_m * p.tiles_n;
-        }
+        ConvGroup g; g.nprob = (int)ops.size();
+        for (int i = 0; i < g.nprob; ++i) g.p[i] = ops[i]->conv;
         SConvGroup small; size_t lds = 0;
-        taken[2 + d] = plan_sconv(&net, g, win, ci, small, lds) ? 1 : 0;
+        taken[2 + d] = plan_conv(&net, ops.data(), g.nprob, g, small, lds).small ? 1 : 0;
     }
     return LP_OK;
 }

@@ -1,8 +1,12 @@
 // bf16 implicit-GEMM convolution (forward / data-gradient) for the wide layers on gfx950.
 //
-// Each wave owns a 64-pixel x 160-channel output tile (2 x 5 micro-tiles of v_mfma_f32_32x32x16_bf16, 160 fp32
-// accumulators); a block is WGM x WGN waves: eight (512x160 or 256x320 tiles), or four (128x320) or two (128x160)
-// for launches that would otherwise have fewer tiles than the chip has CUs.  What was measured on the
+// Each wave owns FM x FN micro-tiles of v_mfma_f32_32x32x16_bf16.  The large tiles: 64 pixels x 160 channels a wave (160 fp32
+// accumulators), a block of WGM x WGN waves: eight (512x160 or 256x320 tiles), or four (128x320) or two (128x160)
+// for launches that would otherwise have fewer tiles than the chip has CUs.  The others: 32 pixels x 64 (or 32) channels a wave,
+// four or eight waves, 48-96 KB of LDS, so that two or three workgroups share a CU and one's prologue and epilogue run beside
+// another's products; their widths are the powers of two that 160 and 320 fill by four fifths (128, 256, 512, 1024 channels).
+// Every variant of a k-tile length adds up an output element in the same order (slab by slab of BK channels, tap by tap): same
+// bits, apart from the batch statistics' partial sums.  What was measured on the
 // machine and shaped this kernel:
 //  * an MFMA loop fed from LDS is bound by LDS bandwidth (about 128 B/clk/CU), so the wave tile is as large
 //    as the register file allows at two waves per SIMD;
@@ -61,9 +65,9 @@ __device__ __forceinline__ void wait_vmcnt_rt(int n) {
 
 }  // namespace
 
-template <int WGM, int WGN, int STAGES, int BK>
+template <int WGM, int WGN, int STAGES, int BK, int FM, int FN>
 __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const ConvGroup g) {
-    constexpr int MT = 32, FM = 2, FN = 5, NW = WGM * WGN, NT = NW * 64;
+    constexpr int MT = 32, NW = WGM * WGN, NT = NW * 64;
     static_assert(NW == 8 || NW == 4 || NW == 2, "eight waves (two per SIMD), four or two");
     static_assert(BK == 32 || BK == 64, "k-tile of 32 or 64 channels");
     constexpr int TM = FM * MT, TN = FN * MT, BM = WGM * TM, BN = WGN * TN;
@@ -75,7 +79,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
     constexpr int NSA = BM / RPS / NW;                // slabs of A per wave
     constexpr int NSBT = BN / RPS;                    // slabs of B in total
     constexpr int NSB = (NSBT + NW - 1) / NW;         // per wave (the last one may be absent)
-    constexpr int EP_PITCH = 336, EP_WAVE = 32 * EP_PITCH;
+    // epilogue staging: the large tiles stage 32 rows of a wave at a time and sum the statistics on the way out; the others keep
+    // the whole tile, from which the statistics are summed afterwards
+    constexpr bool WHOLE = FN != 5;
+    constexpr int EP_PITCH = TN * 2 + 16, EP_WAVE = (WHOLE ? TM : 32) * EP_PITCH;
+    constexpr int CGN = TN / 8, PLN = 64 / CGN;       // epilogue: 16-byte channel groups of a pixel, pixels a wave handles at once
     constexpr int EP_BYTES = NW * EP_WAVE;            // epilogue staging, over the dead operand area
     constexpr int OP_BYTES = STAGES * STAGE_BYTES > EP_BYTES ? STAGES * STAGE_BYTES : EP_BYTES;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -210,7 +218,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
         int st = 0;                      // ring stage of tile kt
         constexpr int NL = NSA + NSB;    // wave-loads per k-tile
         constexpr int NSLOT = KS * FN;   // MFMA pairs of a k-tile = places to issue a load
-        constexpr int PER = (NL + 2 * FN - 1) / (2 * FN);      // loads per place: the tile is issued within 2*FN places
+        constexpr int PLACES = KS > 1 ? 2 * FN : FN;           // the tile is issued within this many places
+        constexpr int PER = (NL + PLACES - 1) / PLACES;        // loads per place
         static_assert(NL <= PER * NSLOT, "more loads than places");
         t_live = false;                  // nothing pending before the first barrier of the loop
         for (int kt = 0; kt < nk; ++kt) {
@@ -259,14 +268,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
     bf16_t* __restrict__ out = reinterpret_cast<bf16_t*>(P.out);
     const bf16_t* __restrict__ add0 = reinterpret_cast<const bf16_t*>(P.add0);
     const bf16_t* __restrict__ add1 = reinterpret_cast<const bf16_t*>(P.add1);
-    unsigned char* E = smem + wave * EP_WAVE;            // staging over the (dead) operand area; the host sizes LDS for it
-    const int cg = lane % 20, pl = lane / 20;           // read-back: 16-byte channel group, pixel lane (pl == 3: idle)
+    unsigned char* E0 = smem + wave * EP_WAVE;           // staging over the (dead) operand area; the host sizes LDS for it
+    const int cg = lane % CGN, pl = lane / CGN;         // read-back: 16-byte channel group, pixel lane (pl == PLN: idle)
     const int colg = n0 + wn * TN + cg * 8;
     float s1[8], s2[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) { s1[e] = 0.f; s2[e] = 0.f; }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
+        unsigned char* const E = WHOLE ? E0 + i * (32 * EP_PITCH) : E0;
         const int prow = wm * TM + i * MT;              // first tile row of this pixel group
         // Addends (skip connections of the data-gradient) come in the way the result goes out: the 32 x 160 piece of the
         // addend tensor is copied into the staging area with 16-byte accesses along the channels, and every lane then
@@ -276,25 +286,25 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
         for (int which = 0; which < 2; ++which) {
             const bf16_t* __restrict__ ap = which == 0 ? add0 : add1;
             if (!ap) continue;
-            constexpr int NLD = (MT + 2) / 3;           // rows per pixel lane
+            constexpr int NLD = (MT + PLN - 1) / PLN;   // rows per pixel lane
             u32x4 araw[NLD];
 #pragma unroll
             for (int t = 0; t < NLD; ++t) {             // all loads first, unconditional (a row that is not there reads element 0)
-                const int p = pl + 3 * t;
+                const int p = pl + PLN * t;
                 const int ro = s_rowoff[prow + (p < MT ? p : MT - 1)];
-                const bool ok = pl < 3 && p < MT && ro >= 0 && colg < P.Ncol;
+                const bool ok = pl < PLN && p < MT && ro >= 0 && colg < P.Ncol;
                 araw[t] = *reinterpret_cast<const u32x4*>(ap + (ok ? (size_t)ro + colg : (size_t)0));
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < NLD; ++t) {
-                const int p = pl + 3 * t;
+                const int p = pl + PLN * t;
                 const int ro = s_rowoff[prow + (p < MT ? p : MT - 1)];
                 const bool ok = ro >= 0 && colg < P.Ncol;
                 u32x4 q = araw[t];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) q[e] = ok ? q[e] : 0u;
-                if (pl < 3 && p < MT) *reinterpret_cast<u32x4*>(E + p * EP_PITCH + cg * 16) = q;
+                if (pl < PLN && p < MT) *reinterpret_cast<u32x4*>(E + p * EP_PITCH + cg * 16) = q;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_s_waitcnt(0xc07f);         // lgkmcnt(0): the piece is in LDS
@@ -325,12 +335,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
             }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0): this wave's LDS writes are done
-        if (pl < 3) {
-            for (int p = pl; p < MT; p += 3) {
+        if (pl < PLN) {
+            for (int p = pl; p < MT; p += PLN) {
                 const u32x4 q = *reinterpret_cast<const u32x4*>(E + p * EP_PITCH + cg * 16);
                 const int ro = s_rowoff[prow + p];
                 if (ro >= 0) {
                     if (colg < P.Ncol) *reinterpret_cast<u32x4*>(out + (size_t)ro + colg) = q;
+                    if constexpr (!WHOLE)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float lo = __uint_as_float(q[e] << 16), hi = __uint_as_float(q[e] & 0xffff0000u);
@@ -343,14 +354,53 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_s_waitcnt(0xc07f);             // reads done before the next group overwrites the staging area
     }
-    if (P.stats) {
+    if constexpr (WHOLE) {
+        // The sums of the large tiles of BM rows, in their order: 64 rows at a time as three runs of every third row, first the
+        // upper 32 and then the lower 32 rows, the runs one after the other (rows beyond M are zeros).
+        if (P.stats) {
+            constexpr int NR = BM / 64;
+            static_assert(EP_BYTES + NR * 3 * BN * 8 <= OP_BYTES, "partial sums behind the staged tile");
+            float* const red = reinterpret_cast<float*>(smem + EP_BYTES);   // [64-row group][run][BN][2]
+            __syncthreads();                            // the tile is staged
+            for (int it = tid; it < BN / 4 * NR * 3; it += NT) {
+                const int c = it % (BN / 4) * 4, u = it / (BN / 4), q = u % 3, w = u / 3, wnc = c / TN;
+                float a1[4] = {0.f, 0.f, 0.f, 0.f}, a2[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r0 = w * 64 + i * 32;
+                    const unsigned char* const T = smem + ((r0 / TM) * WGN + wnc) * EP_WAVE + (r0 % TM) * EP_PITCH + (c - wnc * TN) * 2;
+                    for (int p = q; p < 32; p += 3) {
+                        const uint2 v = *reinterpret_cast<const uint2*>(T + p * EP_PITCH);
+                        const float x[4] = {__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                                            __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { a1[e] += x[e]; a2[e] = fmaf(x[e], x[e], a2[e]); }
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { red[(u * BN + c + e) * 2] = a1[e]; red[(u * BN + c + e) * 2 + 1] = a2[e]; }
+            }
+            __syncthreads();
+            for (int c = tid; c < BN; c += NT) {
+                const int col = n0 + c;
+                if (col < P.Ncol) {
+                    float a1 = 0.f, a2 = 0.f;
+#pragma unroll
+                    for (int u = 0; u < NR * 3; ++u) { a1 += red[(u * BN + c) * 2]; a2 += red[(u * BN + c) * 2 + 1]; }
+                    double* st = P.stats + (size_t)(blockIdx.x % stat_stripes(P.Ncol)) * 2 * P.Ncol;      // this workgroup's stripe
+                    atomicAdd(&st[col], (double)a1);
+                    atomicAdd(&st[P.Ncol + col], (double)a2);
+                }
+            }
+        }
+    } else if (P.stats) {
         __syncthreads();                                // every wave is done with its staging area
-        float* red = reinterpret_cast<float*>(smem);    // [wave][pl][160][2]
-        if (pl < 3) {
+        float* red = reinterpret_cast<float*>(smem);    // [wave][pl][TN][2]
+        if (pl < PLN) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                red[(((wave * 3 + pl) * TN) + cg * 8 + e) * 2 + 0] = s1[e];
-                red[(((wave * 3 + pl) * TN) + cg * 8 + e) * 2 + 1] = s2[e];
+                red[(((wave * PLN + pl) * TN) + cg * 8 + e) * 2 + 0] = s1[e];
+                red[(((wave * PLN + pl) * TN) + cg * 8 + e) * 2 + 1] = s2[e];
             }
         }
         __syncthreads();
@@ -362,8 +412,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
 #pragma unroll
                 for (int w = 0; w < WGM; ++w)
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        const int idx = ((((w * WGN + wn_c) * 3 + q) * TN) + cc) * 2;
+                    for (int q = 0; q < PLN; ++q) {
+                        const int idx = ((((w * WGN + wn_c) * PLN + q) * TN) + cc) * 2;
                         a1 += red[idx]; a2 += red[idx + 1];
                     }
                 double* st = P.stats + (size_t)(blockIdx.x % stat_stripes(P.Ncol)) * 2 * P.Ncol;      // this workgroup's stripe
@@ -376,13 +426,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void conv_igemm_fast_kernel(const C
 
 namespace {
 
-template <int WGM, int WGN, int STAGES, int BK>
+template <int WGM, int WGN, int STAGES, int BK, int FM = 2, int FN = 5>
 hipError_t fast_launch(const ConvGroup& g, hipStream_t s) {
-    constexpr int BM = WGM * 64, BN = WGN * 160;
-    const size_t operands = std::max((size_t)STAGES * (BM + BN) * BK * 2, (size_t)WGM * WGN * 32 * 336);   // ring / epilogue staging
+    constexpr int BM = WGM * FM * 32, BN = WGN * FN * 32;
+    const size_t operands = std::max((size_t)STAGES * (BM + BN) * BK * 2, (size_t)WGM * WGN * (FN != 5 ? FM * 32 : 32) * (FN * 64 + 16));   // ring / epilogue staging
     const size_t lds = operands + BM * sizeof(int);
     static_assert((size_t)STAGES * (BM + BN) * BK * 2 + BM * sizeof(int) <= 160 * 1024, "LDS budget");
-    auto kern = conv_igemm_fast_kernel<WGM, WGN, STAGES, BK>;
+    auto kern = conv_igemm_fast_kernel<WGM, WGN, STAGES, BK, FM, FN>;
     static OncePerDevice configured;
     if (const hipError_t e = raise_lds_limit(configured, {(const void*)kern}, 160 * 1024); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(g.total_tiles), dim3(WGM * WGN * 64), lds, s, g);
@@ -401,6 +451,14 @@ CfgInfo conv_fast_cfg_info(int cfg) {
         case FAST64_128x160: return {128, 160, 64};
         case FAST_256x160: return {256, 160, 32};
         case FAST64_256x160: return {256, 160, 64};
+        case MID_256x128_R3: return {256, 128, 64};
+        case MID_256x64_R3: return {256, 64, 64};
+        case MID_256x32_R4: return {256, 32, 64};
+        case MID_128x128: case MID_128x128_R3: return {128, 128, 64};
+        case MID_128x64: case MID_128x64_R3: return {128, 64, 64};
+        case MID_128x32_R4: return {128, 32, 64};
+        case MID_64x128_R3: return {64, 128, 64};
+        case MID_64x64_R4: return {64, 64, 64};
         default: return {256, 320, 32};
     }
 }
@@ -417,6 +475,16 @@ hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s) {
         case FAST64_128x160: return fast_launch<2, 1, 2, 64>(g, s);
         case FAST_256x160: return fast_launch<4, 1, 4, 32>(g, s);
         case FAST64_256x160: return fast_launch<4, 1, 2, 64>(g, s);
+        case MID_256x128_R3: return fast_launch<4, 2, 3, 64, 2, 2>(g, s);
+        case MID_256x64_R3: return fast_launch<8, 1, 3, 64, 1, 2>(g, s);
+        case MID_256x32_R4: return fast_launch<8, 1, 4, 64, 1, 1>(g, s);
+        case MID_128x128: return fast_launch<4, 2, 2, 64, 1, 2>(g, s);
+        case MID_128x128_R3: return fast_launch<4, 2, 3, 64, 1, 2>(g, s);
+        case MID_128x64: return fast_launch<4, 1, 2, 64, 1, 2>(g, s);
+        case MID_128x64_R3: return fast_launch<4, 1, 3, 64, 1, 2>(g, s);
+        case MID_128x32_R4: return fast_launch<4, 1, 4, 64, 1, 1>(g, s);
+        case MID_64x128_R3: return fast_launch<2, 2, 3, 64, 1, 2>(g, s);
+        case MID_64x64_R4: return fast_launch<2, 2, 4, 64, 1, 1>(g, s);
         default: return hipErrorInvalidValue;
     }
 }
