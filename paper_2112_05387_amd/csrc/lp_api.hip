@@ -1608,17 +1608,17 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
     }
 }
 
-// Pieces of a grouped launch of the wide-layer filter-gradient kernel (lp_wgsplit.h).  The gradients were zeroed at the start
-// of the backward pass and are accumulated atomically, so the split may differ from launch to launch.
-static void plan_wgrad_fast_splits(WgradGroup& g) {
+// Pieces of a grouped launch of the wide-layer filter-gradient kernels (lp_wgsplit.h), in units of `unit` pixels.  The gradients
+// were zeroed at the start of the backward pass and are accumulated atomically, so the split may differ from launch to launch.
+static void plan_wgrad_splits(WgradGroup& g, int unit, const SplitCost& cost, int min_chunk) {
     SplitPart part[kMaxGroup];
-    for (int i = 0; i < g.nprob; ++i) part[i] = {g.p[i].tiles_m * g.p[i].tiles_n, (g.p[i].M + 31) / 32, 1};
-    int rest_split = 1, rest = plan_wgrad_pieces(part, g.nprob, rest_split);
+    for (int i = 0; i < g.nprob; ++i) part[i] = {g.p[i].tiles_m * g.p[i].tiles_n, (g.p[i].M + unit - 1) / unit, 1};
+    int rest_split = 1, rest = plan_wgrad_pieces(part, g.nprob, rest_split, cost, min_chunk);
     if (g.nprob == kMaxGroup) rest = 0;
-    auto set = [](WgradProb& p, int tile0, int ntile, int ks) {
-        const int kt = (p.M + 31) / 32;
+    auto set = [unit](WgradProb& p, int tile0, int ntile, int ks) {
+        const int kt = (p.M + unit - 1) / unit;
         p.tile0 = tile0; p.ntile = ntile;
-        p.kchunk = (kt + ks - 1) / ks * 32;          // equal chunks
+        p.kchunk = (kt + ks - 1) / ks * unit;        // equal chunks
         p.ksplit = (p.M + p.kchunk - 1) / p.kchunk;
     };
     for (int i = 0; i < g.nprob; ++i) set(g.p[i], 0, part[i].tiles, part[i].ksplit);
@@ -1629,6 +1629,19 @@ static void plan_wgrad_fast_splits(WgradGroup& g) {
         set(g.p[n + 1], keep, rest, rest_split);
         ++g.nprob;
     }
+}
+
+// Does a grouped launch of the general filter-gradient kernel go to lp_wgrad_tile.hip?  bf16, whole 16-byte vectors of channels,
+// more than 32 output channels.  The fixed order and the update in the epilogue are the general kernel's.
+static bool wgrad_tile_ok(const lp_net* net, const Op* const* ops, int n) {
+    if (net->dtype != LP_BF16 || net->deterministic || net->fused_update || net->separate || !ops[0]->vec) return false;
+    if (ops[0]->cfg != CFG_N64 && ops[0]->cfg != CFG_N128 && ops[0]->cfg != CFG_N160 && ops[0]->cfg != WGRAD_FAST) return false;
+    for (int i = 0; i < n; ++i) {
+        const WgradProb& p = ops[i]->wg;
+        if (ops[0]->cfg == WGRAD_FAST && (double)p.Cout * p.Cin >= 0.7 * 25600.0 * p.tiles_m * (p.tiles_n / 3)) return false;
+        if ((double)p.M * p.Cout * 2.0 >= 2.0e9 || (double)p.M / ((double)p.Ho * p.Wo) * p.IH * p.IW * p.Cin * 2.0 >= 2.0e9) return false;
+    }
+    return true;
 }
 
 // A launch of the wide-layer kernels as a launch of lp_sconv.hip, if that is the faster one: `g` holds the launch as it would
@@ -2040,12 +2053,23 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         if (b.master && b.master[k]) p.master = (float*)((char*)b.master[k] + o.r[2].off);
                     }
                 }
-                if (ops[base]->cfg == WGRAD_FAST && !net->deterministic) plan_wgrad_fast_splits(g);
+                const bool tile = wgrad_tile_ok(net, &ops[base], n);
+                const int rows = wgrad_tile_rows(g.p[0].Cout);       // (one for the launch: operations of a group have the same cfg)
+                if (tile) {
+                    if (used_cfg) *used_cfg = WGRAD_TILE;
+                    for (int i = 0; i < n; ++i) {
+                        WgradProb& p = g.p[i];
+                        p.tiles_m = (p.Cout + rows - 1) / rows; p.tiles_n = (p.Kg + 127) / 128;
+                        fastdiv_make((unsigned)p.Wo, &p.mulW, &p.shW);
+                        fastdiv_make((unsigned)p.Ho, &p.mulH, &p.shH);
+                    }
+                    plan_wgrad_splits(g, 64, kTileCost, 4);
+                } else if (ops[base]->cfg == WGRAD_FAST && !net->deterministic) plan_wgrad_splits(g, 32, kFastCost, 16);
                 for (int i = 0; i < g.nprob; ++i) { g.p[i].tile_start = tot; tot += g.p[i].ntile * g.p[i].ksplit; }
                 g.total_tiles = tot;
                 g.lr = net->fu_lr; g.momentum = net->fu_momentum; g.wd = net->fu_wd; g.lowp = dt == LP_BF16;
                 if (used_blocks) *used_blocks = tot;
-                err = ops[base]->cfg == WGRAD_FAST ? launch_wgrad_fast(g, s) : launch_wgrad(g, dt, ops[base]->cfg, ops[base]->vec, s);
+                err = tile ? launch_wgrad_tile(g, rows, s) : ops[base]->cfg == WGRAD_FAST ? launch_wgrad_fast(g, s) : launch_wgrad(g, dt, ops[base]->cfg, ops[base]->vec, s);
             } break;
             case OP_BN_APPLY: {
                 BnApplyGroup g; g.nprob = n; g.eps = net->eps; g.cmax = 0; int tot = 0;

@@ -126,8 +126,8 @@ struct WgradProb {
     int Ho, Wo, IH, IW, stride, pad, R, S;
     int ksplit, kchunk;
     int tiles_m, tiles_n, tile_start;
-    int tile0, ntile;                // wide-layer kernel: the output tiles this entry is about (tiles_m * tiles_n of them in one or two entries)
-    unsigned mulW, shW, mulH, shH;   // fast division by IW and IH (wide-layer kernel)
+    int tile0, ntile;                // wide-layer kernels: the output tiles this entry is about (tiles_m * tiles_n of them in one or two entries)
+    unsigned mulW, shW, mulH, shH;   // fast division by IW and IH (lp_wgrad_tile.hip: by Wo and Ho)
     // parameter update in the epilogue (w != NULL): the workgroup that adds the LAST partial sum of an output tile
     // (ticket from cnt[tile], zero before the launch) reads the finished gradient tile back and updates the filter
     void* w;                         // the filter itself, storage type of the activations, layout of dw
@@ -266,7 +266,8 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                MID_256x128_R3 = 28, MID_256x64_R3 = 29, MID_256x32_R4 = 30,
                WIN64_512x160 = 21, WIN64_256x320 = 23,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
                SMALL_128x32 = 24,                      // bf16 wide layers on few pixels, recorded only (lp_sconv.hip)
-               WGRAD_FAST = 8 };                       // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
+               WGRAD_FAST = 8,                         // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
+               WGRAD_TILE = 9 };                       // ... of the other wide layers, recorded only (lp_wgrad_tile.hip)
 struct CfgInfo { int BM, BN, BK; };
 CfgInfo conv_cfg_info(int cfg, int dtype);
 CfgInfo wgrad_cfg_info(int cfg, int dtype);
@@ -291,6 +292,8 @@ hipError_t launch_tile_stats(const TileStatsGroup& g, hipStream_t s);
 hipError_t launch_fconv(const FConvGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_fwgrad(const FWgradGroup& g, int dtype, size_t lds, hipStream_t s);
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
+int wgrad_tile_rows(int Cout);                             // output channels of a tile of the kernel below: 64 or 128, by 128 columns
+hipError_t launch_wgrad_tile(const WgradGroup& g, int rows, hipStream_t s);
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
 hipError_t launch_wgrad(const WgradGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_wtrans(const WtransGroup& g, int dtype, hipStream_t s);

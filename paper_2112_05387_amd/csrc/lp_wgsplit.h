@@ -34,25 +34,28 @@ LP_WG_HD bool xcd_piece(int block, int nprob, Count count, int& prob, int& local
     return false;
 }
 
-// One problem of the plan: `tiles` output tiles of `kt` k-tiles (32 pixels) each, every one cut into `ksplit` pieces.
+// One problem of the plan: `tiles` output tiles of `kt` units each, every one cut into `ksplit` pieces.
 struct SplitPart { int tiles, kt, ksplit; };
 
-// Time of a launch in k-tiles (0.9 us each): a workgroup has a compute unit to itself, and what it does besides its k-tiles is
-// worth kEpilogueAdd where partial sums are added with atomics and kEpilogueStore where its piece is the whole reduction (one
-// and two rounds of 256 and 128 k-tiles: 251 us with stores, 282 with atomics, 337 with atomics and half the length).
-constexpr int kWgradCUs = 256, kEpilogueAdd = 52, kEpilogueStore = 16;
-inline double wgrad_round(int chunk, bool whole) { return chunk + (whole ? kEpilogueStore : kEpilogueAdd); }
+// Time of a launch in units of the reduction: `slots` workgroups run at once, and what one does besides its units is worth `add`
+// of them where partial sums are added with atomics and `store` where its piece is the whole reduction.
+struct SplitCost { int slots, add, store; double round(int chunk, bool whole) const { return chunk + (whole ? store : add); } };
+// lp_wgrad_fast.hip: units of 32 pixels (0.9 us each), a workgroup has a compute unit to itself (8192 pixels x 640 channels, five
+// layers, one and two rounds of 256 and 128 units: 251 us with stores, 282 with atomics, 337 with atomics and half the length).
+constexpr SplitCost kFastCost = {256, 52, 16};
+// lp_wgrad_tile.hip: units of 64 pixels (1 us each with two workgroups on a compute unit), 64 KB of atomics a workgroup.
+constexpr SplitCost kTileCost = {512, 26, 6};
 
 // Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
 // are the pieces and the last round would be nearly empty (288 tiles), the tiles of that round -- the last `rest` of the last
 // problem -- are cut finer, so that one more, short round holds them.  Returns rest (0: nothing more to cut), cuts in
 // `rest_split`.
-inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split) {
-    int max_kt = 1, best_chunk = 16, rest = 0;
+inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split, const SplitCost& c = kFastCost, int min_chunk = 16) {
+    int max_kt = 1, best_chunk = min_chunk, rest = 0;
     double best = 1e300;
     for (int i = 0; i < n; ++i) max_kt = p[i].kt > max_kt ? p[i].kt : max_kt;
     rest_split = 1;
-    for (int chunk = 16; chunk <= (max_kt > 16 ? max_kt : 16); ++chunk) {
+    for (int chunk = min_chunk; chunk <= (max_kt > min_chunk ? max_kt : min_chunk); ++chunk) {
         long blocks = 0;
         bool whole = true;
         for (int i = 0; i < n; ++i) {
@@ -60,12 +63,12 @@ inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split) {
             blocks += (long)p[i].tiles * ks;
             whole = whole && ks == 1;
         }
-        const double cost = (double)((blocks + kWgradCUs - 1) / kWgradCUs) * wgrad_round(chunk, whole);
+        const double cost = (double)((blocks + c.slots - 1) / c.slots) * c.round(chunk, whole);
         if (cost < best) { best = cost; best_chunk = chunk; rest = 0; }
-        const int over = (int)(blocks % kWgradCUs), s = over ? kWgradCUs / over : 1;
+        const int over = (int)(blocks % c.slots), s = over ? c.slots / over : 1;
         const SplitPart& q = p[n - 1];
-        if (!whole || blocks < kWgradCUs || s < 2 || over >= q.tiles || q.kt / s < 8) continue;
-        const double two = (double)(blocks / kWgradCUs) * wgrad_round(chunk, true) + wgrad_round((q.kt + s - 1) / s, false);
+        if (!whole || blocks < c.slots || s < 2 || over >= q.tiles || q.kt / s < 8) continue;
+        const double two = (double)(blocks / c.slots) * c.round(chunk, true) + c.round((q.kt + s - 1) / s, false);
         if (two < best) { best = two; best_chunk = chunk; rest = over; rest_split = s; }
     }
     for (int i = 0; i < n; ++i) p[i].ksplit = (p[i].kt + best_chunk - 1) / best_chunk;
