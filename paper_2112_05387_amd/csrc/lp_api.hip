@@ -2053,6 +2053,19 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         if (b.master && b.master[k]) p.master = (float*)((char*)b.master[k] + o.r[2].off);
                     }
                 }
+                bool stem = dt == LP_BF16 && !net->deterministic && !net->fused_update && !net->separate;
+                for (int i = 0; i < n; ++i) stem = stem && wgrad_stem_ok(g.p[i]) && g.p[i].Cout == g.p[0].Cout && (uintptr_t)g.p[i].x % 4 == 0;
+                if (stem) {                        // consecutive output rows; 160 workgroups do as much as the atomics of more would cost
+                    if (used_cfg) *used_cfg = WGRAD_STEM;
+                    long units = 0;
+                    for (int i = 0; i < n; ++i) units += g.p[i].M / g.p[i].Wo;
+                    const int per = (int)std::max(4l, (units + 159) / 160);
+                    for (int i = 0; i < n; ++i) { g.p[i].kchunk = per; g.p[i].tile_start = tot; tot += (g.p[i].M / g.p[i].Wo + per - 1) / per; }
+                    g.total_tiles = tot;
+                    if (used_blocks) *used_blocks = tot;
+                    err = launch_wgrad_stem(g, s);
+                    break;
+                }
                 const bool tile = wgrad_tile_ok(net, &ops[base], n);
                 const int rows = wgrad_tile_rows(g.p[0].Cout);       // (one for the launch: operations of a group have the same cfg)
                 if (tile) {

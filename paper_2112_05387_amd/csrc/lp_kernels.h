@@ -267,7 +267,8 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                WIN64_512x160 = 21, WIN64_256x320 = 23,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
                SMALL_128x32 = 24,                      // bf16 wide layers on few pixels, recorded only (lp_sconv.hip)
                WGRAD_FAST = 8,                         // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
-               WGRAD_TILE = 9 };                       // ... of the other wide layers, recorded only (lp_wgrad_tile.hip)
+               WGRAD_TILE = 9,                         // ... of the other wide layers, recorded only (lp_wgrad_tile.hip)
+               WGRAD_STEM = 10 };                      // ... of an image-facing layer, recorded only (lp_wgrad_stem.hip)
 struct CfgInfo { int BM, BN, BK; };
 CfgInfo conv_cfg_info(int cfg, int dtype);
 CfgInfo wgrad_cfg_info(int cfg, int dtype);
@@ -294,6 +295,8 @@ hipError_t launch_fwgrad(const FWgradGroup& g, int dtype, size_t lds, hipStream_
 hipError_t launch_wgrad_fast(const WgradGroup& g, hipStream_t s);
 int wgrad_tile_rows(int Cout);                             // output channels of a tile of the kernel below: 64 or 128, by 128 columns
 hipError_t launch_wgrad_tile(const WgradGroup& g, int rows, hipStream_t s);
+bool wgrad_stem_ok(const WgradProb& p);                    // the layers of the image-facing kernel; the image aligned to four bytes as well
+hipError_t launch_wgrad_stem(const WgradGroup& g, hipStream_t s);     // kchunk: output rows of a workgroup; tile_start, total_tiles
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
 hipError_t launch_wgrad(const WgradGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_wtrans(const WtransGroup& g, int dtype, hipStream_t s);
