@@ -25,8 +25,8 @@ namespace lp {
 namespace {
 
 constexpr int FC_NT = 256;
-constexpr int FC_COEF = 0;                         // 5 x 64 floats: transform coefficients
-constexpr int FC_ECOEF = 5 * 64 * 4;               // 6 x 32 floats: sc, sh, mean, invstd of ey; mean, invstd of ey2
+constexpr int FC_COEF = 0;                         // 6 x 64 floats: transform coefficients
+constexpr int FC_ECOEF = 6 * 64 * 4;               // 6 x 32 floats: sc, sh, mean, invstd of ey; mean, invstd of ey2
 constexpr int FC_FILT = FC_ECOEF + 6 * 32 * 4;     // filter fragments of the tile; behind the contraction: 16 x BN x 4 partial sums
 // then the input window, later the result tile
 // More k-steps than the ring holds (64 channels; fp32 with 32): its halves of fconv_half(BN) steps are refilled as they are
@@ -195,40 +195,52 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
         }
         if (!side) owned = 0;
     };
+    // A wave each for the sums of a batch norm: their loads go out ahead of the window's (a wave's loads return in order), all
+    // stripes at once, and no sum waits for another.
+    const double* const sums_of = wave == 0 ? (mode != FX_PLAIN ? P.stats : nullptr) : wave == 1 ? (mode == FX_BN_BN || mode == FX_BWD ? P.stats2 : nullptr)
+                                  : wave == 2 ? (P.ey ? P.estats : nullptr) : (P.ey2 ? P.estats2 : nullptr);
+    const int sc_C = wave < 2 ? Cin : P.Ncol, sc_c = wave < 2 ? lane : n0 + lane;
+    const bool sum_lane = sums_of && lane < (wave < 2 ? Cin : BN);
+    StripeLoads sl;
+    float ga = 1.f, be = 0.f;
+    if (sum_lane) {
+        sl.load(sums_of, sc_c, sc_C);
+        if (wave != 1 || mode != FX_BWD) {
+            const float* const gp = wave == 0 ? P.gamma : wave == 1 ? P.gamma2 : P.egamma;
+            const float* const bp = wave == 0 ? P.beta : wave == 1 ? P.beta2 : P.ebeta;
+            ga = gp[sc_c]; be = bp[sc_c];
+        }
+    }
     if (S > 0) request(0);
     // forward: value = (c0*a + c1) + (c2*b + c3), whatever the mode: c = (1, 0) for a tensor taken as it is, (0, 0) for none
     if (wave == 0 && lane < Cin) {
-        const int Mi = P.nimg * IH * IW;
-        float sc = 1.f, sh = 0.f, mu, is;
-        if (mode != FX_PLAIN) bn_coeffs(P.stats, P.gamma, P.beta, lane, Cin, Mi, eps, sc, sh, mu, is);
+        float sc = 1.f, sh = 0.f, mu = 0.f, is = 1.f;
+        if (mode != FX_PLAIN) bn_coeffs(sl, ga, be, P.nimg * IH * IW, eps, sc, sh, mu, is);
         s_cf[lane] = sc; s_cf[64 + lane] = sh;
+        if (mode == FX_BWD) { s_cf[128 + lane] = is; s_cf[192 + lane] = mu; }
+    }
+    if (wave == 1 && lane < Cin) {
         if (mode == FX_BWD) {
-            const double inv_m = 1.0 / (double)Mi;
+            const double inv_m = 1.0 / (double)(P.nimg * IH * IW);
             double rs0, rs1;
-            stripe_sums(P.stats2, lane, Cin, rs0, rs1);
-            const float k1 = sc;
-            const float k2 = k1 * is * (float)(rs1 * inv_m);
-            s_cf[128 + lane] = k1; s_cf[192 + lane] = k2; s_cf[256 + lane] = fmaf(k2, mu, -(k1 * (float)(rs0 * inv_m)));
+            sl.sums(rs0, rs1);
+            s_cf[256 + lane] = (float)(rs1 * inv_m); s_cf[320 + lane] = (float)(rs0 * inv_m);
             if (t == 0 && P.side) {
                 const_cast<float*>(P.gamma2)[lane] = (float)rs1;
                 const_cast<float*>(P.beta2)[lane] = (float)rs0;
             }
+        } else {
+            float sc = mode == FX_BN_ADD ? 1.f : 0.f, sh = 0.f, mu, is;
+            if (mode == FX_BN_BN) bn_coeffs(sl, ga, be, P.nimg * IH * IW, eps, sc, sh, mu, is);
+            s_cf[128 + lane] = sc; s_cf[192 + lane] = sh;
         }
     }
-    if (wave == 1 && lane < Cin && mode != FX_BWD) {
-        float sc = mode == FX_BN_ADD ? 1.f : 0.f, sh = 0.f, mu, is;
-        if (mode == FX_BN_BN) bn_coeffs(P.stats2, P.gamma2, P.beta2, lane, Cin, P.nimg * IH * IW, eps, sc, sh, mu, is);
-        s_cf[128 + lane] = sc; s_cf[192 + lane] = sh;
-    }
-    if (wave == 2 && lane < BN && P.ey) {
+    if (wave >= 2 && sum_lane) {                   // of a projection's batch norm (wave 3): no ReLU behind it, scale and shift are not needed
         float sc, sh, mu, is;
-        bn_coeffs(P.estats, P.egamma, P.ebeta, n0 + lane, P.Ncol, P.nimg * P.OH * P.OW, eps, sc, sh, mu, is);
-        s_ec[lane] = sc; s_ec[32 + lane] = sh; s_ec[64 + lane] = mu; s_ec[96 + lane] = is;
-    }
-    if (wave == 3 && lane < BN && P.ey2) {         // a projection's batch norm: no ReLU behind it, scale and shift are not needed
-        float sc, sh, mu, is;
-        bn_coeffs(P.estats2, P.egamma, P.ebeta, n0 + lane, P.Ncol, P.nimg * P.OH * P.OW, eps, sc, sh, mu, is);
-        s_ec[128 + lane] = mu; s_ec[160 + lane] = is;
+        bn_coeffs(sl, ga, be, P.nimg * P.OH * P.OW, eps, sc, sh, mu, is);
+        float* const o = wave == 2 ? s_ec + 64 : s_ec + 128;
+        if (wave == 2) { s_ec[lane] = sc; s_ec[32 + lane] = sh; }
+        o[lane] = mu; o[32 + lane] = is;
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0): this wave's filter fragments are in LDS (the window is needed next anyway)
     __syncthreads();
@@ -251,7 +263,16 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
         };
         for (int i0 = 0;;) {
             if (mode == FX_BWD) {
-                coef(4, c4);
+                if (i0 == 0) {                     // k1 * g' - k2 * y + k3 from scale, 1 / sigma, mean and the means of the backward sums
+                    float f1[EPV], f0[EPV];
+                    coef(4, f1); coef(5, f0);
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) {
+                        const float k2 = c0[e] * c2[e] * f1[e];
+                        c4[e] = fmaf(k2, c3[e], -(c0[e] * f0[e]));
+                        c2[e] = c0[e]; c3[e] = k2;
+                    }
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if ((i0 + u) * wstep >= WHW) continue;

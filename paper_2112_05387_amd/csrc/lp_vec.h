@@ -66,6 +66,37 @@ __device__ __forceinline__ void stripe_sums(const double* p, int c, int C, doubl
     s1 = 0.0; s2 = 0.0;
     for (int st = 0; st < ns; ++st) { s1 += p[st * 2 * C + c]; s2 += p[st * 2 * C + C + c]; }
 }
+// the same in two parts, for loads that are to be under way before they are waited for
+struct StripeLoads {
+    double a[kStatStripes], b[kStatStripes];
+    int ns;
+    __device__ __forceinline__ void load(const double* p, int c, int C) {
+        ns = stat_stripes(C);
+#pragma unroll
+        for (int st = 0; st < kStatStripes; ++st) {
+            const int o = (st < ns ? st : 0) * 2 * C + c;
+            a[st] = p[o]; b[st] = p[o + C];
+        }
+    }
+    __device__ __forceinline__ void sums(double& s1, double& s2) const {
+        s1 = a[0]; s2 = b[0];
+#pragma unroll
+        for (int st = 1; st < kStatStripes; ++st)
+            if (st < ns) { s1 += a[st]; s2 += b[st]; }
+    }
+};
+__device__ __forceinline__ void bn_coeffs(const StripeLoads& l, float gamma, float beta, int M, float eps, float& sc, float& sh, float& mean, float& invstd) {
+    const double inv_m = 1.0 / (double)M;
+    double s1, s2;
+    l.sums(s1, s2);
+    const double mu = s1 * inv_m;
+    double var = s2 * inv_m - mu * mu;
+    if (var < 0.0) var = 0.0;
+    mean = (float)mu;
+    invstd = rsqrtf((float)var + eps);
+    sc = gamma * invstd;
+    sh = beta - mean * sc;
+}
 __device__ __forceinline__ void bn_coeffs(const double* stats, const float* gamma, const float* beta, int c, int C,
                                           int M, float eps, float& sc, float& sh, float& mean, float& invstd) {
     const double inv_m = 1.0 / (double)M;          // the same for every channel: the compiler hoists it out of loops
