@@ -19,7 +19,7 @@ EXPORTS = ["lp_net_create", "lp_net_destroy", "lp_net_param_bytes", "lp_net_num_
            "lp_debug_module_info", "lp_debug_filter_load_extent", "lp_debug_conv_geometry", "lp_debug_conv_offsets", "lp_debug_mfma_peak", "lp_debug_layer_kernels", "lp_debug_stream_lanes", "lp_debug_separate_passes", "lp_debug_linear_kernels",
            "lp_debug_saved_tensor", "lp_net_set_fused_update", "lp_profile_enable", "lp_profile_fetch", "lp_last_error", "lp_version"]
 
-KIND_NAMES = {0: "fill", 1: "filter_relayout", 2: "conv_igemm(fwd/dgrad)", 3: "bn_apply", 4: "maxpool_fwd", 5: "head_fwd",
+KIND_NAMES = {0: "clears+filter_relayout", 1: "filter_relayout", 2: "conv_igemm(fwd/dgrad)", 3: "bn_apply", 4: "maxpool_fwd", 5: "head_fwd",
               6: "head_bwd", 7: "maxpool_bwd", 8: "bn_bwd_reduce", 9: "bn_bwd_apply", 10: "conv_wgrad", 11: "bn_stats", 12: "loss", 13: "cross_entropy", 14: "multiplier_update",
               15: "relu_mask", 16: "sgd(small tensors)", 17: "conv_folded(fwd/dgrad)", 18: "conv_wgrad_narrow"}
 

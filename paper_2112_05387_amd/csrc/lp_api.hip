@@ -118,12 +118,12 @@ struct Op {
     FConvProb fc;
     WgradProb wg;
     FWgradProb fw;
-    WtransProb wt;
+    PrepProb prep;                         // OP_WTRANS: the filter's shape
     BnApplyProb bna;
     BnBwdProb bnb;
     PoolProb pool;
     HeadProb head;
-    int key() const { return type == OP_FWGRAD ? type * 64 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
+    int key() const { return type == OP_WTRANS ? OP_FILL * 64 + cfg * 2 + (vec ? 1 : 0) : type == OP_FWGRAD ? type * 64 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
 };
 typedef std::vector<Op> Step;              // operations of one module that may run concurrently
 typedef std::vector<Step> Program;         // steps run in order
@@ -516,8 +516,8 @@ struct Builder {
     }
     Op wtrans(const Unit& u, Ref w, Ref wt) const {
         Op o; o.type = OP_WTRANS;
-        memset(&o.wt, 0, sizeof(o.wt));
-        o.wt.Cout = u.cout; o.wt.RS = u.R * u.R; o.wt.Cin = u.cin;
+        memset(&o.prep, 0, sizeof(o.prep));
+        o.prep.Cout = u.cout; o.prep.RS = u.R * u.R; o.prep.Cin = u.cin;
         o.r[0] = w; o.r[1] = wt;
         return o;
     }
@@ -1016,10 +1016,7 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
         Program& Bw = variant == 0 ? m.bwd : m.bwd_dx0;
         {
             Step s{B.fill(mk(SP_WS, 0, m.ws_red0), m.ws_red_bytes), B.fill(mk(SP_DPARAM, k, 0), m.grad_bytes)};
-            Bw.push_back(s);
-        }
-        {   // filter re-layouts for every data-gradient of this pass
-            Step s;
+            // filter re-layouts for every data-gradient of this pass
             for (size_t i = 0; i < m.bp.size(); ++i) {
                 const bool need_in_grad = (i > 0) || m.has_stem || want_dx_first;
                 BlockPlan& bp = m.bp[i];
@@ -1027,7 +1024,7 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
                     if (j > 0 || need_in_grad) s.push_back(B.wtrans(bp.main[j], wref(bp.main[j]), mk(SP_WS, 0, bp.main[j].ws_wt)));
                 if (bp.has_proj && need_in_grad) s.push_back(B.wtrans(bp.proj, wref(bp.proj), mk(SP_WS, 0, bp.proj.ws_wt)));
             }
-            if (!s.empty()) Bw.push_back(s);
+            Bw.push_back(s);
         }
         Ref g;                                      // gradient with respect to the current block output
         if (last) {
@@ -1319,9 +1316,8 @@ static lp_status build_module_pre(lp_net* net, int k, WsAlloc& ws) {
     for (int variant = 0; variant < (first_block_dx_optional ? 2 : 1); ++variant) {
         const bool want_dx_first = first_block_dx_optional ? (variant == 1) : true;
         Program& Bw = variant == 0 ? m.bwd : m.bwd_dx0;
-        Bw.push_back(Step{B.fill(W_(m.ws_red0), m.ws_red_bytes), B.fill(mk(SP_DPARAM, k, 0), m.grad_bytes)});
         {
-            Step s;
+            Step s{B.fill(W_(m.ws_red0), m.ws_red_bytes), B.fill(mk(SP_DPARAM, k, 0), m.grad_bytes)};
             for (auto& bp : m.bp) {
                 for (auto& u : bp.main) s.push_back(B.wtrans(u, wref(u), W_(u.ws_wt)));
                 if (bp.has_proj) s.push_back(B.wtrans(bp.proj, wref(bp.proj), W_(bp.proj.ws_wt)));
@@ -1383,6 +1379,10 @@ static lp_status build_module_pre(lp_net* net, int k, WsAlloc& ws) {
     return LP_OK;
 }
 
+static bool is_prep(const Step& st) {
+    return std::all_of(st.begin(), st.end(), [](const Op& o) { return o.type == OP_FILL || o.type == OP_WTRANS; });
+}
+
 // the whole local step of module k as one list: forward, loss and terminal adjoint (with the multiplier update), backward
 static void build_step_programs(lp_net* net, int k) {
     ModulePlan& m = net->mods[k];
@@ -1423,8 +1423,13 @@ static void build_step_programs(lp_net* net, int k) {
             out.push_back(loss_step);
             for (Op& o : out.back()) o.phase = 1;
         }
-        for (const Step& st : bw) {
-            out.push_back(st);
+        // the clears and filter re-layouts of the backward pass go with those of the forward pass: nothing in between touches
+        // the sums, gradients, tickets and re-laid-out filters (buffers of their own), nor the parameters
+        size_t at = 0;
+        for (; at < bw.size() && is_prep(bw[at]) && is_prep(out.front()); ++at)
+            out.front().insert(out.front().end(), bw[at].begin(), bw[at].end());
+        for (; at < bw.size(); ++at) {
+            out.push_back(bw[at]);
             for (Op& o : out.back()) o.phase = 2;
         }
     }
@@ -1591,7 +1596,7 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
             const double n_out = 1.0 + (o.r[F_ADD0].space != SP_NONE) + (o.r[F_EY].space != SP_NONE) + (o.r[F_EY2].space != SP_NONE);
             bytes = (in_e * n_in + (double)p.Ncol * p.Cin * p.ntr * p.nts + out_e * n_out) * e;
         } break;
-        case OP_WTRANS: bytes = 2.0 * o.wt.Cout * o.wt.RS * o.wt.Cin * e; break;
+        case OP_WTRANS: bytes = 2.0 * o.prep.Cout * o.prep.RS * o.prep.Cin * e; break;
         case OP_FILL: bytes = (double)o.fill_bytes; break;
         case OP_BN_APPLY:      // fused with the loss / terminal adjoint: + x_next, lam, dy (the multiplier written back: + 1)
             bytes = (double)o.bna.M * o.bna.C * e * ((o.bna.skip_mode ? 3.0 : 2.0) + (o.cfg == 1 ? 3.0 : 0.0)); break;
@@ -1872,8 +1877,9 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
 
 static hipError_t launch_group(lp_net* net, std::vector<const Op*>& ops, const Bindings& b, hipStream_t s) {
     hipError_t err = hipSuccess;
-    for (size_t base = 0; base < ops.size() && err == hipSuccess; base += kMaxGroup) {
-        const int n = (int)std::min<size_t>(kMaxGroup, ops.size() - base);
+    const size_t most = ops[0]->type == OP_FILL || ops[0]->type == OP_WTRANS ? kPrepMax : kMaxGroup;
+    for (size_t base = 0; base < ops.size() && err == hipSuccess; base += most) {
+        const int n = (int)std::min<size_t>(most, ops.size() - base);
         if (ops[base]->type == OP_SGD_REST && !net->fused_update) continue;      // nothing to launch, nothing to record
         if (!net->prof) { err = launch_group_impl(net, ops, base, n, b, s, nullptr, nullptr); continue; }
         lp_net::ProfRec r;
@@ -1898,26 +1904,24 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
     hipError_t err = hipSuccess;
     {
         switch (type) {
-            case OP_FILL: {
-                FillGroup g; g.nprob = n; int tot = 0;
-                for (int i = 0; i < n; ++i) {
-                    const Op& o = *ops[base + i];
-                    g.p[i].ptr = resolve(o.r[0], b); g.p[i].bytes = o.fill_bytes; g.p[i].block_start = tot;
-                    tot += elem_blocks(o.fill_bytes / 16);
-                }
-                g.total_blocks = tot;
-                err = launch_fill(g, s);
-            } break;
+            case OP_FILL:
             case OP_WTRANS: {
-                WtransGroup g; g.nprob = n; int tot = 0;
+                PrepGroup g; g.nprob = n; int tot = 0;
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
-                    g.p[i] = o.wt;
-                    g.p[i].w = resolve(o.r[0], b); g.p[i].wt = resolve(o.r[1], b); g.p[i].block_start = tot;
-                    tot += ((o.wt.Cin + 63) / 64) * ((o.wt.Cout + 63) / 64) * o.wt.RS;
+                    PrepProb& p = g.p[i]; p = o.prep;
+                    g.start[i] = tot;
+                    if (o.type == OP_FILL) {
+                        p.src = nullptr; p.dst = resolve(o.r[0], b); p.vecs = (int)(o.fill_bytes / 16);
+                        tot += elem_blocks(o.fill_bytes / 16);
+                    } else {
+                        p.src = resolve(o.r[0], b); p.dst = resolve(o.r[1], b); p.vecs = 0;
+                        tot += ((p.Cin + 63) / 64) * ((p.Cout + 63) / 64) * p.RS;
+                    }
                 }
+                for (int i = n; i < kPrepMax; ++i) g.start[i] = INT_MAX;
                 g.total_blocks = tot;
-                err = launch_wtrans(g, dt, s);
+                err = launch_prep(g, dt, s);
             } break;
             case OP_CONV: {
                 ConvGroup g; g.nprob = n;
@@ -2771,7 +2775,7 @@ lp_status lp_auxnet_distill_grad(struct lp_net* net, void* stream, const void* i
     Bindings b; b.ws = net->ws; b.image = image; b.auxp = aux_params; b.auxg = daux_params; b.xtgt = x_target;
     st = run_programs(net, pa, b, s);
     if (st != LP_OK) return st;
-    hipError_t err = launch_zero_selected(loss, mask, net->K - 1, s);
+    hipError_t err = launch_zero_selected(loss, mask, net->K - 1, nullptr, 0u, 0, s);
     for (size_t i = 0; i < groups.size() && err == hipSuccess; ++i) err = launch_loss(groups[i], net->dtype, s);
     if (err != hipSuccess) return fail(LP_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(err));
     return run_programs(net, pb, b, s);
@@ -2868,8 +2872,7 @@ lp_status lp_local_loss_grad(struct lp_net* net, void* stream, uint32_t module_m
     }
     if (want_ce && (!logits || !labels || !dlogits)) return fail(LP_ERR_INVALID_ARG, "logits, labels or dlogits is NULL");
     // loss[k] = 0 for the selected modules (the kernels below accumulate with atomics)
-    hipError_t err = launch_zero_selected(loss, module_mask, net->K, s);
-    if (err == hipSuccess && net->r2 && net->K > 1) err = launch_zero_selected(net->r2, module_mask & ((1u << (net->K - 1)) - 1u), net->K - 1, s);
+    hipError_t err = launch_zero_selected(loss, module_mask, net->K, net->K > 1 ? net->r2 : nullptr, module_mask & ((1u << (net->K - 1)) - 1u), net->K - 1, s);
     if (err != hipSuccess) return fail(LP_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(err));
     for (int k = 0; k < net->K - 1; ++k) {
         if (!((module_mask >> k) & 1u)) continue;
@@ -2957,8 +2960,7 @@ lp_status lp_local_step(struct lp_net* net, void* stream, uint32_t module_mask, 
     }
     hipStream_t s = (hipStream_t)stream;
     // loss[k] = 0 for the selected modules, ahead of the fork (the loss kernels accumulate with atomics)
-    hipError_t err = launch_zero_selected(loss, module_mask, net->K, s);
-    if (err == hipSuccess && net->r2 && net->K > 1) err = launch_zero_selected(net->r2, module_mask & ((1u << (net->K - 1)) - 1u), net->K - 1, s);
+    hipError_t err = launch_zero_selected(loss, module_mask, net->K, net->K > 1 ? net->r2 : nullptr, module_mask & ((1u << (net->K - 1)) - 1u), net->K - 1, s);
     if (err != hipSuccess) return fail(LP_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(err));
     Bindings b; b.ws = net->ws; b.x = x; b.params = params; b.y = y; b.logits = logits;
     b.dparams = dparams; b.dy = dy; b.dx = dx; b.dlogits = dlogits;

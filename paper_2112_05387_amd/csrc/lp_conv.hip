@@ -550,22 +550,38 @@ __global__ __launch_bounds__(WGM* WGN * 64) void conv_wgrad_kernel(const WgradGr
 }
 
 // -------------------------------------------------------------------------------------------------
-// filter re-layout for the data-gradient: w[co][rs][ci] -> wt[ci][rs][co]
+// what a pass starts with: sums, gradients and tickets cleared, filters re-laid out for the data-gradient
+// (w[co][rs][ci] -> wt[ci][rs][co]).  Bound by its launch: the clears and re-layouts of a step of a small network are 1 to 3 us
+// of the chip and were three or four launches of 4 to 5 us in the chain of every stream lane, those of the backward pass in the
+// middle of the step.  Nothing of it depends on the forward pass, so a step does all of it in its first launch, any number
+// of modules and filters together.  A thread of the workgroup's first wave looks at one or two entries of the table.
 // -------------------------------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) PrepGroup PrepArg;
 template <typename T>
-__global__ void wtrans_kernel(const WtransGroup g) {
-    int pi = 0;
-    for (int i = 1; i < g.nprob; ++i)
-        if ((int)blockIdx.x >= g.p[i].block_start) pi = i;
-    const WtransProb& P = g.p[pi];
-    const T* __restrict__ w = reinterpret_cast<const T*>(P.w);
-    T* __restrict__ wt = reinterpret_cast<T*>(P.wt);
+__global__ __launch_bounds__(256) void prep_kernel(const PrepGroup) {
+    PrepArg& g = *(PrepArg*)__builtin_amdgcn_kernarg_segment_ptr();      // indexed per lane: not a copy in scratch
+    static_assert(kPrepMax > 64 && kPrepMax <= 128, "two entries a lane");
+    const int lane = threadIdx.x & 63;
+    const int s0 = g.start[lane], s1 = g.start[min(64 + lane, kPrepMax - 1)];
+    const int pi = __popcll(__ballot((int)blockIdx.x >= s0)) + __popcll(__ballot(64 + lane < kPrepMax && (int)blockIdx.x >= s1)) - 1;
+    const int first = g.start[pi];
+    const void* const src = g.p[pi].src;
+    void* const dst = g.p[pi].dst;
+    int b = (int)blockIdx.x - first;
+    if (!src) {
+        const int n = g.p[pi].vecs, v0 = b * kElemVecsPerBlock, v1 = n - v0 < kElemVecsPerBlock ? n : v0 + kElemVecsPerBlock;
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        for (int v = v0 + (int)threadIdx.x; v < v1; v += 256) reinterpret_cast<u32x4*>(dst)[v] = z;
+        return;
+    }
+    const T* __restrict__ w = reinterpret_cast<const T*>(src);
+    T* __restrict__ wt = reinterpret_cast<T*>(dst);
+    const int Cin = g.p[pi].Cin, Cout = g.p[pi].Cout, RS = g.p[pi].RS;
     // 64 x 64 (co, ci) tile of one tap through LDS; both sides move 4 consecutive elements per thread (channel counts
     // are multiples of 4), so a wave reads and writes whole 128-byte (bf16) or 256-byte (fp32) rows
     constexpr int TS = 64;
     __shared__ T tile[TS][TS + 4];
-    const int tiles_ci = (P.Cin + TS - 1) / TS, tiles_co = (P.Cout + TS - 1) / TS;
-    int b = blockIdx.x - P.block_start;
+    const int tiles_ci = (Cin + TS - 1) / TS, tiles_co = (Cout + TS - 1) / TS;
     const int tci = b % tiles_ci; b /= tiles_ci;
     const int tco = b % tiles_co;
     const int rs = b / tiles_co;
@@ -573,8 +589,8 @@ __global__ void wtrans_kernel(const WtransGroup g) {
     struct alignas(4 * sizeof(T)) V4 { T v[4]; };
     for (int r = ty; r < TS; r += 16) {
         const int co = tco * TS + r, ci = tci * TS + tx;
-        if (co < P.Cout && ci < P.Cin) {
-            const V4 q = *reinterpret_cast<const V4*>(w + ((size_t)co * P.RS + rs) * P.Cin + ci);
+        if (co < Cout && ci < Cin) {
+            const V4 q = *reinterpret_cast<const V4*>(w + ((size_t)co * RS + rs) * Cin + ci);
 #pragma unroll
             for (int e = 0; e < 4; ++e) tile[r][tx + e] = q.v[e];
         }
@@ -582,11 +598,11 @@ __global__ void wtrans_kernel(const WtransGroup g) {
     __syncthreads();
     for (int r = ty; r < TS; r += 16) {
         const int ci = tci * TS + r, co = tco * TS + tx;
-        if (co < P.Cout && ci < P.Cin) {
+        if (co < Cout && ci < Cin) {
             V4 q;
 #pragma unroll
             for (int e = 0; e < 4; ++e) q.v[e] = tile[tx + e][r];
-            *reinterpret_cast<V4*>(wt + ((size_t)ci * P.RS + rs) * P.Cout + co) = q;
+            *reinterpret_cast<V4*>(wt + ((size_t)ci * RS + rs) * Cout + co) = q;
         }
     }
 }
@@ -748,10 +764,10 @@ hipError_t launch_wgrad(const WgradGroup& g, int dtype, int cfg, bool vec, hipSt
     if (dtype == 1) return vec ? wgrad_dispatch<bf16_t, true>(g, cfg, s) : wgrad_dispatch<bf16_t, false>(g, cfg, s);
     return vec ? wgrad_dispatch<float, true>(g, cfg, s) : wgrad_dispatch<float, false>(g, cfg, s);
 }
-hipError_t launch_wtrans(const WtransGroup& g, int dtype, hipStream_t s) {
+hipError_t launch_prep(const PrepGroup& g, int dtype, hipStream_t s) {
     if (g.total_blocks <= 0) return hipSuccess;
-    if (dtype == 1) hipLaunchKernelGGL(wtrans_kernel<bf16_t>, dim3(g.total_blocks), dim3(256), 0, s, g);
-    else hipLaunchKernelGGL(wtrans_kernel<float>, dim3(g.total_blocks), dim3(256), 0, s, g);
+    if (dtype == 1) hipLaunchKernelGGL(prep_kernel<bf16_t>, dim3(g.total_blocks), dim3(256), 0, s, g);
+    else hipLaunchKernelGGL(prep_kernel<float>, dim3(g.total_blocks), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 hipError_t launch_im2col_offsets(const ConvProb& p, const int64_t* m, const int64_t* q, int64_t* out, int count, hipStream_t s) {

@@ -375,19 +375,6 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
 }
 
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kElemBlock) void fill_kernel(const FillGroup g) {
-    const FillProb& P = g.p[find_problem(g, blockIdx.x)];
-    const size_t nvec = P.bytes / 16;
-    u32x4* p = reinterpret_cast<u32x4*>(P.ptr);
-    const size_t base = (size_t)(blockIdx.x - P.block_start) * kElemVecsPerBlock;
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int i = threadIdx.x; i < kElemVecsPerBlock; i += kElemBlock) {
-        const size_t v = base + i;
-        if (v >= nvec) break;
-        p[v] = z;
-    }
-}
-
 __device__ __forceinline__ float block_sum(float v, float* s_tmp) {
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) v += __shfl_xor(v, sh, 64);
@@ -743,8 +730,8 @@ __global__ __launch_bounds__(256) void fc_fwd_tiled_kernel(const HeadProb P) {
 }
 // dW[j,c] = sum_n dz[n,j]*pooled[n,c]; db[j] = sum_n dz[n,j]: one thread per element, the samples in order (no
 // partial sums to combine: pooled and dz stay in cache, the whole pass reads 2*N values per thread)
-__global__ void fc_bwd_w_kernel(const HeadProb P) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void fc_bwd_w(const HeadProb& P, int block) {
+    const int i = block * 256 + threadIdx.x;
     if (i >= P.classes * P.C) return;
     const int j = i / P.C, c = i % P.C;
     float s = 0.f, sb = 0.f;
@@ -760,10 +747,10 @@ __global__ void fc_bwd_w_kernel(const HeadProb P) {
 // The same sums where those reads are what it takes (36 us for 64 samples x 1000 classes x 2048 channels): one thread per
 // channel and four classes, pooled read once for them, 32 samples in flight, their dz through LDS, 128 samples at a time.
 // For small layers the longer thread is the slower one: 12 us against 8 for 128 samples x 10 classes x 64 channels.
-__global__ __launch_bounds__(256) void fc_bwd_w_tiled_kernel(const HeadProb P) {
+__device__ __forceinline__ void fc_bwd_w_tiles(const HeadProb& P, int block) {
     constexpr int NB = 128, U = 32;
     __shared__ float s_dz[NB][kFcClasses];
-    const int j0 = blockIdx.x * kFcClasses, c = blockIdx.y * 256 + threadIdx.x;
+    const int jb = (P.classes + kFcClasses - 1) / kFcClasses, j0 = block % jb * kFcClasses, c = block / jb * 256 + threadIdx.x;
     const float* __restrict__ x = P.pooled + min(c, P.C - 1);
     float s[kFcClasses], sb[kFcClasses];
 #pragma unroll
@@ -801,13 +788,13 @@ __global__ __launch_bounds__(256) void fc_bwd_w_tiled_kernel(const HeadProb P) {
 }
 // dfeat[n,p,c] = (sum_j dz[n,j]*W[j,c]) / HW
 template <typename T>
-__global__ __launch_bounds__(256) void fc_bwd_x_kernel(const HeadProb P) {
+__device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block) {
     // One block per sample and chunk of 256 channels: d pooled[c] = sum_j dlogits[j] * w[j][c] (lanes along c: coalesced
     // rows of w, summed in the order of the classes), then the block broadcasts it, divided by the number of pixels, to
     // every pixel of the sample with 16-byte stores.
     constexpr int EPV = Vec<T>::N;
     extern __shared__ float s_dp[];      // 256 floats, then the sample's `classes` logit gradients
-    const int n = blockIdx.x, cbase = blockIdx.y * 256, C = P.C, classes = P.classes;
+    const int n = block % P.N, cbase = block / P.N * 256, C = P.C, classes = P.classes;
     const int nc = min(256, C - cbase);
     const float inv = 1.f / (float)P.HW;
     float* s_dl = s_dp + 256;
@@ -863,6 +850,14 @@ __global__ __launch_bounds__(256) void fc_bwd_x_kernel(const HeadProb P) {
         Vec<T>::store(d + (size_t)p * C + v * EPV, o);
     }
 }
+// Both halves of the linear layer's backward pass: they read the same logit gradients and neither waits for the other, so
+// they are one launch, the workgroups of the half that the next launches wait for (dfeat) first.
+template <typename T, bool TILED>
+__global__ __launch_bounds__(256) void fc_bwd_kernel(const HeadProb P, int xblocks) {
+    if ((int)blockIdx.x < xblocks) { fc_bwd_x<T>(P, blockIdx.x); return; }
+    if (TILED) fc_bwd_w_tiles(P, (int)blockIdx.x - xblocks);
+    else fc_bwd_w(P, (int)blockIdx.x - xblocks);
+}
 
 // softmax cross-entropy, mini-batch mean; one workgroup per sample
 __global__ __launch_bounds__(kElemBlock) void ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
@@ -892,9 +887,10 @@ __global__ __launch_bounds__(kElemBlock) void ce_kernel(const float* __restrict_
     if (threadIdx.x == 0) atomicAdd(loss, (logf(se) + mx - z[lab]) * invN);
 }
 
-__global__ void zero_selected_kernel(float* v, uint32_t mask, int n) {
+__global__ void zero_selected_kernel(float* v, uint32_t mask, int n, float* v2, uint32_t mask2, int n2) {
     const int i = threadIdx.x;
     if (i < n && ((mask >> i) & 1u)) v[i] = 0.f;
+    if (v2 && i < n2 && ((mask2 >> i) & 1u)) v2[i] = 0.f;
 }
 
 }  // namespace
@@ -943,11 +939,6 @@ hipError_t launch_bn_bwd_apply(const BnBwdGroup& g, int dtype, hipStream_t s) {
     const size_t lds = (size_t)5 * g.cmax * sizeof(float);
     if (dtype == 1) hipLaunchKernelGGL(bn_bwd_apply_kernel<bf16_t>, dim3(g.total_blocks), dim3(kElemBlock), lds, s, g);
     else hipLaunchKernelGGL(bn_bwd_apply_kernel<float>, dim3(g.total_blocks), dim3(kElemBlock), lds, s, g);
-    return hipGetLastError();
-}
-hipError_t launch_fill(const FillGroup& g, hipStream_t s) {
-    if (g.total_blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_kernel, dim3(g.total_blocks), dim3(kElemBlock), 0, s, g);
     return hipGetLastError();
 }
 hipError_t launch_relu_mask(const MaskGroup& g, int dtype, hipStream_t s) {
@@ -1006,19 +997,22 @@ hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s) {
         hipLaunchKernelGGL(fc_fwd_kernel, dim3((p.N * p.classes + 3) / 4), dim3(256), 0, s, p);
     return hipGetLastError();
 }
-hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s) {
-    if (fc_bwd_w_tiled(p))
-        hipLaunchKernelGGL(fc_bwd_w_tiled_kernel, dim3((p.classes + kFcClasses - 1) / kFcClasses, (p.C + 255) / 256), dim3(256), 0, s, p);
-    else
-        hipLaunchKernelGGL(fc_bwd_w_kernel, dim3((p.classes * p.C + 255) / 256), dim3(256), 0, s, p);
+template <typename T>
+static void head_bwd(const HeadProb& p, hipStream_t s) {
+    const int cb = (p.C + 255) / 256, xblocks = p.N * cb;
     const size_t lds = (size_t)(256 + p.classes) * sizeof(float);
-    const dim3 grid(p.N, (p.C + 255) / 256);
-    if (dtype == 1) hipLaunchKernelGGL(fc_bwd_x_kernel<bf16_t>, grid, dim3(256), lds, s, p);
-    else hipLaunchKernelGGL(fc_bwd_x_kernel<float>, grid, dim3(256), lds, s, p);
+    if (fc_bwd_w_tiled(p))
+        hipLaunchKernelGGL((fc_bwd_kernel<T, true>), dim3(xblocks + (p.classes + kFcClasses - 1) / kFcClasses * cb), dim3(256), lds, s, p, xblocks);
+    else
+        hipLaunchKernelGGL((fc_bwd_kernel<T, false>), dim3(xblocks + (p.classes * p.C + 255) / 256), dim3(256), lds, s, p, xblocks);
+}
+hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s) {
+    if (dtype == 1) head_bwd<bf16_t>(p, s);
+    else head_bwd<float>(p, s);
     return hipGetLastError();
 }
-hipError_t launch_zero_selected(float* v, uint32_t mask, int n, hipStream_t s) {
-    hipLaunchKernelGGL(zero_selected_kernel, dim3(1), dim3(64), 0, s, v, mask, n);
+hipError_t launch_zero_selected(float* v, uint32_t mask, int n, float* v2, uint32_t mask2, int n2, hipStream_t s) {
+    hipLaunchKernelGGL(zero_selected_kernel, dim3(1), dim3(64), 0, s, v, mask, n, v2, mask2, n2);
     return hipGetLastError();
 }
 hipError_t launch_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits, int N, int classes,

@@ -165,15 +165,17 @@ constexpr int kFwStemElems = 4;
 size_t fwgrad_lds_bytes(const FWgradProb& p, int esz);
 
 // filters [Cout][R][S][Cin] -> [Cin][R][S][Cout]
-struct WtransProb {
-    const void* w;
-    void* wt;
-    int Cout, RS, Cin;
-    int block_start;
+struct PrepProb {
+    const void* src;         // NULL: clear
+    void* dst;
+    int Cout, RS, Cin;       // filter [Cout][RS][Cin] -> [Cin][RS][Cout]
+    int vecs;                // clear: 16-byte vectors
 };
-struct WtransGroup {
+constexpr int kPrepMax = 96;                       // problems of a launch: 3.4 of the 4 KiB of kernel arguments
+struct PrepGroup {
     int nprob, total_blocks;
-    WtransProb p[kMaxGroup];
+    int start[kPrepMax];                           // first workgroup of a problem; INT_MAX behind the last
+    PrepProb p[kPrepMax];
 };
 
 // out = act( bn(y) [+ skip] ),  bn(y) = gamma*(y-mean)*invstd + beta from the summed statistics.
@@ -216,9 +218,6 @@ struct BnBwdGroup {
 // gm = g * [out > 0]: the gradient through a ReLU behind a residual sum, from the stored block output
 struct MaskProb { const void* g; const void* out; void* gm; size_t numel; int block_start, nblocks; };
 struct MaskGroup { int nprob, total_blocks; MaskProb p[kMaxGroup]; };
-
-struct FillProb { void* ptr; size_t bytes; int block_start; };
-struct FillGroup { int nprob, total_blocks; FillProb p[kMaxGroup]; };
 
 // r = y - x_next;  dy = scale*(rho*r + lam);  loss += scale*(rho/2*sum r^2 + sum lam*r)
 struct LossProb {
@@ -299,11 +298,10 @@ bool wgrad_stem_ok(const WgradProb& p);                    // the layers of the 
 hipError_t launch_wgrad_stem(const WgradGroup& g, hipStream_t s);     // kchunk: output rows of a workgroup; tile_start, total_tiles
 void fastdiv_make(unsigned d, unsigned* mul, unsigned* shift);
 hipError_t launch_wgrad(const WgradGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
-hipError_t launch_wtrans(const WtransGroup& g, int dtype, hipStream_t s);
+hipError_t launch_prep(const PrepGroup& g, int dtype, hipStream_t s);
 hipError_t launch_bn_apply(const BnApplyGroup& g, int dtype, bool fused_loss, hipStream_t s);
 hipError_t launch_bn_bwd_reduce(const BnBwdGroup& g, int dtype, hipStream_t s);
 hipError_t launch_bn_bwd_apply(const BnBwdGroup& g, int dtype, hipStream_t s);
-hipError_t launch_fill(const FillGroup& g, hipStream_t s);
 hipError_t launch_relu_mask(const MaskGroup& g, int dtype, hipStream_t s);
 hipError_t launch_loss(const LossGroup& g, int dtype, hipStream_t s);
 hipError_t launch_mult(const MultGroup& g, int dtype, hipStream_t s);
@@ -321,7 +319,8 @@ hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s);
 hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s);
 hipError_t launch_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits,
                      int N, int classes, hipStream_t s);
-hipError_t launch_zero_selected(float* v, uint32_t mask, int n, hipStream_t s);
+// v[i] = 0 where bit i of mask is set (i < n), v2 alike with its own mask and number (v2 may be NULL)
+hipError_t launch_zero_selected(float* v, uint32_t mask, int n, float* v2, uint32_t mask2, int n2, hipStream_t s);
 hipError_t launch_im2col_offsets(const ConvProb& p, const int64_t* m, const int64_t* q, int64_t* out, int count, hipStream_t s);
 hipError_t launch_conv_offsets(const ConvProb& p, int kernel, int BM, int bk, int nw, const int64_t* m, const int64_t* q,
                                const int64_t* col, int64_t* in_off, int64_t* w_off, int64_t* out_off, int count, hipStream_t s);
