@@ -1564,6 +1564,17 @@ static lp_status build_aux(lp_net* net, int j, WsAlloc& ws) {
 // ----------------------------------------------------------------------------------------------------
 static int elem_blocks(size_t nvec) { return (int)((nvec + kElemVecsPerBlock - 1) / kElemVecsPerBlock); }
 
+// Workgroups of one problem of a batch-norm apply pass.  Sliced tensors of fewer than two workgroups a compute unit are cut twice
+// as fine: one trip of loads per thread instead of two.
+template <typename P> static void bn_apply_blocks(P& p, int epv) {
+    const size_t nvec = (size_t)p.M * p.C / epv;
+    p.slice = bn_slice(p.C);
+    p.per = p.slice && elem_blocks(nvec) < 512 ? 4 : 8;
+    if (!p.slice) { p.nblocks = elem_blocks(nvec); return; }
+    const int rows = kElemBlock / (p.slice / epv) * p.per;
+    p.nblocks = (p.M + rows - 1) / rows * (p.C / p.slice);
+}
+
 // algorithmic work of one operation: flops of the contraction, minimum bytes each tensor moves once
 static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes) {
     const double e = (double)net->esz;
@@ -2092,7 +2103,6 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 BnApplyGroup g; g.nprob = n; g.eps = net->eps; g.cmax = 0; int tot = 0;
                 const bool fused_loss = ops[base]->cfg == 1;
                 g.rho = b.rho; g.scale = b.scale; g.step = b.mstep;
-                for (int i = 0; i < n; ++i) g.cmax = std::max(g.cmax, ops[base + i]->bna.C);
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
                     BnApplyProb& p = g.p[i]; p = o.bna;
@@ -2107,7 +2117,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         p.r2 = net->r2 ? net->r2 + (p.loss - b.loss) : nullptr;      // loss + k  ->  r2 + k
                         p.lam_out = b.mstep != 0.f ? const_cast<void*>(p.lam) : nullptr;
                     }
-                    p.block_start = tot; p.nblocks = elem_blocks((size_t)p.M * p.C / epv); tot += p.nblocks;
+                    p.block_start = tot; bn_apply_blocks(p, epv); tot += p.nblocks;
+                    g.cmax = std::max(g.cmax, p.slice ? p.slice : p.C);
                 }
                 g.total_blocks = tot;
                 err = launch_bn_apply(g, dt, fused_loss, s);
@@ -2116,7 +2127,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
             case OP_BN_BWD_REDUCE:
             case OP_BN_BWD_APPLY: {
                 BnBwdGroup g; g.nprob = n; g.eps = net->eps; g.cmax = 0; int tot = 0;
-                for (int i = 0; i < n; ++i) g.cmax = std::max(g.cmax, ops[base + i]->bnb.C);
+                int widest = 0;
+                for (int i = 0; i < n; ++i) widest = std::max(widest, ops[base + i]->bnb.C);
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
                     BnBwdProb& p = g.p[i]; p = o.bnb;
@@ -2128,11 +2140,20 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.block_start = tot;
                     if (type == OP_BN_BWD_REDUCE) {
                         // at least 64 rows per workgroup, and (one trip of the reduction being four rows per row lane) no more
-                        // workgroups than trips
-                        const int rows_trip = 4 * std::max(1, bn_reduce_threads(g.cmax) / (p.C / epv));
-                        p.nblocks = net->deterministic ? 1 : std::max(1, std::min(std::min(256, (p.M + 63) / 64), (p.M + rows_trip - 1) / rows_trip));
+                        // workgroups than trips; slices of channels: the one workgroup a compute unit holds (152
+                        // registers), all with equally many trips
+                        p.slice = bn_slice(p.C);
+                        const int S = p.slice ? p.slice : p.C, ns = p.C / S;
+                        const int rows_trip = 4 * std::max(1, bn_reduce_threads(widest) / (S / epv)), trips = (p.M + rows_trip - 1) / rows_trip;
+                        if (net->deterministic) p.nblocks = ns;
+                        else if (!p.slice) p.nblocks = std::max(1, std::min(std::min(256, (p.M + 63) / 64), trips));
+                        else {
+                            const int most = std::max(1, 256 / ns), per = (trips + most - 1) / most;
+                            p.nblocks = (trips + per - 1) / per * ns;
+                        }
+                        g.cmax = std::max(g.cmax, S);
                     } else if (type != OP_BN_BWD_APPLY) p.nblocks = net->deterministic ? 1 : std::max(1, std::min(256, (p.M + 63) / 64));
-                    else p.nblocks = elem_blocks((size_t)p.M * p.C / epv);
+                    else { bn_apply_blocks(p, epv); g.cmax = std::max(g.cmax, p.slice ? p.slice : p.C); }
                     tot += p.nblocks;
                 }
                 g.total_blocks = tot;

@@ -554,7 +554,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void conv_wgrad_kernel(const WgradGr
 // (w[co][rs][ci] -> wt[ci][rs][co]).  Bound by its launch: the clears and re-layouts of a step of a small network are 1 to 3 us
 // of the chip and were three or four launches of 4 to 5 us in the chain of every stream lane, those of the backward pass in the
 // middle of the step.  Nothing of it depends on the forward pass, so a step does all of it in its first launch, any number
-// of modules and filters together.  A thread of the workgroup's first wave looks at one or two entries of the table.
+// of modules and filters together: tiny 79.5 -> 68.8 us, ResNet-20 of 3 samples 197 -> 182 (with the linear layer's backward pass
+// in one launch).  Every lane of a wave looks at one or two entries of the table.
 // -------------------------------------------------------------------------------------------------
 typedef const __attribute__((address_space(4))) PrepGroup PrepArg;
 template <typename T>

@@ -17,6 +17,28 @@ template <typename G> __device__ __forceinline__ int find_problem(const G& g, in
     return pi;
 }
 
+// Which 16-byte vectors of an [M][C] tensor a thread of a batch-norm apply pass works on: `per` of them, v, v + vstep, ...
+// (those below M * C / EPV), and where their channels lie in the workgroup's coefficients (c, c + cstep mod cmod, ...).
+// Without slices a workgroup has consecutive vectors and the coefficients of all channels; with slices of `slice` channels
+// (bn_slice) it has whole rows of one slice, and every vector of a thread the same channels.
+struct BnSpan { size_t v; size_t vstep; unsigned c, cstep, cmod; int ch0, nch; };
+template <int EPV> __device__ __forceinline__ BnSpan bn_span(int block, int C, int slice, int per) {
+    BnSpan q;
+    const unsigned cv = (unsigned)C / EPV;
+    if (!slice) {
+        q.v = (size_t)block * (per * kElemBlock) + threadIdx.x; q.vstep = kElemBlock;
+        q.cmod = cv; q.cstep = (unsigned)kElemBlock % cv; q.c = (unsigned)(q.v % cv);
+        q.ch0 = 0; q.nch = C;
+    } else {
+        const unsigned ns = (unsigned)C / (unsigned)slice, sv = (unsigned)slice / EPV, rl = kElemBlock / sv;
+        const unsigned rb = (unsigned)block / ns, sl = (unsigned)block - rb * ns, row = rb * (rl * per) + threadIdx.x / sv;
+        q.cmod = sv; q.cstep = 0; q.c = threadIdx.x % sv;
+        q.v = (size_t)row * cv + sl * sv + q.c; q.vstep = (size_t)rl * cv;
+        q.ch0 = (int)sl * slice; q.nch = slice;
+    }
+    return q;
+}
+
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_sum(float v, float* s_tmp);
 
@@ -34,13 +56,15 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
     float* s_ssh = s_coef + 3 * cm;
     const BnApplyProb& P = g.p[find_problem(g, blockIdx.x)];
     const int C = P.C, M = P.M;
-    for (int c = threadIdx.x; c < C; c += kElemBlock) {
+    const BnSpan span = bn_span<EPV>(blockIdx.x - P.block_start, C, P.slice, P.per);
+    for (int i = threadIdx.x; i < span.nch; i += kElemBlock) {
+        const int c = span.ch0 + i;
         float sc, sh, mu, is;
         bn_coeffs(P.stats, P.gamma, P.beta, c, C, M, g.eps, sc, sh, mu, is);
-        s_sc[c] = sc; s_sh[c] = sh;
+        s_sc[i] = sc; s_sh[i] = sh;
         if (P.skip_mode == 2) {
             bn_coeffs(P.sstats, P.sgamma, P.sbeta, c, C, M, g.eps, sc, sh, mu, is);
-            s_ssc[c] = sc; s_ssh[c] = sh;
+            s_ssc[i] = sc; s_ssh[i] = sh;
         }
     }
     __syncthreads();
@@ -48,27 +72,22 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
     const T* __restrict__ skip = reinterpret_cast<const T*>(P.skip);
     T* __restrict__ out = reinterpret_cast<T*>(P.out);
     const size_t nvec = (size_t)M * C / EPV;
-    const int cv = C / EPV;
-    const size_t base = (size_t)(blockIdx.x - P.block_start) * kElemVecsPerBlock;
     // four vectors per trip, loads first: up to eight independent 16-byte loads in flight per thread
     constexpr int U = 4;
-    // channel vector of this thread's first vector; it advances by kElemBlock (mod cv) from vector to vector, which
-    // avoids a 64-bit remainder per vector
-    const unsigned cstep = (unsigned)kElemBlock % (unsigned)cv;
-    unsigned cidx = (unsigned)((base + threadIdx.x) % (size_t)cv);
+    unsigned cidx = span.c;
     const T* __restrict__ xn = reinterpret_cast<const T*>(P.xn);
     const T* lam = reinterpret_cast<const T*>(P.lam);
     T* lam_out = reinterpret_cast<T*>(P.lam_out);          // may alias lam: every vector is read before it is written
     T* __restrict__ dyp = reinterpret_cast<T*>(P.dy);
     float lacc = 0.f, racc = 0.f;
-    for (int i0 = threadIdx.x; i0 < kElemVecsPerBlock; i0 += U * kElemBlock) {
+    for (int i0 = 0; i0 < P.per; i0 += U) {
         // Unconditional loads (a vector beyond the end re-reads the last one and is dropped): behind a per-lane branch
         // the compiler waits for each pair of loads before it issues the next.
         u32x4 fraw[U], skraw[U], xnraw[FUSE ? U : 1], lmraw[FUSE ? U : 1];
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const size_t v = base + i0 + u * kElemBlock;
+            const size_t v = span.v + (i0 + u) * span.vstep;
             ok[u] = v < nvec;
             const size_t vc = ok[u] ? v : nvec - 1;
             fraw[u] = Vec<T>::load_raw(y + vc * EPV);
@@ -82,10 +101,10 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c0 = (int)cidx * EPV;
-            cidx += cstep;
-            if (cidx >= (unsigned)cv) cidx -= (unsigned)cv;
+            cidx += span.cstep;
+            if (cidx >= span.cmod) cidx -= span.cmod;
             if (!ok[u]) continue;
-            const size_t v = base + i0 + u * kElemBlock;
+            const size_t v = span.v + (i0 + u) * span.vstep;
             float f[1][EPV], sk[1][EPV], o[EPV];
             Vec<T>::unpack(fraw[u], f[0]);
             if (P.skip_mode) Vec<T>::unpack(skraw[u], sk[0]);
@@ -144,7 +163,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
 
 // ------------------------------------------------------------------------------------------------
 // red[c] += sum g', red[C+c] += sum g'*yhat over this workgroup's rows.
-// C / EPV <= NT channel vectors (C <= 2048): thread t owns channel vector t % cv and is row lane t / cv.  A trip is
+// S / EPV <= NT channel vectors (S <= 2048): thread t owns channel vector t % cv and is row lane t / cv.  A trip is
 // four rows per row lane, i.e. eight independent 16-byte loads per thread.  The trips of the blocks are interleaved
 // (block b takes trips b, b + nblocks, ...), so that at any time the blocks together read one contiguous, moving window
 // of the two tensors instead of nblocks distant streams.  The first trip is requested before the coefficient prologue
@@ -161,30 +180,31 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     float* s_mu = s_coef + 2 * cm;
     float* s_is = s_coef + 3 * cm;
     const BnBwdProb& P = g.p[find_problem(g, blockIdx.x)];
-    const int C = P.C, M = P.M, cv = C / EPV;
-    const int b = blockIdx.x - P.block_start;
+    // S channels (bn_slice, or all of them) from ch0 on; this workgroup's trips are rb, rb + nrb, ...
+    const int C = P.C, M = P.M, S = P.slice ? P.slice : C, ns = C / S, cv = S / EPV;
+    const int b = blockIdx.x - P.block_start, rb = b / ns, nrb = P.nblocks / ns, ch0 = (b - rb * ns) * S;
     const T* __restrict__ gp = reinterpret_cast<const T*>(P.g);
     const T* __restrict__ y = reinterpret_cast<const T*>(P.y);
     const int rl = NT / cv;                      // row lanes
     const int tcv = threadIdx.x % cv, trl = threadIdx.x / cv;
     const bool active = trl < rl;
-    const int c0 = tcv * EPV;
-    const int rows_trip = 4 * rl, stride = P.nblocks * rows_trip;
+    const int c0 = tcv * EPV;                    // in the slice
+    const int rows_trip = 4 * rl, stride = nrb * rows_trip;
     // a trip as loaded (32 registers); rows past the end read the last row and count as zero when consumed
     auto request = [&](u32x4 (&graw)[4], u32x4 (&yraw)[4], int r0) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int r = min(r0 + trl + u * rl, M - 1);
-            graw[u] = Vec<T>::load_raw(gp + (size_t)r * C + c0);
-            yraw[u] = Vec<T>::load_raw(y + (size_t)r * C + c0);
+            graw[u] = Vec<T>::load_raw(gp + (size_t)r * C + ch0 + c0);
+            yraw[u] = Vec<T>::load_raw(y + (size_t)r * C + ch0 + c0);
         }
     };
     u32x4 ga[4], ya[4], gb[4], yb[4];
-    int r0 = b * rows_trip;
+    int r0 = rb * rows_trip;
     if (active && r0 < M) request(ga, ya, r0);
-    for (int c = threadIdx.x; c < C; c += NT) {
+    for (int c = threadIdx.x; c < S; c += NT) {
         float sc, sh, mu, is;
-        bn_coeffs(P.stats, P.gamma, P.beta, c, C, M, g.eps, sc, sh, mu, is);
+        bn_coeffs(P.stats, P.gamma, P.beta, ch0 + c, C, M, g.eps, sc, sh, mu, is);
         s_sc[c] = sc; s_sh[c] = sh; s_mu[c] = mu; s_is[c] = is;
     }
     __syncthreads();
@@ -233,11 +253,18 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     }
     __syncthreads();
     for (int i = threadIdx.x; i < cv * EPV; i += NT) {
-        float s1 = 0.f, s2 = 0.f;
-        for (int l = 0; l < rl; ++l) { s1 += s_red[((l * cv * EPV) + i) * 2]; s2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
-        double* red = P.red + (size_t)(blockIdx.x % stat_stripes(C)) * 2 * C;
-        atomicAdd(&red[i], (double)s1);
-        atomicAdd(&red[C + i], (double)s2);
+        double s1, s2;
+        if (ns > 1) {            // 16 to 64 row lanes a channel instead of 1 to 16: not another chain of fp32 sums
+            s1 = 0.0; s2 = 0.0;
+            for (int l = 0; l < rl; ++l) { s1 += s_red[((l * cv * EPV) + i) * 2]; s2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
+        } else {
+            float f1 = 0.f, f2 = 0.f;
+            for (int l = 0; l < rl; ++l) { f1 += s_red[((l * cv * EPV) + i) * 2]; f2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
+            s1 = f1; s2 = f2;
+        }
+        double* red = P.red + (size_t)((ns > 1 ? rb : (int)blockIdx.x) % stat_stripes(C)) * 2 * C + ch0;
+        atomicAdd(&red[i], s1);
+        atomicAdd(&red[C + i], s2);
     }
 }
 
@@ -313,8 +340,10 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
     float* s_k3 = s_coef + 4 * cm;
     const BnBwdProb& P = g.p[find_problem(g, blockIdx.x)];
     const int C = P.C, M = P.M;
-    const bool first = (int)blockIdx.x == P.block_start;
-    for (int c = threadIdx.x; c < C; c += kElemBlock) {
+    const BnSpan span = bn_span<EPV>(blockIdx.x - P.block_start, C, P.slice, P.per);
+    const bool first = (int)blockIdx.x - P.block_start < (P.slice ? C / P.slice : 1);      // the first rows (of every slice)
+    for (int i = threadIdx.x; i < span.nch; i += kElemBlock) {
+        const int c = span.ch0 + i;
         float sc, sh, mu, is;
         bn_coeffs(P.stats, P.gamma, P.beta, c, C, M, g.eps, sc, sh, mu, is);
         const double inv_m = 1.0 / (double)M;
@@ -323,8 +352,8 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
         const float r0 = (float)(rs0 * inv_m), r1 = (float)(rs1 * inv_m);
         const float k1 = P.gamma[c] * is;
         const float k2 = k1 * is * r1;
-        s_sc[c] = sc; s_sh[c] = sh;
-        s_k1[c] = k1; s_k2[c] = k2; s_k3[c] = k2 * mu - k1 * r0;
+        s_sc[i] = sc; s_sh[i] = sh;
+        s_k1[i] = k1; s_k2[i] = k2; s_k3[i] = k2 * mu - k1 * r0;
         if (first) {
             P.dgamma[c] = (float)rs1;
             P.dbeta[c] = (float)rs0;
@@ -335,42 +364,54 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
     const T* __restrict__ y = reinterpret_cast<const T*>(P.y);
     T* __restrict__ dy = reinterpret_cast<T*>(P.dy);
     const size_t nvec = (size_t)M * C / EPV;
-    const int cv = C / EPV;
-    const size_t base = (size_t)(blockIdx.x - P.block_start) * kElemVecsPerBlock;
-    const unsigned cstep = (unsigned)kElemBlock % (unsigned)cv;     // channel vector advances by kElemBlock (mod cv)
-    unsigned cidx = (unsigned)((base + threadIdx.x) % (size_t)cv);
-    for (int i = threadIdx.x; i < kElemVecsPerBlock; i += kElemBlock) {
-        const size_t v = base + i;
-        if (v >= nvec) break;
-        const int c0 = (int)cidx * EPV;
-        cidx += cstep;
-        if (cidx >= (unsigned)cv) cidx -= (unsigned)cv;
-        float gv[EPV], yv[EPV], o[EPV];
-        Vec<T>::load(gp + v * EPV, gv);
-        Vec<T>::load(y + v * EPV, yv);
-        // the five coefficient vectors of these EPV channels, as 16-byte LDS reads
-        float sc[EPV], sh[EPV], k1[EPV], k2[EPV], k3[EPV];
+    const T* __restrict__ ap = reinterpret_cast<const T*>(P.add);
+    // U vectors a trip, loads first and unconditional (a vector beyond the end re-reads the last one and is dropped)
+    constexpr int U = 4;
+    unsigned cidx = span.c;
+    for (int i0 = 0; i0 < P.per; i0 += U) {
+        u32x4 graw[U], yraw[U], araw[U];
 #pragma unroll
-        for (int q4 = 0; q4 < EPV / 4; ++q4) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(s_sc + c0 + 4 * q4), b = *reinterpret_cast<const f32x4*>(s_sh + c0 + 4 * q4);
-            const f32x4 c = *reinterpret_cast<const f32x4*>(s_k1 + c0 + 4 * q4), d = *reinterpret_cast<const f32x4*>(s_k2 + c0 + 4 * q4);
-            const f32x4 f = *reinterpret_cast<const f32x4*>(s_k3 + c0 + 4 * q4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { sc[4 * q4 + e] = a[e]; sh[4 * q4 + e] = b[e]; k1[4 * q4 + e] = c[e]; k2[4 * q4 + e] = d[e]; k3[4 * q4 + e] = f[e]; }
+        for (int u = 0; u < U; ++u) {
+            const size_t v = span.v + (i0 + u) * span.vstep, vc = v < nvec ? v : nvec - 1;
+            graw[u] = Vec<T>::load_raw(gp + vc * EPV);
+            yraw[u] = Vec<T>::load_raw(y + vc * EPV);
+            if (ap) araw[u] = Vec<T>::load_raw(ap + vc * EPV);
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-            float gg = gv[e];
-            if (P.relu && !(fmaf(sc[e], yv[e], sh[e]) > 0.f)) gg = 0.f;
-            o[e] = k1[e] * gg - k2[e] * yv[e] + k3[e];
-        }
-        if (P.add) {
-            float av[EPV];
-            Vec<T>::load(reinterpret_cast<const T*>(P.add) + v * EPV, av);
+        for (int u = 0; u < U; ++u) {
+            const size_t v = span.v + (i0 + u) * span.vstep;
+            const int c0 = (int)cidx * EPV;
+            cidx += span.cstep;
+            if (cidx >= span.cmod) cidx -= span.cmod;
+            if (v >= nvec) continue;
+            float gv[EPV], yv[EPV], o[EPV];
+            Vec<T>::unpack(graw[u], gv);
+            Vec<T>::unpack(yraw[u], yv);
+            // the five coefficient vectors of these EPV channels, as 16-byte LDS reads
+            float sc[EPV], sh[EPV], k1[EPV], k2[EPV], k3[EPV];
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) o[e] += av[e];
+            for (int q4 = 0; q4 < EPV / 4; ++q4) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(s_sc + c0 + 4 * q4), b = *reinterpret_cast<const f32x4*>(s_sh + c0 + 4 * q4);
+                const f32x4 c = *reinterpret_cast<const f32x4*>(s_k1 + c0 + 4 * q4), d = *reinterpret_cast<const f32x4*>(s_k2 + c0 + 4 * q4);
+                const f32x4 f = *reinterpret_cast<const f32x4*>(s_k3 + c0 + 4 * q4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { sc[4 * q4 + e] = a[e]; sh[4 * q4 + e] = b[e]; k1[4 * q4 + e] = c[e]; k2[4 * q4 + e] = d[e]; k3[4 * q4 + e] = f[e]; }
+            }
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                float gg = gv[e];
+                if (P.relu && !(fmaf(sc[e], yv[e], sh[e]) > 0.f)) gg = 0.f;
+                o[e] = k1[e] * gg - k2[e] * yv[e] + k3[e];
+            }
+            if (ap) {
+                float av[EPV];
+                Vec<T>::unpack(araw[u], av);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) o[e] += av[e];
+            }
+            Vec<T>::store(dy + v * EPV, o);
         }
-        Vec<T>::store(dy + v * EPV, o);
     }
 }
 
@@ -920,7 +961,9 @@ hipError_t launch_bn_bwd_reduce(const BnBwdGroup& g, int dtype, hipStream_t s) {
     const size_t lds = (size_t)4 * g.cmax * sizeof(float);
     // narrow tensors (at most 64 channels): 256-thread workgroups -- with 512 threads half of the 256 workgroups of a
     // 32 x 32 x 16 tensor have no trip at all and the others' final sum over the row lanes is twice as long
-    if (bn_reduce_threads(g.cmax) == 256) {
+    int widest = 0;
+    for (int i = 0; i < g.nprob; ++i) widest = g.p[i].C > widest ? g.p[i].C : widest;
+    if (bn_reduce_threads(widest) == 256) {
         if (dtype == 1) hipLaunchKernelGGL((bn_bwd_reduce_kernel<bf16_t, 256>), dim3(g.total_blocks), dim3(256), lds, s, g);
         else hipLaunchKernelGGL((bn_bwd_reduce_kernel<float, 256>), dim3(g.total_blocks), dim3(256), lds, s, g);
         return hipGetLastError();

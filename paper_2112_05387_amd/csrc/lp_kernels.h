@@ -189,11 +189,12 @@ struct BnApplyProb {
     const void* skip; const double* sstats; const float* sgamma; const float* sbeta;
     const void* xn; const void* lam; void* dy; void* lam_out; float* loss; float* r2;
     int M, C, relu, skip_mode;
+    int slice, per;       // bn_slice; vectors of a thread, 4 or 8
     int block_start, nblocks;
 };
 struct BnApplyGroup {
     int nprob, total_blocks; float eps;
-    int cmax;             // largest channel count of the group (sizes the coefficient arrays in LDS)
+    int cmax;             // most channels a workgroup of the group has coefficients of (sizes the arrays in LDS)
     float rho, scale, step;   // fused form: penalty coefficient, loss scale, multiplier step
     BnApplyProb p[kMaxGroup];
 };
@@ -207,11 +208,12 @@ struct BnBwdProb {       // add: optional addend of the apply pass with the layo
     const double* stats; const float* gamma; const float* beta;
     double* red; float* dgamma; float* dbeta;
     int M, C, relu;
+    int slice, per;       // as in BnApplyProb (per: apply pass)
     int block_start, nblocks;
 };
 struct BnBwdGroup {
     int nprob, total_blocks; float eps;
-    int cmax;             // largest channel count of the group (sizes the coefficient arrays in LDS)
+    int cmax;             // as above
     BnBwdProb p[kMaxGroup];
 };
 
@@ -341,6 +343,12 @@ __host__ __device__ inline size_t stat_bytes(int C) { return sizeof(double) * 2 
 constexpr int kBnReduceBlock = 512;      // threads per workgroup of the BN backward reduction (measured: 256 -7 %, 1024 -20 %)
 // ... and 256 for launches whose widest tensor has at most 64 channels (see launch_bn_bwd_reduce)
 inline int bn_reduce_threads(int cmax) { return cmax <= 64 ? 256 : kBnReduceBlock; }
+// Channels of a workgroup of the batch-norm passes (apply, backward), 0: all of them.  A workgroup computes the coefficients of its channels
+// from the sums first, 16 bytes a channel, stripe and sum: for 320 to 2048 channels that is as much as its 32 KB of a tensor.
+// A small tensor also has few rows a workgroup can share out: 294 rows of 2048 channels were 5 workgroups of the backward reduction
+// and are 48.  Slices are whole 128-byte lines of bf16.  ResNet-50 step of 6 samples 1529 -> 1432 us, of 64 5724 -> 5695, WRN-28-10
+// in pre-activation order 1942 -> 1892; 160 channels (WRN-28-10's first stage) have no such slice and keep whole rows.
+inline int bn_slice(int C) { return C > 128 && C % 128 == 0 ? 128 : C > 64 && C % 64 == 0 ? 64 : 0; }
 constexpr int kElemVecsPerBlock = 2048;  // 16-byte vectors handled by one workgroup
 
 }  // namespace lp
