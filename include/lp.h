@@ -410,8 +410,8 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
 lp_status lp_debug_linear_kernels(int N, int classes, int C, int* tiled);
 
 /* A per-thread switch read by lp_net_create: nets created while it is on run the kernels that the specialised ones stand in
- * for (batch norms as passes of their own, the large tiles of wide layers, the general filter gradients), for comparisons of
- * the two. */
+ * for (batch norms as passes of their own and over whole rows, the large tiles of wide layers, the general filter gradients),
+ * for comparisons of the two. */
 lp_status lp_debug_separate_passes(int on);
 
 /* How a call over all modules runs (host only; whole_step: lp_local_step, otherwise a pass of its own): *folded = 1 if the passes are the narrow ones with the batch norms folded

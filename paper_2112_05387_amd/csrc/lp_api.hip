@@ -216,7 +216,7 @@ struct lp_net {
     hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
     bool lanes_ready = false;              // every extra stream and event above exists
     bool keep_gradients = false;           // debug layout: no gradient buffer is reused inside a backward pass
-    bool separate = false;                 // debug: no folded passes, no small tiles, no window filter gradients
+    bool separate = false;                 // debug: no folded passes, no small tiles, no window filter gradients, whole rows in the batch-norm passes
     bool narrow = false;                   // every module has the folded programs (ffwd ...)
     bool deep = false;                     // a module of more than three blocks, or AuxNets (see Builder::fconv_exact)
     bool lanes_set = false;                // the caller chose the stream lanes
@@ -1566,9 +1566,9 @@ static int elem_blocks(size_t nvec) { return (int)((nvec + kElemVecsPerBlock - 1
 
 // Workgroups of one problem of a batch-norm apply pass.  Sliced tensors of fewer than two workgroups a compute unit are cut twice
 // as fine: one trip of loads per thread instead of two.
-template <typename P> static void bn_apply_blocks(P& p, int epv) {
+template <typename P> static void bn_apply_blocks(P& p, int epv, bool whole) {
     const size_t nvec = (size_t)p.M * p.C / epv;
-    p.slice = bn_slice(p.C);
+    p.slice = whole ? 0 : bn_slice(p.C);
     p.per = p.slice && elem_blocks(nvec) < 512 ? 4 : 8;
     if (!p.slice) { p.nblocks = elem_blocks(nvec); return; }
     const int rows = kElemBlock / (p.slice / epv) * p.per;
@@ -2117,7 +2117,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         p.r2 = net->r2 ? net->r2 + (p.loss - b.loss) : nullptr;      // loss + k  ->  r2 + k
                         p.lam_out = b.mstep != 0.f ? const_cast<void*>(p.lam) : nullptr;
                     }
-                    p.block_start = tot; bn_apply_blocks(p, epv); tot += p.nblocks;
+                    p.block_start = tot; bn_apply_blocks(p, epv, net->separate); tot += p.nblocks;
                     g.cmax = std::max(g.cmax, p.slice ? p.slice : p.C);
                 }
                 g.total_blocks = tot;
@@ -2128,7 +2128,9 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
             case OP_BN_BWD_APPLY: {
                 BnBwdGroup g; g.nprob = n; g.eps = net->eps; g.cmax = 0; int tot = 0;
                 int widest = 0;
-                for (int i = 0; i < n; ++i) widest = std::max(widest, ops[base + i]->bnb.C);
+                bool sliced = !net->separate;
+                for (int i = 0; i < n; ++i) { widest = std::max(widest, ops[base + i]->bnb.C); sliced = sliced && bn_slice(ops[base + i]->bnb.C); }
+                g.threads = sliced ? 256 : bn_reduce_threads(widest);
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];
                     BnBwdProb& p = g.p[i]; p = o.bnb;
@@ -2139,21 +2141,18 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.add = resolve(o.r[9], b);
                     p.block_start = tot;
                     if (type == OP_BN_BWD_REDUCE) {
-                        // at least 64 rows per workgroup, and (one trip of the reduction being four rows per row lane) no more
-                        // workgroups than trips; slices of channels: the one workgroup a compute unit holds (152
-                        // registers), all with equally many trips
-                        p.slice = bn_slice(p.C);
+                        // at least 64 rows per part, and (one trip of the reduction being four rows per row lane) no more parts
+                        // than trips: the order of the sums, which no slice changes.  A workgroup of a slice takes several parts
+                        // where one each would be more of them than run at once
+                        p.slice = net->separate ? 0 : bn_slice(p.C);
                         const int S = p.slice ? p.slice : p.C, ns = p.C / S;
-                        const int rows_trip = 4 * std::max(1, bn_reduce_threads(widest) / (S / epv)), trips = (p.M + rows_trip - 1) / rows_trip;
-                        if (net->deterministic) p.nblocks = ns;
-                        else if (!p.slice) p.nblocks = std::max(1, std::min(std::min(256, (p.M + 63) / 64), trips));
-                        else {
-                            const int most = std::max(1, 256 / ns), per = (trips + most - 1) / most;
-                            p.nblocks = (trips + per - 1) / per * ns;
-                        }
+                        p.lanes = std::max(1, bn_reduce_threads(widest) / (p.C / epv));
+                        p.parts = net->deterministic ? 1 : std::max(1, std::min(std::min(256, (p.M + 63) / 64), (p.M + 4 * p.lanes - 1) / (4 * p.lanes)));
+                        p.groups = std::max(1, std::min(g.threads / (S / epv) / p.lanes, (p.parts * ns + 767) / 768));
+                        p.nblocks = (p.parts + p.groups - 1) / p.groups * ns;
                         g.cmax = std::max(g.cmax, S);
                     } else if (type != OP_BN_BWD_APPLY) p.nblocks = net->deterministic ? 1 : std::max(1, std::min(256, (p.M + 63) / 64));
-                    else { bn_apply_blocks(p, epv); g.cmax = std::max(g.cmax, p.slice ? p.slice : p.C); }
+                    else { bn_apply_blocks(p, epv, net->separate); g.cmax = std::max(g.cmax, p.slice ? p.slice : p.C); }
                     tot += p.nblocks;
                 }
                 g.total_blocks = tot;

@@ -164,10 +164,18 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
 // ------------------------------------------------------------------------------------------------
 // red[c] += sum g', red[C+c] += sum g'*yhat over this workgroup's rows.
 // S / EPV <= NT channel vectors (S <= 2048): thread t owns channel vector t % cv and is row lane t / cv.  A trip is
-// four rows per row lane, i.e. eight independent 16-byte loads per thread.  The trips of the blocks are interleaved
-// (block b takes trips b, b + nblocks, ...), so that at any time the blocks together read one contiguous, moving window
-// of the two tensors instead of nblocks distant streams.  The first trip is requested before the coefficient prologue
+// four rows per row lane, i.e. eight independent 16-byte loads per thread.  The rows are cut into `parts`, whose trips are
+// interleaved (part b takes trips b, b + parts, ...), so that at any time the parts together read one contiguous, moving
+// window of the two tensors instead of as many distant streams.  The first trip is requested before the coefficient prologue
 // (it does not depend on it) and every further trip before the previous one is consumed.
+// The order of the fp32 sums is that of whole rows, with slices or without: a part has the row lanes that a workgroup has of whole
+// rows, they are added up in fp32 one after the other, and the parts meet in fp64.  A workgroup of whole rows is one part; one of
+// a slice, whose rows are shorter, holds `groups` of them.  With the row lanes of the slice instead, sums as exact but not
+// the same, the bf16 adjoints of wide networks moved by 2e-3 to 8e-3 of their norm, single roundings of the auxiliary
+// variables with them, and the gradient of an AuxNet, which is distilled from just those, by 0.02 to 0.10.
+// Slices run in workgroups of 256 threads, of which three share a compute unit (152 registers), whole rows in 512: the sliced
+// ones in 512 as well, or with three or four trips under way, or one trip and four waves a SIMD, are each the slower choice
+// (ResNet-50 step of 6 / 64 samples 1434 / 5576 us; 1450 / 5597, 1457 / 5663, 1494 / 6048; without slices 1448 / 5531).
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     constexpr int EPV = Vec<T>::N;
@@ -180,16 +188,17 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     float* s_mu = s_coef + 2 * cm;
     float* s_is = s_coef + 3 * cm;
     const BnBwdProb& P = g.p[find_problem(g, blockIdx.x)];
-    // S channels (bn_slice, or all of them) from ch0 on; this workgroup's trips are rb, rb + nrb, ...
+    // S channels (bn_slice, or all of them) from ch0 on; the workgroup's parts are rb * groups, rb * groups + 1, ...
     const int C = P.C, M = P.M, S = P.slice ? P.slice : C, ns = C / S, cv = S / EPV;
-    const int b = blockIdx.x - P.block_start, rb = b / ns, nrb = P.nblocks / ns, ch0 = (b - rb * ns) * S;
+    const int b = blockIdx.x - P.block_start, rb = b / ns, ch0 = (b - rb * ns) * S;
     const T* __restrict__ gp = reinterpret_cast<const T*>(P.g);
     const T* __restrict__ y = reinterpret_cast<const T*>(P.y);
-    const int rl = NT / cv;                      // row lanes
-    const int tcv = threadIdx.x % cv, trl = threadIdx.x / cv;
-    const bool active = trl < rl;
+    const int rl = P.lanes;                      // row lanes of a part
+    const int tcv = threadIdx.x % cv, lane_row = threadIdx.x / cv, group = lane_row / rl, trl = lane_row - group * rl;
+    const int part = rb * P.groups + group;
+    const bool active = group < P.groups && part < P.parts;
     const int c0 = tcv * EPV;                    // in the slice
-    const int rows_trip = 4 * rl, stride = nrb * rows_trip;
+    const int rows_trip = 4 * rl, stride = P.parts * rows_trip;
     // a trip as loaded (32 registers); rows past the end read the last row and count as zero when consumed
     auto request = [&](u32x4 (&graw)[4], u32x4 (&yraw)[4], int r0) {
 #pragma unroll
@@ -200,7 +209,7 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
         }
     };
     u32x4 ga[4], ya[4], gb[4], yb[4];
-    int r0 = rb * rows_trip;
+    int r0 = part * rows_trip;
     if (active && r0 < M) request(ga, ya, r0);
     for (int c = threadIdx.x; c < S; c += NT) {
         float sc, sh, mu, is;
@@ -247,22 +256,20 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     if (active) {
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
-            s_red[((trl * cv + tcv) * EPV + e) * 2] = a1[e];
-            s_red[((trl * cv + tcv) * EPV + e) * 2 + 1] = a2[e];
+            s_red[((lane_row * cv + tcv) * EPV + e) * 2] = a1[e];
+            s_red[((lane_row * cv + tcv) * EPV + e) * 2 + 1] = a2[e];
         }
     }
     __syncthreads();
+    const int here = min(P.groups, P.parts - rb * P.groups);     // parts of this workgroup
     for (int i = threadIdx.x; i < cv * EPV; i += NT) {
-        double s1, s2;
-        if (ns > 1) {            // 16 to 64 row lanes a channel instead of 1 to 16: not another chain of fp32 sums
-            s1 = 0.0; s2 = 0.0;
-            for (int l = 0; l < rl; ++l) { s1 += s_red[((l * cv * EPV) + i) * 2]; s2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
-        } else {
+        double s1 = 0.0, s2 = 0.0;
+        for (int q = 0; q < here; ++q) {
             float f1 = 0.f, f2 = 0.f;
-            for (int l = 0; l < rl; ++l) { f1 += s_red[((l * cv * EPV) + i) * 2]; f2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
-            s1 = f1; s2 = f2;
+            for (int l = q * rl; l < (q + 1) * rl; ++l) { f1 += s_red[((l * cv * EPV) + i) * 2]; f2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
+            s1 += f1; s2 += f2;
         }
-        double* red = P.red + (size_t)((ns > 1 ? rb : (int)blockIdx.x) % stat_stripes(C)) * 2 * C + ch0;
+        double* red = P.red + (size_t)(rb % stat_stripes(C)) * 2 * C + ch0;
         atomicAdd(&red[i], s1);
         atomicAdd(&red[C + i], s2);
     }
@@ -959,11 +966,7 @@ hipError_t launch_bn_apply(const BnApplyGroup& g, int dtype, bool fused_loss, hi
 hipError_t launch_bn_bwd_reduce(const BnBwdGroup& g, int dtype, hipStream_t s) {
     if (g.total_blocks <= 0) return hipSuccess;
     const size_t lds = (size_t)4 * g.cmax * sizeof(float);
-    // narrow tensors (at most 64 channels): 256-thread workgroups -- with 512 threads half of the 256 workgroups of a
-    // 32 x 32 x 16 tensor have no trip at all and the others' final sum over the row lanes is twice as long
-    int widest = 0;
-    for (int i = 0; i < g.nprob; ++i) widest = g.p[i].C > widest ? g.p[i].C : widest;
-    if (bn_reduce_threads(widest) == 256) {
+    if (g.threads == 256) {
         if (dtype == 1) hipLaunchKernelGGL((bn_bwd_reduce_kernel<bf16_t, 256>), dim3(g.total_blocks), dim3(256), lds, s, g);
         else hipLaunchKernelGGL((bn_bwd_reduce_kernel<float, 256>), dim3(g.total_blocks), dim3(256), lds, s, g);
         return hipGetLastError();

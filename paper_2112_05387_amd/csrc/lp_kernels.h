@@ -209,11 +209,13 @@ struct BnBwdProb {       // add: optional addend of the apply pass with the layo
     double* red; float* dgamma; float* dbeta;
     int M, C, relu;
     int slice, per;       // as in BnApplyProb (per: apply pass)
+    int parts, lanes, groups;    // reduction: pieces of the rows, their row lanes, and how many of them a workgroup does
     int block_start, nblocks;
 };
 struct BnBwdGroup {
     int nprob, total_blocks; float eps;
     int cmax;             // as above
+    int threads;          // of a workgroup of the reduction
     BnBwdProb p[kMaxGroup];
 };
 
@@ -341,12 +343,14 @@ constexpr int kStatStripes = 8;
 __host__ __device__ inline int stat_stripes(int C) { return C <= 64 ? 8 : (C <= 320 ? 4 : 1); }
 __host__ __device__ inline size_t stat_bytes(int C) { return sizeof(double) * 2 * (size_t)C * kStatStripes; }
 constexpr int kBnReduceBlock = 512;      // threads per workgroup of the BN backward reduction (measured: 256 -7 %, 1024 -20 %)
-// ... and 256 for launches whose widest tensor has at most 64 channels (see launch_bn_bwd_reduce)
+// ... and 256 for launches whose widest tensor has at most 64 channels: with 512 half of the 256 workgroups of a 32 x 32 x 16
+// tensor have no trip at all and the others' final sum over the row lanes is twice as long.  The row lanes of whole rows
+// follow from it, and the order of the sums from those.
 inline int bn_reduce_threads(int cmax) { return cmax <= 64 ? 256 : kBnReduceBlock; }
 // Channels of a workgroup of the batch-norm passes (apply, backward), 0: all of them.  A workgroup computes the coefficients of its channels
 // from the sums first, 16 bytes a channel, stripe and sum: for 320 to 2048 channels that is as much as its 32 KB of a tensor.
 // A small tensor also has few rows a workgroup can share out: 294 rows of 2048 channels were 5 workgroups of the backward reduction
-// and are 48.  Slices are whole 128-byte lines of bf16.  ResNet-50 step of 6 samples 1529 -> 1432 us, of 64 5724 -> 5695, WRN-28-10
+// and are 80.  Slices are whole 128-byte lines of bf16.  ResNet-50 step of 6 samples 1529 -> 1432 us, of 64 5724 -> 5695, WRN-28-10
 // in pre-activation order 1942 -> 1892; 160 channels (WRN-28-10's first stage) have no such slice and keep whole rows.
 inline int bn_slice(int C) { return C > 128 && C % 128 == 0 ? 128 : C > 64 && C % 64 == 0 ? 64 : 0; }
 constexpr int kElemVecsPerBlock = 2048;  // 16-byte vectors handled by one workgroup
