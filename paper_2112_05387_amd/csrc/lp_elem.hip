@@ -2,6 +2,8 @@
 // (reduce / apply), the local penalty / augmented-Lagrangian loss and terminal adjoint, the multiplier
 // update, the classification head, max pooling and buffer clears.  NHWC, 16-byte accesses with the
 // channel index fastest, fp32 arithmetic, wavefront/LDS reductions, one atomic per channel per workgroup.
+#include <algorithm>
+
 #include "lp_kernels.h"
 #include "lp_mma.h"
 #include "lp_vec.h"
@@ -795,9 +797,10 @@ __device__ __forceinline__ void fc_bwd_w(const HeadProb& P, int block) {
 // The same sums where those reads are what it takes (36 us for 64 samples x 1000 classes x 2048 channels): one thread per
 // channel and four classes, pooled read once for them, 32 samples in flight, their dz through LDS, 128 samples at a time.
 // For small layers the longer thread is the slower one: 12 us against 8 for 128 samples x 10 classes x 64 channels.
-__device__ __forceinline__ void fc_bwd_w_tiles(const HeadProb& P, int block) {
-    constexpr int NB = 128, U = 32;
-    __shared__ float s_dz[NB][kFcClasses];
+constexpr int kFcTileSamples = 128;
+__device__ __forceinline__ void fc_bwd_w_tiles(const HeadProb& P, int block, float* s_dp) {
+    constexpr int NB = kFcTileSamples, U = 32;
+    float (*const s_dz)[kFcClasses] = reinterpret_cast<float (*)[kFcClasses]>(s_dp);
     const int jb = (P.classes + kFcClasses - 1) / kFcClasses, j0 = block % jb * kFcClasses, c = block / jb * 256 + threadIdx.x;
     const float* __restrict__ x = P.pooled + min(c, P.C - 1);
     float s[kFcClasses], sb[kFcClasses];
@@ -835,19 +838,22 @@ __device__ __forceinline__ void fc_bwd_w_tiles(const HeadProb& P, int block) {
     }
 }
 // dfeat[n,p,c] = (sum_j dz[n,j]*W[j,c]) / HW
-template <typename T>
-__device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block) {
+template <typename T, bool IN_LDS>
+__device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block, float* s_dp) {
     // One block per sample and chunk of 256 channels: d pooled[c] = sum_j dlogits[j] * w[j][c] (lanes along c: coalesced
     // rows of w, summed in the order of the classes), then the block broadcasts it, divided by the number of pixels, to
     // every pixel of the sample with 16-byte stores.
     constexpr int EPV = Vec<T>::N;
-    extern __shared__ float s_dp[];      // 256 floats, then the sample's `classes` logit gradients
+    // s_dp: 256 floats, then (IN_LDS) the sample's `classes` logit gradients
     const int n = block % P.N, cbase = block / P.N * 256, C = P.C, classes = P.classes;
     const int nc = min(256, C - cbase);
     const float inv = 1.f / (float)P.HW;
     float* s_dl = s_dp + 256;
-    for (int j = threadIdx.x; j < classes; j += 256) s_dl[j] = P.dlogits[(size_t)n * classes + j];
-    __syncthreads();
+    if (IN_LDS) {
+        for (int j = threadIdx.x; j < classes; j += 256) s_dl[j] = P.dlogits[(size_t)n * classes + j];
+        __syncthreads();
+    }
+    auto dl = [&](int j) __attribute__((always_inline)) { return IN_LDS ? s_dl[j] : P.dlogits[(size_t)n * classes + j]; };
     if ((int)threadIdx.x < nc) {
         const int c = cbase + threadIdx.x;
         float acc = 0.f;
@@ -861,21 +867,21 @@ __device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block) {
 #pragma unroll
             for (int u = 0; u < 64; ++u) w[u] = P.w[(size_t)(j + u) * C + c];
 #pragma unroll
-            for (int u = 0; u < 64; ++u) acc += s_dl[j + u] * w[u];
+            for (int u = 0; u < 64; ++u) acc += dl(j + u) * w[u];
         }
         for (; j + 15 < classes; j += 16) {
             float w[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) w[u] = P.w[(size_t)(j + u) * C + c];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) acc += s_dl[j + u] * w[u];
+            for (int u = 0; u < 16; ++u) acc += dl(j + u) * w[u];
         }
         if (j + 7 < classes) {
             float w[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) w[u] = P.w[(size_t)(j + u) * C + c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += s_dl[j + u] * w[u];
+            for (int u = 0; u < 8; ++u) acc += dl(j + u) * w[u];
             j += 8;
         }
         for (; j < classes; j += 4) {
@@ -883,7 +889,7 @@ __device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) w[u] = P.w[(size_t)min(j + u, classes - 1) * C + c];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) if (j + u < classes) acc += s_dl[j + u] * w[u];
+            for (int u = 0; u < 4; ++u) if (j + u < classes) acc += dl(j + u) * w[u];
         }
         s_dp[threadIdx.x] = acc * inv;
     }
@@ -900,10 +906,13 @@ __device__ __forceinline__ void fc_bwd_x(const HeadProb& P, int block) {
 }
 // Both halves of the linear layer's backward pass: they read the same logit gradients and neither waits for the other, so
 // they are one launch, the workgroups of the half that the next launches wait for (dfeat) first.
-template <typename T, bool TILED>
+// The halves' arrays share their LDS, which a workgroup has one of: 40193 to 40704 classes fit a compute unit's 160 KB only so, and
+// the logit gradients of more are read from memory.
+template <typename T, bool TILED, bool IN_LDS>
 __global__ __launch_bounds__(256) void fc_bwd_kernel(const HeadProb P, int xblocks) {
-    if ((int)blockIdx.x < xblocks) { fc_bwd_x<T>(P, blockIdx.x); return; }
-    if (TILED) fc_bwd_w_tiles(P, (int)blockIdx.x - xblocks);
+    extern __shared__ __attribute__((aligned(16))) float s_dp[];
+    if ((int)blockIdx.x < xblocks) { fc_bwd_x<T, IN_LDS>(P, blockIdx.x, s_dp); return; }
+    if (TILED) fc_bwd_w_tiles(P, (int)blockIdx.x - xblocks, s_dp);
     else fc_bwd_w(P, (int)blockIdx.x - xblocks);
 }
 
@@ -1043,18 +1052,22 @@ hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s) {
         hipLaunchKernelGGL(fc_fwd_kernel, dim3((p.N * p.classes + 3) / 4), dim3(256), 0, s, p);
     return hipGetLastError();
 }
-template <typename T>
+template <typename T, bool IN_LDS>
 static void head_bwd(const HeadProb& p, hipStream_t s) {
     const int cb = (p.C + 255) / 256, xblocks = p.N * cb;
-    const size_t lds = (size_t)(256 + p.classes) * sizeof(float);
+    const size_t lds = std::max(256 + (IN_LDS ? p.classes : 0), kFcTileSamples * kFcClasses) * sizeof(float);
     if (fc_bwd_w_tiled(p))
-        hipLaunchKernelGGL((fc_bwd_kernel<T, true>), dim3(xblocks + (p.classes + kFcClasses - 1) / kFcClasses * cb), dim3(256), lds, s, p, xblocks);
+        hipLaunchKernelGGL((fc_bwd_kernel<T, true, IN_LDS>), dim3(xblocks + (p.classes + kFcClasses - 1) / kFcClasses * cb), dim3(256), lds, s, p, xblocks);
     else
-        hipLaunchKernelGGL((fc_bwd_kernel<T, false>), dim3(xblocks + (p.classes * p.C + 255) / 256), dim3(256), lds, s, p, xblocks);
+        hipLaunchKernelGGL((fc_bwd_kernel<T, false, IN_LDS>), dim3(xblocks + (p.classes * p.C + 255) / 256), dim3(256), lds, s, p, xblocks);
 }
 hipError_t launch_head_bwd(const HeadProb& p, int dtype, hipStream_t s) {
-    if (dtype == 1) head_bwd<bf16_t>(p, s);
-    else head_bwd<float>(p, s);
+    constexpr int kMostInLds = 160 * 1024 / (int)sizeof(float) - 256;
+    if (p.classes <= kMostInLds) {
+        if (dtype == 1) head_bwd<bf16_t, true>(p, s);
+        else head_bwd<float, true>(p, s);
+    } else if (dtype == 1) head_bwd<bf16_t, false>(p, s);
+    else head_bwd<float, false>(p, s);
     return hipGetLastError();
 }
 hipError_t launch_zero_selected(float* v, uint32_t mask, int n, float* v2, uint32_t mask2, int n2, hipStream_t s) {

@@ -169,6 +169,16 @@ def test_linear_layer_kernels(batch, classes, width, tiled):
     assert B.lp_debug_linear_kernels(batch, classes, width) == tiled
     net = cfg._assemble("linear", [[Block("bottleneck", width, width, 8, 1, False)]], batch, 2, 2, width, 0, 0, classes, seed=47)
     check_units(net)
+
+
+@pytest.mark.parametrize("batch,classes,width", [
+    # as many logit gradients as a compute unit's LDS has room for, one more; both filter gradients, the tiled one's array in the same LDS
+    (8, 40600, 16), (8, 40704, 16), (8, 40705, 16), (2, 40704, 8), (2, 40705, 8), (2, 50001, 24)])
+def test_many_classes(batch, classes, width):
+    say("case many classes", batch, classes, width)
+    check_units(cfg._assemble("classes", [[Block("bottleneck", width, width, 8, 1, False)]], batch, 2, 2, width, 0, 0, classes, seed=67))
+
+
 def step_outputs(net, separate):
     """Tensors of one local step through the specialised kernels, or through those they stand in for; and what was launched."""
     import torch
