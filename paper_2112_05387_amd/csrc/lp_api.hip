@@ -1629,8 +1629,8 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
 static void plan_wgrad_splits(WgradGroup& g, int unit, const SplitCost& cost, int min_chunk) {
     SplitPart part[kMaxGroup];
     for (int i = 0; i < g.nprob; ++i) part[i] = {g.p[i].tiles_m * g.p[i].tiles_n, (g.p[i].M + unit - 1) / unit, 1};
-    int rest_split = 1, rest = plan_wgrad_pieces(part, g.nprob, rest_split, cost, min_chunk);
-    if (g.nprob == kMaxGroup) rest = 0;
+    int rest_split = 1;
+    const int rest = plan_wgrad_pieces(part, g.nprob, rest_split, cost, min_chunk, g.nprob < kMaxGroup);
     auto set = [unit](WgradProb& p, int tile0, int ntile, int ks) {
         const int kt = (p.M + unit - 1) / unit;
         p.tile0 = tile0; p.ntile = ntile;

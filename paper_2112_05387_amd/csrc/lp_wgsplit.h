@@ -49,8 +49,8 @@ constexpr SplitCost kTileCost = {512, 26, 6};
 // Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
 // are the pieces and the last round would be nearly empty (288 tiles), the tiles of that round -- the last `rest` of the last
 // problem -- are cut finer, so that one more, short round holds them.  Returns rest (0: nothing more to cut), cuts in
-// `rest_split`.
-inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split, const SplitCost& c = kFastCost, int min_chunk = 16) {
+// `rest_split`.  may_cut: the launch has an entry left for that rest; without one the plan is the best that needs none.
+inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split, const SplitCost& c = kFastCost, int min_chunk = 16, bool may_cut = true) {
     int max_kt = 1, best_chunk = min_chunk, rest = 0;
     double best = 1e300;
     for (int i = 0; i < n; ++i) max_kt = p[i].kt > max_kt ? p[i].kt : max_kt;
@@ -67,7 +67,7 @@ inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split, const SplitCo
         if (cost < best) { best = cost; best_chunk = chunk; rest = 0; }
         const int over = (int)(blocks % c.slots), s = over ? c.slots / over : 1;
         const SplitPart& q = p[n - 1];
-        if (!whole || blocks < c.slots || s < 2 || over >= q.tiles || q.kt / s < 8) continue;
+        if (!may_cut || !whole || blocks < c.slots || s < 2 || over >= q.tiles || q.kt / s < 8) continue;
         const double two = (double)(blocks / c.slots) * c.round(chunk, true) + c.round((q.kt + s - 1) / s, false);
         if (two < best) { best = two; best_chunk = chunk; rest = over; rest_split = s; }
     }

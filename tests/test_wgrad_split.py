@@ -6,6 +6,7 @@ import subprocess
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2112_05387_amd", "csrc")
 
 PROGRAM = r"""
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -36,7 +37,26 @@ static int deal(const std::vector<int>& n) {
     }
     return 0;
 }
+// cost of a plan without a rest, and the lowest of any
+static double cost_of(const SplitPart* p, int n, const SplitCost& c, int chunk) {
+    long blocks = 0;
+    bool whole = true;
+    for (int i = 0; i < n; ++i) { const int ks = (p[i].kt + chunk - 1) / chunk; blocks += (long)p[i].tiles * ks; whole = whole && ks == 1; }
+    return (double)((blocks + c.slots - 1) / c.slots) * c.round(chunk, whole);
+}
+static int full_group(int tiles, int kt, const SplitCost& c) {
+    SplitPart p[16];
+    for (auto& q : p) q = {tiles, kt, 0};
+    int s = 0;
+    CHECK(plan_wgrad_pieces(p, 16, s, c, 16, false) == 0);
+    double best = 1e300;
+    for (int chunk = 16; chunk <= kt; ++chunk) best = std::min(best, cost_of(p, 16, c, chunk));
+    CHECK(cost_of(p, 16, c, (kt + p[0].ksplit - 1) / p[0].ksplit) <= best);
+    return 0;
+}
 int main() {
+    // no entry for a rest: the best plan that needs none (with one, 17 tiles of 1024 units are whole, and 16 of the 272 are the rest)
+    CHECK(!full_group(17, 1024, kFastCost) && !full_group(17, 512, kFastCost) && !full_group(33, 1024, kFastCost) && !full_group(33, 700, kTileCost));
     std::srand(1);
     CHECK(!deal({51, 51, 51, 51, 51}) && !deal({1}) && !deal({7, 9, 0, 8}) && !deal({255}) && !deal({256, 32}));
     for (int t = 0; t < 300; ++t) {
