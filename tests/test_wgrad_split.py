@@ -54,7 +54,34 @@ static int full_group(int tiles, int kt, const SplitCost& c) {
     CHECK(cost_of(p, 16, c, (kt + p[0].ksplit - 1) / p[0].ksplit) <= best);
     return 0;
 }
+// the same plan as a search through every length
+static int every_length(SplitPart* p, int n, const SplitCost& c, int min_chunk, bool may_cut) {
+    SplitPart q[16];
+    int max_kt = 1, best_chunk = min_chunk, rest = 0, rest_split = 1, s = 0;
+    double best = 1e300;
+    for (int i = 0; i < n; ++i) { q[i] = p[i]; max_kt = std::max(max_kt, p[i].kt); }
+    for (int chunk = min_chunk; chunk <= std::max(max_kt, min_chunk); ++chunk) {
+        long blocks = 0;
+        bool whole = true;
+        for (int i = 0; i < n; ++i) { const int ks = (p[i].kt + chunk - 1) / chunk; blocks += (long)p[i].tiles * ks; whole = whole && ks == 1; }
+        const double cost = cost_of(p, n, c, chunk);
+        if (cost < best) { best = cost; best_chunk = chunk; rest = 0; rest_split = 1; }
+        const int over = (int)(blocks % c.slots), cut = over ? c.slots / over : 1;
+        if (!may_cut || !whole || blocks < c.slots || cut < 2 || over >= p[n - 1].tiles || p[n - 1].kt / cut < 8) continue;
+        const double two = (double)(blocks / c.slots) * c.round(chunk, true) + c.round((p[n - 1].kt + cut - 1) / cut, false);
+        if (two < best) { best = two; best_chunk = chunk; rest = over; rest_split = cut; }
+    }
+    CHECK(plan_wgrad_pieces(q, n, s, c, min_chunk, may_cut) == rest && (!rest || s == rest_split));
+    for (int i = 0; i < n; ++i) CHECK(q[i].ksplit == (p[i].kt + best_chunk - 1) / best_chunk);
+    return 0;
+}
 int main() {
+    for (int t = 0; t < 600; ++t) {
+        SplitPart p[16];
+        const int n = 1 + std::rand() % 16, kt = 1 + std::rand() % 4200;
+        for (int i = 0; i < n; ++i) p[i] = {1 + std::rand() % 60, t % 3 == 0 ? kt : 1 + std::rand() % (t % 3 == 1 ? 300 : 4200), 0};
+        CHECK(!every_length(p, n, t % 2 ? kFastCost : kTileCost, t % 2 ? 16 : 4, t % 5 != 0));
+    }
     // no entry for a rest: the best plan that needs none (with one, 17 tiles of 1024 units are whole, and 16 of the 272 are the rest)
     CHECK(!full_group(17, 1024, kFastCost) && !full_group(17, 512, kFastCost) && !full_group(33, 1024, kFastCost) && !full_group(33, 700, kTileCost));
     std::srand(1);
