@@ -402,7 +402,8 @@ lp_status lp_debug_filter_load_extent(int kernel, int bk, int bn, int nw, int Nc
  *   {narrow convolution with the batch norms folded in, forward and data-gradient (every layer of a network has to have it),
  *    filter gradient from one input window, small tiles of the wide layers for the forward launch, ... for the data-gradient
  *    (strides of 1 and 2)}
- * with `lanes` stream lanes in flight and the layer alone in its launch.  Errors: LP_ERR_INVALID_ARG. */
+ * with `lanes` stream lanes in flight and the layer, which has a batch norm behind it, alone in its launch.  Errors:
+ * LP_ERR_INVALID_ARG. */
 lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Cout, int R, int stride, int lanes, int* taken);
 
 /* Does the linear layer of a head (N samples, C channels) run in its tiled kernels (host only)?  tiled[2] = {forward, filter

@@ -3354,7 +3354,8 @@ lp_status lp_debug_layer_kernels(int dtype, int N, int H, int W, int Cin, int Co
         for (const Op& o : st) if (ops.empty() || o.key() == ops[0]->key()) ops.push_back(&o);
         if (ops.empty() || ops.size() > (size_t)kMaxGroup) continue;
         ConvGroup g; g.nprob = (int)ops.size();
-        for (int i = 0; i < g.nprob; ++i) g.p[i] = ops[i]->conv;
+        double stats;                              // a forward layer has batch statistics (planning asks whether, not where)
+        for (int i = 0; i < g.nprob; ++i) { g.p[i] = ops[i]->conv; g.p[i].stats = d == 0 ? &stats : nullptr; }
         SConvGroup small; size_t lds = 0;
         taken[2 + d] = plan_conv(&net, ops.data(), g.nprob, g, small, lds).small ? 1 : 0;
     }

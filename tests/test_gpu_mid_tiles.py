@@ -5,7 +5,7 @@ import pytest
 
 from tests.gpu_common import say
 from tests.gpu_unitwise import check_units
-from tests.test_gpu_narrow import CONV, assert_same_bits, launches
+from tests.test_gpu_narrow import CONV, SMALL_TILES, assert_same_bits, launches
 from workloads import configs as cfg
 from workloads.configs import Block
 
@@ -49,3 +49,25 @@ def test_bits_of_the_large_tiles(case, tiles):
     """Every output of a step, batch statistics included, is the one of the tiles these stand in for, bit for bit."""
     say("case mid tiles, bits", case)
     assert_same_bits(net_of(**case), (CONV, min(tiles)))
+
+
+@pytest.mark.parametrize("batch,side,width", [(8, 8, 320), (1, 14, 256), (1, 16, 320), (1, 28, 256), (6, 14, 256), (1, 8, 160), (3, 8, 640), (2, 32, 192)])
+def test_query_names_the_kernel_that_runs(batch, side, width):
+    """The host's answer for a layer alone in its launch against the launch records of a network of one block (both forward
+    layers, with their batch statistics, and the second one's data gradient)."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    say("case layer query", batch, side, width)
+    net = cfg._assemble("query", [[Block("basic", width, width, width, 1, False)]], batch, side, side, width, 0, 0, 7, seed=71)
+    net.dtype = "bf16"
+    want = B.lp_debug_layer_kernels("bf16", batch, side, side, width, width, 3, 1)
+    ls = LocalStep(net)
+    try:
+        B.lp_profile_enable(ls.net, 2)
+        ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        small = [r["cfg"] == SMALL_TILES for r in B.lp_profile_fetch(ls.net) if r["kind"] == CONV]
+    finally:
+        ls.close()
+    assert small == [want["small_fwd"], want["small_fwd"], want["small_dgrad"]], (small, want)
