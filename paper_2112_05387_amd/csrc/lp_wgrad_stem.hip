@@ -1,4 +1,4 @@
-// bf16 filter gradient of an image-facing layer (3 input channels, 16 / 32 / 64 output channels, R x R up to 7 x 7) on gfx950.
+// bf16 filter gradient of an image-facing layer (3 input channels, 16 / 32 / 64 output channels, 3 x 3 or 7 x 7) on gfx950.
 //
 //   dW[co][(r,s,c)] = sum over output pixels (n,ho,wo) of dY[n,ho,wo][co] * X[n, ho*stride - pad + r, wo*stride - pad + s][c]
 //
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(WS_SETS * WS_NT) void conv_wgrad_stem_kernel(const 
         unsigned char* const row = xs + ((ih + 8 * pad) & 7) * G.plane;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int e = 2 * i + h, col = (e * 43691) >> 17, c = e - col * 3, cp = col + pad;      // e / 3 for e < 2^17
+            const int e = 2 * i + h, col = (e * 43691) >> 17, c = e - col * 3, cp = col + pad;      // e / 3 (rows of at most 1024 pixels: e < 3072)
             const int idx = cp / S, par = cp - idx * S;
             if (cp <= maxcol) *reinterpret_cast<unsigned short*>(row + ((c * S + par) * G.idxp + idx) * 2) = (unsigned short)(h ? v >> 16 : v);
         }
@@ -205,10 +205,12 @@ __global__ __launch_bounds__(WS_SETS * WS_NT) void conv_wgrad_stem_kernel(const 
     }
 }
 
-// the layers this kernel takes (the image has to be aligned to four bytes as well: wgrad_stem_aligned)
+// The layers this kernel takes: those a network has, 3 x 3 with stride 1, 2 or 4 (modules and AuxNets) and 7 x 7 with stride 2.
+// The image has to be aligned to four bytes as well, which the caller sees to.
 bool wgrad_stem_ok(const WgradProb& p) {
     if (p.Cin != WS_C || (p.Cout != 16 && p.Cout != 32 && p.Cout != 64)) return false;
-    if (p.R != p.S || p.R < 1 || p.R > 7 || p.stride < 1 || p.stride > 4 || p.pad < 0 || p.pad >= p.R || p.Wo > 256 || p.IW > 1024) return false;
+    const bool r3 = p.R == 3 && (p.stride == 1 || p.stride == 2 || p.stride == 4), r7 = p.R == 7 && p.stride == 2;
+    if (p.R != p.S || !(r3 || r7) || p.pad != p.R / 2 || p.Wo > 256 || p.IW > 1024) return false;
     if ((p.IW * WS_C) % 2 || std::min(p.stride, p.R) * (p.IW * WS_C / 2) > WS_U * WS_NT || (p.Kg + 15) / 16 > 4 * WS_CG) return false;
     if ((double)p.M * p.Cout * 2.0 >= 2.0e9) return false;
     return stem_geom(p).set_bytes <= 64 * 1024;

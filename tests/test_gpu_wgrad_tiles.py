@@ -47,3 +47,44 @@ def test_odd_image_rows_keep_the_general_kernel():
     net.dtype = "bf16"
     check_units(net)
     assert (WGRAD, STEM) not in launches(net)
+
+
+@pytest.mark.parametrize("stride,side,cout", [(4, (32, 224), 64), (4, (56, 200), 32), (4, (24, 212), 16), (2, (16, 224), 64), (2, (12, 256), 32)])
+def test_strided_image_facing_layers(stride, side, cout):
+    """The filter gradient of an AuxNet with stride 2, and with one that is more than its filter, where a step to the next output row
+    leaves image rows out and one column class has no tap: images too wide for the narrow kernel, rows of 50 to 128 outputs.
+    Oracle's distillation gradient in its storage-rounding mode, at the tolerance of the other tests of it."""
+    import torch
+    import workloads as wl
+    from oracle import lpref
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    from tests.helpers import rel_err, store
+    say("case strided image-facing layer", stride, side, cout)
+    first = [] if stride == 4 else [Block("basic", 16, cout, cout, 2, True)]
+    net = cfg._assemble("strided", [first or [Block("basic", cout, cout, cout, 1, False)], [Block("basic", cout, cout, cout, 1, False)]],
+                        3, side[0], side[1], 3, 2 if stride == 4 else 1, cout if stride == 4 else 16, 7, seed=79)
+    net.dtype = "bf16"
+    m = net.modules[1]
+    assert (m.H, m.W) == (side[0] // stride, side[1] // stride)
+    net.aux = [cfg.AuxDesc(cin=3, cout=cout, stride=stride, relu=False)]
+    image, auxp = wl.make_image(net), wl.make_aux_params(net, 0)
+    out = lpref.auxnet_forward(net.aux[0], image, auxp, net.bn_eps, wl.round_bf16)
+    target = store(net, out + wl.normal(79, "target", out.shape, 0.5))
+    ls = LocalStep(net)
+    try:
+        ls.set_x(0, image)
+        ls.set_aux_params(0, auxp)
+        ls.auxnet_forward()
+        ls.set_x(1, target)
+        B.lp_profile_enable(ls.net, 2)
+        ls.auxnet_distill_grad(0.5)
+        torch.cuda.synchronize()
+        ran = {(r["kind"], r["cfg"]) for r in B.lp_profile_fetch(ls.net)}
+        loss, grads = lpref.auxnet_distill_grad(net.aux[0], image, auxp, target, net.bn_eps, 0.5, wl.round_bf16)
+        errs = [rel_err(g, r) for g, r in zip(ls.get_aux_grads(0), grads)]
+    finally:
+        ls.close()
+    say("    ", ["%.1e" % e for e in errs])
+    assert (WGRAD, STEM) in ran, ran
+    assert all(e <= 2e-2 for e in errs), errs
