@@ -11,7 +11,7 @@ from workloads.configs import Block
 
 pytestmark = pytest.mark.gpu
 
-WGRAD, TILE, STEM = 10, 9, 10
+WGRAD, WGRAD_3X3, TILE, STEM = 10, 8, 9, 10
 
 
 def net_of(batch, side, widths, stem=1, stem_cout=16, kind="basic"):
@@ -88,3 +88,44 @@ def test_strided_image_facing_layers(stride, side, cout):
     say("    ", ["%.1e" % e for e in errs])
     assert (WGRAD, STEM) in ran, ran
     assert all(e <= 2e-2 for e in errs), errs
+
+
+def test_update_with_the_rest_of_a_launch_cut_finer():
+    """288 output tiles, each summed by one workgroup, but for the 32 of the second round, which are cut in eight: the parameter update
+    in the epilogue is then done by whole tiles at once and by the last of eight workgroups that share a tile's ticket.  Oracle's
+    update rule on the gradients of the step, at the tolerance of the other tests of it."""
+    import numpy as np
+    import torch
+    from oracle import lpref
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    from tests.gpu_unitwise import seeded_step_inputs
+    from tests.helpers import rel_err
+    from tests.test_gpu_parity import _read_like_grads, _read_params
+    say("case update, rest cut finer")
+    net = cfg._assemble("rest", [[Block("basic", 640, 640, 640, 1, False) for _ in range(3)]], 32, 8, 8, 640, 0, 0, 7, seed=73)
+    net.dtype = "bf16"
+    check_units(net)
+    params, _, labels, xs, _ = seeded_step_inputs(net)
+    ls = LocalStep(net)
+    try:
+        ls.set_params(0, params[0])
+        ls.set_x(0, xs[0])
+        ls.set_labels(labels)
+        vel = [torch.zeros_like(d) for d in ls.dparams]
+        ls.set_fused_update(True, 1.0, 0.9, 5e-4, velocity=vel)
+        B.lp_profile_enable(ls.net, 2)
+        for _ in range(2):
+            w, v = _read_params(ls, 0), _read_like_grads(ls, vel, 0)
+            ls.local_step(net.rho, 1.0)
+            torch.cuda.synchronize()
+            got_w, got_v = _read_params(ls, 0), _read_like_grads(ls, vel, 0)
+            for i, (info, g) in enumerate(zip(ls.tables[0], ls.get_grads(0))):
+                want_w, want_v = lpref.sgd_update(w[i], g.astype(np.float64), 1.0, v[i], 0.9, 5e-4)
+                tol = 4e-3 if info.dtype == B.LP_BF16 else 1e-6              # one rounding of the stored value
+                assert rel_err(got_w[i], want_w) <= tol and rel_err(got_v[i], want_v) <= 1e-6, i
+                assert np.max(np.abs(want_w - w[i])) >= 5 * tol * np.max(np.abs(want_w)), i       # a missing update would show
+        blocks = [(r["nprob"], r["blocks"]) for r in B.lp_profile_fetch(ls.net) if (r["kind"], r["cfg"]) == (WGRAD, WGRAD_3X3)]
+    finally:
+        ls.close()
+    assert blocks == [(6, 256 + 32 * 8)] * 2, blocks
