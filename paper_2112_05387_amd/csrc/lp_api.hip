@@ -1712,7 +1712,7 @@ static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const Cf
         tot += blocks;
         const double lines = nslab * (npx(TH) * p.segs + ntaps * 32) * 4.5 / 2.1e3;
         t_new += (double)blocks * (lines + 5.0);
-        t_real += (double)blocks * (2.3 * lines + 5.0);    // measured; the comparison with the large tiles is calibrated on t_new
+        t_real += (double)blocks * (2.3 * lines + 5.0);
         work_old += (long)c.tiles_m * c.tiles_n;
         t_old += (double)c.tiles_m * c.tiles_n * (2.0 * ci.BM * ci.BN * c.Kg / (waves >= 8 ? 7.5e6 : waves >= 4 ? 5e6 : 2.5e6) + (waves >= 8 ? 25.0 : 10.0));
     }
@@ -1724,7 +1724,15 @@ static bool plan_sconv(const lp_net* net, const ConvGroup& g, bool win, const Cf
     // average time of a workgroup times the number of rounds; what the model calls equal is left where it was (batch 24 of the
     // same network: launches within 15 % of each other made the step 1 % slower)
     const double r_old = (double)((work_old + cap - 1) / cap) / work_old, r_new = (double)((tot + cap - 1) / cap) / tot;
-    time = t_real * r_new + (g.p[0].stats ? 6.0 : 0.0);    // and the launch that sums its statistics
+    // Two estimates of one workgroup, each good for one comparison.  A line takes 2.3 times the 4.5 clocks where a workgroup waits for
+    // its own (t_real: 8 x 8 x 640 33 us, 16 x 16 x 320 21), which is what the comparison with the 32-pixel waves wants.  The one with the
+    // large tiles below is of two throughputs, whose figures are both too good by about that much (calibrated as a pair on whole steps).
+    // In t_real, workgroups beyond the lane's share find room where the other lanes are not in a convolution: a share and a quarter,
+    // but half a round more than one at the least.  (Whole rounds of the bare share sent WRN-28-10's 640-channel layers of 12 samples,
+    // 120 workgroups, to waves of 32 pixels: step of 12 / 14 samples 1257 / 1291 us, 1160 / 1205 now, 1223 / 1280 with large tiles; 4 / 8 /
+    // 20 / 24 samples within 1 %.  Two shares: 24 and 32 samples 4 and 10 % slower.)
+    const double rounds = tot <= cap ? 1.0 : std::max(1.5, tot / (1.25 * cap));
+    time = t_real / tot * rounds + (g.p[0].stats ? 6.0 : 0.0);         // and the launch that sums its statistics
     return t_new * r_new < 0.85 * t_old * r_old;
 }
 

@@ -329,6 +329,15 @@ def test_specialised_kernels_refuse_sizes_beyond_their_fields(dtype):
             assert not t["small_fwd"] and not t["small_dgrad"], (h, cin, cout, r)
 
 
+def test_small_tiles_beyond_a_lanes_share_of_the_chip():
+    """8 x 8 layers of 640 channels with four stream lanes: the small tiles are 20 workgroups for two samples, and the other lanes leave
+    them more than a quarter of the chip; from some 20 samples on the larger tiles, which read less, are the faster ones."""
+    q = B.lp_debug_layer_kernels
+    for samples, small in ((2, True), (6, True), (12, True), (14, True), (32, False), (64, False)):
+        t = q("bf16", samples, 8, 8, 640, 640, 3, 1, lanes=4)
+        assert (t["small_fwd"], t["small_dgrad"]) == (small, small), (samples, t)
+
+
 def _lanes(net, after=None, whole_step=True):
     h = B.lp_net_create(net.modules, net.aux, net.dtype, net.bn_eps)
     try:
