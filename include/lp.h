@@ -299,6 +299,8 @@ lp_status lp_sgd_update(struct lp_net* net, void* stream, int aux, uint32_t mask
  * net until the update is switched off (on = 0: the other arguments are ignored) or set again.  Results equal those of
  * lp_module_backward followed by lp_sgd_update up to the order in which the partial sums were added; in the
  * deterministic mode bit for bit.  Nothing else of a step may read params[k] while its backward pass runs.
+ * While it is on, the filter gradients of strided, 1x1 and image-facing bf16 layers run in the general kernel: those that run them
+ * otherwise have no update in their epilogue.
  * Errors: LP_ERR_INVALID_ARG. */
 lp_status lp_net_set_fused_update(struct lp_net* net, int on, float lr, float momentum, float weight_decay,
                                   float* const* velocity, float* const* master);

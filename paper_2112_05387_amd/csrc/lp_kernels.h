@@ -264,6 +264,8 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                FAST_128x320 = 10, FAST_128x160 = 11,   // ... its four- and two-wave variants, chosen per launch
                FAST64_256x320 = 12, FAST64_128x320 = 13, FAST64_128x160 = 14,   // ... with k-tiles of 64 channels
                FAST_256x160 = 15, FAST64_256x160 = 16,  // four-wave variants of the 160-wide family
+               // (13, 14 and 16 are launched by nets of separate passes only: elsewhere a layer of whole 64-channel k-tiles that would have
+               // them takes a tile below or the small ones; they say what bits, and how many rows a partial statistic, those have)
                // ... with waves of 32 pixels: a ring of two k-tiles (two or three workgroups per CU), of three or four (R3, R4)
                MID_128x128 = 17, MID_128x128_R3 = 18, MID_128x32_R4 = 19, MID_64x128_R3 = 20, MID_64x64_R4 = 25, MID_128x64 = 26, MID_128x64_R3 = 27,
                MID_256x128_R3 = 28, MID_256x64_R3 = 29, MID_256x32_R4 = 30,

@@ -18,7 +18,7 @@
 // reads) and makes the three fragments of eight from them: tap 0 as they are, tap 2 from the second register on, tap 1 by four
 // v_alignbit.  LDS reads per k-step of 32 pixels: 152 instead of the 240 that twelve waves of 80 x 80 with a fragment per tap
 // took (LDS bandwidth and the wait for the first fragments were what the matrix cores stood still for).  Five layers of
-// 131072 pixels x 160 channels in one launch: 351 -> 282 us (1.07 PFLOP/s); 32768 x 320: 342 -> 275; 8192 x 640: 301 -> 232..257.
+// 131072 pixels x 160 channels in one launch: 351 -> 282 us (1.07 PFLOP/s); 32768 x 320: 342 -> 275; 8192 x 640: 301 -> 250.
 //
 // A ring stage holds 64 pixels: the dY rows of pixels m0..m0+63 and ONE window of X shared by the three taps,
 // the 66 pixels m0-1+(r-1)W .. m0+64+(r-1)W (flattened pixel index; tap s of pixel m reads window row m-m0+s).
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(WF_NT, 2) void conv_wgrad_fast_kernel(const WgradGr
     const __amdgpu_buffer_rsrc_t rsrc_y = make_rsrc(P.dy, (unsigned)((size_t)P.M * Cout * 2));
     const __amdgpu_buffer_rsrc_t rsrc_x = make_rsrc(P.x, (unsigned)((size_t)P.M * Cin * 2));
 
-    // ---- loads: wave-load q = wave + 12*i; q < 20: bytes [1024*q, +1024) of the dY rows, else of the X window.
+    // ---- loads: wave-load q = wave + 8*i; q < 20: bytes [1024*q, +1024) of the dY rows, else of the X window.
     // Lane l supplies the 16 bytes that land at +16*l, i.e. row b/320 and the (swizzled) channel chunk of that row.
     // (Everything is recomputed per stage rather than kept in registers: the accumulators need them.)
     const bool six = wave + WF_NW * (WF_LPW - 1) < WF_SLABS;

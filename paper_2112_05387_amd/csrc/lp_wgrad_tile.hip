@@ -8,7 +8,7 @@
 // pixel-major and the sum runs over the pixels.
 // A block (256 threads, 2 x 2 waves) owns BM (128 or 64) output channels x 128 columns and a chunk of the pixels; its partial
 // sums are added to dW with fp32 atomics, or stored where its chunk is the whole sum.  A ring stage is 64 pixels (32 or 24 KB);
-// with a ring of two, two blocks (BM = 64: three) share a compute unit, and one's atomics and first loads run beside the other's products.
+// with a ring of two, two blocks (BM = 64: three, by LDS and registers) share a compute unit, and one's atomics and first loads run beside the other's products.
 // A lane of a load always serves the same column, so the tap and the channel are found once; per stage it divides its pixel
 // into (image, row, column), which a 1x1 layer without stride does not need.
 // LDS rows are 256 B (64 channels: 128 B); the 32-byte channel pairs of a row trade places so that the eight rows of a

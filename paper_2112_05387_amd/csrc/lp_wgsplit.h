@@ -41,9 +41,17 @@ struct SplitPart { int tiles, kt, ksplit; };
 // of them where partial sums are added with atomics and `store` where its piece is the whole reduction.
 struct SplitCost { int slots, add, store; double round(int chunk, bool whole) const { return chunk + (whole ? store : add); } };
 // lp_wgrad_fast.hip: units of 32 pixels (0.9 us each), a workgroup has a compute unit to itself (8192 pixels x 640 channels, five
-// layers, one and two rounds of 256 and 128 units: 251 us with stores, 282 with atomics, 337 with atomics and half the length).
+// layers, one and two rounds of 256 and 128 units: 250 us with stores, 282 with atomics, 337 with atomics and half the length).
+// Longer pieces are longer chains of fp32 sums.  Six such layers in one launch add up 8192 pixels in one accumulator, where four
+// pieces of 2048 met in atomics before `store` was told apart: their gradients are 0.4 to 1.4e-6 (2-norm) from float64 instead of
+// 0.3 to 1.05e-6.  The 160-channel layers' pieces of 7712 pixels, as ever, are at 0.5e-6.
+// Both costs are of a launch that has the chip to itself, whatever the number of stream lanes.
 constexpr SplitCost kFastCost = {256, 52, 16};
-// lp_wgrad_tile.hip: units of 64 pixels (1 us each with two workgroups on a compute unit), 64 KB of atomics a workgroup.
+// lp_wgrad_tile.hip: units of 64 pixels (1 us each with two workgroups on a compute unit), 64 KB of atomics a workgroup.  Fitted to tiles of
+// 128 rows; those of 64 rows, three to a compute unit, are planned with the same 512 slots.  ResNet-50's 14 x 14 layers of 64 samples are
+// 0.3 to 0.4e-6 from float64 with these pieces (0.15e-6 with the shorter ones of the general kernel), its 7 x 7
+// ones 0.3 to 0.9e-6 (0.15 to 0.5e-6), its 56 x 56 ones 0.13e-6 (0.23e-6).
+// A second level of sums in registers every 1024 pixels takes the former to 0.2e-6; its 64 registers cost ResNet-50's step 0.6 %.
 constexpr SplitCost kTileCost = {512, 26, 6};
 
 // Pieces of one length for the whole launch, the length that makes rounds x (piece + epilogue) shortest.  Where whole tiles
