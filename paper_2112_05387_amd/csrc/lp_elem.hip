@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
 // a slice, whose rows are shorter, holds `groups` of them.  With the row lanes of the slice instead, sums as exact but not
 // the same, the bf16 adjoints of wide networks moved by 2e-3 to 8e-3 of their norm, single roundings of the auxiliary
 // variables with them, and the gradient of an AuxNet, which is distilled from just those, by 0.02 to 0.10.
-// Slices run in workgroups of 256 threads, of which three share a compute unit (152 registers), whole rows in 512: the sliced
+// Slices run in workgroups of 256 threads, of which three share a compute unit (155 registers), whole rows in 512: the sliced
 // ones in 512 as well, or with three or four trips under way, or one trip and four waves a SIMD, are each the slower choice
 // (ResNet-50 step of 6 / 64 samples 1434 / 5576 us; 1450 / 5597, 1457 / 5663, 1494 / 6048; without slices 1448 / 5531).
 template <typename T, int NT>
@@ -196,7 +196,8 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     const T* __restrict__ gp = reinterpret_cast<const T*>(P.g);
     const T* __restrict__ y = reinterpret_cast<const T*>(P.y);
     const int rl = P.lanes;                      // row lanes of a part
-    const int tcv = threadIdx.x % cv, lane_row = threadIdx.x / cv, group = lane_row / rl, trl = lane_row - group * rl;
+    const int tcv = threadIdx.x % cv, lane_row = threadIdx.x / cv;
+    const int group = P.groups > 1 ? lane_row / rl : lane_row >= rl, trl = lane_row - group * rl;
     const int part = rb * P.groups + group;
     const bool active = group < P.groups && part < P.parts;
     const int c0 = tcv * EPV;                    // in the slice
@@ -267,8 +268,10 @@ __global__ __launch_bounds__(NT) void bn_bwd_reduce_kernel(const BnBwdGroup g) {
     for (int i = threadIdx.x; i < cv * EPV; i += NT) {
         double s1 = 0.0, s2 = 0.0;
         for (int q = 0; q < here; ++q) {
+            const float* const p = s_red + (q * rl * cv * EPV + i) * 2;
             float f1 = 0.f, f2 = 0.f;
-            for (int l = q * rl; l < (q + 1) * rl; ++l) { f1 += s_red[((l * cv * EPV) + i) * 2]; f2 += s_red[((l * cv * EPV) + i) * 2 + 1]; }
+#pragma unroll 8
+            for (int l = 0; l < rl; ++l) { f1 += p[l * cv * EPV * 2]; f2 += p[l * cv * EPV * 2 + 1]; }
             s1 += f1; s2 += f2;
         }
         double* red = P.red + (size_t)(rb % stat_stripes(C)) * 2 * C + ch0;
