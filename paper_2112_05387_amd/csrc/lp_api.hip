@@ -498,7 +498,7 @@ struct Builder {
         FWgradProb p; memset(&p, 0, sizeof(p));
         p.Cin = u.cin; p.Cout = u.cout; p.IH = u.H; p.IW = u.W; p.Ho = u.Ho; p.Wo = u.Wo; p.stride = u.stride; p.pad = u.pad; p.R = u.R;
         const int CB = std::min(u.cout, 32), CI = std::min(u.cin, 32), vy = CB * esz / 16, vx = CI * esz / 16;
-        int TH = std::min(u.Ho, std::max(1, (u.cin <= 16 && u.cout <= 16 ? 256 : 128) / u.Wo));
+        int TH = std::min(u.Ho, std::max(1, (u.cin <= 16 && u.cout <= 16 ? 256 : 128) / (fwgrad_split(u.cin, u.cout, esz) ? 2 : 1) / u.Wo));
         for (;; --TH) {
             if (TH < 1) return o;
             p.TH = TH; p.WH = (TH - 1) * u.stride + u.R; p.WW = (u.Wo - 1) * u.stride + u.R;
@@ -2039,11 +2039,11 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.x = resolve(o.r[0], b); p.dy = resolve(o.r[1], b); p.dw = (float*)resolve(o.r[2], b);
                     lds = std::max(lds, fwgrad_lds_bytes(p, (int)net->esz));
                 }
-                // one number of tiles per workgroup for the whole launch: four workgroups per compute unit
+                // one number of tiles per workgroup for the whole launch: two workgroups per compute unit
                 auto blocks = [](const FWgradProb& p) { return (p.Cout == 64 ? 2 : 1) * (p.Cin == 64 ? 2 : 1); };
                 long work = 0;
                 for (int i = 0; i < n; ++i) work += (long)g.p[i].ntiles * blocks(g.p[i]);
-                const int per = (int)std::max(1l, (work + 1023) / 1024);
+                const int per = (int)std::max(1l, (work + 511) / 512);
                 int tot = 0;
                 for (int i = 0; i < kMaxGroup; ++i) {
                     if (i >= n) { g.start[i] = INT_MAX; continue; }

@@ -87,6 +87,39 @@ def test_narrow_units(case, dtype):
     assert FOLDED in kinds and FOLDED_WGRAD in kinds, kinds
 
 
+@pytest.mark.parametrize("batch,side,stride", [(1, (8, 8), 2), (9, (12, 20), 2), (3, (7, 9), 1), (32, (32, 32), 2)])
+def test_fp32_filter_gradients_in_bf16_parts(batch, side, stride):
+    """Blocks wider than 16 x 16 channels multiply fp32 values as sums of three bf16 each.  Bound (2-norm against float64): what the
+    matrix instruction cuts of a product is below 2^-24 of the largest of eight, which is some ten times their root mean
+    square, 6e-7; the chains of fp32 sums 2e-7 to 4e-7.  Without one of the six products it would be 2^-18 / sqrt(3) = 2e-6 or more."""
+    import numpy as np
+    import torch
+    from oracle import lpref
+    from paper_2112_05387_amd import LocalStep
+    say("case fp32 filter gradients", batch, side, stride)
+    net = narrow_net(batch, side, dtype="f32", stride=stride)
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    ls = LocalStep(net, keep_gradients=True)
+    try:
+        for k in range(net.K):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        for k in range(net.K):
+            grads = ls.get_grads(k)
+            for u in ls.units(k):
+                x, dy = ls.fetch(u.in_, (u.N, u.H, u.W, u.cin)), ls.fetch(u.dy, (u.N, u.Ho, u.Wo, u.cout))
+                want = lpref.conv_wgrad(x, dy, params[k][u.t_w].shape, u.stride, u.pad)
+                err = np.linalg.norm(grads[u.t_w] - want) / np.linalg.norm(want)
+                say(f"  m{k} {u.cin} -> {u.cout}, {u.R}x{u.R}/{u.stride}: {err:.1e}")
+                assert err < 1e-6, (k, u.cin, u.cout, err)
+    finally:
+        ls.close()
+
+
 def test_narrow_separate_calls():
     """The single entry points run the folded passes too, each from what the one before has left in the workspace."""
     say("case narrow, separate calls")
