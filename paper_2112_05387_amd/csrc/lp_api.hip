@@ -1415,16 +1415,27 @@ static void build_step_programs(lp_net* net, int k) {
         if (!last && !out.empty() && out.back().size() == 1 && out.back()[0].type == OP_BN_APPLY &&
             out.back()[0].r[1].space == SP_Y)
             last_apply = &out.back()[0];
+        // ... and the head of a small network its cross-entropy
+        Op* head = nullptr;
+        if (last && !out.empty() && out.back().size() == 1 && out.back()[0].type == OP_HEAD_FWD && head_with_loss(out.back()[0].head, (int)net->esz))
+            head = &out.back()[0];
         if (last_apply) {
             last_apply->cfg = 1;
             last_apply->r[9] = mk(SP_XNEXT, k, 0); last_apply->r[10] = mk(SP_LAM, k, 0);
             last_apply->r[11] = mk(SP_DY, k, 0); last_apply->r[12] = mk(SP_LOSS, 0, sizeof(float) * k);
+        } else if (head) {
+            head->r[5] = mk(SP_DLOGITS, 0, 0); head->r[9] = mk(SP_LABELS, 0, 0); head->r[10] = mk(SP_LOSS, 0, sizeof(float) * k);
+            // the pass in front of it shares a launch with the other modules' last passes, which evaluate their losses
+            if (variant >= 2 && out.size() > 1 && out[out.size() - 2].size() == 1 && out[out.size() - 2][0].type == OP_BN_APPLY) out[out.size() - 2][0].cfg = 1;
         } else {
             out.push_back(loss_step);
             for (Op& o : out.back()) o.phase = 1;
         }
         // the clears and filter re-layouts of the backward pass go with those of the forward pass: nothing in between touches
-        // the sums, gradients, tickets and re-laid-out filters (buffers of their own), nor the parameters
+        // the sums, gradients, tickets and re-laid-out filters (buffers of their own), nor the parameters; the module's loss
+        // (and |F_k(x_k) - x_{k+1}|^2), which only its own kernels add to, is cleared there too
+        if (out.empty() || !is_prep(out.front())) out.insert(out.begin(), Step());
+        out.front().push_back(Builder{net}.fill(mk(SP_LOSS, 0, sizeof(float) * k), sizeof(float)));
         size_t at = 0;
         for (; at < bw.size() && is_prep(bw[at]) && is_prep(out.front()); ++at)
             out.front().insert(out.front().end(), bw[at].begin(), bw[at].end());
@@ -1930,7 +1941,12 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     const Op& o = *ops[base + i];
                     PrepProb& p = g.p[i]; p = o.prep;
                     g.start[i] = tot;
-                    if (o.type == OP_FILL) {
+                    if (o.type == OP_FILL && o.r[0].space == SP_LOSS) {
+                        float* const loss = (float*)resolve(o.r[0], b);
+                        const int k = (int)(loss - b.loss);
+                        p.dst = loss; p.src = net->r2 && k < net->K - 1 ? net->r2 + k : nullptr; p.vecs = -1;
+                        ++tot;
+                    } else if (o.type == OP_FILL) {
                         p.src = nullptr; p.dst = resolve(o.r[0], b); p.vecs = (int)(o.fill_bytes / 16);
                         tot += elem_blocks(o.fill_bytes / 16);
                     } else {
@@ -2122,7 +2138,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     if (fused_loss) {      // the local loss and terminal adjoint (and the multiplier update) ride on this pass
                         p.xn = resolve(o.r[9], b); p.lam = resolve(o.r[10], b); p.dy = resolve(o.r[11], b);
                         p.loss = (float*)resolve(o.r[12], b);
-                        p.r2 = net->r2 ? net->r2 + (p.loss - b.loss) : nullptr;      // loss + k  ->  r2 + k
+                        p.r2 = net->r2 && p.loss ? net->r2 + (p.loss - b.loss) : nullptr;      // loss + k  ->  r2 + k
                         p.lam_out = b.mstep != 0.f ? const_cast<void*>(p.lam) : nullptr;
                     }
                     p.block_start = tot; bn_apply_blocks(p, epv, net->separate); tot += p.nblocks;
@@ -2241,6 +2257,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.b = (const float*)resolve(o.r[3], b); p.logits = (float*)resolve(o.r[4], b);
                     p.dlogits = (const float*)resolve(o.r[5], b); p.dw = (float*)resolve(o.r[6], b);
                     p.db = (float*)resolve(o.r[7], b); p.dfeat = resolve(o.r[8], b);
+                    p.labels = (const int32_t*)resolve(o.r[9], b); p.loss = (float*)resolve(o.r[10], b);
                     err = type == OP_HEAD_FWD ? launch_head_fwd(p, dt, s) : launch_head_bwd(p, dt, s);
                 }
                 break;
@@ -2987,9 +3004,6 @@ lp_status lp_local_step(struct lp_net* net, void* stream, uint32_t module_mask, 
         progs.push_back(folded(net) ? (opt_dx ? &m.fstep_dx0 : &m.fstep) : (opt_dx ? &m.step_dx0 : &m.step));
     }
     hipStream_t s = (hipStream_t)stream;
-    // loss[k] = 0 for the selected modules, ahead of the fork (the loss kernels accumulate with atomics)
-    hipError_t err = launch_zero_selected(loss, module_mask, net->K, net->K > 1 ? net->r2 : nullptr, module_mask & ((1u << (net->K - 1)) - 1u), net->K - 1, s);
-    if (err != hipSuccess) return fail(LP_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(err));
     Bindings b; b.ws = net->ws; b.x = x; b.params = params; b.y = y; b.logits = logits;
     b.dparams = dparams; b.dy = dy; b.dx = dx; b.dlogits = dlogits;
     if (net->fused_update) { b.vel = net->fu_vel.data(); b.master = net->fu_master.data(); }

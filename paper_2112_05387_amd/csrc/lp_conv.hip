@@ -568,9 +568,17 @@ __global__ __launch_bounds__(256) void prep_kernel(const PrepGroup) {
     const int first = g.start[pi];
     const void* const src = g.p[pi].src;
     void* const dst = g.p[pi].dst;
+    const int n = g.p[pi].vecs;
     int b = (int)blockIdx.x - first;
+    if (n < 0) {                                   // the scalars a module's loss kernels add to
+        if (threadIdx.x == 0) {
+            *reinterpret_cast<float*>(dst) = 0.f;
+            if (src) *reinterpret_cast<float*>(const_cast<void*>(src)) = 0.f;
+        }
+        return;
+    }
     if (!src) {
-        const int n = g.p[pi].vecs, v0 = b * kElemVecsPerBlock, v1 = n - v0 < kElemVecsPerBlock ? n : v0 + kElemVecsPerBlock;
+        const int v0 = b * kElemVecsPerBlock, v1 = n - v0 < kElemVecsPerBlock ? n : v0 + kElemVecsPerBlock;
         const u32x4 z = {0u, 0u, 0u, 0u};
         for (int v = v0 + (int)threadIdx.x; v < v1; v += 256) reinterpret_cast<u32x4*>(dst)[v] = z;
         return;

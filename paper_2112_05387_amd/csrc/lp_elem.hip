@@ -45,7 +45,7 @@ template <int EPV> __device__ __forceinline__ BnSpan bn_span(int block, int C, i
 __device__ __forceinline__ float block_sum(float v, float* s_tmp);
 
 // FUSE: the pass also evaluates the local loss and terminal adjoint of the interface tensor it writes (exactly the
-// arithmetic of loss_kernel, on the value as stored, vector by vector in the same order)
+// arithmetic of loss_kernel, on the value as stored, vector by vector in the same order), of the problems that have one
 template <typename T, bool FUSE>
 __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup g) {
     constexpr int EPV = Vec<T>::N;
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
             fraw[u] = Vec<T>::load_raw(y + vc * EPV);
             if (P.skip_mode) skraw[u] = Vec<T>::load_raw(skip + vc * EPV);
             if constexpr (FUSE) {
-                xnraw[u] = Vec<T>::load_raw(xn + vc * EPV);
+                if (xn) xnraw[u] = Vec<T>::load_raw(xn + vc * EPV);
                 if (lam) lmraw[u] = Vec<T>::load_raw(lam + vc * EPV);
             }
         }
@@ -125,6 +125,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
             }
             Vec<T>::store(out + v * EPV, o);
             if constexpr (FUSE) {
+                if (!xn) continue;                          // a problem without a loss
                 if constexpr (sizeof(T) == 2) {             // the loss is defined on F_k(x_k) as stored
 #pragma unroll
                     for (int e = 0; e < EPV; e += 2) {
@@ -153,6 +154,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
         }
     }
     if constexpr (FUSE) {
+        if (!xn) return;
         __shared__ float s_tmp[kElemBlock / 64];
         const float tot = block_sum(lacc, s_tmp);
         if (threadIdx.x == 0 && tot != 0.f) atomicAdd(P.loss, g.scale * tot);
@@ -919,13 +921,11 @@ __global__ __launch_bounds__(256) void fc_bwd_kernel(const HeadProb P, int xbloc
     else fc_bwd_w(P, (int)blockIdx.x - xblocks);
 }
 
-// softmax cross-entropy, mini-batch mean; one workgroup per sample
-__global__ __launch_bounds__(kElemBlock) void ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                        float* loss, float* __restrict__ dlogits, int N, int classes) {
+// softmax cross-entropy of sample n by one workgroup, mini-batch mean; z: its logits
+__device__ __forceinline__ void ce_sample(const float* z, const int n, const int32_t* __restrict__ labels, float* loss,
+                                          float* __restrict__ dlogits, int N, int classes) {
     __shared__ float s_tmp[kElemBlock / 64];
     __shared__ float s_max[kElemBlock / 64];
-    const int n = blockIdx.x;
-    const float* z = logits + (size_t)n * classes;
     float mx = -INFINITY;
     for (int j = threadIdx.x; j < classes; j += kElemBlock) mx = fmaxf(mx, z[j]);
 #pragma unroll
@@ -945,6 +945,59 @@ __global__ __launch_bounds__(kElemBlock) void ce_kernel(const float* __restrict_
         dlogits[(size_t)n * classes + j] = p * invN;
     }
     if (threadIdx.x == 0) atomicAdd(loss, (logf(se) + mx - z[lab]) * invN);
+}
+__global__ __launch_bounds__(kElemBlock) void ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
+                                                        float* loss, float* __restrict__ dlogits, int N, int classes) {
+    ce_sample(logits + (size_t)blockIdx.x * classes, blockIdx.x, labels, loss, dlogits, N, classes);
+}
+// The head of a small network in one launch, a workgroup per sample: the sums of avgpool_kernel, fc_fwd_kernel and ce_kernel in
+// their order, with the sample's features, means and logits in LDS between them.  Bound by its three trips to memory (features,
+// then nothing but stores; weights and label are requested with the features).
+template <typename T>
+__global__ __launch_bounds__(kElemBlock) void head_loss_kernel(const HeadProb P) {
+    constexpr int EPV = Vec<T>::N, W = kElemBlock / 64, PRE = 4;
+    extern __shared__ __attribute__((aligned(16))) char s_head[];
+    const int n = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int HW = P.HW, C = P.C, nvec = HW * (C / EPV);
+    T* const s_feat = reinterpret_cast<T*>(s_head);
+    float* const s_pool = reinterpret_cast<float*>(s_head + (size_t)nvec * 16);
+    float* const s_z = s_pool + C;
+    const u32x4* __restrict__ f = reinterpret_cast<const u32x4*>(P.feat) + (size_t)n * nvec;
+    u32x4 v[PRE];                                  // this thread's first vectors, and its wave's first weights
+    float w[PRE];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) v[u] = f[min(tid + u * kElemBlock, nvec - 1)];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) w[u] = P.w[(size_t)min(wave + u * W, P.classes - 1) * C + min(lane, C - 1)];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u)
+        if (tid + u * kElemBlock < nvec) reinterpret_cast<u32x4*>(s_feat)[tid + u * kElemBlock] = v[u];
+    for (int i = tid + PRE * kElemBlock; i < nvec; i += kElemBlock) reinterpret_cast<u32x4*>(s_feat)[i] = f[i];
+    __syncthreads();
+    for (int c = tid; c < C; c += kElemBlock) {
+        float s = 0.f;
+#pragma unroll 16
+        for (int p = 0; p < HW; ++p) s += to_float(s_feat[p * C + c]);
+        s /= (float)HW;
+        s_pool[c] = s;
+        P.pooled[(size_t)n * C + c] = s;
+    }
+    __syncthreads();
+    for (int j = wave, u = 0; j < P.classes; j += W, ++u) {
+        float s = 0.f;
+        const float w0 = u < PRE ? (u == 0 ? w[0] : u == 1 ? w[1] : u == 2 ? w[2] : w[3]) : P.w[(size_t)j * C + min(lane, C - 1)];
+        if (lane < C) s += s_pool[lane] * w0;
+        for (int c = lane + 64; c < C; c += 64) s += s_pool[c] * P.w[(size_t)j * C + c];
+#pragma unroll
+        for (int sh = 32; sh > 0; sh >>= 1) s += __shfl_xor(s, sh, 64);
+        if (lane == 0) {
+            s += P.b[j];
+            s_z[j] = s;
+            P.logits[(size_t)n * P.classes + j] = s;
+        }
+    }
+    __syncthreads();
+    ce_sample(s_z, n, P.labels, P.loss, const_cast<float*>(P.dlogits), P.N, P.classes);
 }
 
 __global__ void zero_selected_kernel(float* v, uint32_t mask, int n, float* v2, uint32_t mask2, int n2) {
@@ -1047,6 +1100,12 @@ bool fc_bwd_w_tiled(const HeadProb& p) {
 }
 hipError_t launch_head_fwd(const HeadProb& p, int dtype, hipStream_t s) {
     const int epv = dtype == 1 ? 8 : 4;
+    if (p.labels) {
+        const size_t lds = (size_t)p.HW * p.C * (dtype == 1 ? 2 : 4) + (p.C + p.classes) * sizeof(float);
+        if (dtype == 1) hipLaunchKernelGGL(head_loss_kernel<bf16_t>, dim3(p.N), dim3(kElemBlock), lds, s, p);
+        else hipLaunchKernelGGL(head_loss_kernel<float>, dim3(p.N), dim3(kElemBlock), lds, s, p);
+        return hipGetLastError();
+    }
     LP_DISPATCH_T(dtype, avgpool_kernel, dim3((p.N * (p.C / epv) + 63) / 64), dim3(64), s, p);
     if (fc_fwd_tiled(p)) {
         const size_t waves = (size_t)((p.N + kFcSamples - 1) / kFcSamples) * ((p.classes + kFcClasses - 1) / kFcClasses);

@@ -172,7 +172,7 @@ struct PrepProb {
     const void* src;         // NULL: clear
     void* dst;
     int Cout, RS, Cin;       // filter [Cout][RS][Cin] -> [Cin][RS][Cout]
-    int vecs;                // clear: 16-byte vectors
+    int vecs;                // clear: 16-byte vectors; -1: one float at dst and, where there is a src, another there
 };
 constexpr int kPrepMax = 96;                       // problems of a launch: 3.4 of the 4 KiB of kernel arguments
 struct PrepGroup {
@@ -255,8 +255,14 @@ struct PoolProb {        // max pooling R x R, stride, pad on NHWC
 struct HeadProb {        // global average pool + linear
     const void* feat; float* pooled; const float* w; const float* b; float* logits;
     const float* dlogits; float* dw; float* db; void* dfeat;
+    const int32_t* labels; float* loss;      // forward with the cross-entropy behind it (head_with_loss): dlogits is written
     int N, HW, C, classes;
 };
+// Is the head of a step one launch, a workgroup per sample (pooling, linear layer, cross-entropy)?  Where a sample's features fit the LDS
+// and every sample can afford to read all weights: three dependent launches of 2 to 6 us otherwise, each of them 4 us of the
+// host's time (with the losses cleared in the step's first launch, not one of their own, and the last module's last
+// pass in the launch of the others': tiny 81 -> 62 us, ResNet-20 of 3 samples in bf16 192 -> 173, of 16 229 -> 209, 2 in fp32 232 -> 211).
+inline bool head_with_loss(const HeadProb& p, int esz) { return (size_t)p.HW * p.C * esz <= 32 * 1024 && p.C * p.classes <= 16384; }
 
 // ---- launchers (host side; return hipError_t of the launch) ----------------------------------------
 // tile configuration ids of the implicit-GEMM kernels

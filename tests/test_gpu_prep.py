@@ -62,3 +62,46 @@ def test_first_launch(K, width, dtype):
     for a, b in zip(one, two):                       # the same kernels on the same inputs, sums of up to 48 pixels in another order
         assert torch.isfinite(a).all()
         assert float((a - b).norm()) <= 1e-4 * float(b.norm())
+
+
+@pytest.mark.parametrize("batch,side,width,classes,dtype,one", [
+    # one pixel, one class; fewer channels than a wave has lanes, a second round of classes; more channels than lanes
+    (1, (1, 1), 16, 1, "f32", True), (3, (4, 4), 16, 23, "f32", True), (5, (3, 3), 72, 7, "bf16", True), (2, (8, 4), 200, 81, "f32", True),
+    # the largest sample (32 KB) and the most weights (16384) of the rule, and one more of each
+    (2, (16, 8), 64, 256, "f32", True), (2, (17, 8), 64, 10, "f32", False), (2, (4, 4), 64, 257, "bf16", False)])
+def test_head_with_loss(batch, side, width, classes, dtype, one):
+    """Pooling, linear layer and cross-entropy of a small head in one launch of the whole step: the logits, their gradients and the losses of
+    the single entry points, which launch them one after the other; every step clears the losses it adds to."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    from tests.gpu_unitwise import seeded_step_inputs
+    say("case head with loss", batch, side, width, classes, dtype)
+    net = cfg._assemble("head", [[Block("basic", width, width, width, 1, False)] for _ in range(2)], batch, side[0], side[1], 3, 1, width, classes, seed=61)
+    net.dtype = dtype
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    ls = LocalStep(net)
+    try:
+        for k in range(2):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        ls.module_forward()
+        ls.local_loss_grad(net.rho, 1.0)
+        want = [t.clone() for t in (ls.logits, ls.dlogits, ls.loss, ls.r2)]
+        for t in (ls.logits, ls.dlogits, ls.loss, ls.r2):
+            t.fill_(7.0)
+        B.lp_profile_enable(ls.net, 2)
+        for _ in range(2):
+            ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        kinds = {r["kind"] for r in B.lp_profile_fetch(ls.net)}
+        B.lp_profile_enable(ls.net, 0)
+        assert (13 in kinds) == (not one), kinds
+        for a, b in zip((ls.logits, ls.dlogits), want):
+            assert torch.equal(a, b) if net.dtype == "f32" else float((a - b).abs().max()) <= 1e-6 * float(b.abs().max() + 1.0)
+        for a, b in zip((ls.loss, ls.r2), want[2:]):      # atomics of up to 50 workgroups in another order
+            assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max() + 1.0)
+    finally:
+        ls.close()
