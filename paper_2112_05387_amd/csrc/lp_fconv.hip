@@ -293,9 +293,13 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
                     if ((i0 + u) * wstep >= WHW) continue;
                     float a[EPV], b[EPV], o[EPV];
                     Vec<T>::unpack(r1[u], a);
-                    Vec<T>::unpack(r2[u], b);
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c0[e], a[e], c1[e]) + fmaf(c2[e], b[e], c3[e]);
+                    for (int e = 0; e < EPV; ++e) o[e] = fmaf(c0[e], a[e], c1[e]);
+                    if (two) {
+                        Vec<T>::unpack(r2[u], b);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) o[e] += fmaf(c2[e], b[e], c3[e]);
+                    }
                     if (relu) {
 #pragma unroll
                         for (int e = 0; e < EPV; ++e) o[e] = fmaxf(o[e], 0.f);
@@ -316,7 +320,7 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
     // separate pass does with its 256 / (Ncol / 8) row lanes, so 64 channels use half of the threads.
     constexpr int LGN = BN / EPV == 2 ? 1 : BN / EPV == 4 ? 2 : 3;                      // log2 vectors per result pixel
     constexpr int ER = ORD == 2 ? 32 : FC_NT >> LGN;
-    constexpr int PART = ORD == 2 ? 64 : 4096 / BN, NP = ORD ? 2 : 1, EI = PART / ER;
+    constexpr int PART = ORD == 2 ? 64 : 4096 / BN, EI = PART / ER;
     const int ev = tid & ((1 << LGN) - 1);
     const int er = tid >> LGN;
     const size_t oimg = (size_t)n * P.OH * P.OW * P.Ncol;
@@ -348,16 +352,21 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nmt = (px + 15) >> 4;                // micro-tiles of 16 pixels in this tile
+    // micro-tile i of this wave: every fourth, in the ordered tiles MP consecutive ones of every part (a run of the statistics is one
+    // wave's, or two neighbours')
+    constexpr int NP = ORD ? 2 : 1, MP = MT / NP;
+    auto mtile = [&](int i) { return ORD ? i / MP * 4 * MP + wave * MP + i % MP : wave + 4 * i; };
     const char* ab[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        const int p = min((wave + 4 * i) * 16 + lr, px - 1);
+        const int p = min(mtile(i) * 16 + lr, px - 1);
         const int a = __mul24(p, P.odiv) >> 16, b = p - __mul24(a, OB);
         const int seg = ORD && segs > 1 && a >= P.TH ? 1 : 0;
         ab[i] = win + __mul24(__mul24((a - (seg ? P.TH : 0)) * P.imul + (seg ? SWH : 0), WW) + b * P.imul, PB) + cl * (int)sizeof(T);
     }
     const char* const fb = s_filt + lane * 16;
-    const int nm = (nmt - wave + 3) >> 2;          // micro-tiles of this wave; the loops compute 1, 2 or 4 without a branch per tile
+    // micro-tiles of this wave (an ordered tile has one part or both); the loops compute 1, 2 or 4 without a branch per tile
+    const int nm = ORD ? (px > PART ? MT : MP) : (nmt - wave + 3) >> 2;
     auto contract = [&](int tab, int slot, int steps) __attribute__((always_inline)) {
         const char* const fs = fb + slot * (NT * 1024);
         if constexpr (MT == 8) {                   // (eight at a time would need 64 registers for fragments)
@@ -412,13 +421,44 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
         if (part > 0) ahead(part);
         __syncthreads();                           // every wave is done with the window, or with the part before
 #pragma unroll
-        for (int i = 0; i < MT / NP; ++i) {
-            const int mt = wave + 4 * (part * (MT / NP) + i);
-            if (mt < nmt) {
+        for (int i = 0; i < MP; ++i) {
+            if (mtile(part * MP + i) < nmt) {
+                const int row = (ORD ? wave * MP + i : wave + 4 * i) * 16 + lg * 4;
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) res[((wave + 4 * i) * 16 + lg * 4 + r) * SP + j * 16 + lr] = acc[part * (MT / NP) + i][j][r];
+                    for (int r = 0; r < 4; ++r) res[(row + r) * SP + j * 16 + lr] = acc[part * MP + i][j][r];
+            }
+        }
+        // Statistics in the order of the implicit-GEMM kernel's epilogue: runs of 4 micro-tiles (2 with 64 channels), a lane's rows one after
+        // the other, of the values as stored.  They are in this wave's accumulators, the first half of a run in its neighbour's where
+        // a wave has half of one: the sums so far go on through LDS.  (Read back from the result's LDS, with a barrier more, the
+        // epilogue of a forward layer took 4.9 us of 16, of which 2.)
+        constexpr int WR = (ORD == 2 ? 2 : 4) / MP;         // waves of a run
+        float s1[NT], s2[NT];
+        auto run_sums = [&]() {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int i = 0; i < MP; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; r += 2) {
+                        const unsigned v = pack_bf16x2(acc[part * MP + i][j][r], acc[part * MP + i][j][r + 1]);
+                        const float lo = __uint_as_float(v << 16), hi = __uint_as_float(v & 0xffff0000u);
+                        s1[j] += lo; s2[j] = fmaf(lo, lo, s2[j]);
+                        s1[j] += hi; s2[j] = fmaf(hi, hi, s2[j]);
+                    }
+        };
+        float* const hop = s_red + 256 + ((wave >> 1) * NT * 64 + lane) * 2;
+        if constexpr (ORD != 0) {
+            if (stat_pass && (WR == 1 || !(wave & 1))) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j) { s1[j] = 0.f; s2[j] = 0.f; }
+                run_sums();
+                if (WR == 2) {
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) { hop[j * 128] = s1[j]; hop[j * 128 + 1] = s2[j]; }
+                }
             }
         }
         __syncthreads();
@@ -459,36 +499,28 @@ __device__ __forceinline__ void fconv_tile(FConvArg& P, const int t, const float
                 ecoef(2, c); ecoef(3, d);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * ((y[e] - c[e]) * d[e]); }
-            } else if (stat_pass) {
-#pragma unroll
-                for (int e = 0; e < EPV; e += 4) *reinterpret_cast<f32x4*>(rp + e) = f32x4{v[e], v[e + 1], v[e + 2], v[e + 3]};
-            } else {
+            } else if (!stat_pass) {
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) { q1[e] += v[e]; q2[e] += v[e] * v[e]; }
             }
         }
         if constexpr (ORD != 0) {
-            if (stat_pass) {
-                // runs of RW rows x 16 channels per wave: 64 rows, or 32 where the tile of that kernel is 64 x 64
-                __syncthreads();
-                constexpr int lgrw = ORD == 2 ? 5 : 6, runs = (PART >> lgrw) * NT;
-                for (int u = wave; u < runs; u += 4) {
-                    const int run = u / NT, j = u - run * NT, row0 = run << lgrw;
-                    float s1 = 0.f, s2 = 0.f;
-                    for (int i = 0; i < 1 << (lgrw - 4); ++i)
+            if (stat_pass && (WR == 1 || (wave & 1))) {
+                if (WR == 2) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int row = row0 + i * 16 + lg * 4 + r;
-                            if (part * PART + row < px) {
-                                const float x = res[row * SP + j * 16 + lr];
-                                s1 += x; s2 = fmaf(x, x, s2);
-                            }
-                        }
-                    s1 += __shfl_xor(s1, 16, 64); s2 += __shfl_xor(s2, 16, 64);
-                    s1 += __shfl_xor(s1, 32, 64); s2 += __shfl_xor(s2, 32, 64);
+                    for (int j = 0; j < NT; ++j) { s1[j] = hop[j * 128]; s2[j] = hop[j * 128 + 1]; }
+                    run_sums();
+                }
+                constexpr int lgrw = ORD == 2 ? 5 : 6;
+                const int run = (part * PART >> lgrw) + wave / WR;
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    float a = s1[j], b = s2[j];
+                    a += __shfl_xor(a, 16, 64); b += __shfl_xor(b, 16, 64);
+                    a += __shfl_xor(a, 32, 64); b += __shfl_xor(b, 32, 64);
                     if (lane < 16) {
-                        float* const q = s_red + (((part * PART >> lgrw) + run) * BN + j * 16 + lane) * 2;
-                        q[0] = s1; q[1] = s2;
+                        float* const q = s_red + (run * BN + j * 16 + lane) * 2;
+                        q[0] = a; q[1] = b;
                     }
                 }
             }
