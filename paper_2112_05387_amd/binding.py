@@ -21,7 +21,7 @@ EXPORTS = ["lp_net_create", "lp_net_destroy", "lp_net_param_bytes", "lp_net_num_
 
 KIND_NAMES = {0: "clears+filter_relayout", 1: "filter_relayout", 2: "conv_igemm(fwd/dgrad)", 3: "bn_apply", 4: "maxpool_fwd", 5: "head_fwd",
               6: "head_bwd", 7: "maxpool_bwd", 8: "bn_bwd_reduce", 9: "bn_bwd_apply", 10: "conv_wgrad", 11: "bn_stats", 12: "loss", 13: "cross_entropy", 14: "multiplier_update",
-              15: "relu_mask", 16: "sgd(small tensors)", 17: "conv_folded(fwd/dgrad)", 18: "conv_wgrad_narrow"}
+              15: "relu_mask", 16: "sgd(small tensors)", 17: "conv_folded(fwd/dgrad)", 18: "conv_wgrad_narrow", 19: "bn_bwd"}
 
 
 class lp_block_desc(ctypes.Structure):

@@ -101,7 +101,7 @@ static void* resolve(const Ref& r, const Bindings& b) {
 }
 
 enum OpType { OP_FILL = 0, OP_WTRANS, OP_CONV, OP_BN_APPLY, OP_POOL_FWD, OP_HEAD_FWD, OP_HEAD_BWD, OP_POOL_BWD,
-              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV, OP_FWGRAD };
+              OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY, OP_WGRAD, OP_BN_STATS, OP_LOSS, OP_CE, OP_MULT_UNUSED, OP_RELU_MASK, OP_SGD_REST, OP_FCONV, OP_FWGRAD, OP_BN_BWD };
 // tensor references of an OP_FCONV operation
 enum FcRef { F_IN = 0, F_IN2, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMMA2, F_BETA2, F_WT, F_OUT, F_ADD0, F_OSTATS,
              F_EY, F_ESTATS, F_EGAMMA, F_EBETA, F_ERED, F_EY2, F_ESTATS2, F_ERED2, F_COUNT };
@@ -591,8 +591,22 @@ struct WsAlloc {
 // gets the filter it belongs to (r[4]) and a run of completion tickets in the workspace (r[3], one per output tile;
 // cleared by the step that clears the gradients); one last step updates the tensors no filter-gradient kernel owns
 // (BN affine, head).  The operations carry these references always; they are bound only while the update is switched on.
+// Batch-norm backward passes of few rows (bn_bwd_small): the apply pass joins the reduction in front of it.
+static void join_small_bn(const lp_net* net, Program& P) {
+    for (size_t i = 0; i + 1 < P.size(); ++i) {
+        Step &s1 = P[i], &s2 = P[i + 1];
+        bool ok = !s1.empty() && s1.size() == s2.size();
+        for (size_t j = 0; ok && j < s1.size(); ++j)
+            ok = s1[j].type == OP_BN_BWD_REDUCE && s2[j].type == OP_BN_BWD_APPLY && s1[j].r[6].off == s2[j].r[6].off &&
+                 bn_bwd_small(s1[j].bnb.M, s1[j].bnb.C, (int)net->esz);
+        if (!ok) continue;
+        for (Op& o : s2) o.type = OP_BN_BWD;       // (it is the one that names the addend)
+        P.erase(P.begin() + i);
+    }
+}
 static void attach_update(lp_net* net, int k, WsAlloc& ws) {
     ModulePlan& m = net->mods[k];
+    for (Program* P : {&m.bwd, &m.bwd_dx0}) join_small_bn(net, *P);
     m.t_in_epilogue.assign(m.tensors.size(), 0);
     std::vector<size_t> cnt_off(m.tensors.size(), 0);
     m.ws_cnt0 = ws.off;
@@ -1567,6 +1581,7 @@ static lp_status build_aux(lp_net* net, int j, WsAlloc& ws) {
         }
     }
     a.bwd_b.push_back(wg_tail);
+    join_small_bn(net, a.bwd_b);
     return LP_OK;
 }
 
@@ -1624,6 +1639,7 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
             bytes = (double)o.bna.M * o.bna.C * e * ((o.bna.skip_mode ? 3.0 : 2.0) + (o.cfg == 1 ? 3.0 : 0.0)); break;
         case OP_BN_BWD_REDUCE: bytes = (double)o.bnb.M * o.bnb.C * e * 2.0; break;
         case OP_BN_BWD_APPLY: bytes = (double)o.bnb.M * o.bnb.C * e * (o.r[9].space != SP_NONE ? 4.0 : 3.0); break;
+        case OP_BN_BWD: bytes = (double)o.bnb.M * o.bnb.C * e * (o.r[9].space != SP_NONE ? 4.0 : 3.0); break;
         case OP_BN_STATS: bytes = (double)o.bnb.M * o.bnb.C * e; break;
         case OP_LOSS: bytes = (double)o.numel * e * 4.0; break;
         case OP_RELU_MASK: bytes = (double)o.numel * e * 3.0; break;
@@ -2147,6 +2163,17 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 g.total_blocks = tot;
                 err = launch_bn_apply(g, dt, fused_loss, s);
             } break;
+            case OP_BN_BWD:
+                if (net->deterministic || net->separate) {
+                    for (int type2 : {OP_BN_BWD_REDUCE, OP_BN_BWD_APPLY}) {
+                        std::vector<Op> two(n);
+                        std::vector<const Op*> at(n);
+                        for (int i = 0; i < n; ++i) { two[i] = *ops[base + i]; two[i].type = type2; at[i] = &two[i]; }
+                        if (err == hipSuccess) err = launch_group_impl(net, at, 0, n, b, s, nullptr, nullptr);
+                    }
+                    break;
+                }
+                [[fallthrough]];
             case OP_BN_STATS:
             case OP_BN_BWD_REDUCE:
             case OP_BN_BWD_APPLY: {
@@ -2164,14 +2191,15 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.dgamma = (float*)resolve(o.r[7], b); p.dbeta = (float*)resolve(o.r[8], b);
                     p.add = resolve(o.r[9], b);
                     p.block_start = tot;
-                    if (type == OP_BN_BWD_REDUCE) {
-                        // at least 64 rows per part, and (one trip of the reduction being four rows per row lane) no more parts
-                        // than trips: the order of the sums, which no slice changes.  A workgroup of a slice takes several parts
-                        // where one each would be more of them than run at once
+                    if (type == OP_BN_BWD) {
+                        bn_reduce_cut(p.M, p.C, epv, kBnReduceBlock, p.lanes, p.parts);
+                        p.nblocks = p.C / kBnSmallChannels;
+                    } else if (type == OP_BN_BWD_REDUCE) {
+                        // a workgroup of a slice takes several parts where one each would be more of them than run at once
                         p.slice = net->separate ? 0 : bn_slice(p.C);
                         const int S = p.slice ? p.slice : p.C, ns = p.C / S;
-                        p.lanes = std::max(1, bn_reduce_threads(widest) / (p.C / epv));
-                        p.parts = net->deterministic ? 1 : std::max(1, std::min(std::min(256, (p.M + 63) / 64), (p.M + 4 * p.lanes - 1) / (4 * p.lanes)));
+                        bn_reduce_cut(p.M, p.C, epv, bn_reduce_threads(widest), p.lanes, p.parts);
+                        if (net->deterministic) p.parts = 1;
                         p.groups = std::max(1, std::min(g.threads / (S / epv) / p.lanes, (p.parts * ns + 767) / 768));
                         p.nblocks = (p.parts + p.groups - 1) / p.groups * ns;
                         g.cmax = std::max(g.cmax, S);
@@ -2180,7 +2208,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     tot += p.nblocks;
                 }
                 g.total_blocks = tot;
-                err = type == OP_BN_STATS ? launch_bn_stats(g, dt, s)
+                err = type == OP_BN_BWD ? launch_bn_bwd_small(g, s)
+                      : type == OP_BN_STATS ? launch_bn_stats(g, dt, s)
                       : type == OP_BN_BWD_REDUCE ? launch_bn_bwd_reduce(g, dt, s) : launch_bn_bwd_apply(g, dt, s);
             } break;
             case OP_SGD_REST: {

@@ -429,6 +429,159 @@ __global__ __launch_bounds__(kElemBlock) void bn_bwd_apply_kernel(const BnBwdGro
     }
 }
 
+// Both passes of the batch-norm backward on few rows, bf16: a workgroup has all rows of 64 channels, so that the sums need no other
+// workgroup.  Two launches of 5 to 8 us, each of them two dependent trips to memory, become one, whose second reading of the two
+// tensors comes from its L2.  A thread has eight channels of a row lane of a part, as bn_bwd_reduce_kernel cuts the rows (parts x
+// lanes, trips of four rows); 64 of those at a time, round by round, the next trip requested ahead of this one's sums.  The order of
+// the fp32 sums is that of the two passes (see there), the parts meet in fp64.
+__global__ __launch_bounds__(kBnSmallThreads, 2) void bn_bwd_small_kernel(const BnBwdGroup g) {
+    constexpr int S = kBnSmallChannels, EPV = 8, CG = S / EPV, CH = kBnSmallThreads / CG, W = kBnSmallThreads / 64;
+    __shared__ __attribute__((aligned(16))) float s_part[CH * S * 2];
+    __shared__ double s_sum[W / 2 * S * 2];
+    __shared__ __attribute__((aligned(16))) float s_c[7 * S];
+    const BnBwdProb& P = g.p[find_problem(g, blockIdx.x)];
+    const int C = P.C, M = P.M, rl = P.lanes, parts = P.parts;
+    const int tid = threadIdx.x, cg = tid % CG, chain = tid / CG, ch0 = ((int)blockIdx.x - P.block_start) * S, c0 = ch0 + cg * EPV;
+    const int pr = CH / rl, my = chain / rl, lane_row = chain - my * rl;         // parts at a time; this thread's part of them and row lane
+    const int stride = parts * 4 * rl, trips = (M + stride - 1) / stride, steps = (parts + pr - 1) / pr * trips;
+    const bf16_t* gp = reinterpret_cast<const bf16_t*>(P.g) + c0;
+    const bf16_t* y = reinterpret_cast<const bf16_t*>(P.y) + c0;
+    const bool norelu = P.relu == 0;
+    if (tid < S) {
+        float sc, sh, mu, is;
+        bn_coeffs(P.stats, P.gamma, P.beta, ch0 + tid, C, M, g.eps, sc, sh, mu, is);
+        s_c[tid] = sc; s_c[S + tid] = sh; s_c[2 * S + tid] = mu; s_c[3 * S + tid] = is;
+    }
+    // first row of this thread's trip t of the parts from `first` on; M: it has none.  Rows beyond the end read the last row and count for nothing
+    auto row_of = [&](int first, int t) { return my < pr && first + my < parts ? (first + my + t * parts) * 4 * rl + lane_row : M; };
+    auto request = [&](u32x4 (&gr)[4], u32x4 (&yr)[4], int row) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned o = (unsigned)min(row + u * rl, M - 1) * (unsigned)C;
+            gr[u] = Vec<bf16_t>::load_raw(gp + o);
+            yr[u] = Vec<bf16_t>::load_raw(y + o);
+        }
+    };
+    u32x4 ga[4], ya[4], gb[4], yb[4];
+    int row = row_of(0, 0), first = 0, t = 0;
+    request(ga, ya, row);
+    __syncthreads();
+    auto coef = [&](int q, float (&c)[EPV]) {
+#pragma unroll
+        for (int e = 0; e < EPV; e += 4) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(s_c + q * S + cg * EPV + e);
+            c[e] = v[0]; c[e + 1] = v[1]; c[e + 2] = v[2]; c[e + 3] = v[3];
+        }
+    };
+    float sc[EPV], sh[EPV];
+    coef(0, sc); coef(1, sh);
+    double sum = 0.0;                              // of sum tid % 128 of every fourth part
+    {
+        float mu[EPV], is[EPV], a1[EPV], a2[EPV];
+        coef(2, mu); coef(3, is);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) { a1[e] = 0.f; a2[e] = 0.f; }
+        auto consume = [&](const u32x4 (&gr)[4], const u32x4 (&yr)[4], int at) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float gv[EPV], yv[EPV];
+                Vec<bf16_t>::unpack(gr[u], gv);
+                Vec<bf16_t>::unpack(yr[u], yv);
+                const bool in = at + u * rl < M;
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float gg = in & (norelu | (fmaf(sc[e], yv[e], sh[e]) > 0.f)) ? gv[e] : 0.f;
+                    a1[e] += gg;
+                    a2[e] += gg * ((yv[e] - mu[e]) * is[e]);
+                }
+            }
+        };
+        // one trip: the next one is requested first; behind a chain's last trip the row lanes of its parts are added up in order
+        auto step = [&](u32x4 (&gr)[4], u32x4 (&yr)[4], u32x4 (&gn)[4], u32x4 (&yn)[4], bool more) {
+            const int at = row, from = first;
+            const bool last = t + 1 == trips;
+            if (last) { t = 0; first += pr; } else ++t;
+            row = row_of(first, t);
+            if (more) request(gn, yn, row);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(gr, yr, at);
+            if (!last) return;
+            float* const q = s_part + (chain * S + cg * EPV) * 2;
+#pragma unroll
+            for (int e = 0; e < EPV; e += 2) {
+                *reinterpret_cast<f32x4*>(q + 2 * e) = f32x4{a1[e], a2[e], a1[e + 1], a2[e + 1]};
+            }
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) { a1[e] = 0.f; a2[e] = 0.f; }
+            __syncthreads();
+            const int here = min(pr, parts - from);
+            for (int p = tid >> 7; p < here; p += W / 2) {
+                const float* const r = s_part + p * rl * (S * 2) + (tid & 127);
+                float f = 0.f;
+#pragma unroll 8
+                for (int l = 0; l < rl; ++l) f += r[l * (S * 2)];
+                sum += (double)f;
+            }
+            __syncthreads();
+        };
+        for (int k = 0; k < steps; k += 2) {
+            step(ga, ya, gb, yb, k + 1 < steps);
+            if (k + 1 < steps) step(gb, yb, ga, ya, k + 2 < steps);
+        }
+    }
+    s_sum[tid] = sum;
+    __syncthreads();
+    if (tid < S) {
+        double rs0 = 0.0, rs1 = 0.0;
+#pragma unroll
+        for (int w = 0; w < W / 2; ++w) { rs0 += s_sum[w * (S * 2) + 2 * tid]; rs1 += s_sum[w * (S * 2) + 2 * tid + 1]; }
+        const int c = ch0 + tid;
+        const double inv_m = 1.0 / (double)M;
+        const float r0 = (float)(rs0 * inv_m), r1 = (float)(rs1 * inv_m);
+        const float is = s_c[3 * S + tid], k1 = P.gamma[c] * is;
+        const float k2 = k1 * is * r1;
+        s_c[4 * S + tid] = k1; s_c[5 * S + tid] = k2; s_c[6 * S + tid] = k2 * s_c[2 * S + tid] - k1 * r0;
+        P.dgamma[c] = (float)rs1;
+        P.dbeta[c] = (float)rs0;
+    }
+    __syncthreads();
+    float k1[EPV], k2[EPV], k3[EPV];
+    coef(4, k1); coef(5, k2); coef(6, k3);
+    const bf16_t* const ap = P.add ? reinterpret_cast<const bf16_t*>(P.add) + c0 : nullptr;
+    bf16_t* const dy = reinterpret_cast<bf16_t*>(P.dy) + c0;
+    for (int r0 = chain; r0 < M; r0 += 4 * CH) {
+        u32x4 gr[4], yr[4], ar[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned o = (unsigned)min(r0 + u * CH, M - 1) * (unsigned)C;
+            gr[u] = Vec<bf16_t>::load_raw(gp + o);
+            yr[u] = Vec<bf16_t>::load_raw(y + o);
+            if (ap) ar[u] = Vec<bf16_t>::load_raw(ap + o);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * CH;
+            if (r >= M) continue;
+            float gv[EPV], yv[EPV], o[EPV];
+            Vec<bf16_t>::unpack(gr[u], gv);
+            Vec<bf16_t>::unpack(yr[u], yv);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                const float gg = norelu | (fmaf(sc[e], yv[e], sh[e]) > 0.f) ? gv[e] : 0.f;
+                o[e] = k1[e] * gg - k2[e] * yv[e] + k3[e];
+            }
+            if (ap) {
+                float av[EPV];
+                Vec<bf16_t>::unpack(ar[u], av);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) o[e] += av[e];
+            }
+            Vec<bf16_t>::store(dy + (unsigned)r * (unsigned)C, o);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_sum(float v, float* s_tmp) {
 #pragma unroll
@@ -1075,6 +1228,11 @@ hipError_t launch_auxvar(const AuxVarGroup& g, int dtype, hipStream_t s) {
 hipError_t launch_mult(const MultGroup& g, int dtype, hipStream_t s) {
     if (g.total_blocks <= 0) return hipSuccess;
     LP_DISPATCH_T(dtype, mult_kernel, dim3(g.total_blocks), dim3(kElemBlock), s, g);
+    return hipGetLastError();
+}
+hipError_t launch_bn_bwd_small(const BnBwdGroup& g, hipStream_t s) {
+    if (g.total_blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(bn_bwd_small_kernel, dim3(g.total_blocks), dim3(kBnSmallThreads), 0, s, g);
     return hipGetLastError();
 }
 hipError_t launch_maxpool_fwd(const PoolProb& p, int dtype, hipStream_t s) {

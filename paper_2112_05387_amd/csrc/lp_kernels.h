@@ -325,6 +325,7 @@ hipError_t launch_sgd(const SgdGroup& g, hipStream_t s);
 // per-channel sum and sum of squares of a stored tensor [M, C] (fields y, red, M, C of BnBwdProb), added to red[2C]
 hipError_t launch_bn_stats(const BnBwdGroup& g, int dtype, hipStream_t s);
 constexpr int kSgdElemsPerBlock = 4096;
+hipError_t launch_bn_bwd_small(const BnBwdGroup& g, hipStream_t s);
 hipError_t launch_maxpool_fwd(const PoolProb& p, int dtype, hipStream_t s);
 hipError_t launch_maxpool_bwd(const PoolProb& p, int dtype, hipStream_t s);
 // does the linear layer of the head run in its tiled kernels (forward, filter gradient)?
@@ -364,6 +365,20 @@ inline int bn_reduce_threads(int cmax) { return cmax <= 64 ? 256 : kBnReduceBloc
 // and are 80.  Slices are whole 128-byte lines of bf16.  ResNet-50 step of 6 samples 1529 -> 1432 us, of 64 5724 -> 5695, WRN-28-10
 // in pre-activation order 1942 -> 1892; 160 channels (WRN-28-10's first stage) have no such slice and keep whole rows.
 inline int bn_slice(int C) { return C > 128 && C % 128 == 0 ? 128 : C > 64 && C % 64 == 0 ? 64 : 0; }
+// How the backward reduction cuts M rows of C channels (epv to a vector): row lanes of a part, and parts, of which each has at least 64
+// rows and (one trip being four rows per row lane) no more are made than there are trips.  The order of the sums.
+inline void bn_reduce_cut(int M, int C, int epv, int threads, int& lanes, int& parts) {
+    lanes = threads / (C / epv) > 1 ? threads / (C / epv) : 1;
+    const int most = (M + 63) / 64 < 256 ? (M + 63) / 64 : 256, trips = (M + 4 * lanes - 1) / (4 * lanes);
+    parts = most < trips ? most : trips;
+    if (parts < 1) parts = 1;
+}
+// Reduction and apply pass in one launch (bn_bwd_small_kernel): a workgroup for all rows of 64 channels.  It is done in 6 us and a line of
+// 128 bytes every 4 to 5 clocks, five lines a row: 49 rows 9 us (timed by itself, with its launch), 196 12, 784 18, 1176 25; the two launches 15 to
+// 18 for any of them.  Whole steps, two launches / one: ResNet-50 of 1 / 3 samples 1300 / 1200 and 1370 / 1253 us, WRN-28-10 of 1 / 4 samples
+// 848 / 780 and 832 / 800, in pre-activation order of 5 857 / 820; up to 1300 rows ResNet-50 of 6 1398 / 1490, up to 2048 of 9 1568 / 1800.
+constexpr int kBnSmallChannels = 64, kBnSmallThreads = 512;
+inline bool bn_bwd_small(int M, int C, int esz) { return esz == 2 && C > 64 && C % kBnSmallChannels == 0 && M <= 600; }
 constexpr int kElemVecsPerBlock = 2048;  // 16-byte vectors handled by one workgroup
 
 }  // namespace lp

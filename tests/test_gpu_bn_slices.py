@@ -98,3 +98,30 @@ def test_slices_have_the_bits_of_whole_rows(case, order, lanes, fixed):
     assert not differ, differ
     for n, g in got_sums.items():                  # fp32 sums of up to 2^16 products in two orders
         assert torch.isfinite(g).all() and float((g - want_sums[n]).norm()) <= 1e-5 * float(want_sums[n].norm()), n
+
+
+@pytest.mark.parametrize("case,order,fixed", [
+    # one row; fewer rows than a trip has; rows that end inside a trip and inside a part, several rounds of parts (256 channels and less)
+    (dict(batch=1, side=(2, 2), widths=(128, 256), dtype="bf16"), "post", False), (dict(batch=3, side=(6, 10), widths=(192, 320), dtype="bf16"), "post", False),
+    # the most rows that one workgroup takes, and more of them beside fewer; the added gradient of an identity skip
+    (dict(batch=6, side=(10, 10), widths=(128, 640), dtype="bf16"), "post", False), (dict(batch=7, side=(10, 10), widths=(192, 384), dtype="bf16"), "pre", False),
+    (dict(batch=5, side=(8, 8), widths=(256, 576), dtype="bf16"), "pre", False),
+    # two row lanes and trips in a row, a projection's batch norm in the same launch; the fixed order takes two launches
+    (dict(batch=3, side=(14, 14), widths=(1024, 2048), dtype="bf16", kind="bottleneck"), "post", False),
+    (dict(batch=3, side=(6, 10), widths=(192, 320), dtype="bf16"), "post", True),
+], ids=lambda c: "-".join(str(v) for v in c.values()).replace(" ", "") if isinstance(c, dict) else str(c).replace(" ", ""))
+def test_few_rows_in_one_launch(case, order, fixed):
+    """Reduction and apply pass of few rows in one launch: the bits of the two."""
+    import torch
+    from tests.test_gpu_narrow import launches
+    say("case few rows", case, order, fixed)
+    net = cfg.with_order(net_of(**case), order)
+    assert 19 in {k for k, _ in launches(net)}
+    m0 = net.modules[0]
+    net.aux = [cfg.AuxDesc(cin=m0.C, cout=m.C, stride=m0.H // m.H, relu=False) for m in net.modules[1:]]
+    got, got_sums = iteration(net, False, None, fixed)
+    want, want_sums = iteration(net, True, None, fixed)
+    differ = {n: int((got[n] != want[n]).sum()) for n in got if not torch.equal(got[n], want[n])}
+    assert not differ, differ
+    for n, g in got_sums.items():                  # fp32 sums of up to 2^10 products in two orders
+        assert torch.isfinite(g).all() and float((g - want_sums[n]).norm()) <= 1e-5 * float(want_sums[n].norm()), n
