@@ -2153,6 +2153,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.xn = nullptr; p.lam = nullptr; p.dy = nullptr; p.lam_out = nullptr; p.loss = nullptr; p.r2 = nullptr;
                     if (fused_loss) {      // the local loss and terminal adjoint (and the multiplier update) ride on this pass
                         p.xn = resolve(o.r[9], b); p.lam = resolve(o.r[10], b); p.dy = resolve(o.r[11], b);
+                        if (!p.xn) p.xn = p.y;       // (no loss: loaded all the same, without a branch, and not used)
                         p.loss = (float*)resolve(o.r[12], b);
                         p.r2 = net->r2 && p.loss ? net->r2 + (p.loss - b.loss) : nullptr;      // loss + k  ->  r2 + k
                         p.lam_out = b.mstep != 0.f ? const_cast<void*>(p.lam) : nullptr;

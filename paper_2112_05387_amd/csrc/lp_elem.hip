@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
             fraw[u] = Vec<T>::load_raw(y + vc * EPV);
             if (P.skip_mode) skraw[u] = Vec<T>::load_raw(skip + vc * EPV);
             if constexpr (FUSE) {
-                if (xn) xnraw[u] = Vec<T>::load_raw(xn + vc * EPV);
+                xnraw[u] = Vec<T>::load_raw(xn + vc * EPV);
                 if (lam) lmraw[u] = Vec<T>::load_raw(lam + vc * EPV);
             }
         }
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
             }
             Vec<T>::store(out + v * EPV, o);
             if constexpr (FUSE) {
-                if (!xn) continue;                          // a problem without a loss
+                if (!dyp) continue;                         // a problem without a loss
                 if constexpr (sizeof(T) == 2) {             // the loss is defined on F_k(x_k) as stored
 #pragma unroll
                     for (int e = 0; e < EPV; e += 2) {
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kElemBlock) void bn_apply_kernel(const BnApplyGroup
         }
     }
     if constexpr (FUSE) {
-        if (!xn) return;
+        if (!dyp) return;
         __shared__ float s_tmp[kElemBlock / 64];
         const float tot = block_sum(lacc, s_tmp);
         if (threadIdx.x == 0 && tot != 0.f) atomicAdd(P.loss, g.scale * tot);
