@@ -1923,7 +1923,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
 
 static hipError_t launch_group(lp_net* net, std::vector<const Op*>& ops, const Bindings& b, hipStream_t s) {
     hipError_t err = hipSuccess;
-    const size_t most = ops[0]->type == OP_FILL || ops[0]->type == OP_WTRANS ? kPrepMax : kMaxGroup;
+    const size_t most = ops[0]->type == OP_FILL || ops[0]->type == OP_WTRANS ? kPrepMax : ops[0]->type == OP_FWGRAD ? kFwMax : kMaxGroup;
     for (size_t base = 0; base < ops.size() && err == hipSuccess; base += most) {
         const int n = (int)std::min<size_t>(most, ops.size() - base);
         if (ops[base]->type == OP_SGD_REST && !net->fused_update) continue;      // nothing to launch, nothing to record
@@ -2059,7 +2059,8 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                         std::vector<const Op*> sub;
                         for (int j = i; j < n; ++j)
                             if (!done[j] && plain[j].key() == plain[i].key()) { sub.push_back(&plain[j]); done[j] = 1; }
-                        err = launch_group_impl(net, sub, 0, (int)sub.size(), b, s, nullptr, nullptr);
+                        for (size_t at = 0; at < sub.size() && err == hipSuccess; at += kMaxGroup)
+                            err = launch_group_impl(net, sub, at, (int)std::min<size_t>(kMaxGroup, sub.size() - at), b, s, nullptr, nullptr);
                     }
                     break;
                 }
@@ -2077,7 +2078,7 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 for (int i = 0; i < n; ++i) work += (long)g.p[i].ntiles * blocks(g.p[i]);
                 const int per = (int)std::max(1l, (work + 511) / 512);
                 int tot = 0;
-                for (int i = 0; i < kMaxGroup; ++i) {
+                for (int i = 0; i < kFwMax; ++i) {
                     if (i >= n) { g.start[i] = INT_MAX; continue; }
                     FWgradProb& p = g.p[i];
                     p.nranges = (p.ntiles + per - 1) / per;

@@ -11,7 +11,9 @@
 // micro-tiles, 36 accumulators) and, where the block has fewer units than there are waves, a share of the pixels.
 // Image-facing layers (3 channels): the columns (r, s, ci) of the filter are 27 of two micro-tiles and a lane reads its own
 // tap and channel; their operands are put into LDS as fp32 and multiplied as such (exact for bf16 inputs).
-// Every layer of every module takes part in the same launches; the number of tiles per workgroup is one for all of them.
+// Every layer of every module takes part in the same launches, up to kFwMax of them in one (16 before, and 17 to 21 layers of a lane were a
+// second launch of 26 to 30 us: ResNet-56 of 128 samples 738 -> 691 us, of 40 477 -> 446, ResNet-20 fp32 of 24 306 -> 284); the number of
+// tiles per workgroup is one for all of them.  fp32: two workgroups a compute unit have 182 registers, at three six of them spill.
 // What bounds it: a workgroup adds its whole block (36 KB of 32 x 32 channels) to the gradient with atomics, 25 us of a launch
 // of 1024 workgroups.  Two workgroups per compute unit instead of four (and the next tile's loads, which have more tiles to run
 // ahead of then): ResNet-56 of 128 samples in bf16 790 -> 762 us, of 20 480 -> 454.  Half as many again, or workgroups of
@@ -37,6 +39,9 @@ namespace lp {
 namespace {
 
 constexpr int FW_NT = 256;
+// the kernel's argument where it lies in constant memory: indexed per lane, not a copy in scratch
+typedef const __attribute__((address_space(4))) FWgradProb FWgradArg;
+typedef const __attribute__((address_space(4))) FWgradGroup FWgradGroupArg;
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -54,7 +59,7 @@ __device__ __forceinline__ void store_split(char* at, int plane, const u32x4& v)
 
 // NTAP micro-tiles of columns: 9 taps, 1 tap, or (STEM) 2 groups of 16 of the 9 * Cin columns
 template <typename T, int NTAP, bool STEM, bool SPLIT>
-__device__ __forceinline__ void fwgrad_body(const FWgradProb& P, const int t, char* const lds) {
+__device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* const lds) {
     typedef typename std::conditional<STEM, float, T>::type E;       // what lies in LDS
     constexpr int EPV = 16 / (int)sizeof(T);
     constexpr int YU = fwgrad_y_vecs((int)sizeof(T)), XU = STEM ? kFwStemElems : fwgrad_x_vecs((int)sizeof(T));
@@ -291,12 +296,13 @@ __device__ __forceinline__ void fwgrad_body(const FWgradProb& P, const int t, ch
 }
 
 template <typename T>
-__global__ __launch_bounds__(FW_NT, 3) void fwgrad_kernel(const FWgradGroup g) {
+__global__ __launch_bounds__(FW_NT, sizeof(T) == 4 ? 2 : 3) void fwgrad_kernel(const FWgradGroup) {
+    FWgradGroupArg& g = *(FWgradGroupArg*)__builtin_amdgcn_kernarg_segment_ptr();
     extern __shared__ __attribute__((aligned(16))) char s_lds[];
-    int pi = 0;
-#pragma unroll
-    for (int i = 1; i < kMaxGroup; ++i) pi += (int)blockIdx.x >= g.start[i] ? 1 : 0;
-    const FWgradProb& P = g.p[pi];
+    static_assert(kFwMax <= 64, "an entry of the table a lane");
+    const int lane = threadIdx.x & 63, first = g.start[min(lane, kFwMax - 1)];
+    const int pi = __popcll(__ballot(lane < kFwMax && (int)blockIdx.x >= first)) - 1;
+    FWgradArg& P = g.p[pi];
     const int t = (int)blockIdx.x - g.start[pi];
     constexpr bool F = sizeof(T) == 4;
     if (P.Cin < 16) fwgrad_body<T, 2, true, false>(P, t, s_lds);

@@ -152,12 +152,14 @@ struct FWgradProb {
     unsigned tdiv;                                           // 2^32 / tpi + 1 (0: one tile per image)
     short Cin, Cout, IH, IW, Ho, Wo, stride, pad, R, TH, tpi, WH, WW;
 };
+constexpr int kFwMax = 40;                                   // problems of a launch: all layers of a stream lane of most networks
 struct FWgradGroup {
     int nprob, total_tiles;
     int pad_[2];
-    int start[kMaxGroup];
-    FWgradProb p[kMaxGroup];
+    int start[kFwMax];
+    FWgradProb p[kFwMax];
 };
+static_assert(sizeof(FWgradGroup) <= 4096, "kernel-argument block");
 // 16-byte vectors of dY and of the input window a thread holds of a tile; elements of the window of an image-facing layer
 __host__ __device__ constexpr int fwgrad_y_vecs(int esz) { return esz == 2 ? 2 : 4; }
 __host__ __device__ constexpr int fwgrad_x_vecs(int esz) { return esz == 2 ? 3 : 6; }

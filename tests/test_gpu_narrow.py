@@ -120,6 +120,42 @@ def test_fp32_filter_gradients_in_bf16_parts(batch, side, stride):
         ls.close()
 
 
+@pytest.mark.parametrize("blocks,dtype,groups", [(8, "f32", [17]), (10, "bf16", [21]), (20, "f32", [40, 1])])
+def test_filter_gradients_of_many_layers(blocks, dtype, groups):
+    """One launch holds up to 40 layers; in the fixed order of sums they go through the general kernels, 16 at a time.  From the device's own
+    operands (as stored, so that bf16 is as exact as fp32) in float64."""
+    import torch
+    from oracle import lpref
+    from tests.helpers import rel_err
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    say("case many layers", blocks, dtype)
+    net = cfg._assemble("deep", [[Block("basic", 16, 16, 16, 1, False)] * blocks], 4, 8, 8, 3, 1, 16, 5, seed=67)
+    net.dtype = dtype
+    params, _, labels, xs, _ = seeded_step_inputs(net)
+    ls = LocalStep(net, keep_gradients=True)
+    try:
+        ls.set_params(0, params[0])
+        ls.set_x(0, xs[0])
+        ls.set_labels(labels)
+        for fixed in (0, 1):
+            B.lp_net_set_deterministic(ls.net, fixed)
+            B.lp_profile_enable(ls.net, 2)
+            ls.local_step(net.rho, 1.0)
+            torch.cuda.synchronize()
+            recs = [r["nprob"] for r in B.lp_profile_fetch(ls.net) if r["kind"] == FOLDED_WGRAD]
+            B.lp_profile_enable(ls.net, 0)
+            assert fixed or recs == groups, recs
+            grads, worst = ls.get_grads(0), 0.0
+            for u in ls.units(0):
+                want = lpref.conv_wgrad(ls.fetch(u.in_, (u.N, u.H, u.W, u.cin)), ls.fetch(u.dy, (u.N, u.Ho, u.Wo, u.cout)), params[0][u.t_w].shape, u.stride, u.pad)
+                worst = max(worst, rel_err(grads[u.t_w], want))
+            say(f"    fixed order {fixed}: worst {worst:.1e}")
+            assert worst <= 1e-4
+    finally:
+        ls.close()
+
+
 def test_narrow_separate_calls():
     """The single entry points run the folded passes too, each from what the one before has left in the workspace."""
     say("case narrow, separate calls")
