@@ -109,6 +109,7 @@ enum FcRef { F_IN = 0, F_IN2, F_SIDE, F_STATS, F_GAMMA, F_BETA, F_STATS2, F_GAMM
 struct Op {
     int type = 0, cfg = 0;
     bool cfg_mid = false;                  // a convolution the tiles of lp_conv_fast.hip may take although its cfg is a general one
+    int image = 0;                         // a convolution of lp_iconv.hip: bytes of its window
     int phase = 0;                         // fused step: 0 forward, 1 loss, 2 backward, 3 multiplier update
     bool vec = true;
     Ref r[F_COUNT];
@@ -123,7 +124,7 @@ struct Op {
     BnBwdProb bnb;
     PoolProb pool;
     HeadProb head;
-    int key() const { return type == OP_WTRANS ? OP_FILL * 64 + cfg * 2 + (vec ? 1 : 0) : type == OP_FWGRAD ? type * 64 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
+    int key() const { return type == OP_WTRANS ? OP_FILL * 64 + cfg * 2 + (vec ? 1 : 0) : type == OP_FWGRAD ? type * 64 : image ? type * 64 + CONV_IMAGE * 2 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
 };
 typedef std::vector<Op> Step;              // operations of one module that may run concurrently
 typedef std::vector<Step> Program;         // steps run in order
@@ -336,6 +337,8 @@ struct Builder {
         pick_fast_cfg(net, c, o.cfg);
         pick_win_cfg(net, c, o.cfg);
         o.r[0] = in; o.r[1] = w; o.r[2] = out; o.r[5] = stats;
+        if (!o.vec && !net->separate && !net->deterministic && (o.cfg == CFG_N16 || o.cfg == CFG_N32 || o.cfg == CFG_N64S))
+            o.image = iconv_window(c, conv_cfg_info(o.cfg, net->dtype).BM, net->esz);
         return o;
     }
     // data-gradient of unit u: dX[N,H,W,cin] from dY[N,Ho,Wo,cout] and the re-laid-out filters [cin][R][R][cout]
@@ -1975,6 +1978,36 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                 err = launch_prep(g, dt, s);
             } break;
             case OP_CONV: {
+                if (ops[base]->image) {
+                    ConvGroup g; g.nprob = n; g.total_tiles = 0;
+                    bool ok = !net->deterministic;
+                    int lds = 0;
+                    for (int i = 0; i < n; ++i) {
+                        const Op& o = *ops[base + i];
+                        ConvProb& p = g.p[i]; p = o.conv;
+                        p.in = resolve(o.r[0], b); p.wt = resolve(o.r[1], b); p.out = resolve(o.r[2], b); p.stats = (double*)resolve(o.r[5], b);
+                        ok = ok && o.r[3].space == SP_NONE && o.r[4].space == SP_NONE;
+                        lds = std::max(lds, o.image);
+                        const CfgInfo ci = conv_cfg_info(o.cfg, dt);
+                        p.tiles_m = (p.M + ci.BM - 1) / ci.BM; p.tiles_n = 1;
+                        p.tile_start = g.total_tiles; g.total_tiles += p.tiles_m;
+                    }
+                    if (ok) {
+                        if (used_cfg) *used_cfg = CONV_IMAGE;
+                        if (used_blocks) *used_blocks = g.total_tiles;
+                        err = launch_iconv(g, dt, lds, s);
+                        break;
+                    }
+                    for (int cfg : {CFG_N16, CFG_N32, CFG_N64S}) {      // a fixed order, an addend: the general kernel, a launch for each tile
+                        std::vector<Op> same;
+                        for (int i = 0; i < n; ++i)
+                            if (ops[base + i]->cfg == cfg) { same.push_back(*ops[base + i]); same.back().image = 0; }
+                        std::vector<const Op*> at;
+                        for (const Op& o : same) at.push_back(&o);
+                        if (err == hipSuccess && !at.empty()) err = launch_group_impl(net, at, 0, (int)at.size(), b, s, nullptr, nullptr);
+                    }
+                    break;
+                }
                 ConvGroup g; g.nprob = n;
                 // longest tiles first: the blocks of a launch are dispatched in order
                 std::stable_sort(ops.begin() + base, ops.begin() + base + n,

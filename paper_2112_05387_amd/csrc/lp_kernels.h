@@ -266,6 +266,22 @@ struct HeadProb {        // global average pool + linear
 // pass in the launch of the others': tiny 81 -> 62 us, ResNet-20 of 3 samples in bf16 192 -> 173, of 16 229 -> 209, 2 in fp32 232 -> 211).
 inline bool head_with_loss(const HeadProb& p, int esz) { return (size_t)p.HW * p.C * esz <= 32 * 1024 && p.C * p.classes <= 16384; }
 
+// Image-facing convolutions (lp_iconv.hip): bytes of the rows of the image that BM consecutive output pixels read at most, in whole
+// wave-loads; 0: not a layer of that kernel.  Up to 24 KB, so that four workgroups and their result slices fit a CU.  The image
+// has to end at a whole 4 bytes (the copy's unit; with an odd number of bf16 elements its last one would be lost).
+inline int iconv_window(const ConvProb& p, int BM, int esz) {
+    if (p.Kg > 32 || p.ntr * p.nts * p.Cin != p.Kg || p.ldw != p.Kg || (p.Ncol != 16 && p.Ncol != 32 && p.Ncol != 64)) return 0;
+    if (p.add0 || p.add1 || p.omul != 1 || p.ooh || p.oow || p.dhs != 1 || p.dws != 1 || p.r0 || p.s0 || p.rs != 1 || p.ss != 1) return 0;
+    if (p.OH != p.OA || p.OW != p.OB || p.dh0 > 0 || p.dw0 > 0) return 0;
+    const int64_t nimg = p.M / (p.OA * p.OB), elems = nimg * p.IH * p.IW * p.Cin;
+    if (elems * esz % 4 || elems > 0x40000000) return 0;
+    const int64_t rows = (BM + p.OB - 2) / p.OB + 1;                       // output rows that the pixels lie in
+    const int64_t cross = std::min(nimg - 1, (rows - 2 + p.OA) / p.OA);    // ends of images among them
+    const int64_t in = std::min(nimg * p.IH, (rows - 1) * p.imul + p.ntr + cross * std::max(0, p.IH - p.OA * p.imul));
+    const int64_t bytes = (in * p.IW * p.Cin * esz + 16 + 1023) / 1024 * 1024;
+    return bytes <= 24 * 1024 ? (int)bytes : 0;
+}
+
 // ---- launchers (host side; return hipError_t of the launch) ----------------------------------------
 // tile configuration ids of the implicit-GEMM kernels
 enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
@@ -282,6 +298,7 @@ enum ConvCfg { CFG_N16 = 0, CFG_N32, CFG_N64, CFG_N128, CFG_N160,
                MID_256x128_R3 = 28, MID_256x64_R3 = 29, MID_256x32_R4 = 30,
                WIN64_512x160 = 21, WIN64_256x320 = 23,  // bf16 3x3 stride-1 kernel with the input window in LDS (lp_conv_win.hip)
                SMALL_128x32 = 24,                      // bf16 wide layers on few pixels, recorded only (lp_sconv.hip)
+               CONV_IMAGE = 31,                        // image-facing layers, recorded only (lp_iconv.hip)
                WGRAD_FAST = 8,                         // bf16 wide-layer filter-gradient kernel (lp_wgrad_fast.hip)
                WGRAD_TILE = 9,                         // ... of the other wide layers, recorded only (lp_wgrad_tile.hip)
                WGRAD_STEM = 10 };                      // ... of an image-facing layer, recorded only (lp_wgrad_stem.hip)
@@ -303,6 +320,7 @@ inline hipError_t raise_lds_limit(OncePerDevice& once, std::initializer_list<con
 }
 hipError_t launch_conv(const ConvGroup& g, int dtype, int cfg, bool vec, hipStream_t s);
 hipError_t launch_conv_fast(const ConvGroup& g, int cfg, hipStream_t s);
+hipError_t launch_iconv(const ConvGroup& g, int dtype, int lds_bytes, hipStream_t s);
 hipError_t launch_conv_win(const ConvGroup& g, int cfg, hipStream_t s);
 hipError_t launch_sconv(const SConvGroup& g, size_t lds, hipStream_t s);
 hipError_t launch_tile_stats(const TileStatsGroup& g, hipStream_t s);

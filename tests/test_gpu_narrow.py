@@ -358,3 +358,50 @@ def test_fixed_order_switched_between_the_passes(fixed_forward):
         ls.close()
     for a, b in zip(*grads):                       # two orders of the same fp32 sums
         assert rel_err(a, b) <= 1e-4
+
+
+IMAGE_LAYERS = 31
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("batch,side,stride,c_img", [
+    # tiles of whole images and of parts; images that end inside a tile; rows that are no power of two; one and two channels
+    (5, (32, 32), 2, 3), (1, (8, 8), 2, 3), (9, (12, 20), 2, 3), (4, (7, 9), 1, 3), (2, (12, 4), 2, 1), (3, (6, 14), 1, 2), (3, (40, 64), 2, 3),
+    # an odd number of elements: bf16 images end inside the copy's unit and stay with the general kernel
+    (3, (7, 9), 1, 3)])
+def test_image_layers_have_the_bits_of_the_general_kernel(batch, side, stride, c_img, dtype):
+    """AuxNets of every width in one launch; results in a fixed order go to the general kernel, a launch for each tile."""
+    import torch
+    import workloads as wl
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    say("case image layers", batch, side, stride, c_img, dtype)
+    net = narrow_net(batch, side, dtype=dtype, stride=stride, c_img=c_img, split=[1, 1, 1, 1])
+    net.aux = [cfg.AuxDesc(cin=c_img, cout=m.C, stride=net.modules[0].H // m.H, relu=False) for m in net.modules[1:]]
+    results = []
+    for separate, fixed in ((True, False), (False, False), (False, True)):
+        B.lp_debug_separate_passes(separate)
+        try:
+            ls = LocalStep(net)
+        finally:
+            B.lp_debug_separate_passes(False)
+        try:
+            B.lp_net_set_deterministic(ls.net, fixed)
+            for j in range(net.K - 1):
+                ls.set_aux_params(j, wl.make_aux_params(net, j))
+            ls.set_x(0, wl.make_image(net))
+            B.lp_profile_enable(ls.net, 2)
+            ls.auxnet_forward()
+            torch.cuda.synchronize()
+            convs = [r["cfg"] for r in B.lp_profile_fetch(ls.net) if r["kind"] == CONV]
+            B.lp_profile_enable(ls.net, 0)
+            results.append([t.clone() for t in ls.x[1:]])
+        finally:
+            ls.close()
+        whole = batch * side[0] * side[1] * c_img * (4 if dtype == "f32" else 2) % 4 == 0
+        assert (convs == [IMAGE_LAYERS]) == (whole and not separate and not fixed), convs
+    assert all(float(t.float().abs().max()) > 0 for t in results[0])
+    assert all(torch.equal(a, b) for a, b in zip(results[0], results[1]))
+    # a fixed order sums the statistics of the stored results in another one: the last place of fp32, a rounding of bf16
+    for a, b in zip(results[0], results[2]):
+        assert float((a.float() - b.float()).abs().max()) <= (2.0 ** -20 if dtype == "f32" else 2.0 ** -7) * float(a.float().abs().max())
