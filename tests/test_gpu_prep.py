@@ -67,6 +67,8 @@ def test_first_launch(K, width, dtype):
 @pytest.mark.parametrize("batch,side,width,classes,dtype,one", [
     # one pixel, one class; fewer channels than a wave has lanes, a second round of classes; more channels than lanes
     (1, (1, 1), 16, 1, "f32", True), (3, (4, 4), 16, 23, "f32", True), (5, (3, 3), 72, 7, "bf16", True), (2, (8, 4), 200, 81, "f32", True),
+    # a round of classes and one more
+    (4, (4, 4), 64, 32, "f32", True), (4, (4, 4), 64, 33, "bf16", True),
     # the largest sample (32 KB) and the most weights (16384) of the rule, and one more of each
     (2, (16, 8), 64, 256, "f32", True), (2, (17, 8), 64, 10, "f32", False), (2, (4, 4), 64, 257, "bf16", False)])
 def test_head_with_loss(batch, side, width, classes, dtype, one):
