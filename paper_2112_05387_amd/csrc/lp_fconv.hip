@@ -8,8 +8,7 @@
 //     the batch-norm coefficients are computed from the summed statistics; then the window is transformed (BN [+ skip]
 //     [ReLU], or the BN backward of g and y) and written to LDS.  The tile that owns a pixel also stores the transformed
 //     value, which the skip path and the filter gradient need.
-//   * the taps read their fragments from the window; filter fragments go from memory straight into registers, D k-steps
-//     ahead (a wave needs each of them once, so LDS would only add a barrier).
+//   * the taps read their fragments from the window, the filter's from a ring in LDS that wave-loads fill ahead of them.
 //   * the epilogue adds the skip gradient, stores 16-byte vectors, and sums either the statistics of the stored result
 //     (forward) or the backward sums of the batch norm(s) the result arrives at.
 // Tiles are whole rows of one image.  One kernel serves every width (a tile picks its shape by its problem), so that

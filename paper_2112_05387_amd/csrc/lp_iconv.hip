@@ -7,8 +7,8 @@
 // a branch, and a layer of one k-tile has nothing to hide that behind.
 // Here the input rows that a tile touches, which lie one after another in memory, go to LDS in one asynchronous copy of whole vectors
 // (1 to 6 KB), the taps are picked out of LDS into registers (8 elements of k a lane, which is one MFMA of bf16 and two k-steps
-// of fp32), and since no operand tile is laid out, the widths share a launch: that step 749 -> 726 us, an iteration of it, which
-// distils the nets as well, 958 -> 938.  A stem alone (512 workgroups) 15.6 -> 12.7 us by itself, 5 of them the timing's own.
+// of fp32), and since no operand tile is laid out, the widths share a launch of 17 us: that step 692 -> 670 us, of 8 samples 390 -> 365,
+// an iteration 925 -> 905; a step of four modules 749 -> 726.  A stem alone (512 workgroups) 15.6 -> 12.7 us by itself, 5 of them the timing's own.
 //
 // The tiles are those of the general kernel (256 pixels x 16 or 32 channels with 64-pixel waves; 64 x 64 in four waves of 32 x 32), and
 // so is the order of every sum, of a product's terms and of the statistics: the results are the same bits.
