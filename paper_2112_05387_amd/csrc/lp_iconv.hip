@@ -7,8 +7,8 @@
 // a branch, and a layer of one k-tile has nothing to hide that behind.
 // Here the input rows that a tile touches, which lie one after another in memory, go to LDS in one asynchronous copy of whole vectors
 // (1 to 6 KB), the taps are picked out of LDS into registers (8 elements of k a lane, which is one MFMA of bf16 and two k-steps
-// of fp32), and since no operand tile is laid out, the widths share a launch of 17 us: that step 692 -> 670 us, of 8 samples 390 -> 365,
-// an iteration 925 -> 905; a step of four modules 749 -> 726.  A stem alone (512 workgroups) 15.6 -> 12.7 us by itself, 5 of them the timing's own.
+// of fp32), and since no operand tile is laid out, the widths share a launch of 14 us: that step 692 -> 665 us, of 8 samples 390 -> 362,
+// an iteration 925 -> 897; a step of four modules 749 -> 726.  A stem alone (512 workgroups) 15.6 -> 10.9 us by itself, 5 of them the timing's own.
 //
 // The tiles are those of the general kernel (256 pixels x 16 or 32 channels with 64-pixel waves; 64 x 64 in four waves of 32 x 32), and
 // so is the order of every sum, of a product's terms and of the statistics: the results are the same bits.
@@ -28,6 +28,7 @@ __global__ __launch_bounds__(IC_NT) void iconv_kernel(ConvGroup g) {
     constexpr int EPV = 16 / (int)sizeof(T);
     constexpr int OP = 32 * (int)sizeof(T) + 16;       // bytes between the pixels of a wave's result slice
     constexpr int KE = 8;                              // elements of k a lane holds: 32 over the four lane groups
+    constexpr int Z = 16 / (int)sizeof(T);             // the window's first elements are zeros: what a tap outside the image reads
     extern __shared__ __attribute__((aligned(16))) char win[];
     __shared__ __attribute__((aligned(16))) char s_out[4 * 16 * OP];
     __shared__ float s_red[256];                       // [wave rows][channels][2]
@@ -54,27 +55,44 @@ __global__ __launch_bounds__(IC_NT) void iconv_kernel(ConvGroup g) {
         const int bytes = (int)(b1 - b0);
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(P.in) + b0, 0, bytes, 0x00020000);
         for (int i = wave; i * 1024 < bytes; i += 4)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(win + i * 1024), 16, lane * 16, i * 1024, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(win + 16 + i * 1024), 16, lane * 16, i * 1024, 0, 0);
         sb = (unsigned)(b0 / sizeof(T));
+        if (tid == 0) *reinterpret_cast<u32x4*>(win) = u32x4{0u, 0u, 0u, 0u};
     }
 
-    // ---- this lane's elements of k (the chunks of a k-step as every kernel here holds them) and the filter fragments
+    // ---- this lane's elements of k (the chunks of a k-step as every kernel here holds them) and the filter fragments.  Lane u works out
+    // element u of k and pixel u of the wave, once, and the others ask it (with every lane's own quotients that launch was 17 us)
     int tr[KE], ts[KE], dq[KE];
+    int q_of, pix_at, pix_off;
+    {
+        const int q = lane & 31, tap = q / Cin, c = q - tap * Cin, r = tap / P.nts;
+        q_of = (q < P.Kg ? r : 64) | (tap - r * P.nts) << 8 | c << 16;      // row 64: none of an image (pix_at below)
+        const int m = m0 + wm * FM * 16 + min(lane, FM * 16 - 1);
+        const int n = m / per, rem = m - n * per, a = rem / OB, b = rem - a * OB;
+        const int ih0 = a * imul + P.dh0, iw0 = b * imul + P.dw0;
+        pix_at = (m < M ? ih0 : -0x4000) * 0x10000 | (iw0 & 0xffff);
+        pix_off = (int)((unsigned)(((n * IH + ih0) * IW + iw0) * Cin) - sb) + Z;
+    }
     T bq[2][KE];
-    const T* __restrict__ wt = reinterpret_cast<const T*>(P.wt);
+    const T* __restrict__ wt = reinterpret_cast<const T*>(P.wt) + (size_t)(col0 + lr) * P.ldw;
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
         const int q = (e / EPV) * 4 * EPV + lg * EPV + e % EPV;
-        const int tap = q / Cin, c = q - tap * Cin;
-        tr[e] = tap / P.nts; ts[e] = tap - tr[e] * P.nts;
+        const int at = __shfl(q_of, q, 64), c = at >> 16;
+        tr[e] = at & 0xff; ts[e] = at >> 8 & 0xff;
         dq[e] = (tr[e] * IW + ts[e]) * Cin + c;
-        const bool ok = q < P.Kg;
-        if (!ok) tr[e] = 1 << 28;                      // no row of an image
+        const bool ok = tr[e] != 64;
+        if (!ok) tr[e] = 1 << 28;
+        const T v = wt[ok ? q : 0];
+        bq[0][e] = ok ? v : from_float<T>(0.f);
+        bq[1][e] = from_float<T>(0.f);
+    }
+    if (FN == 2) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int col = col0 + (j < FN ? j * 16 : 0) + lr;
-            const T v = wt[(size_t)col * P.ldw + (ok ? q : 0)];
-            bq[j][e] = ok ? v : from_float<T>(0.f);
+        for (int e = 0; e < KE; ++e) {
+            const bool ok = tr[e] != 1 << 28;
+            const T v = wt[16 * P.ldw + (ok ? (e / EPV) * 4 * EPV + lg * EPV + e % EPV : 0)];
+            bq[1][e] = ok ? v : from_float<T>(0.f);
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0): this wave's part of the window
@@ -85,20 +103,17 @@ __global__ __launch_bounds__(IC_NT) void iconv_kernel(ConvGroup g) {
     char* const slice = s_out + wave * (16 * OP);
     T* __restrict__ out = reinterpret_cast<T*>(P.out);
     float cs1[2] = {0.f, 0.f}, cs2[2] = {0.f, 0.f};
-    const int G = FN * 16 / EPV;                       // vectors of a pixel
+    const int lgG = (sizeof(T) == 2 ? 1 : 2) + FN - 1, G = 1 << lgG;      // vectors of a pixel
     for (int i = 0; i < FM; ++i) {
         const int r0 = m0 + (wm * FM + i) * 16;        // first pixel
         T aq[KE];
         {
-            const int m = r0 + lr;
-            const int n = m / per, rem = m - n * per, a = rem / OB, b = rem - a * OB;
-            const int ih0 = m < M ? a * imul + P.dh0 : -(1 << 29), iw0 = b * imul + P.dw0;
-            const int base = (int)((unsigned)(((n * IH + a * imul + P.dh0) * IW + iw0) * Cin) - sb);
+            const int at = __shfl(pix_at, i * 16 + lr, 64), base = __shfl(pix_off, i * 16 + lr, 64);
+            const int ih0 = at >> 16, iw0 = (int)(short)at;
 #pragma unroll
             for (int e = 0; e < KE; ++e) {
                 const bool ok = (unsigned)(ih0 + tr[e]) < (unsigned)IH && (unsigned)(iw0 + ts[e]) < (unsigned)IW;
-                const T v = w[ok ? base + dq[e] : 0];
-                aq[e] = ok ? v : from_float<T>(0.f);
+                aq[e] = w[ok ? base + dq[e] : 0];
             }
         }
         f32x4 acc[2];
@@ -128,7 +143,7 @@ __global__ __launch_bounds__(IC_NT) void iconv_kernel(ConvGroup g) {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         for (int item = lane; item < 16 * G; item += 64) {
-            const int row = item / G, v = item - row * G;
+            const int row = item >> lgG, v = item & (G - 1);
             if (r0 + row < M)
                 *reinterpret_cast<u32x4*>(out + (size_t)(r0 + row) * Ncol + col0 + v * EPV) = *reinterpret_cast<const u32x4*>(slice + row * OP + v * 16);
         }

@@ -273,13 +273,14 @@ inline int iconv_window(const ConvProb& p, int BM, int esz) {
     if (p.Kg > 32 || p.ntr * p.nts * p.Cin != p.Kg || p.ldw != p.Kg || (p.Ncol != 16 && p.Ncol != 32 && p.Ncol != 64)) return 0;
     if (p.add0 || p.add1 || p.omul != 1 || p.ooh || p.oow || p.dhs != 1 || p.dws != 1 || p.r0 || p.s0 || p.rs != 1 || p.ss != 1) return 0;
     if (p.OH != p.OA || p.OW != p.OB || p.dh0 > 0 || p.dw0 > 0) return 0;
+    if (p.IH > 8192 || p.IW > 8192 || p.dh0 < -64 || p.dw0 < -64) return 0;      // 16-bit positions
     const int64_t nimg = p.M / (p.OA * p.OB), elems = nimg * p.IH * p.IW * p.Cin;
     if (elems * esz % 4 || elems > 0x40000000) return 0;
     const int64_t rows = (BM + p.OB - 2) / p.OB + 1;                       // output rows that the pixels lie in
     const int64_t cross = std::min(nimg - 1, (rows - 2 + p.OA) / p.OA);    // ends of images among them
     const int64_t in = std::min(nimg * p.IH, (rows - 1) * p.imul + p.ntr + cross * std::max(0, p.IH - p.OA * p.imul));
     const int64_t bytes = (in * p.IW * p.Cin * esz + 16 + 1023) / 1024 * 1024;
-    return bytes <= 24 * 1024 ? (int)bytes : 0;
+    return bytes <= 24 * 1024 ? (int)bytes + 16 : 0;                       // and a vector of zeros
 }
 
 // ---- launchers (host side; return hipError_t of the launch) ----------------------------------------
