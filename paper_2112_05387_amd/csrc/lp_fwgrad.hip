@@ -13,7 +13,7 @@
 // tap and channel; their operands are put into LDS as fp32 and multiplied as such (exact for bf16 inputs).
 // Every layer of every module takes part in the same launches, up to kFwMax of them in one (16 before, and 17 to 21 layers of a lane were a
 // second launch of 26 to 30 us: ResNet-56 of 128 samples 738 -> 691 us, of 40 477 -> 446, ResNet-20 fp32 of 24 306 -> 284); the number of
-// tiles per workgroup is one for all of them.  fp32: two workgroups a compute unit have 182 registers, at three six of them spill.
+// tiles per workgroup is one for all of them, half of it for image-facing layers in bf16 (17 layers with a stem 64 -> 45 us).  fp32: two workgroups a compute unit have 182 registers, at three six of them spill.
 // What bounds it: a workgroup adds its whole block (36 KB of 32 x 32 channels) to the gradient with atomics, 25 us of a launch
 // of 1024 workgroups.  Two workgroups per compute unit instead of four (and the next tile's loads, which have more tiles to run
 // ahead of then): ResNet-56 of 128 samples in bf16 790 -> 762 us, of 20 480 -> 454.  Half as many again, or workgroups of
