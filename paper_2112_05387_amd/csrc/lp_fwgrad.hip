@@ -304,11 +304,9 @@ __global__ __launch_bounds__(FW_NT, sizeof(T) == 4 ? 2 : 3) void fwgrad_kernel(c
     const int pi = __popcll(__ballot(lane < kFwMax && (int)blockIdx.x >= first)) - 1;
     FWgradArg& P = g.p[pi];
     const int t = (int)blockIdx.x - g.start[pi];
-    constexpr bool F = sizeof(T) == 4;
-    if (P.Cin < 16) fwgrad_body<T, 2, true, false>(P, t, s_lds);
-    else if (F && !fwgrad_split(P.Cin, P.Cout, 4)) fwgrad_body<T, 9, false, false>(P, t, s_lds);
-    else if (P.R == 3) fwgrad_body<T, 9, false, F>(P, t, s_lds);
-    else fwgrad_body<T, 1, false, F>(P, t, s_lds);
+    fwgrad_form<(int)sizeof(T)>(P.Cin, P.Cout, P.R, [&](auto ntap, auto stem, auto split) __attribute__((always_inline)) {
+        fwgrad_body<T, decltype(ntap)::value, decltype(stem)::value, decltype(split)::value>(P, t, s_lds);
+    });
 }
 
 }  // namespace
@@ -319,7 +317,9 @@ size_t fwgrad_lds_bytes(const FWgradProb& p, int esz) {
     const int e = stem ? 4 : esz, CB = std::min<int>(p.Cout, 32), CI = std::min<int>(p.Cin, 32);
     const size_t pxpad = ((size_t)p.TH * p.Wo + 31) & ~(size_t)31;
     const size_t tile = pxpad * (split ? CB * 6 : CB * e + 16) + (size_t)p.WH * p.WW * (stem ? 16 : split ? CI * 6 : CI * e + 16);
-    const int units = (CB / 16) * (stem ? 1 : CI / 16), ntap = stem ? 2 : p.R == 3 ? 9 : 1;
+    const int units = (CB / 16) * (stem ? 1 : CI / 16);
+    int ntap = 0;
+    fwgrad_form<4>(p.Cin, p.Cout, p.R, [&](auto n, auto, auto) { ntap = decltype(n)::value; });
     return std::max(tile, units == 4 ? (size_t)0 : (size_t)4 * ntap * 256 * 4);
 }
 

@@ -8,6 +8,7 @@
 
 #include <initializer_list>
 
+#include "lp_fwform.h"
 #include "lp_once.h"
 
 namespace lp {
@@ -164,9 +165,6 @@ static_assert(sizeof(FWgradGroup) <= 4096, "kernel-argument block");
 __host__ __device__ constexpr int fwgrad_y_vecs(int esz) { return esz == 2 ? 2 : 4; }
 __host__ __device__ constexpr int fwgrad_x_vecs(int esz) { return esz == 2 ? 3 : 6; }
 constexpr int kFwStemElems = 4;
-// fp32 blocks whose operands lie in LDS as three bf16 parts: all but 16 x 16 channels, whose sums over the most pixels would lose
-// precision by it, and image-facing layers
-__host__ __device__ constexpr bool fwgrad_split(int Cin, int Cout, int esz) { return esz == 4 && Cin >= 16 && (Cin > 16 || Cout > 16); }
 size_t fwgrad_lds_bytes(const FWgradProb& p, int esz);
 
 // filters [Cout][R][S][Cin] -> [Cin][R][S][Cout]

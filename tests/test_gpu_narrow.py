@@ -87,6 +87,46 @@ def test_narrow_units(case, dtype):
     assert FOLDED in kinds and FOLDED_WGRAD in kinds, kinds
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width,stride,bn,batch", [(16, 1, True, 3), (16, 1, False, 3), (16, 2, True, 3), (16, 2, False, 33), (32, 1, False, 3), (64, 2, True, 2)])
+def test_projections_of_equal_width(width, stride, bn, batch, dtype):
+    """A projection whose input and output have the same width, 1x1 filters of 16 x 16 channels among them: every unit against float64, and
+    nothing written around the gradients (in the gaps between the tensors there may be zeros of the clear)."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    say("case projection of equal width", width, stride, bn, batch, dtype)
+    blocks = [Block("basic", width, width, width, 1, False), Block("basic", width, width, width, stride, True, proj_bn=bn),
+              Block("basic", width, width, width, 1, False)]
+    net = cfg._assemble("square", [blocks[:2], blocks[2:]], batch, 16, 8, 3, 1, width, 5, seed=71)
+    net.dtype = dtype
+    check_units(net, note=f" {width}, stride {stride}, bn {bn}")
+    assert FOLDED_WGRAD in {k for k, _ in launches(net)}
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    ls = LocalStep(net)
+    try:
+        guard, all_of = 4096, []
+        for k in range(net.K):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+            n = ls.dparams[k].numel()
+            all_of.append(torch.full((n + 2 * guard,), 7.0, device=ls.dev))
+            ls.dparams[k] = all_of[k][guard:guard + n]
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        for k in range(net.K):
+            outside = torch.ones_like(all_of[k], dtype=torch.bool)
+            for info in ls.tables[k]:
+                o = guard + info.grad_offset // 4
+                outside[o:o + int(info.numel)] = False
+            v = all_of[k]
+            assert bool((v[:guard] == 7.0).all()) and bool((v[-guard:] == 7.0).all()), k
+            assert bool(((v == 7.0) | (v == 0.0))[outside].all()), k
+    finally:
+        ls.close()
+
+
 @pytest.mark.parametrize("batch,side,stride", [(1, (8, 8), 2), (9, (12, 20), 2), (3, (7, 9), 1), (32, (32, 32), 2)])
 def test_fp32_filter_gradients_in_bf16_parts(batch, side, stride):
     """Blocks wider than 16 x 16 channels multiply fp32 values as sums of three bf16 each.  Bound (2-norm against float64): what the
