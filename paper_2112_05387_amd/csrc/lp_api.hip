@@ -501,7 +501,7 @@ struct Builder {
         FWgradProb p; memset(&p, 0, sizeof(p));
         p.Cin = u.cin; p.Cout = u.cout; p.IH = u.H; p.IW = u.W; p.Ho = u.Ho; p.Wo = u.Wo; p.stride = u.stride; p.pad = u.pad; p.R = u.R;
         const int CB = std::min(u.cout, 32), CI = std::min(u.cin, 32), vy = CB * esz / 16, vx = CI * esz / 16;
-        int TH = std::min(u.Ho, std::max(1, (u.cin <= 16 && u.cout <= 16 ? 256 : 128) / (fwgrad_split(u.cin, u.cout, esz) ? 2 : 1) / u.Wo));
+        int TH = std::min(u.Ho, std::max(1, (u.cin <= 16 && u.cout <= 16 ? 256 : 128) / u.Wo));
         for (;; --TH) {
             if (TH < 1) return o;
             p.TH = TH; p.WH = (TH - 1) * u.stride + u.R; p.WW = (u.Wo - 1) * u.stride + u.R;
@@ -2111,14 +2111,16 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
                     p.x = resolve(o.r[0], b); p.dy = resolve(o.r[1], b); p.dw = (float*)resolve(o.r[2], b);
                     lds = std::max(lds, fwgrad_lds_bytes(p, (int)net->esz));
                 }
-                // one number of tiles per workgroup for the whole launch: two workgroups per compute unit; of a layer that reads the
-                // image in bf16 half as many, since its products are fp32 ones (17 layers of ResNet-56, 128 samples, with its
-                // stem: 64 -> 45 us, 17 of the others 40 to 48)
+                // one number of tiles per workgroup for the whole launch: two workgroups per compute unit in bf16, where adding to the gradient
+                // is most of it, four in fp32 (ResNet-20 of 128 / 80 samples, of 128 in one module, us with two / three / four: 658 / 672 / 666,
+                // 521 / 515 / 503, 864 / 842 / 816); of a layer that reads the image in bf16 half as many, since its products are fp32 ones
+                // (17 layers of ResNet-56, 128 samples, with its stem: 64 -> 45 us, 17 of the others 40 to 48)
+                const long most_blocks = dt == LP_F32 ? 1024 : 512;
                 auto blocks = [](const FWgradProb& p) { return (p.Cout == 64 ? 2 : 1) * (p.Cin == 64 ? 2 : 1); };
                 auto cost = [&](const FWgradProb& p) { return dt == LP_BF16 && p.Cin < 16 ? 2 : 1; };
                 long work = 0;
                 for (int i = 0; i < n; ++i) work += (long)g.p[i].ntiles * blocks(g.p[i]) * cost(g.p[i]);
-                const int per = (int)std::max(1l, (work + 511) / 512);
+                const int per = (int)std::max(1l, (work + most_blocks - 1) / most_blocks);
                 int tot = 0;
                 for (int i = 0; i < kFwMax; ++i) {
                     if (i >= n) { g.start[i] = INT_MAX; continue; }

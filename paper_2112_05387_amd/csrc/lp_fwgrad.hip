@@ -3,31 +3,21 @@
 //
 // As an implicit GEMM over (r, s, ci) the input is gathered nine times, in k-tiles of 32 or 64 pixels with a trip to
 // memory each: 50 to 115 us for launches that move 60 MB.  Here a workgroup walks over tiles of whole image rows; a tile's
-// dY pixels and the ONE window of input pixels its taps read are requested a tile ahead and put into LDS as
-// [pixel][channel], and all taps take their fragments from there: the reduction runs over pixels, so bf16
-// fragments are read with the transposing LDS read (four pixels of a channel per lane), fp32 ones of 16 x 16 blocks element by
-// element.
+// dY pixels and the ONE window of input pixels its taps read are requested a tile ahead and put into LDS as they are
+// stored, [pixel][channel], and all taps take their fragments from there: the reduction runs over pixels, so bf16
+// fragments are read with the transposing LDS read (four pixels of a channel per lane), fp32 ones element by element.
 // A workgroup owns a block of at most 32 x 32 (co, ci) channels and all taps; a wave owns one 16 x 16 unit of it (nine
 // micro-tiles, 36 accumulators) and, where the block has fewer units than there are waves, a share of the pixels.
 // Image-facing layers (3 channels): the columns (r, s, ci) of the filter are 27 of two micro-tiles and a lane reads its own
 // tap and channel; their operands are put into LDS as fp32 and multiplied as such (exact for bf16 inputs).
-// Every layer of every module takes part in the same launches, up to kFwMax of them in one (16 before, and 17 to 21 layers of a lane were a
-// second launch of 26 to 30 us: ResNet-56 of 128 samples 738 -> 691 us, of 40 477 -> 446, ResNet-20 fp32 of 24 306 -> 284); the number of
-// tiles per workgroup is one for all of them, half of it for image-facing layers in bf16 (17 layers with a stem 64 -> 45 us).  fp32: two workgroups a compute unit have 182 registers, at three six of them spill.
-// What bounds it: a workgroup adds its whole block (36 KB of 32 x 32 channels) to the gradient with atomics, 25 us of a launch
-// of 1024 workgroups.  Two workgroups per compute unit instead of four (and the next tile's loads, which have more tiles to run
-// ahead of then): ResNet-56 of 128 samples in bf16 790 -> 762 us, of 20 480 -> 454.  Half as many again, or workgroups of
-// eight waves that meet in LDS first, are no faster (ResNet-20 in bf16 430 us, 410 with these).  A longer walk would be a
-// longer chain of fp32 sums, so a tile's sums start from zero and are added to the workgroup's.
-// fp32 blocks wider than 16 x 16: a value is the sum of three bf16 (split3), a product six of the fast matrix instruction,
-// 96 clocks a micro-tile of 32 pixels instead of 256, on half-size tiles, whose three planes take the LDS that fp32 did.  Launches of
-// ResNet-20 at 128 samples 62 -> 48 us.  The instruction cuts products at 2^-24 of the largest of eight pixels, towards zero,
-// and its sum is a little low on average: the sign of dY alternates from tile to tile, which takes the second of these out.
-// Against float64 (2-norm, layers of 128 to 256 samples): 32 x 32 channels 1.6 .. 8.7e-7 -> 1.1 .. 2.8e-7, 64 x 64 3.3 .. 7.6e-7 ->
-// 1.4 .. 3.0e-7.  Not so 16 x 16 blocks: over the 131072 pixels of 128 images what is cut from small values of one sign (dY behind a
-// ReLU's zeros) adds up, 3.7e-7 -> 9.7e-7 in one layer of ResNet-20; they stay with the fp32 instruction (16 x 16, 1.5 .. 4.1e-7 ->
-// 1.0 .. 2.8e-7 with the sums of a tile).  Together: ResNet-20 fp32 of 128 / 80 / 24 samples 634 / 527 / 330 -> 594 / 486 / 319 us, one module
-// 843 -> 818, ResNet-56 fp32 1595 -> 1498.
+// Every layer of every module takes part in the same launches, up to kFwMax of them in one.
+// What bounds it: a workgroup adds its whole block (36 KB of 32 x 32 channels) to the gradient with atomics, 25 us of a launch of 1024
+// workgroups.  Hence two workgroups per compute unit in bf16 (ResNet-56 of 128 samples 790 us a step with four, 762 with two).  A longer
+// walk would be a longer chain of fp32 sums, so a tile's sums start from zero and are added to the workgroup's.
+// fp32 is bound by its products (256 clocks a micro-tile of 32 pixels) and wants four workgroups per compute unit (see the launcher); its
+// registers hold two at a time.  Products of three bf16 parts on the fast instruction are not precise enough: it cuts what lies
+// below 2^-24 of the largest of eight products towards zero, and over operands of one sign that adds up with the pixels (32 x 32 channels, 3x3
+// behind a batch norm, 131072 pixels of positive inputs: 2.9e-6 of the gradient's norm against float64, here 4.7e-7).
 #include <algorithm>
 #include <type_traits>
 
@@ -49,16 +39,8 @@ __device__ __forceinline__ u32x2 tr_read(const char* p) {
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lds_ptr_t)const_cast<char*>(p)));
 }
 
-// four fp32 values to the three bf16 planes of a pixel
-__device__ __forceinline__ void store_split(char* at, int plane, const u32x4& v) {
-    u32x2 h[3];
-    split3(v, h);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(at + q * plane) = h[q];
-}
-
 // NTAP micro-tiles of columns: 9 taps, 1 tap, or (STEM) 2 groups of 16 of the 9 * Cin columns
-template <typename T, int NTAP, bool STEM, bool SPLIT>
+template <typename T, int NTAP, bool STEM>
 __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* const lds) {
     typedef typename std::conditional<STEM, float, T>::type E;       // what lies in LDS
     constexpr int EPV = 16 / (int)sizeof(T);
@@ -70,7 +52,7 @@ __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* con
     const int range = t >> (lgco + lgci), blk = t & ((1 << (lgco + lgci)) - 1);
     const int co0 = (blk & ((1 << lgco) - 1)) * 32, ci0 = (blk >> lgco) * 32;
     const int IH = P.IH, IW = P.IW, OB = P.Wo, WW = P.WW, stride = P.stride;
-    const int YP = SPLIT ? CB * 6 : CB * (int)sizeof(E) + 16, XP = STEM ? 16 : SPLIT ? CI * 6 : CI * (int)sizeof(E) + 16;      // LDS pitches
+    const int YP = CB * (int)sizeof(E) + 16, XP = STEM ? 16 : CI * (int)sizeof(E) + 16;      // LDS pitches
     const int pxmax = P.TH * OB, pxpad = (pxmax + 31) & ~31;
     char* const s_y = lds;
     char* const s_x = lds + pxpad * YP;
@@ -122,15 +104,13 @@ __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* con
             }
         }
     };
-    unsigned flip = 0;                             // SPLIT: the sign of dY in this tile (see compute)
     auto store_tile = [&]() {
 #pragma unroll
         for (int u = 0; u < YU; ++u) {
             const int p = yp0 + u * yst;
             if (p >= pxpad) continue;
             const u32x4 v = (ylive >> u) & 1u ? yr[u] : u32x4{0u, 0u, 0u, 0u};      // pixels that are not there count as zero
-            if constexpr (SPLIT) store_split(s_y + __mul24(p, YP) + yv * 8, CB * 2, v ^ flip);
-            else if constexpr (sizeof(E) == sizeof(T)) *reinterpret_cast<u32x4*>(s_y + __mul24(p, YP) + yv * 16) = v;
+            if constexpr (sizeof(E) == sizeof(T)) *reinterpret_cast<u32x4*>(s_y + __mul24(p, YP) + yv * 16) = v;
             else {
                 float f[EPV];
                 Vec<T>::unpack(v, f);
@@ -149,10 +129,7 @@ __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* con
 #pragma unroll
             for (int u = 0; u < XU; ++u) {
                 const int wp = xp0 + u * xst;
-                if (wp >= WHW) continue;
-                const u32x4 v = (xlive >> u) & 1u ? xr[u] : u32x4{0u, 0u, 0u, 0u};
-                if constexpr (SPLIT) store_split(s_x + __mul24(wp, XP) + xv * 8, CI * 2, v);
-                else *reinterpret_cast<u32x4*>(s_x + __mul24(wp, XP) + xv * 16) = v;
+                if (wp < WHW) *reinterpret_cast<u32x4*>(s_x + __mul24(wp, XP) + xv * 16) = (xlive >> u) & 1u ? xr[u] : u32x4{0u, 0u, 0u, 0u};
             }
         }
     };
@@ -181,35 +158,7 @@ __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* con
         return __mul24(__mul24(a * stride, WW) + b * stride, XP);
     };
     auto compute = [&]() {
-        if constexpr (SPLIT) {
-            const float sign = flip ? -1.f : 1.f;
-            for (int c = slice; c < pxpad >> 5; c += nslices) {
-                const int p0 = c * 32 + 8 * lg + (lq >> 2);
-                const char* const pa = s_y + __mul24(p0, YP) + cot * 32 + (lq & 3) * 8;
-                const char* const pb0 = s_x + win_pos(p0) + cit * 32 + (lq & 3) * 8;
-                const char* const pb1 = s_x + win_pos(p0 + 4) + cit * 32 + (lq & 3) * 8;
-                auto frag = [&](const char* lo, const char* hi) {
-                    const u32x2 a = tr_read(lo), b = tr_read(hi);
-                    return __builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]});
-                };
-                bf16x8 a[3], b[2][3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q) a[q] = frag(pa + q * CB * 2, pa + 4 * YP + q * CB * 2);
-                auto load_b = [&](int j) {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) b[j & 1][q] = frag(pb0 + toff[j] + q * CI * 2, pb1 + toff[j] + q * CI * 2);
-                };
-                load_b(0);
-#pragma unroll
-                for (int j = 0; j < NTAP; ++j) {
-                    if (j + 1 < NTAP) load_b(j + 1);
-                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
-                    mma_split(a, b[j & 1], t);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(sign, t[e], acc[j][e]);
-                }
-            }
-        } else if constexpr (sizeof(E) == 2) {
+        if constexpr (sizeof(E) == 2) {
             f32x4 t[NTAP];                         // the sums of a tile
 #pragma unroll
             for (int j = 0; j < NTAP; ++j) t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -256,7 +205,6 @@ __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* con
     const int t0 = range * P.per, t1 = min(P.ntiles, t0 + P.per);
     load_tile(t0);
     for (int i = t0; i < t1; ++i) {
-        if constexpr (SPLIT) flip = (unsigned)i << 31;
         store_tile();
         __syncthreads();
         if (i + 1 < t1) load_tile(i + 1);
@@ -304,8 +252,8 @@ __global__ __launch_bounds__(FW_NT, sizeof(T) == 4 ? 2 : 3) void fwgrad_kernel(c
     const int pi = __popcll(__ballot(lane < kFwMax && (int)blockIdx.x >= first)) - 1;
     FWgradArg& P = g.p[pi];
     const int t = (int)blockIdx.x - g.start[pi];
-    fwgrad_form<(int)sizeof(T)>(P.Cin, P.Cout, P.R, [&](auto ntap, auto stem, auto split) __attribute__((always_inline)) {
-        fwgrad_body<T, decltype(ntap)::value, decltype(stem)::value, decltype(split)::value>(P, t, s_lds);
+    fwgrad_form(P.Cin, P.R, [&](auto ntap, auto stem) __attribute__((always_inline)) {
+        fwgrad_body<T, decltype(ntap)::value, decltype(stem)::value>(P, t, s_lds);
     });
 }
 
@@ -313,13 +261,12 @@ __global__ __launch_bounds__(FW_NT, sizeof(T) == 4 ? 2 : 3) void fwgrad_kernel(c
 
 size_t fwgrad_lds_bytes(const FWgradProb& p, int esz) {
     const bool stem = p.Cin < 16;
-    const bool split = fwgrad_split(p.Cin, p.Cout, esz);
     const int e = stem ? 4 : esz, CB = std::min<int>(p.Cout, 32), CI = std::min<int>(p.Cin, 32);
     const size_t pxpad = ((size_t)p.TH * p.Wo + 31) & ~(size_t)31;
-    const size_t tile = pxpad * (split ? CB * 6 : CB * e + 16) + (size_t)p.WH * p.WW * (stem ? 16 : split ? CI * 6 : CI * e + 16);
+    const size_t tile = pxpad * (CB * e + 16) + (size_t)p.WH * p.WW * (stem ? 16 : CI * e + 16);
     const int units = (CB / 16) * (stem ? 1 : CI / 16);
     int ntap = 0;
-    fwgrad_form<4>(p.Cin, p.Cout, p.R, [&](auto n, auto, auto) { ntap = decltype(n)::value; });
+    fwgrad_form(p.Cin, p.R, [&](auto n, auto) { ntap = decltype(n)::value; });
     return std::max(tile, units == 4 ? (size_t)0 : (size_t)4 * ntap * 256 * 4);
 }
 

@@ -40,30 +40,6 @@ __device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
     const f32x2_t v = {a, b};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_t));
 }
-// four floats as sums of three bf16 each, x = h[0] + h[1] + h[2] to 2^-27 of x (every remainder is exact, rounded to nearest)
-__device__ __forceinline__ void split3(const u32x4& x, u32x2 (&h)[3]) {
-    float r[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(x[e]);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            h[p][e] = pack_bf16x2(r[2 * e], r[2 * e + 1]);
-            if (p < 2) { r[2 * e] -= __uint_as_float(h[p][e] << 16); r[2 * e + 1] -= __uint_as_float(h[p][e] & 0xffff0000u); }
-        }
-    }
-}
-// c += a * b of fp32 operands in three bf16 parts: the six products that count (what is left out is below 2^-26 of a product),
-// smallest first
-__device__ __forceinline__ void mma_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x4& c) {
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], c, 0, 0, 0);
-}
 template <typename T> __device__ __forceinline__ T from_float(float f);
 template <> __device__ __forceinline__ float from_float<float>(float f) { return f; }
 template <> __device__ __forceinline__ bf16_t from_float<bf16_t>(float f) { bf16_t r; r.v = float_to_bf16_bits(f); return r; }

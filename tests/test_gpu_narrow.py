@@ -128,10 +128,9 @@ def test_projections_of_equal_width(width, stride, bn, batch, dtype):
 
 
 @pytest.mark.parametrize("batch,side,stride", [(1, (8, 8), 2), (9, (12, 20), 2), (3, (7, 9), 1), (32, (32, 32), 2)])
-def test_fp32_filter_gradients_in_bf16_parts(batch, side, stride):
-    """Blocks wider than 16 x 16 channels multiply fp32 values as sums of three bf16 each.  Bound (2-norm against float64): what the
-    matrix instruction cuts of a product is below 2^-24 of the largest of eight, which is some ten times their root mean
-    square, 6e-7; the chains of fp32 sums 2e-7 to 4e-7.  Without one of the six products it would be 2^-18 / sqrt(3) = 2e-6 or more."""
+def test_fp32_filter_gradients(batch, side, stride):
+    """The fp32 filter gradients of every layer of a step to the precision of fp32 sums: 1e-6 (2-norm) against float64, where their chains give
+    1e-7 to 4e-7; with operands cut to 16 bits it would be 2^-18 / sqrt(3) = 2e-6 or more."""
     import numpy as np
     import torch
     from oracle import lpref
@@ -156,6 +155,86 @@ def test_fp32_filter_gradients_in_bf16_parts(batch, side, stride):
                 err = np.linalg.norm(grads[u.t_w] - want) / np.linalg.norm(want)
                 say(f"  m{k} {u.cin} -> {u.cout}, {u.R}x{u.R}/{u.stride}: {err:.1e}")
                 assert err < 1e-6, (k, u.cin, u.cout, err)
+    finally:
+        ls.close()
+
+
+def middle_module(width, batch, side):
+    """A module between two others, of one block of `width` channels with a bare projection: its input and the gradient of its output are the
+    caller's, and so are both operands of the projection's filter gradient."""
+    from paper_2112_05387_amd import LocalStep
+    import workloads as wl
+    blocks = lambda proj: [Block("basic", width, width, width, 1, proj, proj_bn=False)]  # noqa: E731
+    net = cfg._assemble("middle", [blocks(False), blocks(True), blocks(False)], batch, side, side, 3, 1, width, 5, seed=73)
+    ls = LocalStep(net, keep_gradients=True)
+    ls.set_params(1, wl.make_params(net, 1))
+    return ls
+
+
+@pytest.mark.parametrize("width", [16, 32, 64])
+def test_fp32_filter_gradients_of_one_sign(width):
+    """Over many pixels whatever every product is short of adds up where the operands have one sign, and the batch norm behind the first
+    convolution takes the mean of dY out, so that the large sums cancel.  Sums rounded to nearest (2-norm against float64): a chain of n terms is off by
+    2^-24 sqrt(n / 6) of its random walk; 32 k-steps of a tile and 512 workgroups one after the other give 6e-7, seen are up to 5e-7.  Products cut
+    at 2^-24 of the largest of eight, towards zero: 2.9e-6 with 32 channels.  (64 channels take this kernel up to 32768 pixels.)"""
+    import torch
+    import torch.nn.functional as F
+    batch = 32 if width == 64 else 128
+    say("case filter gradients of one sign", width, batch)
+    from paper_2112_05387_amd import binding as B
+    ls = middle_module(width, batch, 32)
+    try:
+        g = torch.Generator(device=ls.dev)
+        g.manual_seed(5)
+        ls.x[1].copy_(torch.rand(ls.x_shapes[1], generator=g, device=ls.dev))
+        ls.dy[1].copy_(torch.rand(ls.x_shapes[1], generator=g, device=ls.dev))
+        B.lp_profile_enable(ls.net, 2)
+        ls.module_forward(mask=2)
+        ls.module_backward(mask=2)
+        torch.cuda.synchronize()
+        kinds = {r["kind"] for r in B.lp_profile_fetch(ls.net)}
+        B.lp_profile_enable(ls.net, 0)
+        assert FOLDED_WGRAD in kinds, kinds
+        grads = ls.get_grads(1)
+        dev = lambda ref, u, c: torch.from_numpy(ls.fetch(ref, (u.N, u.H, u.W, c))).to(ls.dev)  # noqa: E731
+        for u in ls.units(1):
+            x, dy = dev(u.in_, u, u.cin), dev(u.gout if u.plain else u.dy, u, u.cout).reshape(-1, u.cout)
+            xp = F.pad(x, (0, 0, u.pad, u.pad, u.pad, u.pad))
+            want = torch.stack([dy.t().contiguous() @ xp[:, r:r + u.H, s:s + u.W].reshape(-1, u.cin) for r in range(u.R) for s in range(u.R)], 1)
+            got = torch.from_numpy(grads[u.t_w]).to(ls.dev).reshape(want.shape)
+            err = float((got - want).norm() / want.norm())
+            say(f"  {u.R}x{u.R}: {err:.1e}")
+            assert err < 1.2e-6, (width, u.R, err)
+    finally:
+        ls.close()
+
+
+def test_infinities_in_fp32_filter_gradients():
+    """An infinite element of a gradient makes its own row of a filter gradient infinite, and no other; the largest finite values multiply as
+    such."""
+    import numpy as np
+    import torch
+    say("case infinities")
+    ls = middle_module(32, 2, 8)
+    try:
+        u = next(u for u in ls.units(1) if u.plain)
+        rng = np.random.default_rng(3)
+        x = rng.uniform(0.5, 1.0, ls.x_shapes[1]).astype(np.float32)
+        dy = rng.uniform(0.5, 1.0, ls.x_shapes[1]).astype(np.float32)
+        dy[1, 3, 4, 7], dy[0, 2, 2, 9] = np.inf, -np.inf
+        x[..., 5] *= np.float32(1e-6)
+        dy[1, 0, 1, 11] = np.float32(3.4e38)
+        ls.x[1].copy_(torch.from_numpy(x))
+        ls.dy[1].copy_(torch.from_numpy(dy))
+        ls.module_forward(mask=2)
+        ls.module_backward(mask=2)
+        torch.cuda.synchronize()
+        got = ls.get_grads(1)[u.t_w].reshape(32, 32)
+        with np.errstate(invalid="ignore"):
+            want = dy.reshape(-1, 32).T.astype(np.float64) @ x.reshape(-1, 32).astype(np.float64)
+        assert (got[7] == np.inf).all() and (got[9] == -np.inf).all(), (got[7], got[9])
+        rows = [r for r in range(32) if r not in (7, 9)]
+        assert (np.abs(got[rows] - want[rows]) <= 1e-5 * np.abs(want[rows])).all()
     finally:
         ls.close()
 
