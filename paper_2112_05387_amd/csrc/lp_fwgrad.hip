@@ -39,15 +39,15 @@ __device__ __forceinline__ u32x2 tr_read(const char* p) {
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lds_ptr_t)const_cast<char*>(p)));
 }
 
-// NTAP micro-tiles of columns: 9 taps, 1 tap, or (STEM) 2 groups of 16 of the 9 * Cin columns
-template <typename T, int NTAP, bool STEM>
+// NTAP micro-tiles of columns: 9 taps, 1 tap, or (STEM) 2 groups of 16 of the 9 * Cin columns.  SIXTEEN: 16 -> 16 channels
+template <typename T, int NTAP, bool STEM, bool SIXTEEN>
 __device__ __forceinline__ void fwgrad_body(FWgradArg& P, const int t, char* const lds) {
     typedef typename std::conditional<STEM, float, T>::type E;       // what lies in LDS
     constexpr int EPV = 16 / (int)sizeof(T);
     constexpr int YU = fwgrad_y_vecs((int)sizeof(T)), XU = STEM ? kFwStemElems : fwgrad_x_vecs((int)sizeof(T));
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lq = lane & 15, lg = lane >> 4;
-    const int Cin = P.Cin, Cout = P.Cout, CB = min(Cout, 32), CI = STEM ? 4 : min(Cin, 32);
+    const int Cin = SIXTEEN ? 16 : P.Cin, Cout = SIXTEEN ? 16 : P.Cout, CB = min(Cout, 32), CI = STEM ? 4 : min(Cin, 32);
     const int lgco = Cout == 64 ? 1 : 0, lgci = !STEM && Cin == 64 ? 1 : 0;
     const int range = t >> (lgco + lgci), blk = t & ((1 << (lgco + lgci)) - 1);
     const int co0 = (blk & ((1 << lgco) - 1)) * 32, ci0 = (blk >> lgco) * 32;
@@ -252,8 +252,8 @@ __global__ __launch_bounds__(FW_NT, sizeof(T) == 4 ? 2 : 3) void fwgrad_kernel(c
     const int pi = __popcll(__ballot(lane < kFwMax && (int)blockIdx.x >= first)) - 1;
     FWgradArg& P = g.p[pi];
     const int t = (int)blockIdx.x - g.start[pi];
-    fwgrad_form(P.Cin, P.R, [&](auto ntap, auto stem) __attribute__((always_inline)) {
-        fwgrad_body<T, decltype(ntap)::value, decltype(stem)::value>(P, t, s_lds);
+    fwgrad_form<(int)sizeof(T)>(P.Cin, P.Cout, P.R, [&](auto ntap, auto stem, auto sixteen) __attribute__((always_inline)) {
+        fwgrad_body<T, decltype(ntap)::value, decltype(stem)::value, decltype(sixteen)::value>(P, t, s_lds);
     });
 }
 
@@ -266,7 +266,7 @@ size_t fwgrad_lds_bytes(const FWgradProb& p, int esz) {
     const size_t tile = pxpad * (CB * e + 16) + (size_t)p.WH * p.WW * (stem ? 16 : CI * e + 16);
     const int units = (CB / 16) * (stem ? 1 : CI / 16);
     int ntap = 0;
-    fwgrad_form(p.Cin, p.R, [&](auto n, auto) { ntap = decltype(n)::value; });
+    fwgrad_form<4>(p.Cin, p.Cout, p.R, [&](auto n, auto, auto) { ntap = decltype(n)::value; });
     return std::max(tile, units == 4 ? (size_t)0 : (size_t)4 * ntap * 256 * 4);
 }
 

@@ -9,22 +9,25 @@ PROGRAM = r"""
 #include <cstdio>
 #include <initializer_list>
 #include "lp_fwform.h"
-#define CHECK(c) do { if (!(c)) { std::printf("failed: %s (%d channels, %d x %d)\n", #c, cin, R, R); bad = 1; } } while (0)
-int main() {
+#define CHECK(c) do { if (!(c)) { std::printf("failed: %s (%d -> %d channels, %d x %d)\n", #c, cin, cout, R, R); bad = 1; } } while (0)
+template <int ESZ> static int forms() {
     int bad = 0;
     for (int cin : {1, 2, 3, 16, 32, 64})
-        for (int R : {1, 3}) {
-            if (cin < 16 && R != 3) continue;
-            int calls = 0, taps = 0;
-            bool stem = false;
-            lp::fwgrad_form(cin, R, [&](auto n, auto s) { ++calls; taps = decltype(n)::value; stem = decltype(s)::value; });
-            CHECK(calls == 1);
-            CHECK(stem == (cin < 16));
-            if (stem) CHECK(taps * 16 >= R * R * cin);      // groups of 16 of the R * R * cin columns
-            else CHECK(taps == R * R);                      // a tap a group: no column that the filter does not have
-        }
+        for (int cout : {16, 32, 64})
+            for (int R : {1, 3}) {
+                if (cin < 16 && R != 3) continue;
+                int calls = 0, taps = 0;
+                bool stem = false, sixteen = false;
+                lp::fwgrad_form<ESZ>(cin, cout, R, [&](auto n, auto s, auto w) { ++calls; taps = decltype(n)::value; stem = decltype(s)::value; sixteen = decltype(w)::value; });
+                CHECK(calls == 1);
+                CHECK(stem == (cin < 16));
+                if (stem) CHECK(taps * 16 >= R * R * cin);      // groups of 16 of the R * R * cin columns
+                else CHECK(taps == R * R);                      // a tap a group: no column that the filter does not have
+                CHECK(sixteen == (ESZ == 4 && cin == 16 && cout == 16 && R == 3));
+            }
     return bad;
 }
+int main() { return forms<2>() | forms<4>(); }
 """
 
 
