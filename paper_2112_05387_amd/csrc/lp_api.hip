@@ -126,6 +126,8 @@ struct Op {
     HeadProb head;
     int key() const { return type == OP_WTRANS ? OP_FILL * 64 + cfg * 2 + (vec ? 1 : 0) : type == OP_FWGRAD ? type * 64 : image ? type * 64 + CONV_IMAGE * 2 : type * 64 + cfg * 2 + (vec ? 1 : 0); }
 };
+// does this BN apply evaluate a module's loss and terminal adjoint
+static bool has_loss(const Op& o) { return o.type == OP_BN_APPLY && o.r[12].space != SP_NONE; }
 typedef std::vector<Op> Step;              // operations of one module that may run concurrently
 typedef std::vector<Step> Program;         // steps run in order
 
@@ -1448,7 +1450,7 @@ static void build_step_programs(lp_net* net, int k) {
             last_apply->r[11] = mk(SP_DY, k, 0); last_apply->r[12] = mk(SP_LOSS, 0, sizeof(float) * k);
         } else if (head) {
             head->r[5] = mk(SP_DLOGITS, 0, 0); head->r[9] = mk(SP_LABELS, 0, 0); head->r[10] = mk(SP_LOSS, 0, sizeof(float) * k);
-            // the pass in front of it shares a launch with the other modules' last passes, which evaluate their losses
+            // the pass in front of it shares a launch with the last passes of the other modules of its lane, which evaluate their losses
             if (variant >= 2 && out.size() > 1 && out[out.size() - 2].size() == 1 && out[out.size() - 2][0].type == OP_BN_APPLY) out[out.size() - 2][0].cfg = 1;
         } else {
             out.push_back(loss_step);
@@ -1645,7 +1647,7 @@ static void op_work(const lp_net* net, const Op& o, double& flops, double& bytes
         case OP_WTRANS: bytes = 2.0 * o.prep.Cout * o.prep.RS * o.prep.Cin * e; break;
         case OP_FILL: bytes = (double)o.fill_bytes; break;
         case OP_BN_APPLY:      // fused with the loss / terminal adjoint: + x_next, lam, dy (the multiplier written back: + 1)
-            bytes = (double)o.bna.M * o.bna.C * e * ((o.bna.skip_mode ? 3.0 : 2.0) + (o.cfg == 1 ? 3.0 : 0.0)); break;
+            bytes = (double)o.bna.M * o.bna.C * e * ((o.bna.skip_mode ? 3.0 : 2.0) + (has_loss(o) ? 3.0 : 0.0)); break;
         case OP_BN_BWD_REDUCE: bytes = (double)o.bnb.M * o.bnb.C * e * 2.0; break;
         case OP_BN_BWD_APPLY: bytes = (double)o.bnb.M * o.bnb.C * e * (o.r[9].space != SP_NONE ? 4.0 : 3.0); break;
         case OP_BN_BWD: bytes = (double)o.bnb.M * o.bnb.C * e * (o.r[9].space != SP_NONE ? 4.0 : 3.0); break;
@@ -2187,7 +2189,9 @@ static hipError_t launch_group_impl(lp_net* net, std::vector<const Op*>& ops, si
             } break;
             case OP_BN_APPLY: {
                 BnApplyGroup g; g.nprob = n; g.eps = net->eps; g.cmax = 0; int tot = 0;
-                const bool fused_loss = ops[base]->cfg == 1;
+                // (the last module's pass may be marked to share this launch and find no other in it: its head has the loss)
+                const bool fused_loss = std::any_of(ops.begin() + base, ops.begin() + base + n, [](const Op* o) { return has_loss(*o); });
+                if (used_cfg) *used_cfg = fused_loss ? 1 : 0;
                 g.rho = b.rho; g.scale = b.scale; g.step = b.mstep;
                 for (int i = 0; i < n; ++i) {
                     const Op& o = *ops[base + i];

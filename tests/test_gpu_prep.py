@@ -107,3 +107,42 @@ def test_head_with_loss(batch, side, width, classes, dtype, one):
             assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max() + 1.0)
     finally:
         ls.close()
+
+
+@pytest.mark.parametrize("modules,lanes", [(1, None), (2, None), (2, [0, 1]), (3, [0, 1, 0])])
+def test_last_pass_evaluates_a_loss_only_in_company(modules, lanes):
+    """The last module's last pass has no loss (its head has it): in a lane of its own it is the plain pass, with others of its lane it
+    shares their launch, and its record counts the tensors that it reads and writes."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    from tests.gpu_unitwise import seeded_step_inputs
+    say("case last pass", modules, lanes)
+    batch, width = 2, 16
+    net = cfg._assemble("last", [[Block("basic", width, width, width, 1, False)] for _ in range(modules)], batch, 8, 8, 3, 1, width, 5, seed=79)
+    net.dtype = "f32"
+    params, _, labels, xs, lams = seeded_step_inputs(net)
+    ls = LocalStep(net)
+    try:
+        for k in range(modules):
+            ls.set_params(k, params[k])
+            ls.set_x(k, xs[k])
+        ls.set_lams(lams)
+        ls.set_labels(labels)
+        ls.set_stream_lanes(lanes)
+        B.lp_profile_enable(ls.net, 2)
+        ls.local_step(net.rho, 1.0)
+        torch.cuda.synchronize()
+        recs = [(r["cfg"], r["nprob"], r["bytes"]) for r in B.lp_profile_fetch(ls.net) if r["kind"] == 3]
+        B.lp_profile_enable(ls.net, 0)
+    finally:
+        ls.close()
+    tensor = batch * 8 * 8 * width * 4
+    plain, loss = 3 * tensor, 6 * tensor           # y, skip, out; and x_next, lam, dy
+    in_lane = [[k for k in range(modules) if (lanes or [0] * modules)[k] == l] for l in range(2)]
+    want = []
+    for ks in in_lane:
+        with_loss = sum(k < modules - 1 for k in ks)
+        if ks:
+            want.append((1 if with_loss else 0, len(ks), with_loss * loss + (len(ks) - with_loss) * plain))
+    assert sorted(recs) == sorted(want), (recs, want)
