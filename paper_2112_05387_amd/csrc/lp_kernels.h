@@ -262,7 +262,7 @@ struct HeadProb {        // global average pool + linear
 // and every sample can afford to read all weights: three dependent launches of 2 to 6 us otherwise, each of them 4 us of the
 // host's time (with the losses cleared in the step's first launch, not one of their own, and the last module's last
 // pass in the launch of the others': tiny 81 -> 62 us, ResNet-20 of 3 samples in bf16 192 -> 173, of 16 229 -> 209, 2 in fp32 232 -> 211).
-inline bool head_with_loss(const HeadProb& p, int esz) { return (size_t)p.HW * p.C * esz <= 32 * 1024 && p.C * p.classes <= 16384; }
+inline bool head_with_loss(const HeadProb& p, int esz) { return (size_t)p.HW * p.C * esz <= 32 * 1024 && (size_t)p.C * p.classes <= 16384; }
 
 // Image-facing convolutions (lp_iconv.hip): bytes of the rows of the image that BM consecutive output pixels read at most, in whole
 // wave-loads; 0: not a layer of that kernel.  Up to 24 KB, so that four workgroups and their result slices fit a CU.  The image
