@@ -592,10 +592,6 @@ struct WsAlloc {
     size_t take(size_t bytes) { const size_t o = off; off = align_up(off + std::max<size_t>(bytes, 16)); return o; }
 };
 
-// Parameter update inside the backward pass: every filter-gradient operation of module k that writes into dparams[k]
-// gets the filter it belongs to (r[4]) and a run of completion tickets in the workspace (r[3], one per output tile;
-// cleared by the step that clears the gradients); one last step updates the tensors no filter-gradient kernel owns
-// (BN affine, head).  The operations carry these references always; they are bound only while the update is switched on.
 // Batch-norm backward passes of few rows (bn_bwd_small): the apply pass joins the reduction in front of it.
 static void join_small_bn(const lp_net* net, Program& P) {
     for (size_t i = 0; i + 1 < P.size(); ++i) {
@@ -609,9 +605,13 @@ static void join_small_bn(const lp_net* net, Program& P) {
         P.erase(P.begin() + i);
     }
 }
+
+// Parameter update inside the backward pass: every filter-gradient operation of module k that writes into dparams[k]
+// gets the filter it belongs to (r[4]) and a run of completion tickets in the workspace (r[3], one per output tile;
+// cleared by the step that clears the gradients); one last step updates the tensors no filter-gradient kernel owns
+// (BN affine, head).  The operations carry these references always; they are bound only while the update is switched on.
 static void attach_update(lp_net* net, int k, WsAlloc& ws) {
     ModulePlan& m = net->mods[k];
-    for (Program* P : {&m.bwd, &m.bwd_dx0}) join_small_bn(net, *P);
     m.t_in_epilogue.assign(m.tensors.size(), 0);
     std::vector<size_t> cnt_off(m.tensors.size(), 0);
     m.ws_cnt0 = ws.off;
@@ -1149,6 +1149,7 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
         Bw.push_back(wg_tail);
     }
     if (!build_module_folded(net, k)) net->narrow = false;
+    for (Program* P : {&m.bwd, &m.bwd_dx0}) join_small_bn(net, *P);
     attach_update(net, k, ws);
     return LP_OK;
 }
@@ -1400,6 +1401,7 @@ static lp_status build_module_pre(lp_net* net, int k, WsAlloc& ws) {
         Bw.push_back(wg_tail);
     }
     net->narrow = false;
+    for (Program* P : {&m.bwd, &m.bwd_dx0}) join_small_bn(net, *P);
     attach_update(net, k, ws);
     return LP_OK;
 }
