@@ -987,9 +987,6 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
     if (m.has_stem) {
         const Unit& u = m.stem;
         F.push_back(Step{B.conv_fwd(u, mk(SP_X, k, 0), wref(u), yref(u), stats(u))});
-        // Beside the large tiles of other lanes the stem of a wide network stays with the general kernel: lp_iconv.hip's is the faster one
-        // by itself (120 workgroups 12.6 -> 9.3 us with the timing's 5), but forward passes of WRN-28-10 of 16 / 30 samples are not, 432 -> 436, 547 -> 554 us
-        F.back()[0].image = 0;
         F.push_back(Step{B.bn_apply(Mof(u), u.cout, yref(u), mk(SP_WS, 0, m.ws_stem_act), stats(u), gref(u), bref(u), true)});
         if (d.stem == 2) {
             Op o; o.type = OP_POOL_FWD;
@@ -1302,10 +1299,7 @@ static lp_status build_module_pre(lp_net* net, int k, WsAlloc& ws) {
     F.push_back(Step{B.fill(W_(m.ws_stats0), m.ws_stats_bytes)});
     {
         const Unit& f0 = m.bp[0].main[0];
-        if (m.has_stem) {
-            F.push_back(Step{B.conv_fwd(m.stem, mk(SP_X, k, 0), wref(m.stem), W_(m.ws_stem_act), W_(f0.ws_stats))});
-            F.back()[0].image = 0;                 // (as in the other order)
-        }
+        if (m.has_stem) F.push_back(Step{B.conv_fwd(m.stem, mk(SP_X, k, 0), wref(m.stem), W_(m.ws_stem_act), W_(f0.ws_stats))});
         else F.push_back(Step{B.bn_stats(Min(f0), f0.cin, mk(SP_X, k, 0), W_(f0.ws_stats))});
     }
     for (size_t i = 0; i < nb; ++i) {

@@ -524,3 +524,39 @@ def test_image_layers_have_the_bits_of_the_general_kernel(batch, side, stride, c
     # a fixed order sums the statistics of the stored results in another one: the last place of fp32, a rounding of bf16
     for a, b in zip(results[0], results[2]):
         assert float((a.float() - b.float()).abs().max()) <= (2.0 ** -20 if dtype == "f32" else 2.0 ** -7) * float(a.float().abs().max())
+
+
+@pytest.mark.parametrize("order,widths,batch,side,c_img,dtype", [
+    ("pre", (16, 32), 5, (12, 20), 3, "f32"), ("pre", (16, 64), 3, (32, 32), 3, "bf16"), ("pre", (32, 64), 2, (6, 14), 1, "f32"), ("pre", (64, 16), 2, (8, 8), 2, "bf16"),
+    ("post", (16, 160), 2, (8, 8), 3, "bf16"), ("post", (64, 128), 3, (12, 4), 3, "f32")])
+def test_stems_outside_the_folded_passes(order, widths, batch, side, c_img, dtype):
+    """The stem of a network whose batch norms run in passes of their own (pre-activation order, wide layers) takes the image-facing kernel too."""
+    import torch
+    from paper_2112_05387_amd import LocalStep
+    from paper_2112_05387_amd import binding as B
+    say("case stems", order, widths, batch, side, c_img, dtype)
+    net = cfg.with_order(narrow_net(batch, side, widths=widths, dtype=dtype, c_img=c_img), order)
+    params, _, _, xs, _ = seeded_step_inputs(net)
+    results = []
+    for separate in (False, True):
+        B.lp_debug_separate_passes(separate)
+        try:
+            ls = LocalStep(net)
+        finally:
+            B.lp_debug_separate_passes(False)
+        try:
+            for k in range(net.K):
+                ls.set_params(k, params[k])
+                ls.set_x(k, xs[k])
+            B.lp_profile_enable(ls.net, 2)
+            ls.module_forward()
+            torch.cuda.synchronize()
+            convs = [r["cfg"] for r in B.lp_profile_fetch(ls.net) if r["kind"] == CONV]
+            B.lp_profile_enable(ls.net, 0)
+            assert (IMAGE_LAYERS in convs) == (not separate), convs
+            results.append([ls.y[0].clone(), ls.logits.clone()])
+        finally:
+            ls.close()
+    assert float(results[0][0].float().abs().max()) > 0
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
