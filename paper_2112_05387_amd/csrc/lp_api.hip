@@ -2509,11 +2509,15 @@ static bool folded(const lp_net* net) { return net->narrow && !net->deterministi
 // the lanes by default: in a call of their own, and in the step that does both passes in one call.  One launch holds the tiles of
 // all modules, whatever their widths, so on small mini-batches lanes only split it: the host cannot issue several times the
 // launches fast enough, and fork and join cost 10 us a call.  Where a lane's own launches fill the chip, the lanes fill each other's
-// tails and dependent trips to memory.  One stream / lanes, us, over networks of two to four lanes (the host's share varies):
-//   step     ResNet-20 bf16 64 samples (6 MB a lane) 356 / 420, 128 (12) 429 / 414, 192 (18) 534 / 493; fp32 96 (18) 647 / 534,
-//            512 (98) 2540 / 2156; ResNet-56 in four modules bf16 64 (17) 731 / 746, 96 (25) 833 / 750
-//   forward  ResNet-20 bf16 192 (18) 188 / 223, 256 (25) 237 / 226; ResNet-56 in four modules fp32 64 (33) 386 / 406, 96 (50)
-//            550 / 501, bf16 128 (33) 325 / 378, 160 (42) 405 / 376; the backward pass crosses over between 20 and 37 MB
+// tails and dependent trips to memory.  One stream / lanes, us, each pass waited for:
+//   step      ResNet-20 bf16 160 samples (15 MB a lane) 438 / 435, 256 (25) 613 / 570; fp32 96 (18) 597 / 563, 256 (49) 1255 / 1101; in three
+//             modules bf16 192 (25) 469 / 483, 256 (33) 585 / 578; ResNet-56 bf16 48 (17) 454 / 413, in four modules bf16 96 (25)
+//             743 / 787, 160 (42) 1020 / 952, fp32 32 (17) 814 / 777
+//   forward   ResNet-20 fp32 160 (31) 303 / 315, 192 (37) 346 / 348, 256 (49) 440 / 433; ResNet-56 bf16 128 (44) 304 / 323, 160 (55)
+//             373 / 361, in four modules bf16 192 (50) 439 / 462
+//   backward  ResNet-20 bf16 192 (18) 300 / 328, 256 (25) 371 / 363; fp32 160 (31) 559 / 556; ResNet-56 bf16 64 (22) 306 / 294, in four
+//             modules bf16 128 (33) 503 / 529, 160 (42) 622 / 585
+// (Pass after pass with the host ahead the lanes win earlier, steps and backward passes from 12 to 17 MB on, forward passes from 25 to 42.)
 constexpr size_t kFoldLaneBytesCall = 40u << 20, kFoldLaneBytesStep = 18u << 20;
 static size_t lane_bytes(const lp_net* net) {
     size_t elems = 0;
