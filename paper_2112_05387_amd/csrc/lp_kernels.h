@@ -396,8 +396,10 @@ inline void bn_reduce_cut(int M, int C, int epv, int threads, int& lanes, int& p
 // 128 bytes every 4 to 5 clocks, five lines a row: 49 rows 9 us (timed by itself, with its launch), 196 12, 784 18, 1176 25; the two launches 15 to
 // 18 for any of them.  Whole steps, two launches / one: ResNet-50 of 1 / 3 samples 1300 / 1200 and 1370 / 1253 us, WRN-28-10 of 1 / 4 samples
 // 848 / 780 and 832 / 800, in pre-activation order of 5 857 / 820; up to 1300 rows ResNet-50 of 6 1398 / 1490, up to 2048 of 9 1568 / 1800.
+// Between 449 and 600 rows a step is as long either way, but not the AuxNets' backward pass, which has nothing beside it: iterations of
+// WRN-28-10 of 8 / 9 samples (512 / 576 rows) 1517 / 1536 and 1695 / 1713, of ResNet-50 of 3 (588) 1568 / 1581.
 constexpr int kBnSmallChannels = 64, kBnSmallThreads = 512;
-inline bool bn_bwd_small(int M, int C, int esz) { return esz == 2 && C > 64 && C % kBnSmallChannels == 0 && M <= 600; }
+inline bool bn_bwd_small(int M, int C, int esz) { return esz == 2 && C > 64 && C % kBnSmallChannels == 0 && M <= 448; }
 constexpr int kElemVecsPerBlock = 2048;  // 16-byte vectors handled by one workgroup
 
 }  // namespace lp

@@ -103,9 +103,10 @@ def test_slices_have_the_bits_of_whole_rows(case, order, lanes, fixed):
 @pytest.mark.parametrize("case,order,fixed", [
     # one row; fewer rows than a trip has; rows that end inside a trip and inside a part, several rounds of parts (256 channels and less)
     (dict(batch=1, side=(2, 2), widths=(128, 256), dtype="bf16"), "post", False), (dict(batch=3, side=(6, 10), widths=(192, 320), dtype="bf16"), "post", False),
-    # the most rows that one workgroup takes, and more of them beside fewer; the added gradient of an identity skip
+    # the most rows that one workgroup takes, more of them beside fewer; the added gradient of an identity skip
     (dict(batch=6, side=(10, 10), widths=(128, 640), dtype="bf16"), "post", False), (dict(batch=7, side=(10, 10), widths=(192, 384), dtype="bf16"), "pre", False),
     (dict(batch=5, side=(8, 8), widths=(256, 576), dtype="bf16"), "pre", False),
+    (dict(batch=7, side=(8, 8), widths=(128, 640), dtype="bf16"), "post", False), (dict(batch=8, side=(8, 8), widths=(640, 192), dtype="bf16"), "pre", False),
     # two row lanes and trips in a row, a projection's batch norm in the same launch; the fixed order takes two launches
     (dict(batch=3, side=(14, 14), widths=(1024, 2048), dtype="bf16", kind="bottleneck"), "post", False),
     (dict(batch=3, side=(6, 10), widths=(192, 320), dtype="bf16"), "post", True),
