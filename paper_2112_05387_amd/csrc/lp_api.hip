@@ -987,6 +987,10 @@ static lp_status build_module(lp_net* net, int k, WsAlloc& ws) {
     if (m.has_stem) {
         const Unit& u = m.stem;
         F.push_back(Step{B.conv_fwd(u, mk(SP_X, k, 0), wref(u), yref(u), stats(u))});
+        // Beside the large tiles of other lanes a stem in front of wide layers is as good in the general kernel, or better: WRN-28-10 forward
+        // of 9 samples in three modules 551 us, 555 with lp_iconv.hip's (the step 1392 / 1383, forward of 30 in two modules 1064 / 1056).  In
+        // front of narrow layers, and in the pre-activation order, lp_iconv.hip's is nowhere the slower one.
+        if (std::any_of(m.blocks.begin(), m.blocks.end(), [](const lp_block_desc& b) { return b.cout > 64; })) F.back()[0].image = 0;
         F.push_back(Step{B.bn_apply(Mof(u), u.cout, yref(u), mk(SP_WS, 0, m.ws_stem_act), stats(u), gref(u), bref(u), true)});
         if (d.stem == 2) {
             Op o; o.type = OP_POOL_FWD;

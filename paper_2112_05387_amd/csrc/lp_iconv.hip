@@ -9,7 +9,7 @@
 // (1 to 6 KB), the taps are picked out of LDS into registers (8 elements of k a lane, which is one MFMA of bf16 and two k-steps
 // of fp32), and since no operand tile is laid out, the widths share a launch of 14 us: that step 692 -> 665 us, of 8 samples 390 -> 362,
 // an iteration 925 -> 897; a step of four modules 749 -> 726.  A stem alone (512 workgroups) 15.6 -> 10.9 us by itself, 5 of them the timing's own; beside other lanes
-// the whole pass gains little: pre-activation ResNet-20, 256 samples forward 527 -> 515, WRN-28-10 of 16 / 75 samples 537 / 1043 -> 537 / 1038.
+// the whole pass gains little: pre-activation ResNet-20, 256 samples forward 527 -> 515, and in front of wide layers nothing (build_module).
 //
 // The tiles are those of the general kernel (256 pixels x 16 or 32 channels with 64-pixel waves; 64 x 64 in four waves of 32 x 32), and
 // so is the order of every sum, of a product's terms and of the statistics: the results are the same bits.
